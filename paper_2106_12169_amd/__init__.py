@@ -3,7 +3,7 @@
 The package holds two things only:
   * ``workloads``  seeded synthetic input generators and workload shapes
                    (pure numpy, none of the method's arithmetic);
-  * ``binding``    the thin ctypes binding over the C-ABI library ``libapnn.so``
+  * ``binding``    the thin binding over the C-ABI library ``libapnn.so``
                    built from ``csrc/`` (argument marshalling only).
 
 Nothing is imported eagerly so that ``workloads`` stays usable without the

@@ -1,8 +1,11 @@
-"""Thin ctypes binding over libapnn.so: argument marshalling only.
+"""Thin binding over libapnn.so: argument marshalling only.
 
 Every function has the name of the C entry point it calls (``include/apnn.h``);
 tensors are PyTorch device tensors used purely as device memory, the stream is
 PyTorch's current stream.  No computation of the method happens in Python.
+The calls of a network's forward pass go through the ``_native`` module
+(``csrc/native_binding.cpp``), which unpacks the tensors and calls the entry
+point without ctypes; packing of weights, sizes and the overrides use ctypes.
 The library must have been built (``python -m paper_2106_12169_amd.build``);
 a missing library is an error, there is no fallback path.
 """
@@ -37,6 +40,25 @@ class ApnnError(RuntimeError):
     def __init__(self, status: int, text: str):
         super().__init__(f"apnn status {status}: {text}")
         self.status = status
+
+
+class _Missing:
+    """Stands in for the native module until it is built, so that the package can be imported to build it."""
+
+    def __getattr__(self, name):
+        raise ImportError("paper_2106_12169_amd._native is missing: build it with `python -m paper_2106_12169_amd.build`")
+
+
+try:
+    from . import _native as _N
+    _N.set_error_class(ApnnError)
+except ModuleNotFoundError:
+    _N = _Missing()
+
+
+def native():
+    """The native module (argument marshalling; csrc/native_binding.cpp)."""
+    return _N
 
 
 class ConvDesc(C.Structure):
@@ -138,22 +160,21 @@ def apnn_fmap_words(pixels: int, Cc: int, bits: int) -> int:
 
 def apnn_pack(src: torch.Tensor, bits: int, enc: int, out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """src: rows x K uint8/int8 device tensor -> packed matrix operand (int32 words)."""
-    rows, K = src.shape
     if out is None:
-        out = _words(apnn_packed_words(rows, K, bits), src.device)
-    _check(lib().apnn_pack(_ptr(src), rows, K, bits, enc, _ptr(out), _stream()))
+        out = _words(apnn_packed_words(*src.shape, bits), src.device)
+    _N.pack(src, bits, enc, out)
     return out
 
 
 def apnn_pack_fmap(src: torch.Tensor, layout: int, bits: int, enc: int,
                    out: Optional[torch.Tensor] = None) -> torch.Tensor:
-    if layout == LAYOUT_NHWC:
-        N, H, W, Cc = src.shape
-    else:
-        N, Cc, H, W = src.shape
     if out is None:
+        if layout == LAYOUT_NHWC:
+            N, H, W, Cc = src.shape
+        else:
+            N, Cc, H, W = src.shape
         out = _words(apnn_fmap_words(N * H * W, Cc, bits), src.device)
-    _check(lib().apnn_pack_fmap(_ptr(src), layout, N, H, W, Cc, bits, enc, _ptr(out), _stream()))
+    _N.pack_fmap(src, layout, bits, enc, out)
     return out
 
 
@@ -183,11 +204,10 @@ def apnn_pack_patch_weights(src: torch.Tensor, bits: int, enc: int) -> torch.Ten
 
 def apnn_quantize(src: torch.Tensor, zero: float, step: float, bits: int,
                   out: Optional[torch.Tensor] = None) -> torch.Tensor:
-    rows, K = src.shape
     assert src.dtype == torch.float32
     if out is None:
-        out = _words(apnn_packed_words(rows, K, bits), src.device)
-    _check(lib().apnn_quantize(_ptr(src), rows, K, zero, step, bits, _ptr(out), _stream()))
+        out = _words(apnn_packed_words(*src.shape, bits), src.device)
+    _N.quantize(src, zero, step, bits, out)
     return out
 
 
@@ -195,7 +215,7 @@ def apnn_gemm(W: torch.Tensor, X: torch.Tensor, M: int, N: int, K: int, p: int, 
               encW: int, encX: int, out: Optional[torch.Tensor] = None) -> torch.Tensor:
     if out is None:
         out = torch.empty((M, N), dtype=torch.int32, device=W.device)
-    _check(lib().apnn_gemm(_ptr(W), _ptr(X), _ptr(out) if out.numel() else None, M, N, K, p, q, encW, encX, _stream()))
+    _N.gemm(W, X, M, N, K, p, q, encW, encX, out)
     return out
 
 
@@ -232,8 +252,7 @@ class Conv:
 def apnn_conv2d(d: Conv, W: torch.Tensor, X: torch.Tensor, out: Optional[torch.Tensor] = None) -> torch.Tensor:
     if out is None:
         out = torch.empty((d.N, d.Ho, d.Wo, d.Cout), dtype=torch.int32, device=X.device)
-    desc = d.c()
-    _check(lib().apnn_conv2d(C.byref(desc), _ptr(W), _ptr(X), _ptr(out), _stream()))
+    _N.conv2d(d, W, X, out)
     return out
 
 
@@ -243,12 +262,10 @@ def apnn_layer(d: Conv, W: torch.Tensor, X: torch.Tensor, *, is_gemm: bool = Fal
                acc_out: Optional[torch.Tensor] = None, float_out: Optional[torch.Tensor] = None,
                out: Optional[torch.Tensor] = None, pool: int = 0) -> Optional[torch.Tensor]:
     """Returns the packed output codes (or None when q_out == 0).  pool: POOL_NONE / POOL_MAX2 / POOL_SUM2."""
-    pixels = d.N * (1 if is_gemm else ((d.Ho // 2) * (d.Wo // 2) if pool else d.Ho * d.Wo))
     if q_out > 0 and out is None:
+        pixels = d.N * (1 if is_gemm else ((d.Ho // 2) * (d.Wo // 2) if pool else d.Ho * d.Wo))
         out = _words(apnn_fmap_words(pixels, d.Cout, q_out), X.device)
-    L = LayerDesc(d.c(), int(is_gemm), q_out, _ptr(scale), _ptr(bias), _ptr(residual), q_res, res_scale,
-                  _ptr(acc_out), _ptr(float_out), pool)
-    _check(lib().apnn_layer(C.byref(L), _ptr(W), _ptr(X), _ptr(out) if q_out > 0 else None, _stream()))
+    _N.layer(d, W, X, is_gemm, q_out, scale, bias, residual, q_res, res_scale, acc_out, float_out, out, pool)
     return out if q_out > 0 else None
 
 
@@ -256,16 +273,15 @@ def apnn_layer_pair(a: dict, b: dict) -> None:
     """Two independent layers, one launch where the library can share it.  a, b: the arguments of apnn_layer as
     dicts with keys d, W, X and optionally q_out, scale, bias, residual, q_res, res_scale, acc_out, float_out, out,
     pool; packed outputs must be preallocated (out)."""
-    def desc(k):
-        q_out = k.get("q_out", 0)
-        assert q_out == 0 or k.get("out") is not None, "preallocate the packed output"
-        L = LayerDesc(k["d"].c(), 0, q_out, _ptr(k.get("scale")), _ptr(k.get("bias")), _ptr(k.get("residual")),
-                      k.get("q_res", 0), k.get("res_scale", 0.0), _ptr(k.get("acc_out")), _ptr(k.get("float_out")),
-                      k.get("pool", 0))
-        return L, _ptr(k["W"]), _ptr(k["X"]), (_ptr(k["out"]) if q_out > 0 else None)
-    La, Wa, Xa, Oa = desc(a)
-    Lb, Wb, Xb, Ob = desc(b)
-    _check(lib().apnn_layer_pair(C.byref(La), Wa, Xa, Oa, C.byref(Lb), Wb, Xb, Ob, _stream()))
+    _N.layer_pair(*layer_args(a), *layer_args(b))
+
+
+def layer_args(k: dict) -> tuple:
+    """A layer given as a dict (see apnn_layer_pair) in the argument order of the native module."""
+    q_out = k.get("q_out", 0)
+    assert q_out == 0 or k.get("out") is not None, "preallocate the packed output"
+    return (k["d"], k["W"], k["X"], False, q_out, k.get("scale"), k.get("bias"), k.get("residual"), k.get("q_res", 0),
+            k.get("res_scale", 0.0), k.get("acc_out"), k.get("float_out"), k.get("out"), k.get("pool", 0))
 
 
 def apnn_pack_input_weights(src: torch.Tensor, bits: int, enc: int) -> torch.Tensor:
@@ -285,18 +301,16 @@ def apnn_input_layer(d: Conv, W: torch.Tensor, image: torch.Tensor, *, q_out: in
     as in apnn_layer.  Returns the packed output codes (or None when q_out == 0)."""
     if q_out > 0 and out is None:
         out = _words(apnn_fmap_words(d.N * d.Ho * d.Wo, d.Cout, q_out), image.device)
-    L = LayerDesc(d.c(), 0, q_out, _ptr(scale), _ptr(bias), _ptr(residual), q_res, res_scale,
-                  _ptr(acc_out), _ptr(float_out), 0)
-    _check(lib().apnn_input_layer(C.byref(L), _ptr(W), _ptr(image), _ptr(out) if q_out > 0 else None, _stream()))
+    _N.input_layer(d, W, image, False, q_out, scale, bias, residual, q_res, res_scale, acc_out, float_out, out, 0)
     return out if q_out > 0 else None
 
 
 def apnn_maxpool(X: torch.Tensor, N: int, H: int, W: int, Cc: int, bits: int, k: int, stride: int, pad: int,
                  out: Optional[torch.Tensor] = None) -> torch.Tensor:
-    Ho, Wo = (H + 2 * pad - k) // stride + 1, (W + 2 * pad - k) // stride + 1
     if out is None:
+        Ho, Wo = (H + 2 * pad - k) // stride + 1, (W + 2 * pad - k) // stride + 1
         out = _words(apnn_fmap_words(N * Ho * Wo, Cc, bits), X.device)
-    _check(lib().apnn_maxpool(_ptr(X), N, H, W, Cc, bits, k, stride, pad, _ptr(out), _stream()))
+    _N.maxpool(X, N, H, W, Cc, bits, k, stride, pad, out)
     return out
 
 
@@ -304,7 +318,7 @@ def apnn_sumpool(X: torch.Tensor, N: int, H: int, W: int, Cc: int, bits: int, ou
                  out: Optional[torch.Tensor] = None) -> torch.Tensor:
     if out is None:
         out = _words(apnn_packed_words(N, Cc, out_bits), X.device)
-    _check(lib().apnn_sumpool(_ptr(X), N, H, W, Cc, bits, out_bits, _ptr(out), _stream()))
+    _N.sumpool(X, N, H, W, Cc, bits, out_bits, out)
     return out
 
 
@@ -313,7 +327,7 @@ def apnn_sumpool_fc(X: torch.Tensor, N: int, H: int, W: int, Cc: int, bits: int,
     """Global sum pooling + fully connected layer in one launch -> int32 [N][Cout]."""
     if out is None:
         out = torch.empty((N, Cout), dtype=torch.int32, device=X.device)
-    _check(lib().apnn_sumpool_fc(_ptr(X), N, H, W, Cc, bits, _ptr(Wp), Cout, p, encW, _ptr(out), _stream()))
+    _N.sumpool_fc(X, N, H, W, Cc, bits, Wp, Cout, p, encW, out)
     return out
 
 

@@ -1,4 +1,5 @@
-"""Build libapnn.so (the C-ABI library) and libapnn_bench.so (measurement probes) for gfx950 with hipcc, in-tree.
+"""Build libapnn.so (the C-ABI library), libapnn_bench.so (measurement probes) and _native.so (the Python module that
+binding.py calls through) for gfx950 with hipcc and g++, in-tree.
 
     python -m paper_2106_12169_amd.build        # incremental
     python -m paper_2106_12169_amd.build -f     # rebuild everything
@@ -20,6 +21,7 @@ OBJ = os.path.join(CSRC, "_build")
 LIB = os.path.join(HERE, "libapnn.so")
 BENCH_LIB = os.path.join(HERE, "libapnn_bench.so")
 BENCH_SOURCES = ["bench_probes.hip"]
+NATIVE = os.path.join(HERE, "_native.so")             # Python module over libapnn.so and torch's C++ interface
 
 # slowest translation units first, so that the parallel build is not left waiting for them
 SOURCES = ["mfma_inst_i8w_c4.hip", "mfma_inst_i8w_c2.hip", "mfma_inst_i8w_c8.hip", "mfma_inst_i8_c8.hip", "mfma_inst_i8_c4.hip", "mfma_inst_i8_c2.hip", "mfma_inst_256_pm1.hip", "mfma_inst_256_u2.hip", "mfma_inst_256_u1.hip",
@@ -68,7 +70,27 @@ def build(force: bool = False, extra=()) -> str:
         if (force or not os.path.exists(lib)
                 or os.path.getmtime(lib) < max(os.path.getmtime(o) for o in members)):
             subprocess.check_call(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", *members, "-o", lib])
+    build_native(force)
     return LIB
+
+
+def build_native(force: bool = False) -> str:
+    """Host code only: compiled against torch's headers, linked to libapnn.so beside it."""
+    import sysconfig
+
+    import torch
+    src, obj = os.path.join(CSRC, "native_binding.cpp"), os.path.join(OBJ, "native_binding.o")
+    root = os.path.dirname(torch.__file__)
+    if force or not os.path.exists(obj) or os.path.getmtime(obj) < _newest_dependency(obj, src):
+        subprocess.check_call(["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+                               "-I" + sysconfig.get_paths()["include"], "-isystem", os.path.join(root, "include"),
+                               "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+                               "-isystem", os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"),
+                               "-MD", "-MF", obj + ".d", "-c", src, "-o", obj])
+    if force or not os.path.exists(NATIVE) or os.path.getmtime(NATIVE) < max(os.path.getmtime(obj), os.path.getmtime(LIB)):
+        subprocess.check_call(["g++", "-shared", "-fPIC", obj, "-o", NATIVE, "-L" + HERE, "-lapnn", "-Wl,-rpath,$ORIGIN",
+                               "-L" + os.path.join(root, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"])
+    return NATIVE
 
 
 if __name__ == "__main__":

@@ -1,8 +1,9 @@
 """Layer chaining for a packed-activation network (minimal-traffic dataflow,
 Sec. 5.1): marshalling only.
 
-Weights are packed once at construction (off the timed path, as in Sec. 5.1);
-``forward`` enqueues one library call per node on the current stream: the 8-bit
+Weights are packed once at construction (off the timed path, as in Sec. 5.1), and
+the library calls of a pass are recorded once in a native Chain; ``forward``
+enqueues them, one per node, on the current stream: the 8-bit
 image goes to the input layer as it is, every other convolution reads packed
 bit planes and writes packed bit planes through the fused epilogue, the last
 layer produces int32 logits without requantisation.  All buffers are
@@ -53,6 +54,7 @@ class PackedNet:
                 self.buf[L.name] = torch.empty(B.apnn_packed_words(batch, L.Cout, L.q_out), dtype=torch.int32, device=device)
             else:
                 self.buf[L.name] = torch.empty(B.apnn_fmap_words(pixels, L.Cout, L.q_out), dtype=torch.int32, device=device)
+        self._record()
         torch.cuda.synchronize()
 
     def _conv_args(self, L: NetLayer) -> dict:
@@ -62,46 +64,49 @@ class PackedNet:
                     q_res=self._by_name[L.res].q_out if L.res else 0,
                     res_scale=L.res_scale, out=self.buf[L.name], pool=B.POOL_MAX2 if L.pool else B.POOL_NONE)
 
-    def forward(self, image: torch.Tensor) -> torch.Tensor:
-        """image: batch x 3 x H x W uint8 device tensor -> int32 logits batch x classes."""
+    def _record(self):
+        """The library calls of a pass, in order, on the buffers allocated above: what ``forward`` enqueues."""
+        chain = B.native().Chain()
         first = self.layers[0]
         paired = None
-        self.launches = 0                               # library calls (= kernel launches) of this pass
         for i, L in enumerate(self.layers):
             out = self.buf[L.name]
             if L is paired:
                 continue
-            self.launches += 1
             if L is first:
                 d = B.Conv(self.batch, L.H, L.W, L.Cin, L.Cout, L.R, L.S, L.stride, L.pad, L.p, L.q)
-                B.apnn_input_layer(d, self.w[L.name], image, q_out=L.q_out,
-                                   scale=self.scale[L.name], bias=self.bias[L.name], out=out)
+                chain.input_layer(d, self.w[L.name], None, False, L.q_out, self.scale[L.name], self.bias[L.name],
+                                  None, 0, 0.0, None, None, out, 0)
             elif L.kind == "conv":
                 nxt = self.layers[i + 1] if i + 1 < len(self.layers) else None
                 if (nxt is not None and nxt.kind == "conv" and nxt.src == L.src
                         and nxt.res != L.name and L.res != nxt.name and not L.pool and not nxt.pool):
                     # two convolutions of the same features that do not depend on each other (a down-sampling
                     # block's 3 x 3 convolution and its 1 x 1 shortcut): one call, one launch
-                    B.apnn_layer_pair(self._conv_args(L), self._conv_args(nxt))
+                    chain.layer_pair(*B.layer_args(self._conv_args(L)), *B.layer_args(self._conv_args(nxt)))
                     paired = nxt
                 else:
-                    a = self._conv_args(L)
-                    B.apnn_layer(a.pop("d"), a.pop("W"), a.pop("X"), **a)
+                    chain.layer(*B.layer_args(self._conv_args(L)))
             elif L.kind == "maxpool":
-                B.apnn_maxpool(self.buf[L.src], self.batch, L.H, L.W, L.Cin, L.q, L.R, L.stride, L.pad, out=out)
+                chain.maxpool(self.buf[L.src], self.batch, L.H, L.W, L.Cin, L.q, L.R, L.stride, L.pad, out)
             elif L.kind == "sumpool":
-                if L.name == self.fused_tail:
-                    self.launches -= 1                  # computed in the launch of the layer that reads it
-                    continue
-                B.apnn_sumpool(self.buf[L.src], self.batch, L.H, L.W, L.Cin, L.q, L.q_out, out=out)
+                if L.name != self.fused_tail:           # (else computed in the launch of the layer that reads it)
+                    chain.sumpool(self.buf[L.src], self.batch, L.H, L.W, L.Cin, L.q, L.q_out, out)
             elif L.kind == "fc" and L.src == self.fused_tail:
                 S = self._by_name[L.src]
-                B.apnn_sumpool_fc(self.buf[S.src], self.batch, S.H, S.W, S.Cin, S.q, self.w[L.name], L.Cout, L.p,
-                                  B.ENC_PM1, out=out)
+                chain.sumpool_fc(self.buf[S.src], self.batch, S.H, S.W, S.Cin, S.q, self.w[L.name], L.Cout, L.p,
+                                 B.ENC_PM1, out)
             elif L.kind == "fc":
                 # the pooled sums are a matrix operand; a 1 x 1 feature map is read as one (a 1 x 1 convolution)
                 d = B.Conv(self.batch, 1, 1, L.Cin, L.Cout, 1, 1, 1, 0, L.p, L.q)
-                B.apnn_layer(d, self.w[L.name], self.buf[L.src], is_gemm=self._by_name[L.src].kind == "sumpool", acc_out=out)
+                chain.layer(d, self.w[L.name], self.buf[L.src], self._by_name[L.src].kind == "sumpool", 0, None, None,
+                            None, 0, 0.0, out, None, None, 0)
             else:
                 raise ValueError(L.kind)
+        self._chain = chain
+        self.launches = len(chain)                      # library calls (= kernel launches) of a pass
+
+    def forward(self, image: torch.Tensor) -> torch.Tensor:
+        """image: batch x 3 x H x W uint8 device tensor -> int32 logits batch x classes."""
+        self._chain.run(image)
         return self.buf[self.layers[-1].name]

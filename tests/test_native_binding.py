@@ -1,0 +1,33 @@
+"""Host side of the native call path: what it refuses before the library is called, and the library's own errors."""
+import pytest
+import torch
+
+from paper_2106_12169_amd import binding as B
+
+
+def test_refuses_host_tensors_and_wrong_argument_types():
+    x = torch.zeros((4, 64), dtype=torch.uint8)
+    w = torch.zeros(64, dtype=torch.int32)
+    with pytest.raises(AssertionError):
+        B.apnn_pack(x, 2, B.ENC_UNSIGNED, out=w)
+    with pytest.raises(AssertionError):
+        B.apnn_gemm(w, w, 4, 4, 64, 1, 2, B.ENC_PM1, B.ENC_UNSIGNED, out=torch.zeros((4, 4), dtype=torch.int32))
+    with pytest.raises(AssertionError):
+        B.apnn_layer(B.Conv(1, 4, 4, 32, 32, 3, 3, 1, 1), w, w, q_out=2, scale=w, bias=w, out=w)
+    with pytest.raises(TypeError):
+        B.native().gemm(1, 2)
+    with pytest.raises(TypeError):
+        B.native().gemm(w.numpy(), None, 4, 4, 64, 1, 2, 1, 0, None)
+
+
+@pytest.mark.gpu
+def test_library_errors_arrive_with_status_and_text():
+    with pytest.raises(B.ApnnError) as e:
+        B.native().layer(B.Conv(1, 4, 4, 33, 32, 3, 3, 1, 1), None, None, False, 2, None, None, None, 0, 0.0, None, None, None, 0)
+    assert e.value.status == 1 and "multiple of 32" in str(e.value)
+    chain = B.native().Chain()
+    chain.maxpool(None, 1, 8, 8, 64, 2, 3, 2, 3, None)          # recorded as it is, refused when it runs: pad >= window
+    assert len(chain) == 1
+    with pytest.raises(B.ApnnError) as e:
+        chain.run(None)
+    assert e.value.status == 1 and "pad" in str(e.value)
