@@ -5,6 +5,8 @@
 // planes: it reads 32 source values, takes bit t of each (Eq. 2) and gathers
 // them LSB-first into the word of plane t.  The work is HBM-bound: rows*K bytes
 // in, rows*K*bits/8 bytes out.
+#include <type_traits>
+
 #include "common.h"
 #include "lane_util.h"
 
@@ -135,84 +137,153 @@ __global__ __launch_bounds__(256) void quantize_pack_wave_kernel(const float *__
     if (t < bits && kw < ldw) dst[(static_cast<size_t>(row) * bits + t) * ldw + kw] = static_cast<uint32_t>(word);
 }
 
-// Row-major source (matrix operand or NHWC feature map) whose rows start 16-byte aligned: the same work as
-// pack_generic_kernel with 32-bit index arithmetic and one division; the generic kernel's four 64-bit divisions per
-// thread cost more vector instructions than the bit gathering itself and kept a 16 MiB operand at 2.8 TB/s.
+// ---- bytes -> plane words.  x[i], i = 0 .. 7, holds the codes of positions i, 8 + i, 16 + i, 24 + i in its four bytes
+// (or, with one byte per pixel, channel i of four pixels): bit t of byte j of x[i] goes to bit 8 j + i of w[t].
+
+// Bits selected by m of b change places with the bits D higher in a.
+template <int D> __device__ __forceinline__ void swap_bits(uint32_t &a, uint32_t &b, uint32_t m)
+{
+    const uint32_t na = (a & m) | ((b << D) & ~m), nb = ((a >> D) & m) | (b & ~m);
+    a = na;
+    b = nb;
+}
+
+// One or two planes: the bits of a plane are OR-ed together position by position.  More: 8 x 8 bit-matrix
+// transposition inside every byte column (the stores of planes that do not exist drop the work behind them).
+template <int BITS> __device__ __forceinline__ void bytes_to_planes(uint32_t (&x)[8], uint32_t (&w)[BITS])
+{
+    if constexpr (BITS <= 2) {
+#pragma unroll
+        for (int t = 0; t < BITS; ++t) {
+            w[t] = 0;
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                w[t] |= (i >= t ? x[i] << (i - t) : x[i] >> (t - i)) & (0x01010101u << i);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) swap_bits<4>(x[i], x[i + 4], 0x0F0F0F0Fu);
+#pragma unroll
+        for (int i = 0; i < 8; i += 4) {
+            swap_bits<2>(x[i], x[i + 2], 0x33333333u);
+            swap_bits<2>(x[i + 1], x[i + 3], 0x33333333u);
+        }
+#pragma unroll
+        for (int i = 0; i < 8; i += 2) swap_bits<1>(x[i], x[i + 1], 0x55555555u);
+#pragma unroll
+        for (int t = 0; t < BITS; ++t) w[t] = x[t];
+    }
+}
+
+// Transposition of 4 x 4 bytes: byte j of r[i] <-> byte i of r[j].
+__device__ __forceinline__ void transpose_bytes(uint32_t &r0, uint32_t &r1, uint32_t &r2, uint32_t &r3)
+{
+    // __builtin_amdgcn_perm(hi, lo, sel): selector 0-3 takes a byte of lo, 4-7 of hi
+    const uint32_t a = __builtin_amdgcn_perm(r1, r0, 0x05010400u), b = __builtin_amdgcn_perm(r1, r0, 0x07030602u);
+    const uint32_t c = __builtin_amdgcn_perm(r3, r2, 0x05010400u), d = __builtin_amdgcn_perm(r3, r2, 0x07030602u);
+    r0 = __builtin_amdgcn_perm(c, a, 0x05040100u);
+    r1 = __builtin_amdgcn_perm(c, a, 0x07060302u);
+    r2 = __builtin_amdgcn_perm(d, b, 0x05040100u);
+    r3 = __builtin_amdgcn_perm(d, b, 0x07060302u);
+}
+
+// Row-major source (matrix operand or NHWC feature map), any K and any alignment; one thread per word of a row.  The 32
+// bytes of a word are two 16-byte loads at byte addresses; the last, incomplete word of a row loads the row's last 32
+// bytes and shifts its planes down, so no byte outside the row is read (rows of fewer than 32 bytes go byte by byte).
+// Bound by HBM: 4096 x 4096 2-bit codes take 4.5 us.  The generic kernel, which took every row whose length is no
+// multiple of 16, read such rows byte by byte: 777 rows of 1999 codes 9.6 us, here under 3 us.
+template <int BITS, bool PM1>
 __global__ __launch_bounds__(256) void pack_rows_kernel(const uint8_t *__restrict__ src, uint32_t *__restrict__ dst,
-                                                        uint32_t total, int K, int ldw, int bits, int pm1)
+                                                        uint32_t total, int K, int ldw)
 {
     const uint32_t idx = blockIdx.x * 256u + threadIdx.x;
     if (idx >= total) return;
     const uint32_t row = idx / static_cast<uint32_t>(ldw);
     const int kw = static_cast<int>(idx - row * ldw);
     const uint8_t *s = src + static_cast<size_t>(row) * K;
-    uint32_t w[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     const int k0 = kw * 32;
-    if (k0 + 32 <= K) {
-        const uint4 lo = *reinterpret_cast<const uint4 *>(s + k0);
-        const uint4 hi = *reinterpret_cast<const uint4 *>(s + k0 + 16);
-        const uint32_t d[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+    uint32_t w[BITS];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            if (pm1) {
-                w[0] |= gather4(positive_bytes(d[i])) << (4 * i);
-            } else {
+    for (int t = 0; t < BITS; ++t) w[t] = 0;
+    if (k0 < K) {
+        uint32_t x[8];
+        int down = 0;                                   // plane bits below the word's first position
+        if (K >= 32) {
+            const int kl = min(k0, K - 32);
+            down = k0 - kl;
+            uint32_t d[8];
+            __builtin_memcpy(d, s + kl, 16);
+            __builtin_memcpy(d + 4, s + kl + 16, 16);
+            // dwords of positions 8 j .. 8 j + 3 (even) and 8 j + 4 .. 8 j + 7 (odd) -> one register per position mod 8
 #pragma unroll
-                for (int t = 0; t < 8; ++t)
-                    if (t < bits) w[t] |= gather4((d[i] >> t) & 0x01010101u) << (4 * i);
-            }
+            for (int i = 0; i < 4; ++i) { x[i] = d[2 * i]; x[4 + i] = d[2 * i + 1]; }
+            transpose_bytes(x[0], x[1], x[2], x[3]);
+            transpose_bytes(x[4], x[5], x[6], x[7]);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) x[i] = 0;
+#pragma unroll
+            for (int k = 0; k < 32; ++k)
+                if (k < K) x[k & 7] |= static_cast<uint32_t>(s[k]) << (k & 24);
         }
-    } else {
-        for (int b = 0; b < 32 && k0 + b < K; ++b) {
-            const uint8_t v = s[k0 + b];
-            if (pm1) {
-                w[0] |= static_cast<uint32_t>(static_cast<int8_t>(v) > 0) << b;
-            } else {
+        if constexpr (PM1) {
 #pragma unroll
-                for (int t = 0; t < 8; ++t)
-                    if (t < bits) w[t] |= ((static_cast<uint32_t>(v) >> t) & 1u) << b;
-            }
+            for (int i = 0; i < 8; ++i) x[i] = positive_bytes(x[i]);
         }
+        bytes_to_planes<BITS>(x, w);
+#pragma unroll
+        for (int t = 0; t < BITS; ++t) w[t] >>= down;
     }
-    uint32_t *o = dst + static_cast<size_t>(row) * bits * ldw + kw;
+    uint32_t *o = dst + static_cast<size_t>(row) * BITS * ldw + kw;
 #pragma unroll
-    for (int t = 0; t < 8; ++t)
-        if (t < bits) o[static_cast<size_t>(t) * ldw] = w[t];
+    for (int t = 0; t < BITS; ++t) o[static_cast<size_t>(t) * ldw] = w[t];
 }
 
-// N x C x H x W source into the fmap layout.  A block owns 256 consecutive pixels of one image: wave w takes the
-// channel words w, w + 4, ...; lane = four consecutive pixels, one dword load per channel, contiguous across the
-// wave.  The plane words go to an LDS image of the block's output record ([pixel][plane][channel word], the pixel
-// stride padded to an odd number of words) and leave as contiguous 4-byte-per-lane stores: both sides of the
-// transposition are coalesced.  H W must be a multiple of 4 and the source 4-byte aligned (otherwise the generic
-// kernel, one byte per load, takes over); dynamic LDS: 256 * (bits * Cw | 1) words.
+// N x C x H x W source into the fmap layout.  A block owns PX consecutive pixels of one image: thread = four consecutive
+// pixels of one channel word, one dword load per channel (at byte addresses: H W need not be a multiple of 4; the
+// last four pixels of an image are loaded whole, overlapping their neighbours), contiguous across PX / 4 lanes.  The
+// plane words go to an LDS image of the block's output record ([pixel][plane][channel word], the pixel stride padded
+// to an odd number of words) and leave as contiguous 4-byte-per-lane stores: both sides of the transposition are
+// coalesced.  PX = 256 keeps whole cache lines together; PX = 64 gives small feature maps four times the blocks (4 x 96
+// x 27 x 31, 4 bits: 10.8 us in the generic kernel, one byte per load, here under 4 us).  Dynamic LDS: PX (BITS Cw | 1) words.
+template <int BITS, bool PM1, int PX>
 __global__ __launch_bounds__(256) void pack_nchw_kernel(const uint8_t *__restrict__ src, uint32_t *__restrict__ dst,
-                                                        int C, int HW, int Cw, int bits, int pm1, int blocks_per_image)
+                                                        int C, int HW, int Cw, int blocks_per_image)
 {
     extern __shared__ uint32_t rec[];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int n = blockIdx.x / blocks_per_image, p0 = (blockIdx.x - n * blocks_per_image) * 256;   // first pixel of the block
-    const int npix = min(256, HW - p0);                 // a multiple of 4
-    const int RW = bits * Cw, PS = RW | 1;              // words per pixel record, padded stride in LDS
-    const bool have = 4 * lane < npix;
-    for (int cw = wave; cw < Cw; cw += 4) {
-        const uint8_t *s = src + (static_cast<size_t>(n) * C + 32 * cw) * HW + p0 + 4 * lane;
-        uint32_t d[32];
+    constexpr int G = PX / 4;                           // groups of four pixels
+    const int n = blockIdx.x / blocks_per_image, p0 = (blockIdx.x - n * blocks_per_image) * PX;    // first pixel of the block
+    const int npix = min(PX, HW - p0);
+    const int RW = BITS * Cw, PS = RW | 1;              // words per pixel record, padded stride in LDS
+    const int l0 = 4 * (static_cast<int>(threadIdx.x) % G);
+    const int first = min(p0 + l0, HW - 4);             // (HW >= 4: host)
+    if (l0 < npix) {
+        for (int cw = threadIdx.x / G; cw < Cw; cw += 256 / G) {
+            const uint8_t *s = src + (static_cast<size_t>(n) * C + 32 * cw) * HW + first;
+            uint32_t d[32];
 #pragma unroll
-        for (int c = 0; c < 32; ++c) {
-            d[c] = (have && 32 * cw + c < C) ? *reinterpret_cast<const uint32_t *>(s + static_cast<size_t>(c) * HW) : 0u;
-            if (pm1) d[c] = positive_bytes(d[c]);       // bit 0 of every byte: value > 0
-        }
+            for (int c = 0; c < 32; ++c) {
+                d[c] = 0;
+                if (32 * cw + c < C) __builtin_memcpy(&d[c], s + static_cast<size_t>(c) * HW, 4);
+            }
+            uint32_t pl[4][BITS];                       // [channels 8 k .. 8 k + 7][plane], byte = pixel
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+            for (int k = 0; k < 4; ++k) {
+                uint32_t x[8];
 #pragma unroll
-            for (int t = 0; t < 8; ++t)
-                if (t < bits) {
-                    uint32_t w = 0;
+                for (int i = 0; i < 8; ++i) x[i] = PM1 ? positive_bytes(d[8 * k + i]) : d[8 * k + i];
+                bytes_to_planes<BITS>(x, pl[k]);
+            }
 #pragma unroll
-                    for (int c = 0; c < 32; ++c) w |= ((d[c] >> (8 * j + t)) & 1u) << c;
-                    rec[(4 * lane + j) * PS + t * Cw + cw] = w;
+            for (int t = 0; t < BITS; ++t) {
+                transpose_bytes(pl[0][t], pl[1][t], pl[2][t], pl[3][t]);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int px = first - p0 + j;      // below 0: a pixel of the previous block
+                    if (px >= 0) rec[px * PS + t * Cw + cw] = pl[j][t];
                 }
+            }
+        }
     }
     __syncthreads();
     uint32_t *o = dst + (static_cast<size_t>(n) * HW + p0) * RW;
@@ -399,18 +470,37 @@ __global__ __launch_bounds__(256) void pack_patch_weights_kernel(const uint8_t *
         if (t < bits) dst[(static_cast<size_t>(co) * bits + t) * ldw + r] = w[t];
 }
 
+// f(integral_constant<int, bits>, integral_constant<bool, -1/+1>)
+template <class F> static void with_bits(int bits, bool pm1, F &&f)
+{
+    using std::integral_constant;
+    if (pm1) return f(integral_constant<int, 1>{}, std::true_type{});
+    switch (bits) {
+        case 1: return f(integral_constant<int, 1>{}, std::false_type{});
+        case 2: return f(integral_constant<int, 2>{}, std::false_type{});
+        case 3: return f(integral_constant<int, 3>{}, std::false_type{});
+        case 4: return f(integral_constant<int, 4>{}, std::false_type{});
+        case 5: return f(integral_constant<int, 5>{}, std::false_type{});
+        case 6: return f(integral_constant<int, 6>{}, std::false_type{});
+        case 7: return f(integral_constant<int, 7>{}, std::false_type{});
+        default: return f(integral_constant<int, 8>{}, std::false_type{});
+    }
+}
+
 static int launch_pack(const char *who, const void *src, uint32_t *dst, const PackGeom &g, void *stream)
 {
     const int64_t total = g.rows * g.ldw;
     if (total == 0) return APNN_OK;
     if (total > (int64_t(1) << 38)) return fail(APNN_ERR_INVALID_ARG, "%s: tensor too large", who);
     const unsigned grid = static_cast<unsigned>(ceil_div(total, 256));
-    // plain rows of K contiguous bytes, every row 16-byte aligned, destination planes of a row adjacent
+    // plain rows of K contiguous bytes, destination planes of a row adjacent
     const bool rows_form = g.k_stride == 1 && g.row_stride == g.K && g.outer_div == g.rows && g.inner_n == 1 &&
-                           g.K % 16 == 0 && aligned16(src) && total < (int64_t(1) << 32) - 256 && g.K <= INT32_MAX;
+                           total < (int64_t(1) << 32) - 256 && g.K <= INT32_MAX - 32;
     if (rows_form)
-        hipLaunchKernelGGL(pack_rows_kernel, dim3(grid), dim3(256), 0, as_stream(stream), static_cast<const uint8_t *>(src),
-                           dst, static_cast<uint32_t>(total), static_cast<int>(g.K), g.ldw, g.bits, g.pm1);
+        with_bits(g.bits, g.pm1, [&](auto bc, auto pc) {
+            hipLaunchKernelGGL((pack_rows_kernel<decltype(bc)::value, decltype(pc)::value>), dim3(grid), dim3(256), 0, as_stream(stream),
+                               static_cast<const uint8_t *>(src), dst, static_cast<uint32_t>(total), static_cast<int>(g.K), g.ldw);
+        });
     else
         hipLaunchKernelGGL(pack_generic_kernel, dim3(grid), dim3(256), 0, as_stream(stream),
                            static_cast<const uint8_t *>(src), dst, g);
@@ -454,12 +544,19 @@ extern "C" int apnn_pack_fmap(const void *src_dev, apnn_layout layout, int64_t N
         g.row_stride = C; g.k_stride = 1; g.outer_div = g.rows; g.outer_stride = 0;
     } else {
         g.row_stride = 1; g.k_stride = HW; g.outer_div = HW; g.outer_stride = C * HW;
-        const int64_t bpi = ceil_div(HW, 256), lds = 4 * 256 * ((static_cast<int64_t>(bits) * g.ldw) | 1);
-        if (HW % 4 == 0 && (reinterpret_cast<uintptr_t>(src_dev) & 3u) == 0 && N * bpi <= 0x7FFFFFFF && lds <= 48 * 1024 &&
-            HW <= INT32_MAX - 256 && C <= INT32_MAX - 32) {
-            hipLaunchKernelGGL(pack_nchw_kernel, dim3(static_cast<unsigned>(N * bpi)), dim3(256), static_cast<size_t>(lds),
-                               as_stream(stream), static_cast<const uint8_t *>(src_dev), dst_dev, static_cast<int>(C),
-                               static_cast<int>(HW), g.ldw, bits, g.pm1, static_cast<int>(bpi));
+        // 64 pixels per block while 256 would leave compute units without a second one, and where 256 records of wide
+        // pixels exceed the LDS
+        const int px = N * ceil_div(HW, 256) < 512 || static_cast<int64_t>(bits) * g.ldw > 47 ? 64 : 256;
+        const int64_t bpi = ceil_div(HW, px), lds = 4 * px * ((static_cast<int64_t>(bits) * g.ldw) | 1);
+        if (HW >= 4 && N * bpi <= 0x7FFFFFFF && lds <= 48 * 1024 && HW <= INT32_MAX - 256 && C <= INT32_MAX - 32) {
+            with_bits(bits, g.pm1, [&](auto bc, auto pc) {
+                constexpr int BITS = decltype(bc)::value;
+                constexpr bool PM1 = decltype(pc)::value;
+                hipLaunchKernelGGL((px == 64 ? pack_nchw_kernel<BITS, PM1, 64> : pack_nchw_kernel<BITS, PM1, 256>),
+                                   dim3(static_cast<unsigned>(N * bpi)), dim3(256), static_cast<size_t>(lds), as_stream(stream),
+                                   static_cast<const uint8_t *>(src_dev), dst_dev, static_cast<int>(C), static_cast<int>(HW), g.ldw,
+                                   static_cast<int>(bpi));
+            });
             return check_launch("apnn_pack_fmap");
         }
     }

@@ -82,3 +82,24 @@ def test_quantize_matches_oracle(bits, rows, K):
     words = hp.words_u32(B.apnn_quantize(dev(x), zero, step, bits))
     codes, pad = hp.unpack_matrix(words, rows, K, bits)
     assert np.array_equal(codes, oracle.quantize(x, zero, step, bits)) and pad == 0
+
+
+@pytest.mark.parametrize("bits,enc", [(1, P), (1, U), (2, U), (4, U), (5, U), (8, U)])
+@pytest.mark.parametrize("K", [15, 31, 32, 33, 63, 65, 127, 1999])
+def test_pack_rows_of_any_length_and_alignment(K, bits, enc):
+    rows = 7
+    src = wl.operand(200 + K, rows, K, bits, enc)
+    buf = torch.zeros(rows * K + 3, dtype=dev(src).dtype, device="cuda")
+    view = buf[3:].view(rows, K)                       # rows at odd addresses
+    view.copy_(dev(src))
+    codes, pad = hp.unpack_matrix(hp.words_u32(B.apnn_pack(view, bits, enc)), rows, K, bits)
+    assert np.array_equal(codes, hp.pm1_to_bits(src) if enc == P else src) and pad == 0
+
+
+@pytest.mark.parametrize("bits,enc", [(1, P), (2, U), (5, U)])
+@pytest.mark.parametrize("N,C,H,W", [(2, 96, 27, 31), (1, 32, 1, 5), (1, 33, 1, 3), (3, 64, 5, 13), (1, 512, 17, 1), (40, 32, 65, 61)])
+def test_pack_nchw_of_any_frame(N, C, H, W, bits, enc):
+    nchw = wl.fair_signs(11, (N, C, H, W)) if enc == P else wl.uniform_codes(11, (N, C, H, W), bits)
+    words = hp.words_u32(B.apnn_pack_fmap(dev(nchw), B.LAYOUT_NCHW, bits, enc))
+    codes, pad = hp.unpack_fmap(words, N, H, W, C, bits)
+    assert np.array_equal(codes, hp.pm1_to_bits(nchw) if enc == P else nchw) and pad == 0
