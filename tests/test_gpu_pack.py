@@ -103,3 +103,15 @@ def test_pack_nchw_of_any_frame(N, C, H, W, bits, enc):
     words = hp.words_u32(B.apnn_pack_fmap(dev(nchw), B.LAYOUT_NCHW, bits, enc))
     codes, pad = hp.unpack_fmap(words, N, H, W, C, bits)
     assert np.array_equal(codes, hp.pm1_to_bits(nchw) if enc == P else nchw) and pad == 0
+
+
+@pytest.mark.parametrize("rows,K", [(3, 255), (2, 257), (2100, 513), (2050, 2049)])
+@pytest.mark.parametrize("bits,step", [(2, 0.5), (8, 2.0 ** -7), (3, 0.7), (8, 1.0 / 3)])
+def test_quantize_steps_and_segments(bits, step, rows, K):
+    x = wl.normals(12, (rows, K), 1.0, 1.5)
+    # values on and next to the boundaries of the codes
+    edge = np.float32(-1.0) + np.float32(step) * np.arange(1, min(K, 1 << bits), dtype=np.float32)
+    x[0, :edge.size] = edge
+    x[1, :edge.size] = np.nextafter(edge, np.float32(-100.0))
+    codes, pad = hp.unpack_matrix(hp.words_u32(B.apnn_quantize(dev(x), -1.0, step, bits)), rows, K, bits)
+    assert np.array_equal(codes, oracle.quantize(x, -1.0, step, bits)) and pad == 0
