@@ -80,8 +80,7 @@ struct Problem {
 
 // ---- FP4 matrix-core path --------------------------------------------------------
 // Applies when every partial sum stays an exact fp32 integer
-// (K max|a| max|b| < 2^24), the encodings are ones the kernel has a digit kind
-// for, and (convolution) the channel count allows 8-byte loader vectors.
+// (K max|a| max|b| < 2^24), the encodings are ones the kernel has a digit kind for.
 // The MFMA override set to 0 forces the AND+popcount kernel (the literal AP-Bit emulation).
 static bool mfma_kind(int planes, apnn_encoding enc, int &kind, int &digits, int64_t &maxabs)
 {
@@ -192,12 +191,20 @@ static bool try_mfma(const Problem &pr, MfmaParams &mp, void *stream, int &rc, S
     const bool fp4_exact = pr.Ktotal > 0 && round_up(pr.Ktotal, 1024) * maxA * maxB * (mp.pool == 2 ? 4 : 1) < (int64_t(1) << 24);
     if (!plan && try_int8(pr, mp, fp4_exact, stream, rc)) return true;
     if (!fp4_exact) return false;
-    if (pr.conv && mp.Cw % 2 != 0) return false;
+    // An odd number of channel words (Cin = 32, 96, ...) is gathered word by word, in the lane-private kernels only,
+    // with 32-bit offsets inside an image.  It costs about ten instructions a word where the 8- and 16-byte loaders
+    // spend three, and is still far ahead of the AND+popcount kernel (4 x 27 x 31, 96 -> 160 channels, 3 x 3, w2a4 with
+    // its pack: 34.4 us there, 11.1 here).
+    const bool odd_words = pr.conv && mp.Cw % 2 != 0;
+    if (odd_words) {
+        const double reach = (static_cast<double>(mp.H) + 2.0 * mp.pad + mp.R) * (static_cast<double>(mp.W) + 2.0 * mp.pad + mp.S);
+        if (ov(OV_MFMA_SMALL) == 0 || reach * pr.PA * mp.Cw >= 2147483648.0) return false;
+    }
     if (pr.conv && kA == OPK_PM1) kA = OPK_PM1Z;         // -1/+1 features: taps outside the frame must contribute 0
     mp.PA = pr.PA; mp.PB = pr.PB;
     mp.out_scale = (kA == OPK_U2 ? 2.0f : 1.0f) * (kB == OPK_U2 ? 2.0f : 1.0f);
     // 0 pad bits of two -1/+1 operands multiply to +1 at every padded K position
-    int t = pick_mfma_tile(pr.M, pr.N, pr.conv);
+    int t = odd_words ? 32 : pick_mfma_tile(pr.M, pr.N, pr.conv);
     if (kA == OPK_PM1Z && t == 128) t = 64;              // instantiated for the 64-tile and the small-layer kernel
     if ((t == 256 || t == 128) && !pr.conv) {   // the pipelined kernel addresses operands and output with 31-bit byte offsets
         const int64_t lim = int64_t(1) << 31;
@@ -227,15 +234,15 @@ static bool try_mfma(const Problem &pr, MfmaParams &mp, void *stream, int &rc, S
         const int64_t wave_tiles = ceil_div(pr.M, 32) * ceil_div(pr.N, 32 * fn);
         const unsigned g = static_cast<unsigned>(nsplit == 1 ? ceil_div(wave_tiles, 4) : tiles);
         const int gmax = static_cast<int>(ceil_div(nse / 4, nsplit));  // most groups of four steps a wave has
+        const int vw = mp.Cw % 4 == 0 ? 4 : odd_words ? 1 : 2;
         if (plan) {
-            if (pr.conv && nsplit == 4) {
+            if (pr.conv && nsplit == 4 && vw > 1) {
                 plan->ok = true; plan->mp = mp; plan->kA = kA; plan->kB = kB;
-                plan->vw = mp.Cw % 4 == 0 ? 4 : 2; plan->gmax = gmax; plan->grid = g;
+                plan->vw = vw; plan->gmax = gmax; plan->grid = g;
             }
             rc = APNN_OK;
             return true;
         }
-        const int vw = mp.Cw % 4 == 0 ? 4 : 2;
         ok = !pr.conv ? launch_mfma_small_matrix(mp, kA, kB, nsplit, g, as_stream(stream))
              : fn > 1 ? launch_mfma_small_conv_wide(mp, kA, kB, vw, fn, g, as_stream(stream))
                       : launch_mfma_small_conv(mp, kA, kB, vw, nsplit, gmax, g, as_stream(stream));

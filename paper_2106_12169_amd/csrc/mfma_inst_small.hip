@@ -1,5 +1,5 @@
 // Convolution instances of the small-layer matrix-core kernel (lane-private
-// operand loads, 32 x 32 tiles): loader vector width 4 or 2 words, one tile per
+// operand loads, 32 x 32 tiles): loader vector width 4, 2 or 1 words, one tile per
 // wave or one tile per block with K split over its four waves.
 #include "mfma_launch.h"
 #include "mfma_small.h"
@@ -18,7 +18,8 @@ template <int KA, int KB, int VW> static void go_vw(const MfmaParams &p, int nsp
 template <int KA, int KB> static void go(const MfmaParams &p, int vw, int nsplit, int gmax, unsigned grid, hipStream_t st)
 {
     if (vw == 4) go_vw<KA, KB, 4>(p, nsplit, gmax, grid, st);
-    else go_vw<KA, KB, 2>(p, nsplit, gmax, grid, st);
+    else if (vw == 2) go_vw<KA, KB, 2>(p, nsplit, gmax, grid, st);
+    else go_vw<KA, KB, 1>(p, nsplit, gmax, grid, st);
 }
 
 bool launch_mfma_small_conv(const MfmaParams &p, int kindA, int kindB, int vw, int nsplit, int gmax, unsigned grid,

@@ -9,7 +9,8 @@ template <int KA, int KB> static void go(const MfmaParams &p, int vw, int fn, un
 {
     (void)fn;                             // 2: the only width instantiated (4 measured slower)
     if (vw == 4) hipLaunchKernelGGL((mfma_small_wide_kernel<KA, KB, 4, 2>), dim3(grid), dim3(256), 0, st, p);
-    else hipLaunchKernelGGL((mfma_small_wide_kernel<KA, KB, 2, 2>), dim3(grid), dim3(256), 0, st, p);
+    else if (vw == 2) hipLaunchKernelGGL((mfma_small_wide_kernel<KA, KB, 2, 2>), dim3(grid), dim3(256), 0, st, p);
+    else hipLaunchKernelGGL((mfma_small_wide_kernel<KA, KB, 1, 2>), dim3(grid), dim3(256), 0, st, p);
 }
 
 bool launch_mfma_small_conv_wide(const MfmaParams &p, int kindA, int kindB, int vw, int fn, unsigned grid, hipStream_t st)

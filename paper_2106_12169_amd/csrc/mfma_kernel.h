@@ -312,6 +312,54 @@ __device__ __forceinline__ void tap_to_rs(const MfmaParams &p, int tap, int &r, 
     sc = tap - r * p.S;
 }
 
+// Convolution operands of one channel word per loader step (Cin an odd multiple of 32), for the lane-private kernels: K
+// words kk .. kk + 3 of a pixel's receptive field, zero beyond Kw and outside the frame.  Consecutive words lie in up to
+// four taps; one division finds the first, the others follow by counting.  The loads are unconditional (words that
+// contribute nothing read the operand's first word) so that all of them are in flight together instead of one behind
+// each test.  `image` is the pixel's image; offsets inside it are 32-bit (checked by the host).
+__device__ __forceinline__ uint4 load_conv_a_words(const MfmaParams &p, const uint32_t *image, int plane, int kk, int h0,
+                                                   int w0, bool validity)
+{
+    const int tap = static_cast<int>((static_cast<float>(kk) + 0.5f) * p.invCw);
+    int cw = kk - tap * p.Cw, r, sc;
+    tap_to_rs(p, tap, r, sc);
+    int off = (((h0 + r) * p.W + w0 + sc) * p.PA + plane) * p.Cw + cw;
+    const int next_tap = (p.PA - 1) * p.Cw, next_row = (p.W - p.S) * p.PA * p.Cw;
+    uint32_t t[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const bool in = kk + i < p.Kw && static_cast<unsigned>(h0 + r) < static_cast<unsigned>(p.H) &&
+                        static_cast<unsigned>(w0 + sc) < static_cast<unsigned>(p.W);
+        const uint32_t *src = in ? image + off : p.A;
+        const uint32_t w = validity ? ~0u : *src;
+        t[i] = in ? w : 0u;
+        ++off;
+        const bool wt = ++cw == p.Cw;
+        cw = wt ? 0 : cw;
+        off += wt ? next_tap : 0;
+        sc += wt ? 1 : 0;
+        const bool wr = sc == p.S;
+        sc = wr ? 0 : sc;
+        off += wr ? next_row : 0;
+        r += wr ? 1 : 0;
+    }
+    return make_uint4(t[0], t[1], t[2], t[3]);
+}
+
+// Words 0 .. 3 of a weight row of odd length, `left` of them inside the row: one 16-byte load from a 4-byte boundary.
+__device__ __forceinline__ uint4 load_conv_b_words(const uint32_t *src, int left)
+{
+    uint4 v = make_uint4(0, 0, 0, 0);
+    if (left >= 4) {
+        __builtin_memcpy(&v, src, 16);
+    } else {
+        if (left > 0) v.x = src[0];
+        if (left > 1) v.y = src[1];
+        if (left > 2) v.z = src[2];
+    }
+    return v;
+}
+
 // The four results of a pooling grid (exact integers in fp32): maximum or sum.
 __device__ __forceinline__ float pool4(int mode, float a, float b, float c, float d)
 {

@@ -54,6 +54,7 @@ __device__ __forceinline__ void mfma_small_wide_body(const MfmaParams &p, const 
         a_w0 = wo * p.stride - p.pad;
         a_pix = static_cast<int64_t>(n) * p.H * p.W;
     }
+    const uint32_t *a_image = p.A + a_pix * p.PA * p.Cw;                          // convolution: this lane's image
     const uint32_t *a_row = p.A + static_cast<int64_t>(gmA) * p.PA * p.ldwA;      // matrix mode
     const uint32_t *b_row[FN];
     bool b_ok[FN];
@@ -70,7 +71,9 @@ __device__ __forceinline__ void mfma_small_wide_body(const MfmaParams &p, const 
         const bool validity = KA == OPK_PM1Z && plane == 1;     // all ones for taps inside the frame, made up here
         if (validity) plane = 0;
         if (!a_ok || kk >= p.Kw || plane >= p.PA) return v;
-        if (CONV) {
+        if constexpr (CONV && VW == 1) {        // up to four taps
+            v = load_conv_a_words(p, a_image, plane, kk, a_h0, a_w0, validity);
+        } else if (CONV) {
             // VW = 4: the four words lie in one tap; VW = 2: two taps of two words each
 #pragma unroll
             for (int part = 0; part < 4 / VW; ++part) {
@@ -106,6 +109,8 @@ __device__ __forceinline__ void mfma_small_wide_body(const MfmaParams &p, const 
         const uint32_t *src = b_row[j] + static_cast<int64_t>(plane) * p.ldwB + kk;
         if (!CONV) {
             v = *reinterpret_cast<const uint4 *>(src);
+        } else if (VW == 1) {                   // conv weight rows of an odd number of words
+            v = load_conv_b_words(src, p.Kw - kk);
         } else {                                // conv weight rows are 8-byte aligned and an even number of words long
             const uint2 lo = *reinterpret_cast<const uint2 *>(src);
             v.x = lo.x; v.y = lo.y;

@@ -100,7 +100,7 @@ PM1_FEATURE_CONVS = [
     (64, 64, 7, 7, 5, 1, 2, U, 2, 1),            # mirrored Case III: unsigned 2-bit weights, two rings of overhang
     (256, 64, 6, 6, 3, 1, 1, U, 1, 1),
     (64, 64, 56, 56, 3, 1, 1, P, 1, 1),          # enough output pixels for the 64 x 64 block tile
-    (32, 64, 10, 9, 3, 1, 1, P, 1, 2),           # one channel word: only the AND+popcount kernel has this shape
+    (32, 64, 10, 9, 3, 1, 1, P, 1, 2),           # one channel word
     (96, 32, 7, 8, 3, 2, 2, U, 3, 1),            # three channel words, three weight planes, two rings of padding
     (160, 64, 5, 5, 4, 1, 2, P, 1, 1),           # K words not a multiple of the LDS read group
 ]
@@ -367,7 +367,7 @@ def test_patch_packer_geometries(C, H, W, R, S, stride, pad, bits):
     (1, 128, 96, 9, 11, 3, 1, 1, True),        # odd output frame: the last row and column of results are dropped
     (2, 64, 32, 12, 12, 1, 1, 0, False),       # 1 x 1
     (1, 64, 64, 56, 56, 3, 1, 1, True),        # enough rows for the 64 x 64 block tile
-    (3, 32, 64, 7, 10, 3, 1, 1, True),         # one channel word: only the AND+popcount kernel has this shape
+    (3, 32, 64, 7, 10, 3, 1, 1, True),         # one channel word
     (1, 96, 32, 13, 6, 2, 1, 1, False),        # three channel words, 2 x 2 kernel
 ])
 def test_fused_pooling_matches_oracle(force, mode, BS, Cin, Cout, H, Wd, R, stride, pad, with_res):
