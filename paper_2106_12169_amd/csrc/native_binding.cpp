@@ -4,7 +4,7 @@
 // Through ctypes (argument conversion, a tensor check and a stream look-up in Python per call) that was 6 - 8 us, of
 // which the launch itself is about 2; a network pass of 19 launches was bound by it (181 us of host work against
 // 131 us on the GPU).  Here the tensors are unpacked through torch's own C++ interface and the entry point of
-// include/apnn.h is called directly; a Chain holds the descriptors and pointers of a whole network and enqueues it
+// include/apnn.h is called directly; a Chain holds the descriptors and tensors of a whole network and enqueues it
 // with one call.  Nothing is computed here, and nothing depends on values: marshalling only.
 //
 // As with ctypes, the interpreter lock is released while the library runs (a launch can wait for queue space).
@@ -12,7 +12,10 @@
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include <cstring>
 #include <exception>
+#include <type_traits>
+#include <utility>
 #include <vector>
 
 #include "../../include/apnn.h"
@@ -39,6 +42,12 @@ PyObject *finish(int status)
     return nullptr;
 }
 
+// A tensor whose device pointer stands `offset` bytes into a recorded step.
+struct Ref {
+    size_t offset;
+    at::Tensor tensor;
+};
+
 // Reads positional arguments in order; after the first failure (Python error set) everything reads as zero.
 class Args {
 public:
@@ -52,6 +61,15 @@ public:
     int small() { return static_cast<int>(integer()); }
     float real() { return real(object()); }
     void *tensor() { return tensor(object()); }
+
+    // Pointers read by `tensor_into` are also noted in `refs`, by their place in the record that starts at `base`.
+    void note(const void *base, std::vector<Ref> *refs) { base_ = static_cast<const char *>(base); refs_ = refs; }
+    template <class T> void tensor_into(T *&field)
+    {
+        PyObject *o = object();
+        field = static_cast<T *>(tensor(o));
+        if (refs_ && field) refs_->push_back({static_cast<size_t>(reinterpret_cast<const char *>(&field) - base_), THPVariable_Unpack(o)});
+    }
 
     long long integer(PyObject *o)
     {
@@ -84,12 +102,14 @@ public:
             return nullptr;
         }
         const at::Tensor &t = THPVariable_Unpack(o);
-        if (!t.is_cuda() || !t.is_contiguous()) {
-            ok_ = false;
+        try {
+            if (t.is_cuda() && t.is_contiguous()) return t.data_ptr();
             PyErr_SetString(PyExc_AssertionError, "device, contiguous tensors only");
-            return nullptr;
+        } catch (const std::exception &e) {               // (a tensor without storage)
+            PyErr_SetString(PyExc_RuntimeError, e.what());
         }
-        return t.data_ptr();
+        ok_ = false;
+        return nullptr;
     }
     // sizes of a tensor of `n` dimensions
     void sizes(PyObject *o, int n, int64_t *out)
@@ -137,6 +157,8 @@ private:
     PyObject *const *a_;
     Py_ssize_t i_ = 0;
     bool ok_ = true;
+    const char *base_ = nullptr;
+    std::vector<Ref> *refs_ = nullptr;
 };
 
 template <class F> PyObject *call(F &&f)
@@ -164,25 +186,23 @@ struct Layer {
 
 // (d, W, X, is_gemm, q_out, scale, bias, residual, q_res, res_scale, acc_out, float_out, out, pool)
 constexpr Py_ssize_t kLayerArgs = 14;
-Layer read_layer(Args &a)
+void read_layer(Args &a, Layer &y)
 {
-    Layer y{};
     y.L.conv = a.conv();
-    y.W = static_cast<const uint32_t *>(a.tensor());
-    y.X = static_cast<const uint32_t *>(a.tensor());
+    a.tensor_into(y.W);
+    a.tensor_into(y.X);
     y.L.is_gemm = a.small();
     y.L.q_out = a.small();
-    y.L.scale_dev = static_cast<const float *>(a.tensor());
-    y.L.bias_dev = static_cast<const float *>(a.tensor());
-    y.L.residual_dev = static_cast<const uint32_t *>(a.tensor());
+    a.tensor_into(y.L.scale_dev);
+    a.tensor_into(y.L.bias_dev);
+    a.tensor_into(y.L.residual_dev);
     y.L.q_res = a.small();
     y.L.res_scale = a.real();
-    y.L.acc_out_dev = static_cast<int32_t *>(a.tensor());
-    y.L.float_out_dev = static_cast<float *>(a.tensor());
-    void *out = a.tensor();
-    y.out = y.L.q_out > 0 ? static_cast<uint32_t *>(out) : nullptr;
+    a.tensor_into(y.L.acc_out_dev);
+    a.tensor_into(y.L.float_out_dev);
+    if (y.L.q_out > 0) a.tensor_into(y.out);
+    else a.tensor();                                      // (checked, not passed on)
     y.L.pool = a.small();
-    return y;
 }
 
 PyObject *py_set_error(PyObject *, PyObject *cls)
@@ -265,7 +285,8 @@ PyObject *py_conv2d(PyObject *, PyObject *const *args, Py_ssize_t n)    // (d, W
 PyObject *py_layer(PyObject *, PyObject *const *args, Py_ssize_t n)
 {
     Args a(args, n, kLayerArgs);
-    const Layer y = read_layer(a);
+    Layer y{};
+    read_layer(a, y);
     if (!a.ok()) return nullptr;
     return call([&](void *st) { return apnn_layer(&y.L, y.W, y.X, y.out, st); });
 }
@@ -273,7 +294,9 @@ PyObject *py_layer(PyObject *, PyObject *const *args, Py_ssize_t n)
 PyObject *py_layer_pair(PyObject *, PyObject *const *args, Py_ssize_t n)
 {
     Args a(args, n, 2 * kLayerArgs);
-    const Layer x = read_layer(a), y = read_layer(a);
+    Layer x{}, y{};
+    read_layer(a, x);
+    read_layer(a, y);
     if (!a.ok()) return nullptr;
     return call([&](void *st) { return apnn_layer_pair(&x.L, x.W, x.X, x.out, &y.L, y.W, y.X, y.out, st); });
 }
@@ -281,7 +304,8 @@ PyObject *py_layer_pair(PyObject *, PyObject *const *args, Py_ssize_t n)
 PyObject *py_input_layer(PyObject *, PyObject *const *args, Py_ssize_t n)
 {
     Args a(args, n, kLayerArgs);
-    const Layer y = read_layer(a);
+    Layer y{};
+    read_layer(a, y);
     if (!a.ok()) return nullptr;
     return call([&](void *st) { return apnn_input_layer(&y.L, y.W, reinterpret_cast<const uint8_t *>(y.X), y.out, st); });
 }
@@ -322,9 +346,9 @@ PyObject *py_sumpool_fc(PyObject *, PyObject *const *args, Py_ssize_t n)    // (
     return call([&](void *st) { return apnn_sumpool_fc(X, N, H, W, C, bits, Wt, Cout, p, static_cast<apnn_encoding>(encW), out, st); });
 }
 
-// ---- Chain: the library calls of a network in order, recorded once (descriptors and the device pointers of the
-// weights and of the network's own buffers, which the owner keeps alive) and enqueued by one call.  Only the image
-// and the stream change between passes.
+// ---- Chain: the library calls of a network in order, recorded once (descriptors and the tensors they were given) and
+// enqueued by one call.  The tensors are held, and their device pointers are taken anew by every pass, so that one whose
+// storage is exchanged is read where it is now.
 struct Step {
     enum Kind { INPUT, LAYER, PAIR, MAXPOOL, SUMPOOL, SUMPOOL_FC } kind;
     Layer a, b;                                           // INPUT, LAYER: a; PAIR: a and b
@@ -334,84 +358,106 @@ struct Step {
     int bits, k, stride, pad, out_bits, p, encW;
     void *out;
 };
+static_assert(std::is_trivially_copyable<Step>::value, "pointers are written into copies by offset");
+
+struct Record {
+    Step step{};
+    std::vector<Ref> refs;
+
+    Step resolved() const
+    {
+        Step s = step;
+        for (const Ref &r : refs) {
+            void *p = r.tensor.data_ptr();
+            std::memcpy(reinterpret_cast<char *>(&s) + r.offset, &p, sizeof p);
+        }
+        return s;
+    }
+};
 
 struct ChainObject {
     PyObject_HEAD
-    std::vector<Step> *steps;
+    std::vector<Record> *records;
 };
 
 PyObject *chain_new(PyTypeObject *type, PyObject *, PyObject *)
 {
     auto *self = reinterpret_cast<ChainObject *>(type->tp_alloc(type, 0));
-    if (self) self->steps = new std::vector<Step>();
+    if (self) self->records = new std::vector<Record>();
     return reinterpret_cast<PyObject *>(self);
 }
 
 void chain_dealloc(PyObject *self)
 {
-    delete reinterpret_cast<ChainObject *>(self)->steps;
+    delete reinterpret_cast<ChainObject *>(self)->records;
     PyTypeObject *type = Py_TYPE(self);
     type->tp_free(self);
     Py_DECREF(type);
 }
 
-PyObject *append(PyObject *self, const Args &a, const Step &s)
+// Reads one call's arguments with `read` into a new record.
+template <class F> PyObject *append(PyObject *self, Args a, Step::Kind kind, F &&read)
 {
+    Record r;
+    r.step.kind = kind;
+    a.note(&r.step, &r.refs);
+    read(a, r.step);
     if (!a.ok()) return nullptr;
-    reinterpret_cast<ChainObject *>(self)->steps->push_back(s);
+    reinterpret_cast<ChainObject *>(self)->records->push_back(std::move(r));
     Py_RETURN_NONE;
 }
 
-PyObject *chain_layer_kind(PyObject *self, PyObject *const *args, Py_ssize_t n, Step::Kind kind)
+PyObject *chain_input_layer(PyObject *self, PyObject *const *args, Py_ssize_t n)
 {
-    Args a(args, n, kind == Step::PAIR ? 2 * kLayerArgs : kLayerArgs);
-    Step s{};
-    s.kind = kind;
-    s.a = read_layer(a);
-    if (kind == Step::PAIR) s.b = read_layer(a);
-    return append(self, a, s);
+    return append(self, Args(args, n, kLayerArgs), Step::INPUT, [](Args &a, Step &s) { read_layer(a, s.a); });
 }
 
-PyObject *chain_input_layer(PyObject *self, PyObject *const *args, Py_ssize_t n) { return chain_layer_kind(self, args, n, Step::INPUT); }
-PyObject *chain_layer(PyObject *self, PyObject *const *args, Py_ssize_t n) { return chain_layer_kind(self, args, n, Step::LAYER); }
-PyObject *chain_layer_pair(PyObject *self, PyObject *const *args, Py_ssize_t n) { return chain_layer_kind(self, args, n, Step::PAIR); }
+PyObject *chain_layer(PyObject *self, PyObject *const *args, Py_ssize_t n)
+{
+    return append(self, Args(args, n, kLayerArgs), Step::LAYER, [](Args &a, Step &s) { read_layer(a, s.a); });
+}
+
+PyObject *chain_layer_pair(PyObject *self, PyObject *const *args, Py_ssize_t n)
+{
+    return append(self, Args(args, n, 2 * kLayerArgs), Step::PAIR, [](Args &a, Step &s) {
+        read_layer(a, s.a);
+        read_layer(a, s.b);
+    });
+}
+
+void read_frame(Args &a, Step &s)
+{
+    a.tensor_into(s.X);
+    s.N = a.integer(); s.H = a.integer(); s.W = a.integer(); s.C = a.integer();
+    s.bits = a.small();
+}
 
 PyObject *chain_maxpool(PyObject *self, PyObject *const *args, Py_ssize_t n)
 {
-    Args a(args, n, 10);
-    Step s{};
-    s.kind = Step::MAXPOOL;
-    s.X = static_cast<const uint32_t *>(a.tensor());
-    s.N = a.integer(); s.H = a.integer(); s.W = a.integer(); s.C = a.integer();
-    s.bits = a.small(); s.k = a.small(); s.stride = a.small(); s.pad = a.small();
-    s.out = a.tensor();
-    return append(self, a, s);
+    return append(self, Args(args, n, 10), Step::MAXPOOL, [](Args &a, Step &s) {
+        read_frame(a, s);
+        s.k = a.small(); s.stride = a.small(); s.pad = a.small();
+        a.tensor_into(s.out);
+    });
 }
 
 PyObject *chain_sumpool(PyObject *self, PyObject *const *args, Py_ssize_t n)
 {
-    Args a(args, n, 8);
-    Step s{};
-    s.kind = Step::SUMPOOL;
-    s.X = static_cast<const uint32_t *>(a.tensor());
-    s.N = a.integer(); s.H = a.integer(); s.W = a.integer(); s.C = a.integer();
-    s.bits = a.small(); s.out_bits = a.small();
-    s.out = a.tensor();
-    return append(self, a, s);
+    return append(self, Args(args, n, 8), Step::SUMPOOL, [](Args &a, Step &s) {
+        read_frame(a, s);
+        s.out_bits = a.small();
+        a.tensor_into(s.out);
+    });
 }
 
 PyObject *chain_sumpool_fc(PyObject *self, PyObject *const *args, Py_ssize_t n)
 {
-    Args a(args, n, 11);
-    Step s{};
-    s.kind = Step::SUMPOOL_FC;
-    s.X = static_cast<const uint32_t *>(a.tensor());
-    s.N = a.integer(); s.H = a.integer(); s.W = a.integer(); s.C = a.integer();
-    s.bits = a.small();
-    s.Wt = static_cast<const uint32_t *>(a.tensor());
-    s.Cout = a.integer(); s.p = a.small(); s.encW = a.small();
-    s.out = a.tensor();
-    return append(self, a, s);
+    return append(self, Args(args, n, 11), Step::SUMPOOL_FC, [](Args &a, Step &s) {
+        read_frame(a, s);
+        a.tensor_into(s.Wt);
+        s.Cout = a.integer(); s.p = a.small(); s.encW = a.small();
+        a.tensor_into(s.out);
+    });
 }
 
 int run_step(const Step &s, const void *image, void *stream)
@@ -435,7 +481,15 @@ PyObject *chain_run(PyObject *self, PyObject *const *args, Py_ssize_t n)    // (
     Args a(args, n, 1);
     const void *image = a.tensor();
     if (!a.ok()) return nullptr;
-    const auto &steps = *reinterpret_cast<ChainObject *>(self)->steps;
+    const auto &records = *reinterpret_cast<ChainObject *>(self)->records;
+    std::vector<Step> steps;                              // this pass's own, made while the interpreter lock is held
+    try {
+        steps.reserve(records.size());
+        for (const Record &r : records) steps.push_back(r.resolved());
+    } catch (const std::exception &e) {
+        PyErr_SetString(PyExc_RuntimeError, e.what());
+        return nullptr;
+    }
     return call([&](void *st) {
         for (const Step &s : steps)
             if (const int rc = run_step(s, image, st)) return rc;
@@ -443,7 +497,7 @@ PyObject *chain_run(PyObject *self, PyObject *const *args, Py_ssize_t n)    // (
     });
 }
 
-Py_ssize_t chain_length(PyObject *self) { return static_cast<Py_ssize_t>(reinterpret_cast<ChainObject *>(self)->steps->size()); }
+Py_ssize_t chain_length(PyObject *self) { return static_cast<Py_ssize_t>(reinterpret_cast<ChainObject *>(self)->records->size()); }
 
 #define FAST(name, f) {name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(f)), METH_FASTCALL, nullptr}
 

@@ -21,6 +21,24 @@ from . import binding as B
 from .workloads import NetLayer
 
 
+class _Tensors(dict):
+    """Device tensors by layer name; notes that an entry was exchanged, so that the next pass is recorded with it."""
+    changed = False
+
+
+def _noting(name):
+    method = getattr(dict, name)
+
+    def call(self, *args, **kwargs):
+        self.changed = True
+        return method(self, *args, **kwargs)
+    return call
+
+
+for _name in ("__setitem__", "__delitem__", "__ior__", "update", "setdefault", "pop", "popitem", "clear"):
+    setattr(_Tensors, _name, _noting(_name))
+
+
 class PackedNet:
     def __init__(self, layers: List[NetLayer], params: Dict[str, tuple], batch: int, device="cuda", fuse_tail: bool = True):
         """fuse_tail: a global sum pooling whose only reader is the last fully connected layer shares that layer's
@@ -56,6 +74,15 @@ class PackedNet:
                 self.buf[L.name] = torch.empty(B.apnn_fmap_words(pixels, L.Cout, L.q_out), dtype=torch.int32, device=device)
         self._record()
         torch.cuda.synchronize()
+
+    def __setattr__(self, name, value):
+        if name in ("w", "scale", "bias", "buf"):
+            value = _Tensors(value)
+            value.changed = True
+        object.__setattr__(self, name, value)
+
+    def __getstate__(self):
+        return {**self.__dict__, "_chain": None}        # the recording belongs to this object's tensors
 
     def _conv_args(self, L: NetLayer) -> dict:
         d = B.Conv(self.batch, L.H, L.W, L.Cin, L.Cout, L.R, L.S, L.stride, L.pad, L.p, L.q)
@@ -105,8 +132,12 @@ class PackedNet:
                 raise ValueError(L.kind)
         self._chain = chain
         self.launches = len(chain)                      # library calls (= kernel launches) of a pass
+        for tensors in (self.w, self.scale, self.bias, self.buf):
+            tensors.changed = False
 
     def forward(self, image: torch.Tensor) -> torch.Tensor:
         """image: batch x 3 x H x W uint8 device tensor -> int32 logits batch x classes."""
+        if self._chain is None or self.w.changed or self.scale.changed or self.bias.changed or self.buf.changed:
+            self._record()
         self._chain.run(image)
         return self.buf[self.layers[-1].name]

@@ -1,5 +1,7 @@
 """GPU parity of the chained networks (ResNet-18-, AlexNet- and VGG-16-shaped): every node's packed codes and
 the int32 logits bit-exact against the chained oracle."""
+import copy
+
 import numpy as np
 import pytest
 import torch
@@ -69,6 +71,34 @@ def test_resnet18_shape_batch8_logits_and_graph_replay():
         g.replay()
         torch.cuda.synchronize()
         assert np.array_equal(net.buf["fc"].cpu().numpy(), want["fc"])
+
+
+@pytest.mark.parametrize("how", ["in place", "entry", "storage", "dict", "copy"])
+def test_a_pass_uses_the_tensors_the_network_holds_now(how):
+    """Weights, constants and buffers exchanged between passes: nothing of the old ones is used."""
+    layers = wl.resnet18_layers(image_hw=64, num_classes=100, widths=(32, 64, 96, 128))
+    old, new = wl.network_params(layers, seed=1), wl.network_params(layers, seed=2)
+    img = wl.image_batch(3, 2, 64)
+    net, other = PackedNet(layers, old, 2, fuse_tail=False), PackedNet(layers, new, 2, fuse_tail=False)
+    net.forward(torch.from_numpy(img).cuda())
+    if how == "copy":
+        net = copy.deepcopy(net)
+    for name in ("w", "scale", "bias", "buf"):
+        mine, theirs = getattr(net, name), getattr(other, name)
+        if how == "dict":
+            setattr(net, name, {k: v.clone() for k, v in theirs.items()})
+            continue
+        for k in theirs:
+            if how == "entry":
+                mine[k] = theirs[k].clone()
+            elif how == "storage":
+                mine[k].data = theirs[k].clone()
+            else:
+                mine[k].copy_(theirs[k])
+    logits = net.forward(torch.from_numpy(img).cuda())
+    torch.cuda.synchronize()
+    assert logits is net.buf["fc"]
+    _check_all_nodes(layers, net, onet.run(layers, new, img), 2)
 
 
 def test_resnet18_shape_batch32_every_node():

@@ -115,3 +115,12 @@ def test_quantize_steps_and_segments(bits, step, rows, K):
     x[1, :edge.size] = np.nextafter(edge, np.float32(-100.0))
     codes, pad = hp.unpack_matrix(hp.words_u32(B.apnn_quantize(dev(x), -1.0, step, bits)), rows, K, bits)
     assert np.array_equal(codes, oracle.quantize(x, -1.0, step, bits)) and pad == 0
+
+
+@pytest.mark.parametrize("K", [260, 2048])
+@pytest.mark.parametrize("zero,step", [(-1.0, 0.25), (0.5, 0.3), (0.0, 2.0 ** 100), (0.0, 3e-30)])
+def test_quantize_of_infinities_nan_and_the_ends_of_the_range(zero, step, K):
+    special = np.array([np.inf, -np.inf, np.nan, 3.4e38, -3.4e38, 1e-45, -1e-45, 0.0, -0.0], dtype=np.float32)
+    x = np.resize(special, (2050, K))
+    codes, pad = hp.unpack_matrix(hp.words_u32(B.apnn_quantize(dev(x), zero, step, 5)), 2050, K, 5)
+    assert np.array_equal(codes, oracle.quantize(x, zero, step, 5)) and pad == 0
