@@ -76,6 +76,7 @@ struct Problem {
     int64_t M, N, Ktotal;      // rows, columns, logical reduction length
     int PA, PB;
     apnn_encoding encA, encB;
+    int64_t images;            // convolution: N
 };
 
 // ---- FP4 matrix-core path --------------------------------------------------------
@@ -196,10 +197,9 @@ static bool try_mfma(const Problem &pr, MfmaParams &mp, void *stream, int &rc, S
     // spend three, and is still far ahead of the AND+popcount kernel (4 x 27 x 31, 96 -> 160 channels, 3 x 3, w2a4 with
     // its pack: 34.4 us there, 11.1 here).
     const bool odd_words = pr.conv && mp.Cw % 2 != 0;
-    if (odd_words) {
-        const double reach = (static_cast<double>(mp.H) + 2.0 * mp.pad + mp.R) * (static_cast<double>(mp.W) + 2.0 * mp.pad + mp.S);
-        if (ov(OV_MFMA_SMALL) == 0 || reach * pr.PA * mp.Cw >= 2147483648.0) return false;
-    }
+    // words of one padded image
+    const double reach = (static_cast<double>(mp.H) + 2.0 * mp.pad + mp.R) * (static_cast<double>(mp.W) + 2.0 * mp.pad + mp.S) * pr.PA * mp.Cw;
+    if (odd_words && (ov(OV_MFMA_SMALL) == 0 || reach >= 2147483648.0)) return false;
     if (pr.conv && kA == OPK_PM1) kA = OPK_PM1Z;         // -1/+1 features: taps outside the frame must contribute 0
     mp.PA = pr.PA; mp.PB = pr.PB;
     mp.out_scale = (kA == OPK_U2 ? 2.0f : 1.0f) * (kB == OPK_U2 ? 2.0f : 1.0f);
@@ -228,9 +228,16 @@ static bool try_mfma(const Problem &pr, MfmaParams &mp, void *stream, int &rc, S
         mp.c0 = (kA == OPK_PM1 && kB == OPK_PM1) ? -static_cast<int>(nse * 64 - pr.Ktotal) : 0;
         // Large convolution layers (one wave tile per wave): 32 x 64 wave tiles, so that the row operand is loaded,
         // decoded and expanded once for 64 output channels.
+        // That kernel addresses both operands with 32-bit byte offsets, and walks up to eight rows past a frame.
+        const double bytesA = 4.0 * pr.images * mp.H * mp.W * pr.PA * mp.Cw, bytesB = 4.0 * pr.N * pr.PB * mp.ldwB;
+        const bool wide_fits = pr.conv && reach < 134217728.0 && bytesA < 2147483648.0 && bytesB < 2147483648.0;
+        if (wide_fits) {
+            mp.bytesA = static_cast<uint32_t>(bytesA);
+            mp.bytesB = static_cast<uint32_t>(bytesB);
+        }
         int fn = 1;
-        if (pr.conv && nsplit == 1) fn = pr.N % 64 == 0 ? 2 : 1;
-        if (const int f = ov(OV_MFMA_FN); f == 1 || (f == 2 && pr.conv && nsplit == 1)) fn = f;   // (tests, experiments)
+        if (wide_fits && nsplit == 1) fn = pr.N % 64 == 0 ? 2 : 1;
+        if (const int f = ov(OV_MFMA_FN); f == 1 || (f == 2 && wide_fits && nsplit == 1)) fn = f;   // (tests, experiments)
         const int64_t wave_tiles = ceil_div(pr.M, 32) * ceil_div(pr.N, 32 * fn);
         const unsigned g = static_cast<unsigned>(nsplit == 1 ? ceil_div(wave_tiles, 4) : tiles);
         const int gmax = static_cast<int>(ceil_div(nse / 4, nsplit));  // most groups of four steps a wave has
@@ -438,7 +445,7 @@ static int layer_impl(const char *who, const apnn_layer_desc &L, const uint32_t 
         p.out = L.q_out > 0 ? out_packed : nullptr; p.q_out = L.q_out;
     }
     p.NW = static_cast<int>(N / 32);
-    Problem pr{who, !is_gemm, M, N, is_gemm ? d.Cin : d.Cin * d.R * d.S, p.PA, p.PB, d.encX, d.encW};
+    Problem pr{who, !is_gemm, M, N, is_gemm ? d.Cin : d.Cin * d.R * d.S, p.PA, p.PB, d.encX, d.encW, d.N};
     return run_either(pr, p, vw, stream, plan);
 }
 
@@ -472,7 +479,7 @@ extern "C" int apnn_gemm(const uint32_t *W_dev, const uint32_t *X_dev, int32_t *
     if (const char *e = std::getenv("APNN_DBG_PTR")) t.T = reinterpret_cast<float *>(std::strtoull(e, nullptr, 0));
 #endif
     t.NW = static_cast<int>(N / 32);
-    Problem pr{"apnn_gemm", false, M, N, K, p, q, encW, encX};
+    Problem pr{"apnn_gemm", false, M, N, K, p, q, encW, encX, 0};
     return run_either(pr, t, 4, stream, nullptr);
 }
 

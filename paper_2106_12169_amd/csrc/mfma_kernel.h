@@ -96,6 +96,7 @@ struct MfmaParams {
     // the decoded row sums of the operands; flipA / flipB invert the top plane of an 8-plane operand (value - 128)
     uint32_t flipA, flipB;
     int accmul, mulA, mulB;
+    uint32_t bytesA, bytesB; // mfma_small_wide_kernel: sizes of the operands (host: below 2^31)
 };
 
 // A 32-bit constant the optimiser cannot fold: it then lives in a register, so
@@ -131,10 +132,13 @@ template <int KIND> __device__ __forceinline__ void expand_fp4(uint32_t x0, uint
     } else {                                    // v = 2 x1 + x0 -> code x1 x0 = v / 2 (0, 0.5, 1, 1.5):
         // the two planes ARE the FP4 code of half the value, so no recoding is needed;
         // the host-set out_scale (2 per two-plane operand) restores the factor exactly
-        out[0] = ((x1 << 1) & k.m2) | (x0 & k.m1);
-        out[1] = (x1 & k.m2) | ((x0 >> 1) & k.m1);
-        out[2] = ((x1 >> 1) & k.m2) | ((x0 >> 2) & k.m1);
-        out[3] = ((x1 >> 2) & k.m2) | ((x0 >> 3) & k.m1);
+        // (the pairs of even and of odd positions side by side first: ten instructions instead of fourteen)
+        const uint32_t m3 = k.m1 | k.m2;
+        const uint32_t even = ((x1 << 1) & 0xAAAAAAAAu) | (x0 & 0x55555555u), odd = (x1 & 0xAAAAAAAAu) | ((x0 >> 1) & 0x55555555u);
+        out[0] = even & m3;
+        out[1] = odd & m3;
+        out[2] = (even >> 2) & m3;
+        out[3] = (odd >> 2) & m3;
     }
     out[4] = out[5] = out[6] = out[7] = 0;
 }
@@ -183,7 +187,7 @@ __device__ __forceinline__ uint32_t load_res_rows8(const MfmaParams &p, int row0
     const int b = lane >> 3, row = row0 + (lane & 7);
     uint32_t w = 0;
     if (p.res && b < p.q_res && row < p.M && wcol < p.NW)
-        w = p.res[(static_cast<int64_t>(row) * p.q_res + b) * p.NW + wcol];
+        w = p.res[static_cast<int64_t>(row) * (p.q_res * p.NW) + (b * p.NW + wcol)];     // one 64-bit multiply-add
     return w;
 }
 
@@ -272,7 +276,7 @@ __device__ __forceinline__ void finish_rows8(const MfmaParams &p, const float (&
     const int b = lane >> 3, row = row0 + (lane & 7);
     const int wcol = gn >> 5;                           // (a block tile can reach beyond N: whole 32-column tiles then)
     if (b < p.q_out && row < p.M && wcol < p.NW)
-        p.out[(static_cast<int64_t>(row) * p.q_out + b) * p.NW + wcol] = static_cast<uint32_t>(word);
+        p.out[static_cast<int64_t>(row) * (p.q_out * p.NW) + (b * p.NW + wcol)] = static_cast<uint32_t>(word);
 }
 
 __device__ __forceinline__ int div_by_reciprocal(int n, float inv)
