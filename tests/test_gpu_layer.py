@@ -509,3 +509,22 @@ def test_layer_pair_mixed_kinds_and_validation():
                                  C.byref(Lb), conv["W"].data_ptr(), conv["X"].data_ptr(), None, st)
     torch.cuda.synchronize()
     assert rc == 1 and (acc.cpu().numpy() == -5).all()
+
+
+@pytest.mark.parametrize("Cin,Cout,H,Wd,R,S,stride,pad,encW,p,encX,q", [
+    (64, 64, 8, 9, 3, 3, 1, 1, P, 1, U, 2),      # two words a tap: the last group has two of four steps
+    (64, 96, 5, 5, 1, 1, 1, 0, U, 3, U, 3),      # one step per lane half, a missing high plane on both sides, half a column tile
+    (192, 32, 4, 33, 2, 3, 1, 1, U, 1, U, 5),    # six words a tap, three feature digits, one row tile over several image rows
+    (128, 64, 1, 1, 5, 5, 1, 2, P, 1, U, 4),     # a frame of one pixel: every other tap outside
+    (128, 160, 7, 3, 3, 1, 2, 4, U, 2, P, 1),    # more padding than kernel, -1/+1 features
+    (32, 64, 6, 7, 3, 3, 1, 1, P, 1, U, 3),      # one word a tap: lane halves of unequal length
+    (160, 64, 3, 4, 3, 2, 3, 1, U, 2, U, 2),     # five words a tap
+])
+def test_wide_wave_tiles_at_their_edges(Cin, Cout, H, Wd, R, S, stride, pad, encW, p, encX, q):
+    _force("32split1wide2")
+    Wv = wl.operand(301 + Cin, Cout, Cin * R * S, p, encW).reshape(Cout, Cin, R, S)
+    Xv = wl.operand(302 + H, 3 * Cin, H * Wd, q, encX).reshape(3, Cin, H, Wd)
+    d = B.Conv(3, H, Wd, Cin, Cout, R, S, stride, pad, p, q, encW, encX)
+    Y = B.apnn_conv2d(d, B.apnn_pack_conv_weights(dev(Wv), p, encW), B.apnn_pack_fmap(dev(Xv), B.LAYOUT_NCHW, q, encX))
+    torch.cuda.synchronize()
+    assert np.array_equal(Y.cpu().numpy().transpose(0, 3, 1, 2), oracle.conv2d(Wv, encW, p, Xv, encX, q, stride, pad))
