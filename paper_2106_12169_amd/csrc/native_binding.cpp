@@ -48,6 +48,21 @@ struct Ref {
     at::Tensor tensor;
 };
 
+// What a kernel is given of a tensor: its device pointer.  False (Python error set) if it has none that can be used.
+bool device_pointer(const at::Tensor &t, void *&p)
+{
+    try {
+        if (t.is_cuda() && t.is_contiguous()) {
+            p = t.data_ptr();
+            return true;
+        }
+        PyErr_SetString(PyExc_AssertionError, "device, contiguous tensors only");
+    } catch (const std::exception &e) {                   // (a tensor without storage)
+        PyErr_SetString(PyExc_RuntimeError, e.what());
+    }
+    return false;
+}
+
 // Reads positional arguments in order; after the first failure (Python error set) everything reads as zero.
 class Args {
 public:
@@ -68,7 +83,7 @@ public:
     {
         PyObject *o = object();
         field = static_cast<T *>(tensor(o));
-        if (refs_ && field) refs_->push_back({static_cast<size_t>(reinterpret_cast<const char *>(&field) - base_), THPVariable_Unpack(o)});
+        if (refs_ && ok_ && o != Py_None) refs_->push_back({static_cast<size_t>(reinterpret_cast<const char *>(&field) - base_), THPVariable_Unpack(o)});
     }
 
     long long integer(PyObject *o)
@@ -101,15 +116,9 @@ public:
             PyErr_SetString(PyExc_TypeError, "a torch tensor is expected");
             return nullptr;
         }
-        const at::Tensor &t = THPVariable_Unpack(o);
-        try {
-            if (t.is_cuda() && t.is_contiguous()) return t.data_ptr();
-            PyErr_SetString(PyExc_AssertionError, "device, contiguous tensors only");
-        } catch (const std::exception &e) {               // (a tensor without storage)
-            PyErr_SetString(PyExc_RuntimeError, e.what());
-        }
-        ok_ = false;
-        return nullptr;
+        void *p = nullptr;
+        ok_ = device_pointer(THPVariable_Unpack(o), p);
+        return p;
     }
     // sizes of a tensor of `n` dimensions
     void sizes(PyObject *o, int n, int64_t *out)
@@ -347,8 +356,8 @@ PyObject *py_sumpool_fc(PyObject *, PyObject *const *args, Py_ssize_t n)    // (
 }
 
 // ---- Chain: the library calls of a network in order, recorded once (descriptors and the tensors they were given) and
-// enqueued by one call.  The tensors are held, and their device pointers are taken anew by every pass, so that one whose
-// storage is exchanged is read where it is now.
+// enqueued by one call.  The tensors are held, and their device pointers are checked and taken anew by every pass, so that
+// one whose storage is exchanged is read where it is now, and refused if it now lies on the host or is strided.
 struct Step {
     enum Kind { INPUT, LAYER, PAIR, MAXPOOL, SUMPOOL, SUMPOOL_FC } kind;
     Layer a, b;                                           // INPUT, LAYER: a; PAIR: a and b
@@ -364,14 +373,16 @@ struct Record {
     Step step{};
     std::vector<Ref> refs;
 
-    Step resolved() const
+    // The step with the pointers of now; false (Python error set) if a tensor has none that can be used.
+    bool resolve(Step &s) const
     {
-        Step s = step;
+        s = step;
         for (const Ref &r : refs) {
-            void *p = r.tensor.data_ptr();
+            void *p = nullptr;
+            if (!device_pointer(r.tensor, p)) return false;
             std::memcpy(reinterpret_cast<char *>(&s) + r.offset, &p, sizeof p);
         }
-        return s;
+        return true;
     }
 };
 
@@ -482,14 +493,9 @@ PyObject *chain_run(PyObject *self, PyObject *const *args, Py_ssize_t n)    // (
     const void *image = a.tensor();
     if (!a.ok()) return nullptr;
     const auto &records = *reinterpret_cast<ChainObject *>(self)->records;
-    std::vector<Step> steps;                              // this pass's own, made while the interpreter lock is held
-    try {
-        steps.reserve(records.size());
-        for (const Record &r : records) steps.push_back(r.resolved());
-    } catch (const std::exception &e) {
-        PyErr_SetString(PyExc_RuntimeError, e.what());
-        return nullptr;
-    }
+    std::vector<Step> steps(records.size());              // this pass's own, made while the interpreter lock is held
+    for (size_t i = 0; i < records.size(); ++i)
+        if (!records[i].resolve(steps[i])) return nullptr;
     return call([&](void *st) {
         for (const Step &s : steps)
             if (const int rc = run_step(s, image, st)) return rc;

@@ -31,3 +31,24 @@ def test_library_errors_arrive_with_status_and_text():
     with pytest.raises(B.ApnnError) as e:
         chain.run(None)
     assert e.value.status == 1 and "pad" in str(e.value)
+
+
+@pytest.mark.gpu
+def test_a_recorded_step_checks_its_tensors_in_every_pass():
+    X = torch.full((8 * 8 * 2 * 2,), -1, dtype=torch.int32, device="cuda")
+    out = torch.empty(0, dtype=torch.int32, device="cuda")      # no storage yet when the step is recorded
+    chain = B.native().Chain()
+    chain.maxpool(X, 1, 8, 8, 64, 2, 2, 2, 0, out)
+    out.data = torch.zeros(4 * 4 * 2 * 2, dtype=torch.int32, device="cuda")
+    chain.run(None)
+    assert (out.cpu() == -1).all()
+    out.zero_()
+    good = X.data
+    for bad in (good.cpu(), good.repeat_interleave(2)[::2]):     # the host's memory, every second word
+        X.data = bad
+        with pytest.raises(AssertionError):
+            chain.run(None)
+    X.data = good
+    assert (out.cpu() == 0).all()                                # a refused pass enqueues nothing
+    chain.run(None)
+    assert (out.cpu() == -1).all()
