@@ -503,6 +503,23 @@ PyObject *chain_run(PyObject *self, PyObject *const *args, Py_ssize_t n)    // (
     });
 }
 
+// What the dicts hold now, as bytes: equal for as long as no entry of any of them is set, exchanged or removed.  The
+// interpreter gives a dict a number that no dict has had before whenever it is made or modified.  None if that cannot be
+// told: a subclass of dict (entries can come from its own methods), or an interpreter that counts otherwise.
+PyObject *py_versions(PyObject *, PyObject *const *args, Py_ssize_t n)
+{
+#if PY_VERSION_HEX < 0x030B0000
+    std::vector<uint64_t> tags;
+    for (Py_ssize_t i = 0; i < n; ++i) {
+        if (!PyDict_CheckExact(args[i])) Py_RETURN_NONE;
+        tags.push_back(reinterpret_cast<PyDictObject *>(args[i])->ma_version_tag);
+    }
+    return PyBytes_FromStringAndSize(reinterpret_cast<const char *>(tags.data()), static_cast<Py_ssize_t>(tags.size() * sizeof(uint64_t)));
+#else
+    Py_RETURN_NONE;
+#endif
+}
+
 Py_ssize_t chain_length(PyObject *self) { return static_cast<Py_ssize_t>(reinterpret_cast<ChainObject *>(self)->records->size()); }
 
 #define FAST(name, f) {name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(f)), METH_FASTCALL, nullptr}
@@ -520,7 +537,7 @@ PyMethodDef methods[] = {
     {"set_error_class", py_set_error, METH_O, nullptr},
     FAST("pack", py_pack), FAST("pack_fmap", py_pack_fmap), FAST("quantize", py_quantize), FAST("gemm", py_gemm),
     FAST("conv2d", py_conv2d), FAST("layer", py_layer), FAST("layer_pair", py_layer_pair), FAST("input_layer", py_input_layer),
-    FAST("maxpool", py_maxpool), FAST("sumpool", py_sumpool), FAST("sumpool_fc", py_sumpool_fc),
+    FAST("maxpool", py_maxpool), FAST("sumpool", py_sumpool), FAST("sumpool_fc", py_sumpool_fc), FAST("versions", py_versions),
     {nullptr, nullptr, 0, nullptr}};
 
 PyModuleDef module_def = {PyModuleDef_HEAD_INIT, "_native", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};

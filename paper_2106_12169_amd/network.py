@@ -21,25 +21,9 @@ from . import binding as B
 from .workloads import NetLayer
 
 
-class _Tensors(dict):
-    """Device tensors by layer name; notes that an entry was exchanged, so that the next pass is recorded with it."""
-    changed = False
-
-
-def _noting(name):
-    method = getattr(dict, name)
-
-    def call(self, *args, **kwargs):
-        self.changed = True
-        return method(self, *args, **kwargs)
-    return call
-
-
-for _name in ("__setitem__", "__delitem__", "__ior__", "update", "setdefault", "pop", "popitem", "clear"):
-    setattr(_Tensors, _name, _noting(_name))
-
-
 class PackedNet:
+    _recording = None           # (what it was made from, native Chain): the library calls of a pass
+
     def __init__(self, layers: List[NetLayer], params: Dict[str, tuple], batch: int, device="cuda", fuse_tail: bool = True):
         """fuse_tail: a global sum pooling whose only reader is the last fully connected layer shares that layer's
         launch (apnn_sumpool_fc); its own buffer is then not written."""
@@ -75,14 +59,12 @@ class PackedNet:
         self._record()
         torch.cuda.synchronize()
 
-    def __setattr__(self, name, value):
-        if name in ("w", "scale", "bias", "buf"):
-            value = _Tensors(value)
-            value.changed = True
-        object.__setattr__(self, name, value)
-
     def __getstate__(self):
-        return {**self.__dict__, "_chain": None}        # the recording belongs to this object's tensors
+        return {**self.__dict__, "_recording": None}    # the recording belongs to this object's tensors
+
+    def _state(self):
+        """What a recording is made from, to compare with what it was made from; None: not to be told."""
+        return B.native().versions(self.w, self.scale, self.bias, self.buf)
 
     def _conv_args(self, L: NetLayer) -> dict:
         d = B.Conv(self.batch, L.H, L.W, L.Cin, L.Cout, L.R, L.S, L.stride, L.pad, L.p, L.q)
@@ -93,6 +75,7 @@ class PackedNet:
 
     def _record(self):
         """The library calls of a pass, in order, on the buffers allocated above: what ``forward`` enqueues."""
+        state = self._state()
         chain = B.native().Chain()
         first = self.layers[0]
         paired = None
@@ -130,14 +113,14 @@ class PackedNet:
                             None, 0, 0.0, out, None, None, 0)
             else:
                 raise ValueError(L.kind)
-        self._chain = chain
         self.launches = len(chain)                      # library calls (= kernel launches) of a pass
-        for tensors in (self.w, self.scale, self.bias, self.buf):
-            tensors.changed = False
+        self._recording = (state, chain)
+        return chain
 
     def forward(self, image: torch.Tensor) -> torch.Tensor:
         """image: batch x 3 x H x W uint8 device tensor -> int32 logits batch x classes."""
-        if self._chain is None or self.w.changed or self.scale.changed or self.bias.changed or self.buf.changed:
-            self._record()
-        self._chain.run(image)
+        state, chain = self._recording or (None, None)
+        if state is None or state != self._state():     # (an entry was exchanged since)
+            chain = self._record()
+        chain.run(image)
         return self.buf[self.layers[-1].name]
