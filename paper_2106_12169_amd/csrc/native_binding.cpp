@@ -503,17 +503,39 @@ PyObject *chain_run(PyObject *self, PyObject *const *args, Py_ssize_t n)    // (
     });
 }
 
-// What the dicts hold now, as bytes: equal for as long as no entry of any of them is set, exchanged or removed.  The
-// interpreter gives a dict a number that no dict has had before whenever it is made or modified.  None if that cannot be
-// told: a subclass of dict (entries can come from its own methods), or an interpreter that counts otherwise.
+// What a network is made of, as bytes that stay equal for as long as no entry of any of it is set, exchanged or removed:
+// (class of its layers, list of layers, dict of layers, dicts ...).  The interpreter gives a dict a number that no dict has
+// had before whenever it is made or modified; a layer counts by the dict of its attributes.  None if it cannot be told:
+// containers or layers of another class (what they answer can come from methods), or an interpreter that counts otherwise.
+#if PY_VERSION_HEX < 0x030B0000
+bool add_version(std::vector<uint64_t> &out, PyObject *dict)
+{
+    if (!dict || !PyDict_CheckExact(dict)) return false;
+    out.push_back(reinterpret_cast<PyDictObject *>(dict)->ma_version_tag);
+    return true;
+}
+
+bool add_layer_version(std::vector<uint64_t> &out, PyObject *layer, PyObject *cls)
+{
+    if (reinterpret_cast<PyObject *>(Py_TYPE(layer)) != cls) return false;
+    PyObject **dict = _PyObject_GetDictPtr(layer);
+    return dict && add_version(out, *dict);
+}
+#endif
+
 PyObject *py_versions(PyObject *, PyObject *const *args, Py_ssize_t n)
 {
 #if PY_VERSION_HEX < 0x030B0000
+    if (n < 3) { PyErr_SetString(PyExc_TypeError, "a class, a list and at least one dict are expected"); return nullptr; }
     std::vector<uint64_t> tags;
-    for (Py_ssize_t i = 0; i < n; ++i) {
-        if (!PyDict_CheckExact(args[i])) Py_RETURN_NONE;
-        tags.push_back(reinterpret_cast<PyDictObject *>(args[i])->ma_version_tag);
-    }
+    if (!PyList_CheckExact(args[1]) && !PyTuple_CheckExact(args[1])) Py_RETURN_NONE;
+    for (Py_ssize_t i = 0; i < PySequence_Fast_GET_SIZE(args[1]); ++i)
+        if (!add_layer_version(tags, PySequence_Fast_GET_ITEM(args[1], i), args[0])) Py_RETURN_NONE;
+    for (Py_ssize_t i = 2; i < n; ++i)
+        if (!add_version(tags, args[i])) Py_RETURN_NONE;
+    PyObject *key, *layer;
+    for (Py_ssize_t at = 0; PyDict_Next(args[2], &at, &key, &layer);)
+        if (!add_layer_version(tags, layer, args[0])) Py_RETURN_NONE;
     return PyBytes_FromStringAndSize(reinterpret_cast<const char *>(tags.data()), static_cast<Py_ssize_t>(tags.size() * sizeof(uint64_t)));
 #else
     Py_RETURN_NONE;

@@ -63,8 +63,9 @@ class PackedNet:
         return {**self.__dict__, "_recording": None}    # the recording belongs to this object's tensors
 
     def _state(self):
-        """What a recording is made from, to compare with what it was made from; None: not to be told."""
-        return B.native().versions(self.w, self.scale, self.bias, self.buf)
+        """What a recording is made from, to compare with what it was made from; without versions (None): not to be told."""
+        return (B.native().versions(NetLayer, self.layers, self._by_name, self.w, self.scale, self.bias, self.buf),
+                self.batch, self.fused_tail)
 
     def _conv_args(self, L: NetLayer) -> dict:
         d = B.Conv(self.batch, L.H, L.W, L.Cin, L.Cout, L.R, L.S, L.stride, L.pad, L.p, L.q)
@@ -120,7 +121,7 @@ class PackedNet:
     def forward(self, image: torch.Tensor) -> torch.Tensor:
         """image: batch x 3 x H x W uint8 device tensor -> int32 logits batch x classes."""
         state, chain = self._recording or (None, None)
-        if state is None or state != self._state():     # (an entry was exchanged since)
+        if state is None or state[0] is None or state != self._state():     # (something was exchanged since)
             chain = self._record()
         chain.run(image)
         return self.buf[self.layers[-1].name]

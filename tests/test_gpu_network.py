@@ -101,6 +101,19 @@ def test_a_pass_uses_the_tensors_the_network_holds_now(how):
     _check_all_nodes(layers, net, onet.run(layers, new, img), 2)
 
 
+def test_a_pass_of_fewer_images_than_the_buffers_hold():
+    layers = wl.resnet18_layers(image_hw=64, num_classes=100, widths=(32, 64, 96, 128))
+    params = wl.network_params(layers)
+    img = wl.image_batch(4, 4, 64)
+    net = PackedNet(layers, params, 4)
+    net.forward(torch.from_numpy(img).cuda())
+    net.batch = 1
+    net.buf["fc"].fill_(-7)
+    logits = net.forward(torch.from_numpy(img[3:]).cuda()).cpu().numpy()
+    assert np.array_equal(logits[:1], onet.run(layers, params, img[3:])["fc"])
+    assert (logits[1:] == -7).all()                      # the images of the batch, and no more
+
+
 def test_resnet18_shape_batch32_every_node():
     """A larger batch takes other kernel variants (one tile per wave instead of K split over a block's waves, no
     paired launches for the early stages): every node against the chained oracle again."""

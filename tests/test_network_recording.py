@@ -97,3 +97,60 @@ def test_entries_from_a_dict_with_methods_of_its_own_are_asked_for_in_every_pass
     net.w = Latest(net.w)
     for latest in (torch.zeros(1), torch.zeros(1)):
         assert id(latest) in held(calls(net))
+
+
+def described(calls):
+    """The calls with tensors left out: descriptors and scalars."""
+    return [(name, [a for a in args if not isinstance(a, torch.Tensor)]) for name, args in calls]
+
+
+def test_a_changed_batch_is_the_batch_of_the_next_pass(make):
+    net = make(8)
+    calls(net)
+    net.batch = 3
+    assert described(calls(net)) == described(calls(make(3)))
+    net.batch = 8
+    assert described(calls(net)) == described(calls(make(8)))
+
+
+@pytest.mark.parametrize("how", ["field", "dict", "entry", "list", "by name", "subclass"])
+def test_a_changed_layer_is_the_layer_of_the_next_pass(make, how):
+    net = make()
+    i = next(i for i, L in enumerate(net.layers) if L.res)
+    if how == "subclass":                                # whose fields may come from anywhere
+        class Scaled(wl.NetLayer):
+            res_scale = property(lambda self: scale, lambda self, value: None)
+        scale = 0.0
+        net.layers[i] = Scaled(**vars(net.layers[i]))
+    calls(net)
+    scale = 7.25
+    if how == "field":
+        net.layers[i].res_scale = scale
+    elif how == "dict":
+        vars(net.layers[i])["res_scale"] = scale
+    elif how in ("entry", "list"):
+        new = copy.copy(net.layers[i])
+        new.res_scale = scale
+        if how == "entry":
+            net.layers[i] = new
+        else:
+            net.layers = tuple(new if L is net.layers[i] else L for L in net.layers)
+    elif how == "by name":                               # the source of a residual connection tells its bits
+        L = net.layers[i]
+        net._by_name[L.res] = src = copy.copy(net._by_name[L.res])
+        src.q_out = scale
+    assert any(scale in args for _, args in described(calls(net)))
+
+
+def test_a_changed_tail_is_the_tail_of_the_next_pass(make):
+    net = make()
+    assert [name for name, _ in calls(net)][-1] == "sumpool_fc"
+    net.fused_tail = None
+    assert [name for name, _ in calls(net)][-2:] == ["sumpool", "layer"] and net.launches == len(Chain.ran)
+
+
+def test_a_network_without_a_recording_makes_one(make):
+    net = make()
+    old = copy.copy(net)
+    old.__dict__.pop("_recording")                       # as stored when passes were not recorded
+    assert described(calls(old)) == described(calls(net))
