@@ -210,7 +210,7 @@ void read_layer(Args &a, Layer &y)
     a.tensor_into(y.L.acc_out_dev);
     a.tensor_into(y.L.float_out_dev);
     if (y.L.q_out > 0) a.tensor_into(y.out);
-    else a.tensor();                                      // (checked, not passed on)
+    else a.object();                                      // (there is no packed output: whatever is given is not looked at)
     y.L.pool = a.small();
 }
 

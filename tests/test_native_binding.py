@@ -20,6 +20,13 @@ def test_refuses_host_tensors_and_wrong_argument_types():
         B.native().gemm(w.numpy(), None, 4, 4, 64, 1, 2, 1, 0, None)
 
 
+@pytest.mark.parametrize("call", [B.apnn_layer, B.apnn_input_layer])
+@pytest.mark.parametrize("out", [torch.zeros(4), "no tensor"])
+def test_an_output_that_is_not_written_is_not_looked_at(call, out):
+    with pytest.raises(RuntimeError):                            # the library's refusal of null pointers (or: no device)
+        call(B.Conv(1, 4, 4, 32, 32), None, None, q_out=0, out=out)
+
+
 @pytest.mark.gpu
 def test_library_errors_arrive_with_status_and_text():
     with pytest.raises(B.ApnnError) as e:
