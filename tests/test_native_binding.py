@@ -1,4 +1,5 @@
 """Host side of the native call path: what it refuses before the library is called, and the library's own errors."""
+import numpy as np
 import pytest
 import torch
 
@@ -25,6 +26,12 @@ def test_refuses_host_tensors_and_wrong_argument_types():
 def test_an_output_that_is_not_written_is_not_looked_at(call, out):
     with pytest.raises(RuntimeError):                            # the library's refusal of null pointers (or: no device)
         call(B.Conv(1, 4, 4, 32, 32), None, None, q_out=0, out=out)
+
+
+@pytest.mark.parametrize("flag", [np.bool_(True), 1.0])
+def test_a_flag_is_whatever_converts_to_an_integer(flag):
+    with pytest.raises(RuntimeError):
+        B.apnn_layer(B.Conv(1, 1, 1, 32, 32), None, None, is_gemm=flag)
 
 
 @pytest.mark.gpu
