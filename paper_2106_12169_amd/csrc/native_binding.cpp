@@ -14,6 +14,7 @@
 
 #include <cstring>
 #include <exception>
+#include <new>
 #include <type_traits>
 #include <utility>
 #include <vector>
@@ -51,15 +52,11 @@ struct Ref {
 // What a kernel is given of a tensor: its device pointer.  False (Python error set) if it has none that can be used.
 bool device_pointer(const at::Tensor &t, void *&p)
 {
-    try {
-        if (t.is_cuda() && t.is_contiguous()) {
-            p = t.data_ptr();
-            return true;
-        }
-        PyErr_SetString(PyExc_AssertionError, "device, contiguous tensors only");
-    } catch (const std::exception &e) {                   // (a tensor without storage)
-        PyErr_SetString(PyExc_RuntimeError, e.what());
+    if (t.is_cuda() && t.is_contiguous()) {
+        p = t.data_ptr();
+        return true;
     }
+    PyErr_SetString(PyExc_AssertionError, "device, contiguous tensors only");
     return false;
 }
 
@@ -172,13 +169,7 @@ private:
 
 template <class F> PyObject *call(F &&f)
 {
-    void *stream;
-    try {
-        stream = current_stream();
-    } catch (const std::exception &e) {                   // (no device)
-        PyErr_SetString(PyExc_RuntimeError, e.what());
-        return nullptr;
-    }
+    void *stream = current_stream();
     int rc;
     Py_BEGIN_ALLOW_THREADS
     rc = f(stream);
@@ -394,7 +385,10 @@ struct ChainObject {
 PyObject *chain_new(PyTypeObject *type, PyObject *, PyObject *)
 {
     auto *self = reinterpret_cast<ChainObject *>(type->tp_alloc(type, 0));
-    if (self) self->records = new std::vector<Record>();
+    if (self && !(self->records = new (std::nothrow) std::vector<Record>())) {
+        Py_DECREF(self);
+        return PyErr_NoMemory();
+    }
     return reinterpret_cast<PyObject *>(self);
 }
 
@@ -544,7 +538,20 @@ PyObject *py_versions(PyObject *, PyObject *const *args, Py_ssize_t n)
 
 Py_ssize_t chain_length(PyObject *self) { return static_cast<Py_ssize_t>(reinterpret_cast<ChainObject *>(self)->records->size()); }
 
-#define FAST(name, f) {name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(f)), METH_FASTCALL, nullptr}
+// What torch or the standard library throws (a tensor without storage or sizes, no device, no memory) becomes a Python
+// error: no exception leaves a function that the interpreter calls.
+using Function = PyObject *(PyObject *, PyObject *const *, Py_ssize_t);
+template <Function F> PyObject *guarded(PyObject *self, PyObject *const *args, Py_ssize_t n)
+{
+    try {
+        return F(self, args, n);
+    } catch (const std::exception &e) {
+        PyErr_SetString(PyExc_RuntimeError, e.what());
+        return nullptr;
+    }
+}
+
+#define FAST(name, f) {name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(guarded<f>)), METH_FASTCALL, nullptr}
 
 PyMethodDef chain_methods[] = {
     FAST("input_layer", chain_input_layer), FAST("layer", chain_layer), FAST("layer_pair", chain_layer_pair),

@@ -34,6 +34,13 @@ def test_a_flag_is_whatever_converts_to_an_integer(flag):
         B.apnn_layer(B.Conv(1, 1, 1, 32, 32), None, None, is_gemm=flag)
 
 
+@pytest.mark.filterwarnings("ignore:The PyTorch API of nested tensors")
+def test_a_tensor_without_sizes_is_refused():
+    x = torch.nested.nested_tensor([torch.zeros(3), torch.zeros(5)])
+    with pytest.raises(RuntimeError):
+        B.apnn_quantize(x, 0.0, 1.0, 2, out=torch.zeros(8, dtype=torch.int32))
+
+
 @pytest.mark.gpu
 def test_library_errors_arrive_with_status_and_text():
     with pytest.raises(B.ApnnError) as e:
