@@ -264,7 +264,9 @@ PyObject *py_gemm(PyObject *, PyObject *const *args, Py_ssize_t n)      // (W, X
     const auto *X = static_cast<const uint32_t *>(a.tensor());
     const int64_t M = a.integer(), N = a.integer(), K = a.integer();
     const int p = a.small(), q = a.small(), encW = a.small(), encX = a.small();
-    auto *out = static_cast<int32_t *>(a.tensor());
+    PyObject *result = a.object();                        // (one without elements is not written, wherever it is)
+    const bool empty = result && THPVariable_Check(result) && THPVariable_Unpack(result).numel() == 0;
+    auto *out = empty ? nullptr : static_cast<int32_t *>(a.tensor(result));
     if (!a.ok()) return nullptr;
     return call([&](void *st) {
         return apnn_gemm(W, X, out, M, N, K, p, q, static_cast<apnn_encoding>(encW), static_cast<apnn_encoding>(encX), st);

@@ -34,6 +34,11 @@ def test_a_flag_is_whatever_converts_to_an_integer(flag):
         B.apnn_layer(B.Conv(1, 1, 1, 32, 32), None, None, is_gemm=flag)
 
 
+def test_an_empty_product_takes_any_empty_output():
+    with pytest.raises(RuntimeError):                            # (no device; or the library: null operands)
+        B.apnn_gemm(None, None, 4, 4, 64, 1, 2, B.ENC_PM1, B.ENC_UNSIGNED, out=torch.empty((0, 4), dtype=torch.int32))
+
+
 @pytest.mark.filterwarnings("ignore:The PyTorch API of nested tensors")
 def test_a_tensor_without_sizes_is_refused():
     x = torch.nested.nested_tensor([torch.zeros(3), torch.zeros(5)])
