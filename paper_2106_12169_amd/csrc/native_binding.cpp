@@ -43,10 +43,24 @@ PyObject *finish(int status)
     return nullptr;
 }
 
-// A tensor whose device pointer stands `offset` bytes into a recorded step.
+// A Python object that is held (made, moved and dropped with the interpreter lock).
+class Held {
+public:
+    explicit Held(PyObject *o) : o_(o) { Py_INCREF(o_); }
+    Held(Held &&other) noexcept : o_(std::exchange(other.o_, nullptr)) {}
+    Held &operator=(Held &&) = delete;
+    ~Held() { Py_XDECREF(o_); }
+    PyObject *get() const { return o_; }
+
+private:
+    PyObject *o_;
+};
+
+// A tensor whose device pointer stands `offset` bytes into a recorded step.  The Python object is held, as by any other
+// owner: what it stands for can be exchanged (torch.utils.swap_tensors), which a reference to its tensor would forbid.
 struct Ref {
     size_t offset;
-    at::Tensor tensor;
+    Held tensor;
 };
 
 // What a kernel is given of a tensor: its device pointer.  False (Python error set) if it has none that can be used.
@@ -80,7 +94,7 @@ public:
     {
         PyObject *o = object();
         field = static_cast<T *>(tensor(o));
-        if (refs_ && ok_ && o != Py_None) refs_->push_back({static_cast<size_t>(reinterpret_cast<const char *>(&field) - base_), THPVariable_Unpack(o)});
+        if (refs_ && ok_ && o != Py_None) refs_->push_back({static_cast<size_t>(reinterpret_cast<const char *>(&field) - base_), Held(o)});
     }
 
     long long integer(PyObject *o)
@@ -372,7 +386,7 @@ struct Record {
         s = step;
         for (const Ref &r : refs) {
             void *p = nullptr;
-            if (!device_pointer(r.tensor, p)) return false;
+            if (!device_pointer(THPVariable_Unpack(r.tensor.get()), p)) return false;
             std::memcpy(reinterpret_cast<char *>(&s) + r.offset, &p, sizeof p);
         }
         return true;

@@ -73,7 +73,7 @@ def test_resnet18_shape_batch8_logits_and_graph_replay():
         assert np.array_equal(net.buf["fc"].cpu().numpy(), want["fc"])
 
 
-@pytest.mark.parametrize("how", ["in place", "entry", "storage", "dict", "copy"])
+@pytest.mark.parametrize("how", ["in place", "entry", "storage", "swap", "dict", "copy"])
 def test_a_pass_uses_the_tensors_the_network_holds_now(how):
     """Weights, constants and buffers exchanged between passes: nothing of the old ones is used."""
     layers = wl.resnet18_layers(image_hw=64, num_classes=100, widths=(32, 64, 96, 128))
@@ -93,6 +93,8 @@ def test_a_pass_uses_the_tensors_the_network_holds_now(how):
                 mine[k] = theirs[k].clone()
             elif how == "storage":
                 mine[k].data = theirs[k].clone()
+            elif how == "swap":
+                torch.utils.swap_tensors(mine[k], theirs[k].clone())
             else:
                 mine[k].copy_(theirs[k])
     logits = net.forward(torch.from_numpy(img).cuda())
