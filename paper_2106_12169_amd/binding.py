@@ -265,7 +265,7 @@ def apnn_layer(d: Conv, W: torch.Tensor, X: torch.Tensor, *, is_gemm: bool = Fal
     if q_out > 0 and out is None:
         pixels = d.N * (1 if is_gemm else ((d.Ho // 2) * (d.Wo // 2) if pool else d.Ho * d.Wo))
         out = _words(apnn_fmap_words(pixels, d.Cout, q_out), X.device)
-    _N.layer(d, W, X, int(is_gemm), q_out, scale, bias, residual, q_res, res_scale, acc_out, float_out, out, pool)
+    _N.layer(d, W, X, is_gemm, q_out, scale, bias, residual, q_res, res_scale, acc_out, float_out, out, pool)
     return out if q_out > 0 else None
 
 

@@ -111,6 +111,17 @@ public:
         }
         return v;
     }
+    // what int(o) gives
+    int flag()
+    {
+        PyObject *o = object();
+        if (!ok_ || PyLong_Check(o)) return static_cast<int>(integer(o));
+        PyObject *n = PyNumber_Long(o);
+        if (!n) ok_ = false;
+        const int v = static_cast<int>(integer(n));
+        Py_XDECREF(n);
+        return v;
+    }
     float real(PyObject *o)
     {
         if (!ok_) return 0.0f;
@@ -205,7 +216,7 @@ void read_layer(Args &a, Layer &y)
     y.L.conv = a.conv();
     a.tensor_into(y.W);
     a.tensor_into(y.X);
-    y.L.is_gemm = a.small();
+    y.L.is_gemm = a.flag();
     y.L.q_out = a.small();
     a.tensor_into(y.L.scale_dev);
     a.tensor_into(y.L.bias_dev);
