@@ -16,11 +16,10 @@ namespace apnn {
 template <int KA, int KB, int VW, int GMAX, int FN>
 __device__ __forceinline__ void mfma_small_wide_body(const MfmaParams &p, const int block)
 {
-    // GMAX: groups of four steps whose loads are in flight together.  The load buffers set the register count and
-    // with it the number of blocks a compute unit holds at once: 1 or 2 for layers with a short K and many blocks,
-    // 5 for a long K.  FN: 32-column tiles per wave tile: a row operand is loaded, expanded and its
-    // pixel decoded once for 32 FN output channels.  A large layer is bound by the instructions its waves issue,
-    // and the row side is about a third of them.
+    // GMAX: groups of four steps whose loads are in flight together; the load buffers set the register count and with it the
+    // waves a SIMD holds.  2 here: four waves for single planes on a side, as 1 x 1 layers need, which are mostly epilogue.
+    // FN: 32-column tiles per wave tile: a row operand is loaded, expanded and its pixel decoded once for 32 FN output
+    // channels.  A large layer is bound by the instructions its waves issue, and the row side is about a third of them.
     constexpr int LA = DigitPlanes<KA>::value, LB = DigitPlanes<KB>::value;
 
     const int tid = threadIdx.x;
@@ -205,13 +204,18 @@ __device__ __forceinline__ void mfma_small_wide_body(const MfmaParams &p, const 
         }
     };
 
-    if (p.DA * p.DB == 1) {                             // one digit pair (most layers): unit scales, plain group loop
+    // Single planes on both sides: never more than one digit pair.  The general loop, compiled in all the same, and the loads of
+    // a group that does not exist had taken these forms from 74 - 80 registers to 97 - 104 (three waves per SIMD instead of
+    // four): 64 x 56 x 56, 128 -> 128 channels, 1 x 1, w1a1 24.4 us, without them 19.0.
+    constexpr bool ONE_PAIR = KA != OPK_U2 && KB != OPK_U2;
+    if (ONE_PAIR || p.DA * p.DB == 1) {                 // one digit pair (most layers): unit scales, plain group loop
         Walk t = walk_to(kbase);
         for (int g0 = 0; g0 < (p.Kw > 0 ? G : 0); g0 += GMAX) {
             uint4 wa[GMAX][LA], wb[GMAX][FN][LB];
 #pragma unroll
             for (int g = 0; g < GMAX; ++g) {
-                const int kk = kbase + 4 * (g0 + g);    // (beyond the last group: read, not used)
+                if (g > 0 && g0 + g >= G) break;        // uniform
+                const int kk = kbase + 4 * (g0 + g);
                 load_a(wa[g], 0, t);
 #pragma unroll
                 for (int j = 0; j < FN; ++j)
@@ -226,13 +230,13 @@ __device__ __forceinline__ void mfma_small_wide_body(const MfmaParams &p, const 
     int da = 0, db = 0, grp = 0;                        // position in the flat sequence (scalar counters, no divisions)
     const Walk start = walk_to(kbase);
     Walk t = start;
-    for (int e0 = 0; e0 < (p.DA * p.DB == 1 ? 0 : total); e0 += GMAX) {
+    for (int e0 = 0; e0 < (ONE_PAIR || p.DA * p.DB == 1 ? 0 : total); e0 += GMAX) {
         uint4 wa[GMAX][LA], wb[GMAX][FN][LB];
         int sa[GMAX], sb[GMAX], steps[GMAX];
 #pragma unroll
         for (int g = 0; g < GMAX; ++g) {
             const int planeA = LA == 2 ? 2 * da : da, planeB = LB == 2 ? 2 * db : db;
-            const int kk = kbase + 4 * grp;             // (beyond the end: read, not used)
+            const int kk = kbase + 4 * grp;             // (beyond the end: read, not used; jumping over it measured slower)
             steps[g] = NS - 4 * grp;
             sa[g] = 0x7f7f7f7f + 0x02020202 * da;
             sb[g] = 0x7f7f7f7f + 0x02020202 * db;
@@ -278,8 +282,11 @@ __device__ __forceinline__ void mfma_small_wide_body(const MfmaParams &p, const 
     });
 }
 
+// One plane of features with two of weights is held to the 128 registers of four waves per SIMD, which it exceeds by a few;
+// the forms with one plane of weights stay within them, the others are far above.  64 x 56 x 56, 192 -> 64 channels, 1 x 1,
+// w2a1: 16.4 us with three waves, 14.1 with four and two registers kept in memory.
 template <int KA, int KB, int VW, int FN>
-__global__ __launch_bounds__(256) void mfma_small_wide_kernel(const MfmaParams p)
+__global__ __launch_bounds__(256, (KA == OPK_U1 && KB == OPK_U2 ? 4 : 1)) void mfma_small_wide_kernel(const MfmaParams p)
 {
     mfma_small_wide_body<KA, KB, VW, 2, FN>(p, blockIdx.x);
 }

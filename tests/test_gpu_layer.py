@@ -528,3 +528,15 @@ def test_wide_wave_tiles_at_their_edges(Cin, Cout, H, Wd, R, S, stride, pad, enc
     Y = B.apnn_conv2d(d, B.apnn_pack_conv_weights(dev(Wv), p, encW), B.apnn_pack_fmap(dev(Xv), B.LAYOUT_NCHW, q, encX))
     torch.cuda.synchronize()
     assert np.array_equal(Y.cpu().numpy().transpose(0, 3, 1, 2), oracle.conv2d(Wv, encW, p, Xv, encX, q, stride, pad))
+
+
+@pytest.mark.parametrize("encW,p,encX,q", [(P, 1, P, 1), (U, 1, U, 1), (P, 1, U, 1), (U, 2, U, 1), (U, 3, U, 1), (P, 1, U, 2)])
+@pytest.mark.parametrize("Cin,R", [(64, 1), (128, 1), (192, 1), (512, 1), (192, 2), (128, 3), (64, 3)])   # one to five groups
+def test_wide_wave_tiles_of_any_number_of_groups(Cin, R, encW, p, encX, q):
+    _force("32split1wide2")
+    Wv = wl.operand(311 + Cin, 64, Cin * R * R, p, encW).reshape(64, Cin, R, R)
+    Xv = wl.operand(312 + R, 2 * Cin, 42, q, encX).reshape(2, Cin, 6, 7)
+    d = B.Conv(2, 6, 7, Cin, 64, R, R, 1, R // 2, p, q, encW, encX)
+    Y = B.apnn_conv2d(d, B.apnn_pack_conv_weights(dev(Wv), p, encW), B.apnn_pack_fmap(dev(Xv), B.LAYOUT_NCHW, q, encX))
+    torch.cuda.synchronize()
+    assert np.array_equal(Y.cpu().numpy().transpose(0, 3, 1, 2), oracle.conv2d(Wv, encW, p, Xv, encX, q, 1, R // 2))
