@@ -106,28 +106,44 @@ __global__ __launch_bounds__(256) void pack_generic_kernel(const uint8_t *__rest
 // hold one that does, they are divided.  Zeros, as a rectifier leaves them, saturated values and positions beyond K are
 // decided without.  The test is of the whole wave, a scalar branch: as a branch of the lane the compiler turned it into a
 // division for every value and a selection (4096 x 4096, step 0.7, to 2 bits 14.6 us, to 8 bits 21.4; now 13.1 and 16.9).
-template <int NL, bool EXACT>
+//
+// SHORT: rows of at most 128 values, whose planes are four words.  A load takes two rows, lanes 0 - 31 and 32 - 63, and a
+// wave owns 2 NL rows: with a wave per row most lanes have nothing to do (50000 x 64 -> 2 bits: 10.5 us, here 6.1).
+template <int NL, bool EXACT, bool SHORT>
 __global__ __launch_bounds__(256) void quantize_pack_wave_kernel(const float *__restrict__ src, uint32_t *__restrict__ dst,
-                                                                 uint32_t nseg, int segs, int K, int ldw, int bits,
-                                                                 float zero, float step, float inv)
+                                                                 uint32_t waves, int segs, uint32_t rows, int K, int ldw,
+                                                                 int bits, float zero, float step, float inv)
 {
     const int lane = threadIdx.x & 63;
-    const uint32_t wave = blockIdx.x * 4u + (threadIdx.x >> 6);
-    if (wave >= nseg) return;                           // wave-uniform
-    const uint32_t row = wave / static_cast<uint32_t>(segs);
-    const int seg = static_cast<int>(wave - row * segs);
-    const float *s = src + static_cast<size_t>(row) * K;
+    const uint32_t wave = blockIdx.x * 4u + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);     // scalar: so are segment and row
+    if (wave >= waves) return;
     const float hi = static_cast<float>((1 << bits) - 1);
-    const int k0 = seg * (256 * NL) + 4 * lane;
+    // this lane's values: k0 .. k0 + 3 of load 0; load i is 256 values on, or (SHORT) two rows
+    const uint32_t row = SHORT ? wave * (2u * NL) + (lane >> 5) : wave / static_cast<uint32_t>(segs);
+    const int first = SHORT ? 0 : static_cast<int>(wave - row * segs) * (256 * NL);
+    const int k0 = SHORT ? 4 * (lane & 31) : first + 4 * lane;
+    constexpr int KSTEP = SHORT ? 0 : 256;
+    constexpr int RSTEP = SHORT ? 2 : 0;
+    const float *s = src + static_cast<size_t>(row) * K + k0;
     float x[NL][4];
-    if (seg * (256 * NL) + 256 * NL <= K) {             // wave-uniform: the whole segment exists
+    if (!SHORT && first + 256 * NL <= K) {              // wave-uniform: the whole segment exists
 #pragma unroll
-        for (int i = 0; i < NL; ++i) __builtin_memcpy(x[i], s + k0 + 256 * i, 16);
+        for (int i = 0; i < NL; ++i) __builtin_memcpy(x[i], s + 256 * i, 16);
     } else {
 #pragma unroll
-        for (int i = 0; i < NL; ++i)
+        for (int i = 0; i < NL; ++i) {
+            const float *si = s + static_cast<size_t>(RSTEP * i) * K + KSTEP * i;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) x[i][j] = k0 + 256 * i + j < K ? s[k0 + 256 * i + j] : -__builtin_inff();
+            for (int j = 0; j < 4; ++j) x[i][j] = -__builtin_inff();
+            if (SHORT && row + RSTEP * i >= rows) continue;
+            if (k0 + KSTEP * i + 4 <= K) {
+                __builtin_memcpy(x[i], si, 16);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 3; ++j)
+                    if (k0 + KSTEP * i + j < K) x[i][j] = si[j];
+            }
+        }
     }
     uint32_t code[NL];                                  // four codes, one per byte (below zero, -inf, NaN: 0)
 #pragma unroll
@@ -148,14 +164,16 @@ __global__ __launch_bounds__(256) void quantize_pack_wave_kernel(const float *__
         }
 #pragma unroll
         for (int j = 0; j < 4; ++j) code[i] = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_amdgcn_fmed3f(floorf(v[j]), 0.0f, hi), j, code[i]);
-        if (seg * (256 * NL) + 256 * NL > K) {          // positions beyond K are 0 (-inf - zero may be NaN or clamp to 0)
+        if (first + (SHORT ? 128 : 256 * NL) > K) {     // positions beyond K are 0 (-inf - zero may be NaN or clamp to 0)
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                if (k0 + 256 * i + j >= K) code[i] &= ~(0xFFu << (8 * j));
+                if (k0 + KSTEP * i + j >= K) code[i] &= ~(0xFFu << (8 * j));
         }
     }
-    const int nibble = 4 * (lane & 7), k_word = seg * (8 * NL) + 8 * (lane & 7) + (lane >> 3);
-    const bool mine = (lane & 7) < NL && k_word < ldw;
+    // the word that this lane keeps and stores
+    const int nibble = 4 * (lane & 7), k_word = SHORT ? (lane >> 3) & 3 : first / 32 + 8 * (lane & 7) + (lane >> 3);
+    const uint32_t my_row = SHORT ? row + 2 * (lane & 7) : row;
+    const bool mine = (lane & 7) < NL && (SHORT ? my_row < rows : k_word < ldw);
     for (int t = 0; t < bits; ++t) {
         uint32_t word = 0;
 #pragma unroll
@@ -167,7 +185,7 @@ __global__ __launch_bounds__(256) void quantize_pack_wave_kernel(const float *__
             w |= static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(w), 0x141, 0xF, 0xF, true));
             word = (lane & 7) == i ? w : word;
         }
-        if (mine) dst[(static_cast<size_t>(row) * bits + t) * ldw + k_word] = word;
+        if (mine) dst[(static_cast<size_t>(my_row) * bits + t) * ldw + k_word] = word;
     }
 }
 
@@ -678,21 +696,33 @@ extern "C" int apnn_quantize(const float *src_dev, int64_t rows, int64_t K, floa
     if (!src_dev || !dst_dev) return fail(APNN_ERR_INVALID_ARG, "apnn_quantize: null pointer");
     if (!aligned16(dst_dev)) return fail(APNN_ERR_ALIGNMENT, "apnn_quantize: dst_dev not 16-byte aligned");
     const int ldw = static_cast<int>(apnn_row_words(K));
-    // 2048 values per wave where rows are that long and enough waves remain to fill the chip, else 256
-    const int nl = K >= 2048 && rows * ceil_div(K, 2048) >= 2048 ? 8 : K >= 512 && rows * ceil_div(K, 512) >= 2048 ? 2 : 1;
-    const int64_t segs = ceil_div(K, 256 * nl), nseg = rows * segs;
+    // 2048 values per wave (or 16 rows of at most 128) where the rows are that long, no more than a third of their last segments
+    // would be padding, and 2048 waves get that many values to fill the chip with; else 512 (4 rows), else 256 (2 rows).
+    // To 2 bits: 20000 x 2049 30.1 us by 2048, 27.7 by 512; 700 x 4100 5.0 and 3.5.
+    const bool short_rows = K <= 128;
+    auto fills = [&](int64_t n) {
+        if (short_rows) return rows >= 2048 * 2 * n;
+        return K >= 256 * n && 2 * round_up(K, 256 * n) <= 3 * K && rows >= ceil_div(2048 * 256 * n, K);
+    };
+    const int nl = fills(8) ? 8 : fills(2) ? 2 : 1;
+    const int64_t segs = short_rows ? 1 : ceil_div(K, 256 * nl), waves = short_rows ? ceil_div(rows, 2 * nl) : rows * segs;
     const float inv = 1.0f / step;
-    if (nseg < (int64_t(1) << 32) - 4 && K <= INT32_MAX - 2048 && inv >= 0x1p-126f && inv <= 0x1p126f) {
+    if (waves < (int64_t(1) << 32) - 4 && rows < (int64_t(1) << 32) - 16 && K <= INT32_MAX - 2048 && inv >= 0x1p-126f && inv <= 0x1p126f) {
         int e;
         const bool exact = std::frexp(step, &e) == 0.5f;
         auto go = [&](auto kernel) {
-            hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(ceil_div(nseg, 4))), dim3(256), 0, as_stream(stream), src_dev,
-                               dst_dev, static_cast<uint32_t>(nseg), static_cast<int>(segs), static_cast<int>(K), ldw, bits, zero,
-                               step, inv);
+            hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(ceil_div(waves, 4))), dim3(256), 0, as_stream(stream), src_dev,
+                               dst_dev, static_cast<uint32_t>(waves), static_cast<int>(segs), static_cast<uint32_t>(rows),
+                               static_cast<int>(K), ldw, bits, zero, step, inv);
         };
-        if (nl == 8) exact ? go(quantize_pack_wave_kernel<8, true>) : go(quantize_pack_wave_kernel<8, false>);
-        else if (nl == 2) exact ? go(quantize_pack_wave_kernel<2, true>) : go(quantize_pack_wave_kernel<2, false>);
-        else exact ? go(quantize_pack_wave_kernel<1, true>) : go(quantize_pack_wave_kernel<1, false>);
+        auto by_form = [&](auto n) {
+            constexpr int NL = decltype(n)::value;
+            if (short_rows) exact ? go(quantize_pack_wave_kernel<NL, true, true>) : go(quantize_pack_wave_kernel<NL, false, true>);
+            else exact ? go(quantize_pack_wave_kernel<NL, true, false>) : go(quantize_pack_wave_kernel<NL, false, false>);
+        };
+        if (nl == 8) by_form(std::integral_constant<int, 8>{});
+        else if (nl == 2) by_form(std::integral_constant<int, 2>{});
+        else by_form(std::integral_constant<int, 1>{});
     } else {
         const unsigned grid = static_cast<unsigned>(ceil_div(rows * ldw, 256));
         hipLaunchKernelGGL(quantize_pack_kernel, dim3(grid), dim3(256), 0, as_stream(stream), src_dev, dst_dev, rows, K,

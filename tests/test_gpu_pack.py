@@ -124,3 +124,15 @@ def test_quantize_of_infinities_nan_and_the_ends_of_the_range(zero, step, K):
     x = np.resize(special, (2050, K))
     codes, pad = hp.unpack_matrix(hp.words_u32(B.apnn_quantize(dev(x), zero, step, 5)), 2050, K, 5)
     assert np.array_equal(codes, oracle.quantize(x, zero, step, 5)) and pad == 0
+
+
+@pytest.mark.parametrize("bits,step", [(2, 0.5), (3, 0.7), (8, 1.0 / 3)])
+@pytest.mark.parametrize("rows,K", [(1, 1), (3, 3), (7, 4), (5, 31), (9, 97), (33, 127), (6, 128), (8192, 5), (8195, 126), (32768, 2),
+                                    (32783, 128), (2100, 700), (2050, 3001)])
+def test_quantize_rows_that_share_a_wave_and_segments_partly_filled(bits, step, rows, K):
+    """Rows of at most 128 values, two, four and sixteen to a wave, and the partial last wave; last segments of every width."""
+    x = wl.normals(13, (rows, K), 1.0, 1.5)
+    x[x < 0] = 0.0                                      # as a rectifier leaves them
+    x[rows // 2] *= 1e6
+    codes, pad = hp.unpack_matrix(hp.words_u32(B.apnn_quantize(dev(x), 0.0, step, bits)), rows, K, bits)
+    assert np.array_equal(codes, oracle.quantize(x, 0.0, step, bits)) and pad == 0
