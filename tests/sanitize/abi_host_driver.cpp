@@ -150,6 +150,30 @@ int main()
     (void)apnn_layer(&P, fw, fw, nullptr, nullptr);
     EXPECT(g_kernel == "small_conv" && g_mp.pool == 2);
 
+    // ---- 32-bit ranges of the large-layer kernel: operands below 2^31 bytes, one padded image below 2^27 words
+    apnn_layer_desc V{};
+    V.acc_out_dev = fy;
+    auto chosen = [&](int64_t images, int64_t H, int64_t W, int64_t Cin, int64_t Cout, int R, int pad, int q) {
+        V.conv = apnn_conv_desc{images, H, W, Cin, Cout, R, R, 1, pad, 1, q, APNN_ENC_PM1, APNN_ENC_UNSIGNED};
+        g_kernel.clear();
+        (void)apnn_layer(&V, fw, fw, nullptr, nullptr);
+        return g_kernel;
+    };
+    EXPECT(chosen(1023, 128, 128, 512, 64, 3, 1, 2) == "small_conv_wide" && g_mp.bytesA == 1023u << 21 && g_mp.bytesB == 64 * 144 * 4);
+    EXPECT(chosen(1024, 128, 128, 512, 64, 3, 1, 2) == "small_conv");                                      // features of 2^31 bytes
+    EXPECT(chosen(1, 16, 16, 2048, 932032, 3, 1, 2) == "small_conv_wide" && g_mp.bytesB == 932032u * 2304);
+    EXPECT(chosen(1, 16, 16, 2048, 932096, 3, 1, 2) == "small_conv");                                      // weights beyond
+    EXPECT(chosen(1, 2043, 2044, 512, 64, 3, 0, 2) == "small_conv_wide");                                   // (2043 + 3)(2044 + 3) 32 words
+    EXPECT(chosen(1, 2045, 2045, 512, 64, 3, 0, 2) == "small_conv");                                        // 2048^2 32 = 2^27
+    // an odd number of channel words: one padded image below 2^31 words, else the popcount kernel
+    EXPECT(chosen(1, 32760, 32766, 32, 32, 1, 0, 2) == "small_conv");
+    EXPECT(chosen(1, 32767, 32767, 32, 32, 1, 0, 2) == "tile2");                                            // 32768^2 2 = 2^31
+    EXPECT(chosen(1, 28, 28, 96, 64, 3, 1, 2) == "small_conv" && g_mp.Cw == 3);
+    EXPECT(apnn_debug_force("MFMA_SMALL", 0) == APNN_OK && chosen(1, 28, 28, 96, 64, 3, 1, 2) == "tile2");
+    apnn_debug_reset();
+    EXPECT(chosen(64, 56, 56, 64, 64, 3, 1, 2) == "small_conv_wide" && chosen(64, 56, 56, 64, 96, 3, 1, 2) == "small_conv");
+    EXPECT(chosen(1, 14, 14, 64, 64, 3, 1, 2) == "small_conv");                                             // few tiles: K split
+
     if (failures == 0) std::puts("abi host sanitizer run ok");
     return failures != 0;
 }

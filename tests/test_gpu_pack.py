@@ -136,3 +136,26 @@ def test_quantize_rows_that_share_a_wave_and_segments_partly_filled(bits, step, 
     x[rows // 2] *= 1e6
     codes, pad = hp.unpack_matrix(hp.words_u32(B.apnn_quantize(dev(x), 0.0, step, bits)), rows, K, bits)
     assert np.array_equal(codes, oracle.quantize(x, 0.0, step, bits)) and pad == 0
+
+
+@pytest.mark.parametrize("N,C,H,W,bits", [
+    (40, 96, 65, 61, 2), (40, 96, 65, 61, 5),           # 256 pixels a block, several words a pixel
+    (128, 1504, 2, 255, 1), (128, 1536, 2, 255, 1),     # 47 words a pixel: the last that 256 records leave room for; 48: 64 pixels
+    (1, 768, 9, 8, 8), (2, 800, 9, 8, 8),               # 192, 200 words a pixel: the byte-by-byte kernel (191 at most fit)
+    (1, 760, 9, 8, 7),                                  # 168
+])
+def test_pack_nchw_records_at_the_limits_of_a_block(N, C, H, W, bits):
+    nchw = wl.uniform_codes(14, (N, C, H, W), bits)
+    codes, pad = hp.unpack_fmap(hp.words_u32(B.apnn_pack_fmap(dev(nchw), B.LAYOUT_NCHW, bits, U)), N, H, W, C, bits)
+    assert np.array_equal(codes, nchw) and pad == 0
+
+
+@pytest.mark.parametrize("step", [2.0 ** 127, 2.0 ** 126, 2.0 ** -126, 1e-39, 1.3e38, 3e-38])
+@pytest.mark.parametrize("rows,K", [(3, 40), (2, 300)])
+def test_quantize_steps_whose_reciprocal_leaves_the_range(step, rows, K):
+    """Reciprocals below 2^-126 or above 2^126 are not used: the kernel that divides takes those steps."""
+    with np.errstate(over="ignore"):                    # (codes 0 .. 7 and beyond, or infinity)
+        x = np.resize(np.float32(step) * np.arange(-1, 9, dtype=np.float32) / 2, (rows, K))
+    x[:, ::7] = np.array([3.4e38, -3.4e38, 1e-45, 0.0, np.inf, -np.inf, np.nan], np.float32)[np.arange(x[:, ::7].shape[1]) % 7]
+    codes, pad = hp.unpack_matrix(hp.words_u32(B.apnn_quantize(dev(x), 0.0, step, 3)), rows, K, 3)
+    assert np.array_equal(codes, oracle.quantize(x, 0.0, step, 3)) and pad == 0
