@@ -600,7 +600,8 @@ extern "C" int apnn_pack_fmap(const void *src_dev, apnn_layout layout, int64_t N
         // pixels exceed the LDS
         const int px = N * ceil_div(HW, 256) < 512 || static_cast<int64_t>(bits) * g.ldw > 47 ? 64 : 256;
         const int64_t bpi = ceil_div(HW, px), lds = 4 * px * ((static_cast<int64_t>(bits) * g.ldw) | 1);
-        if (HW >= 4 && N * bpi <= 0x7FFFFFFF && lds <= 48 * 1024 && HW <= INT32_MAX - 256 && C <= INT32_MAX - 32) {
+        // (a launch has less than 2^32 threads: beyond, the runtime drops blocks without an error)
+        if (HW >= 4 && N * bpi < (int64_t(1) << 24) && lds <= 48 * 1024 && HW <= INT32_MAX - 256 && C <= INT32_MAX - 32) {
             with_bits(bits, g.pm1, [&](auto bc, auto pc) {
                 constexpr int BITS = decltype(bc)::value;
                 constexpr bool PM1 = decltype(pc)::value;

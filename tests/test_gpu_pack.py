@@ -150,6 +150,13 @@ def test_pack_nchw_records_at_the_limits_of_a_block(N, C, H, W, bits):
     assert np.array_equal(codes, nchw) and pad == 0
 
 
+def test_pack_nchw_of_more_frames_than_a_grid_has_blocks():
+    """A launch has less than 2^32 threads: 2^24 blocks of 256."""
+    src = torch.randint(0, 4, ((1 << 24) + 3, 1, 1, 5), dtype=torch.uint8, device="cuda")
+    words = B.apnn_pack_fmap(src, B.LAYOUT_NCHW, 2, U).view(-1, 2)
+    assert torch.equal(words[:, 0] + 2 * words[:, 1], src.view(-1).int())
+
+
 @pytest.mark.parametrize("step", [2.0 ** 127, 2.0 ** 126, 2.0 ** -126, 1e-39, 1.3e38, 3e-38])
 @pytest.mark.parametrize("rows,K", [(3, 40), (2, 300)])
 def test_quantize_steps_whose_reciprocal_leaves_the_range(step, rows, K):
