@@ -6,8 +6,9 @@
 // footprint was slower again).  For the same reason the loader is not that of mfma_small_kernel: receptive-field
 // positions are walked instead of divided, offsets are 32-bit into range-checked buffers (no branch, select or 64-bit
 // address per load), a digit's planes share one position, K is padded to a loader vector per lane half instead of to four
-// steps, and the wave's tile is held in scalar registers.  Whole passes, before -> walk and scalar tile -> buffers and
-// expand_fp4's ten instructions: ResNet-18 shape batch 128 690 -> 642 -> 622 us, VGG-16 shape batch 8 322 -> 302 -> 285.
+// steps, and the wave's tile is held in scalar registers.  Whole passes with that loader, and with the loads of missing groups
+// left out as well: ResNet-18 shape batch 128 690 -> 637 -> 611 us, VGG-16 shape batch 8 322 -> 301 -> 289.  One word per step
+// (an odd number of channel words) still divides for its position, once for four words (load_conv_a_words).
 #pragma once
 #include "mfma_kernel.h"
 
@@ -54,8 +55,9 @@ __device__ __forceinline__ void mfma_small_wide_body(const MfmaParams &p, const 
     }
     // Both operands are buffers with 32-bit byte offsets (the host checks their sizes), and every load is unconditional:
     // row words that contribute nothing (taps outside the frame, K beyond Kw, rows beyond M, a missing plane) get an offset
-    // beyond the buffer, for which the load returns zero.  The row operand alone needs that: a zero code of it cancels
-    // whatever the column operand holds there.
+    // beyond the buffer, for which the load returns zero.  K beyond Kw and rows beyond the operand need that on the row side
+    // alone: a zero code there cancels whatever the column operand holds.  A missing plane needs it on its own side, since the
+    // other operand's codes are not zero there: hence `exists` in load_b.
     const __amdgpu_buffer_rsrc_t bufA = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(p.A), 0, p.bytesA, 0x00020000);
     const __amdgpu_buffer_rsrc_t bufB = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(p.B), 0, p.bytesB, 0x00020000);
     constexpr uint32_t NOWHERE = 0x80000000u;

@@ -93,12 +93,12 @@ __global__ __launch_bounds__(256) void pack_generic_kernel(const uint8_t *__rest
 }
 
 // Quantiser + packer.  A wave owns 256 NL consecutive values of a row: NL loads of 16 bytes per lane, all in flight
-// together, lane l holding values 4 l .. 4 l + 3 of each 256.  Per value: subtract, divide, clamp, truncate into a byte
+// together, lane l holding values 4 l .. 4 l + 3 of each 256.  Per value: subtract, multiply or divide, clamp, truncate into a byte
 // (v_cvt_pk_u8_f32 of a clamped floor); per load and plane the four bits are gathered by one dot product with (1, 2, 4,
 // 8), shifted to their nibble of the word and OR-ed over the eight lanes of the word by three lane exchanges inside
 // a row; lane l then keeps word l / 8 of load l % 8, and a plane of the segment leaves in one store.
-// Bound by HBM: 4096 x 4096 fp32 -> 2 bits take 12.1 us (5.9 TB/s).  The ballot form it replaces spent some 40 vector instructions per value,
-// half of them on the division, and took 20.8 us.
+// Bound by HBM: 4096 x 4096 fp32 -> 2 bits take 12.1 us (5.9 TB/s).  The ballot form it replaces spent some 40 vector
+// instructions per value, half of them on the division, and took 20.8 us.
 //
 // The quotient must be that of one IEEE division, fl(d / step).  EXACT: step is a power of two, so d * (1 / step) is
 // that number.  Otherwise v = d * fl(1 / step) is within 2 ulp of it, i.e. within 2^-13 for |v| <= 257, and the code,
@@ -242,7 +242,7 @@ __device__ __forceinline__ void transpose_bytes(uint32_t &r0, uint32_t &r1, uint
 // Row-major source (matrix operand or NHWC feature map), any K and any alignment; one thread per word of a row.  The 32
 // bytes of a word are two 16-byte loads at byte addresses; the last, incomplete word of a row loads the row's last 32
 // bytes and shifts its planes down, so no byte outside the row is read (rows of fewer than 32 bytes go byte by byte).
-// Bound by HBM: 4096 x 4096 2-bit codes take 4.5 us.  The generic kernel, which took every row whose length is no
+// Bound by HBM: 4096 x 4096 2-bit codes take 3.5 us, 1.9 of them the launch.  The generic kernel, which took every row whose length is no
 // multiple of 16, read such rows byte by byte: 777 rows of 1999 codes 9.6 us, here under 3 us.
 template <int BITS, bool PM1>
 __global__ __launch_bounds__(256) void pack_rows_kernel(const uint8_t *__restrict__ src, uint32_t *__restrict__ dst,
