@@ -22,6 +22,16 @@ inline int64_t round_up(int64_t a, int64_t b) { return ceil_div(a, b) * b; }
 // Checks the status of the launch just issued (no synchronisation).
 int check_launch(const char *what);
 
+// A launch has less than 2^32 threads: of a larger one the runtime drops blocks without an error.  A kernel with a thread per
+// item is launched in slices: launch(first item, blocks of 256).
+template <class F> void in_slices(int64_t items, F &&launch)
+{
+    constexpr int64_t slice = int64_t(1) << 31;
+    for (int64_t first = 0; first < items; first += slice)
+        launch(first, static_cast<unsigned>(ceil_div(items - first < slice ? items - first : slice, 256)));
+}
+constexpr int64_t kMaxBlocks = (int64_t(1) << 24) - 1;      // of 256 threads
+
 inline hipStream_t as_stream(void *s) { return reinterpret_cast<hipStream_t>(s); }
 
 // bits in 1..8; +-1 only with one bit (Sec. 3.2 defines it for 1-bit operands).

@@ -240,6 +240,7 @@ static bool try_mfma(const Problem &pr, MfmaParams &mp, void *stream, int &rc, S
         if (const int f = ov(OV_MFMA_FN); f == 1 || (f == 2 && wide_fits && nsplit == 1)) fn = f;   // (tests, experiments)
         const int64_t wave_tiles = ceil_div(pr.M, 32) * ceil_div(pr.N, 32 * fn);
         const unsigned g = static_cast<unsigned>(nsplit == 1 ? ceil_div(wave_tiles, 4) : tiles);
+        if (g > kMaxBlocks) return false;
         const int gmax = static_cast<int>(ceil_div(nse / 4, nsplit));  // most groups of four steps a wave has
         const int vw = mp.Cw % 4 == 0 ? 4 : odd_words ? 1 : 2;
         if (plan) {
@@ -309,7 +310,7 @@ static int run_tile(const Problem &pr, TileParams &p, int vw, void *stream)
             return fail(APNN_ERR_OVERFLOW, "%s: the pooled sum of four results may exceed int32", pr.who);
     }
     const int64_t tiles = ceil_div(pr.M, 16 * r) * ceil_div(pr.N, 16 * r);
-    if (tiles > 0x7FFFFFFF) return fail(APNN_ERR_INVALID_ARG, "%s: problem too large for one launch", pr.who);
+    if (tiles > kMaxBlocks) return fail(APNN_ERR_INVALID_ARG, "%s: problem too large for one launch", pr.who);
     // XCD-aware tile order: among the factorizations of 8 that divide the tile
     // grid, take the one with the smallest per-XCD operand footprint.
     p.xm = p.xn = 0;

@@ -48,9 +48,9 @@ __device__ __forceinline__ size_t dst_index(const PackGeom &g, int64_t row, int 
 }
 
 __global__ __launch_bounds__(256) void pack_generic_kernel(const uint8_t *__restrict__ src,
-                                                           uint32_t *__restrict__ dst, PackGeom g)
+                                                           uint32_t *__restrict__ dst, PackGeom g, int64_t first)
 {
-    const int64_t idx = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    const int64_t idx = first + static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
     const int64_t total = g.rows * g.ldw;
     if (idx >= total) return;
     const int64_t row = idx / g.ldw;
@@ -348,9 +348,9 @@ __global__ __launch_bounds__(256) void pack_nchw_kernel(const uint8_t *__restric
 __global__ __launch_bounds__(256) void quantize_pack_kernel(const float *__restrict__ src,
                                                             uint32_t *__restrict__ dst, int64_t rows,
                                                             int64_t K, int ldw, int bits, float zero,
-                                                            float step)
+                                                            float step, int64_t first)
 {
-    const int64_t idx = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    const int64_t idx = first + static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
     if (idx >= rows * ldw) return;
     const int64_t row = idx / ldw;
     const int kw = static_cast<int>(idx - row * ldw);
@@ -544,18 +544,19 @@ static int launch_pack(const char *who, const void *src, uint32_t *dst, const Pa
     const int64_t total = g.rows * g.ldw;
     if (total == 0) return APNN_OK;
     if (total > (int64_t(1) << 38)) return fail(APNN_ERR_INVALID_ARG, "%s: tensor too large", who);
-    const unsigned grid = static_cast<unsigned>(ceil_div(total, 256));
     // plain rows of K contiguous bytes, destination planes of a row adjacent
     const bool rows_form = g.k_stride == 1 && g.row_stride == g.K && g.outer_div == g.rows && g.inner_n == 1 &&
                            total < (int64_t(1) << 32) - 256 && g.K <= INT32_MAX - 32;
     if (rows_form)
         with_bits(g.bits, g.pm1, [&](auto bc, auto pc) {
-            hipLaunchKernelGGL((pack_rows_kernel<decltype(bc)::value, decltype(pc)::value>), dim3(grid), dim3(256), 0, as_stream(stream),
+            hipLaunchKernelGGL((pack_rows_kernel<decltype(bc)::value, decltype(pc)::value>), dim3(static_cast<unsigned>(ceil_div(total, 256))), dim3(256), 0, as_stream(stream),
                                static_cast<const uint8_t *>(src), dst, static_cast<uint32_t>(total), static_cast<int>(g.K), g.ldw);
         });
     else
-        hipLaunchKernelGGL(pack_generic_kernel, dim3(grid), dim3(256), 0, as_stream(stream),
-                           static_cast<const uint8_t *>(src), dst, g);
+        in_slices(total, [&](int64_t first, unsigned blocks) {
+            hipLaunchKernelGGL(pack_generic_kernel, dim3(blocks), dim3(256), 0, as_stream(stream),
+                               static_cast<const uint8_t *>(src), dst, g, first);
+        });
     return check_launch(who);
 }
 
@@ -600,8 +601,7 @@ extern "C" int apnn_pack_fmap(const void *src_dev, apnn_layout layout, int64_t N
         // pixels exceed the LDS
         const int px = N * ceil_div(HW, 256) < 512 || static_cast<int64_t>(bits) * g.ldw > 47 ? 64 : 256;
         const int64_t bpi = ceil_div(HW, px), lds = 4 * px * ((static_cast<int64_t>(bits) * g.ldw) | 1);
-        // (a launch has less than 2^32 threads: beyond, the runtime drops blocks without an error)
-        if (HW >= 4 && N * bpi < (int64_t(1) << 24) && lds <= 48 * 1024 && HW <= INT32_MAX - 256 && C <= INT32_MAX - 32) {
+        if (HW >= 4 && N * bpi <= kMaxBlocks && lds <= 48 * 1024 && HW <= INT32_MAX - 256 && C <= INT32_MAX - 32) {
             with_bits(bits, g.pm1, [&](auto bc, auto pc) {
                 constexpr int BITS = decltype(bc)::value;
                 constexpr bool PM1 = decltype(pc)::value;
@@ -655,12 +655,13 @@ extern "C" int apnn_pack_patches(const uint8_t *src_dev, int64_t N, int64_t C, i
     // row kernel: needs pad <= 32 (non-negative string positions) and the plane strings of R x C rows in LDS
     const int rw = static_cast<int>((W + 31) / 32) + 4;
     const size_t lds = static_cast<size_t>(R) * C * bits * rw * sizeof(uint32_t);
-    if (pad <= 32 && lds <= 48 * 1024 && N * Ho <= 0x7FFFFFFF && (N * C * H * W) < (int64_t(1) << 40)) {
+    if (pad <= 32 && lds <= 48 * 1024 && N * Ho <= kMaxBlocks && (N * C * H * W) < (int64_t(1) << 40)) {
         hipLaunchKernelGGL(pack_patches_rows_kernel, dim3(static_cast<unsigned>(N * Ho)), dim3(256), lds, as_stream(stream),
                            src_dev, dst_dev, static_cast<int>(C), static_cast<int>(H), static_cast<int>(W), Ho, Wo, R, S,
                            stride, pad, bits, ldw, rw);
         return check_launch("apnn_pack_patches");
     }
+    if (ceil_div(npix, 32) > kMaxBlocks) return fail(APNN_ERR_INVALID_ARG, "apnn_pack_patches: too many pixels for one launch");
     const unsigned grid = static_cast<unsigned>(ceil_div(npix, 32));
     hipLaunchKernelGGL(pack_patches_kernel, dim3(grid), dim3(256), 0, as_stream(stream), src_dev, dst_dev, npix,
                        static_cast<int>(C), static_cast<int>(H), static_cast<int>(W), Ho, Wo, R, S, stride, pad, bits, ldw);
@@ -708,7 +709,7 @@ extern "C" int apnn_quantize(const float *src_dev, int64_t rows, int64_t K, floa
     const int nl = fills(8) ? 8 : fills(2) ? 2 : 1;
     const int64_t segs = short_rows ? 1 : ceil_div(K, 256 * nl), waves = short_rows ? ceil_div(rows, 2 * nl) : rows * segs;
     const float inv = 1.0f / step;
-    if (waves < (int64_t(1) << 32) - 4 && rows < (int64_t(1) << 32) - 16 && K <= INT32_MAX - 2048 && inv >= 0x1p-126f && inv <= 0x1p126f) {
+    if (ceil_div(waves, 4) <= kMaxBlocks && rows < (int64_t(1) << 32) - 16 && K <= INT32_MAX - 2048 && inv >= 0x1p-126f && inv <= 0x1p126f) {
         int e;
         const bool exact = std::frexp(step, &e) == 0.5f;
         auto go = [&](auto kernel) {
@@ -725,9 +726,10 @@ extern "C" int apnn_quantize(const float *src_dev, int64_t rows, int64_t K, floa
         else if (nl == 2) by_form(std::integral_constant<int, 2>{});
         else by_form(std::integral_constant<int, 1>{});
     } else {
-        const unsigned grid = static_cast<unsigned>(ceil_div(rows * ldw, 256));
-        hipLaunchKernelGGL(quantize_pack_kernel, dim3(grid), dim3(256), 0, as_stream(stream), src_dev, dst_dev, rows, K,
-                           ldw, bits, zero, step);
+        in_slices(rows * ldw, [&](int64_t item, unsigned blocks) {
+            hipLaunchKernelGGL(quantize_pack_kernel, dim3(blocks), dim3(256), 0, as_stream(stream), src_dev, dst_dev, rows, K,
+                               ldw, bits, zero, step, item);
+        });
     }
     return check_launch("apnn_quantize");
 }

@@ -8,9 +8,9 @@ namespace apnn {
 // a time, so codes are never unpacked.
 __global__ __launch_bounds__(256) void maxpool_kernel(const uint32_t *__restrict__ X, uint32_t *__restrict__ out,
                                                       int64_t npix_out, int H, int W, int Ho, int Wo, int Cw,
-                                                      int bits, int k, int stride, int pad)
+                                                      int bits, int k, int stride, int pad, int64_t first)
 {
-    const int64_t idx = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    const int64_t idx = first + static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
     if (idx >= npix_out * Cw) return;
     const int64_t pix = idx / Cw;
     const int cw = static_cast<int>(idx - pix * Cw);
@@ -48,9 +48,9 @@ __global__ __launch_bounds__(256) void maxpool_kernel(const uint32_t *__restrict
 template <int BITS>
 __global__ __launch_bounds__(256) void maxpool3_kernel(const uint32_t *__restrict__ X, uint32_t *__restrict__ out,
                                                        int64_t npix_out, int H, int W, int Ho, int Wo, int Cw,
-                                                       int bits, int k, int stride, int pad)
+                                                       int bits, int k, int stride, int pad, int64_t first)
 {
-    const int64_t idx = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    const int64_t idx = first + static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
     if (idx >= npix_out * Cw) return;
     const int64_t pix = idx / Cw;
     const int cw = static_cast<int>(idx - pix * Cw);
@@ -267,16 +267,15 @@ extern "C" int apnn_maxpool(const uint32_t *X_dev, int64_t N, int64_t H, int64_t
     const int Ho = static_cast<int>((H + 2 * pad - k) / stride + 1), Wo = static_cast<int>((W + 2 * pad - k) / stride + 1);
     const int Cw = static_cast<int>(ceil_div(C, 32));
     const int64_t npix = N * Ho * Wo;
-    const unsigned grid = static_cast<unsigned>(ceil_div(npix * Cw, 256));
-    if (k <= 3 && bits <= 2)
-        hipLaunchKernelGGL(maxpool3_kernel<2>, dim3(grid), dim3(256), 0, as_stream(stream), X_dev, out_dev, npix,
-                           static_cast<int>(H), static_cast<int>(W), Ho, Wo, Cw, bits, k, stride, pad);
-    else if (k <= 3 && bits <= 4)
-        hipLaunchKernelGGL(maxpool3_kernel<4>, dim3(grid), dim3(256), 0, as_stream(stream), X_dev, out_dev, npix,
-                           static_cast<int>(H), static_cast<int>(W), Ho, Wo, Cw, bits, k, stride, pad);
-    else
-        hipLaunchKernelGGL(maxpool_kernel, dim3(grid), dim3(256), 0, as_stream(stream), X_dev, out_dev, npix,
-                           static_cast<int>(H), static_cast<int>(W), Ho, Wo, Cw, bits, k, stride, pad);
+    auto go = [&](auto kernel) {
+        in_slices(npix * Cw, [&](int64_t first, unsigned blocks) {
+            hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, as_stream(stream), X_dev, out_dev, npix, static_cast<int>(H),
+                               static_cast<int>(W), Ho, Wo, Cw, bits, k, stride, pad, first);
+        });
+    };
+    if (k <= 3 && bits <= 2) go(maxpool3_kernel<2>);
+    else if (k <= 3 && bits <= 4) go(maxpool3_kernel<4>);
+    else go(maxpool_kernel);
     return check_launch("apnn_maxpool");
 }
 

@@ -153,8 +153,8 @@ int main()
     // ---- 32-bit ranges of the large-layer kernel: operands below 2^31 bytes, one padded image below 2^27 words
     apnn_layer_desc V{};
     V.acc_out_dev = fy;
-    auto chosen = [&](int64_t images, int64_t H, int64_t W, int64_t Cin, int64_t Cout, int R, int pad, int q) {
-        V.conv = apnn_conv_desc{images, H, W, Cin, Cout, R, R, 1, pad, 1, q, APNN_ENC_PM1, APNN_ENC_UNSIGNED};
+    auto chosen = [&](int64_t images, int64_t H, int64_t W, int64_t Cin, int64_t Cout, int R, int pad, int q, int stride = 1) {
+        V.conv = apnn_conv_desc{images, H, W, Cin, Cout, R, R, stride, pad, 1, q, APNN_ENC_PM1, APNN_ENC_UNSIGNED};
         g_kernel.clear();
         (void)apnn_layer(&V, fw, fw, nullptr, nullptr);
         return g_kernel;
@@ -165,9 +165,12 @@ int main()
     EXPECT(chosen(1, 16, 16, 2048, 932096, 3, 1, 2) == "small_conv");                                      // weights beyond
     EXPECT(chosen(1, 2043, 2044, 512, 64, 3, 0, 2) == "small_conv_wide");                                   // (2043 + 3)(2044 + 3) 32 words
     EXPECT(chosen(1, 2045, 2045, 512, 64, 3, 0, 2) == "small_conv");                                        // 2048^2 32 = 2^27
+    // at most 2^24 - 1 blocks of four 32 x 32 tiles, and no more in the popcount kernel: else refused
+    EXPECT(chosen(682, 1024, 1024, 64, 96, 1, 0, 1) == "small_conv" && g_grid == 682u * 3 << 13);
+    EXPECT(chosen(683, 1024, 1024, 64, 96, 1, 0, 1) == "" && std::strstr(apnn_last_error(), "too large"));
     // an odd number of channel words: one padded image below 2^31 words, else the popcount kernel
-    EXPECT(chosen(1, 32760, 32766, 32, 32, 1, 0, 2) == "small_conv");
-    EXPECT(chosen(1, 32767, 32767, 32, 32, 1, 0, 2) == "tile2");                                            // 32768^2 2 = 2^31
+    EXPECT(chosen(1, 32760, 32766, 32, 32, 1, 0, 2, 2) == "small_conv");
+    EXPECT(chosen(1, 32767, 32767, 32, 32, 1, 0, 2, 2) == "tile2");                                            // 32768^2 2 = 2^31
     EXPECT(chosen(1, 28, 28, 96, 64, 3, 1, 2) == "small_conv" && g_mp.Cw == 3);
     EXPECT(apnn_debug_force("MFMA_SMALL", 0) == APNN_OK && chosen(1, 28, 28, 96, 64, 3, 1, 2) == "tile2");
     apnn_debug_reset();

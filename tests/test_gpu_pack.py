@@ -166,3 +166,19 @@ def test_quantize_steps_whose_reciprocal_leaves_the_range(step, rows, K):
     x[:, ::7] = np.array([3.4e38, -3.4e38, 1e-45, 0.0, np.inf, -np.inf, np.nan], np.float32)[np.arange(x[:, ::7].shape[1]) % 7]
     codes, pad = hp.unpack_matrix(hp.words_u32(B.apnn_quantize(dev(x), 0.0, step, 3)), rows, K, 3)
     assert np.array_equal(codes, oracle.quantize(x, 0.0, step, 3)) and pad == 0
+
+
+@pytest.mark.parametrize("call", ["pack", "quantize", "maxpool"])
+def test_more_words_than_a_launch_has_threads(call):
+    """2^32 words and a few: more than one launch."""
+    n = (1 << 30) + 5
+    if call == "maxpool":                               # one-pixel frames of one channel word
+        x = torch.arange(n, dtype=torch.int32, device="cuda").repeat(4)
+        out = B.apnn_maxpool(x, 4 * n, 1, 1, 32, 1, 1, 1, 0)
+        assert torch.equal(out, x)
+    else:                                               # rows of one value: four words each
+        x = torch.randint(0, 2, (n, 1), dtype=torch.uint8, device="cuda")
+        out = B.apnn_pack(x, 1, U) if call == "pack" else B.apnn_quantize(x.float(), 0.0, 1.0, 1)
+        assert torch.equal(out.view(n, 4)[:, 0], x.view(-1).int()) and not out.view(n, 4)[:, 1:].any()
+    del x, out
+    torch.cuda.empty_cache()
