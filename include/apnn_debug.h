@@ -22,6 +22,9 @@
  *   MFMA_NSPLIT   1 | 4: waves of a block that split K of a 32 x 32 tile
  *   MFMA_FN       1 | 2: 32 x 32 or 32 x 64 wave tiles of the small-layer kernel
  *   MFMA_SHORTK   0: no special case for K <= 256
+ *   MFMA_HALO     convolutions staged once per block: 0 never; 1 | 2: whenever it
+ *                 applies, with 128 or 256 pixels a block (unset: not where
+ *                 MFMA_TILE, _SMALL, _NSPLIT or _FN asks for another form)
  * A forced value the dispatch cannot honour for a call is ignored for that call.
  */
 #ifndef APNN_DEBUG_H

@@ -1,0 +1,126 @@
+// Host side of conv_halo_kernel: which layers it takes and how they are laid out in LDS.
+#include "conv_halo_launch.h"
+
+#include "common.h"
+#include "mfma_launch.h"
+
+namespace apnn {
+
+static Divisor divisor(int64_t d)
+{
+    Divisor r{0, 0, static_cast<int>(d)};
+    int bits = 0;
+    while ((int64_t(1) << bits) < d) ++bits;
+    r.s = 31 + bits;                                     // n < 2^31: the error n (m d - 2^s) / 2^s stays below 1
+    r.m = static_cast<uint32_t>((uint64_t(1) << r.s) / static_cast<uint64_t>(d) + 1);
+    return r;
+}
+
+bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB, int force, hipStream_t st)
+{
+    // int32 results alone, or planes of one or two bits alone (the epilogue keeps no other output)
+    const bool ints = mp.Y && !mp.scale && !mp.T && !mp.pool && mp.N % 4 == 0;
+    const bool planes = mp.out && !mp.Y && !mp.T && mp.q_out <= 2 && (!mp.res || mp.q_res <= 2);
+    if (!ints && !planes) return false;
+    // Few tiles leave the chip to the layers that split K over more waves (tiles of 64 x 128 outputs, us, the other kernels
+    // first): 9 steps on 196 tiles 6.9, 5.1; 18 on 98 5.7, 5.4; 36 on 100 8.8, 7.9; 36 on 52 6.1, 7.7; stride 2: 9 on 98 4.9,
+    // 5.5, 36 on 104 8.9, 8.5; pooled, 72 on 104 28.3, 20.1, 36 on 28 8.4, 12.6.
+    const int tilesN = static_cast<int>(ceil_div(mp.N, 64));
+    if (force < 0 && ceil_div(mp.M, mp.pool ? 512 : 128) * tilesN < (mp.stride > 1 ? 128 : 96)) return false;
+    const int64_t Hq = mp.H + 2 * static_cast<int64_t>(mp.pad), Wq = mp.W + 2 * static_cast<int64_t>(mp.pad);
+    const int64_t Kw = static_cast<int64_t>(mp.R) * mp.S * mp.Cw, lim = int64_t(1) << 31;
+    if ((images + 1) * Hq * Wq >= lim || 4 * images * mp.H * mp.W * mp.PA * mp.Cw >= lim || 4 * mp.N * mp.PB * Kw >= lim) return false;
+    if (mp.M > lim - 1024) return false;
+
+    ConvHaloParams p{};
+    p.A = mp.A; p.B = mp.B;
+    p.bytesA = static_cast<uint32_t>(4 * images * mp.H * mp.W * mp.PA * mp.Cw);
+    p.bytesB = static_cast<uint32_t>(4 * mp.N * mp.PB * Kw);
+    p.M = mp.M; p.N = mp.N;
+    p.images = static_cast<int>(images); p.H = mp.H; p.W = mp.W;
+    p.Hq = static_cast<int>(Hq); p.Wq = static_cast<int>(Wq);
+    const int64_t rows = mp.pool ? mp.Hp : mp.Ho, cols = mp.pool ? mp.Wp : mp.Wo;
+    p.per_image = divisor(rows * cols); p.per_row = divisor(cols);
+    p.frame = divisor(Hq * Wq); p.line = divisor(Wq);
+    p.stride = mp.stride; p.pad = mp.pad; p.R = mp.R; p.S = mp.S;
+    p.Cw = mp.Cw; p.half = (mp.Cw + 1) / 2;
+    p.PA = mp.PA; p.PB = mp.PB; p.DA = mp.DA; p.DB = mp.DB;
+    p.digits = divisor(p.DA); p.halves = divisor(p.half);
+    p.pm1 = kindB == OPK_PM1;
+    p.pool = mp.pool;
+    p.steps = static_cast<int>(Kw / mp.Cw) * p.half;
+    p.scale = mp.scale; p.bias = mp.bias; p.res = mp.res; p.q_res = mp.q_res; p.res_scale = mp.res_scale;
+    p.out = mp.out; p.q_out = mp.q_out; p.NW = mp.NW; p.Y = mp.Y;
+    // a two-plane digit enters as half its value; planes are made of a quarter of the result
+    p.scaleA = 0x01010101 * (0x7f + (kindA == OPK_U2 ? 1 : 0) - (planes ? 2 : 0));
+    p.scaleB = 0x01010101 * (0x7f + (kindB == OPK_PM1 ? 0 : 1));
+
+    // steps read together, words staged together (as the launcher instantiates them)
+    const int hw = p.Cw % 4 == 0 ? 2 : 1, sw = p.Cw % 4 == 0 ? 4 : p.Cw % 2 == 0 ? 2 : 1, granule = (kindA == OPK_U1 ? 1 : 2) * hw;
+    // records are an odd number of granules apart: a step's reads of consecutive pixels hit all banks
+    const int granules = p.DA * 2 * (p.half / hw);
+    p.rec = granule * (granules % 2 == 0 ? granules + 1 : granules);
+    p.pieces = p.DA * static_cast<int>(ceil_div(2 * p.half, sw));
+    while ((1 << p.share) < p.pieces) ++p.share;
+
+    // Weights of up to kHaloStay steps stay in LDS while a block walks over its tiles; longer ones pass through in chunks of
+    // whole taps.
+    const bool stay = p.DB == 1 && p.steps <= kHaloStay;
+    if (!stay && p.half > kHaloChunk) return false;
+    p.chunk = stay ? p.steps : kHaloChunk / p.half * p.half;
+    const int64_t codes = (stay ? 1 : 2) * p.chunk * 512;
+
+    struct Tiling { int64_t tilesM, records, lds, blocks, buffers; };     // blocks: that a compute unit holds
+    auto tiling = [&](int fp) {
+        Tiling t{};
+        const int64_t pixels = 128 * fp;
+        t.tilesM = ceil_div(mp.M, pixels);
+        // the longest range of padded positions a tile touches: row steps and image steps between its first and last pixel
+        const int64_t px = mp.pool ? pixels / 4 : pixels, step = mp.pool ? 2 * mp.stride : mp.stride;
+        const int64_t new_rows = (px - 1 + cols - 1) / cols, new_images = (px - 1 + rows * cols - 1) / (rows * cols);
+        const int64_t between = Hq - rows * step;          // lines an image has beyond its rows' steps
+        const int64_t reach = new_rows * step * Wq + (cols - 1) * step + new_images * (between > 0 ? between : 0) * Wq +
+                              (mp.pool ? mp.stride * (Wq + 1) : 0) + (mp.R - 1) * Wq + mp.S;
+        t.records = (reach < images * Hq * Wq ? reach : images * Hq * Wq) * p.rec;
+        const int64_t most = fp == 4 ? 2 : fp == 2 ? 3 : 4;                // by registers: waves a SIMD holds
+        for (t.buffers = stay ? 2 : 1; t.buffers > 0; --t.buffers) {
+            t.lds = 4 * (128 + codes + t.buffers * t.records);
+            t.blocks = 160 * 1024 / t.lds < most ? 160 * 1024 / t.lds : most;
+            // a second buffer of records is for blocks that have a second tile
+            if (t.buffers == 1 || (t.blocks > 0 && t.tilesM * tilesN > 256 * t.blocks / tilesN * tilesN && 256 * t.blocks >= tilesN)) break;
+        }
+        return t;
+    };
+    // 64 x 256 outputs a block, or 64 x 128 (measured, us, 64 x 128 against 64 x 256):
+    //   weights that stay: 9 steps on 1568 tiles of 256 17.9, 15.3; 18 steps 23.6, 29.2; 9 steps with stride 2 on 784 13.5, 17.9
+    //   chunks: what a compute unit holds of pixels decides; 36 steps on 392 tiles 17.2, 14.7 (512 pixels against 384); 72 steps
+    //   on 784 tiles 47, 59 (256 either way)
+    // Pooled layers have one form, 64 channels x 128 pooled pixels.
+    int fp = 4;
+    Tiling t = tiling(mp.pool ? 4 : 1);
+    if (!mp.pool) {
+        const Tiling two = tiling(2);
+        fp = force == 1 || force == 2 ? force
+             : stay ? (p.steps <= 12 && mp.stride == 1 && two.blocks > 0 && two.tilesM * tilesN >= 256 ? 2 : 1)
+                    : (2 * two.blocks > t.blocks && two.tilesM * tilesN >= 192 ? 2 : 1);
+        if (fp == 2) t = two;
+    }
+    const int64_t tiles = t.tilesM * tilesN;
+    if (t.blocks < 1 || tiles > kMaxBlocks) return false;
+    int64_t grid = tiles;
+    if (t.buffers == 2) grid = 256 * t.blocks / tilesN * tilesN;           // whole rows of channel tiles
+    p.tilesM = static_cast<int>(t.tilesM);
+    p.per_column = divisor(tilesN);
+    p.words_codes = static_cast<int>(codes);
+    p.tile_step = static_cast<int>(grid / tilesN);
+    p.words_records = static_cast<int>(t.records);
+    const unsigned g = static_cast<unsigned>(grid);
+    const int bytes = static_cast<int>(t.lds);
+    switch (kindA) {
+        case OPK_U1: return launch_conv_halo_u1(p, stay, fp, g, bytes, st);
+        case OPK_U2: return launch_conv_halo_u2(p, stay, fp, g, bytes, st);
+        default: return launch_conv_halo_pm1(p, stay, fp, g, bytes, st);
+    }
+}
+
+}  // namespace apnn

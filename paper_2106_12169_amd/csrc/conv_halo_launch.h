@@ -1,0 +1,51 @@
+// Launcher of conv_halo_kernel: one translation unit per kind of features, so they compile in parallel.
+#pragma once
+#include <atomic>
+
+#include "conv_halo.h"
+
+namespace apnn {
+
+template <int KA, int HW, int SW, int FP, int PT, bool POOL, bool MULTI, bool STAY>
+bool launch_conv_halo(const ConvHaloParams &p, unsigned grid, int lds, hipStream_t st)
+{
+    const auto kernel = conv_halo_kernel<KA, HW, SW, 2, FP, PT, POOL, MULTI, STAY>;
+    static std::atomic<int> granted{0};                  // most dynamic LDS asked for so far (per instance)
+    if (lds > granted.load(std::memory_order_relaxed)) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
+            return false;
+        granted.store(lds, std::memory_order_relaxed);
+    }
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), lds, st, p);
+    return true;
+}
+
+template <int KA, int HW, int SW, int PT, bool MULTI, bool STAY>
+bool launch_conv_halo(const ConvHaloParams &p, int fp, unsigned grid, int lds, hipStream_t st)
+{
+    if (p.pool) return launch_conv_halo<KA, HW, SW, 4, PT, true, MULTI, STAY>(p, grid, lds, st);
+    return fp == 2 ? launch_conv_halo<KA, HW, SW, 2, PT, false, MULTI, STAY>(p, grid, lds, st)
+                   : launch_conv_halo<KA, HW, SW, 1, PT, false, MULTI, STAY>(p, grid, lds, st);
+}
+
+template <int KA, bool MULTI, bool STAY> bool launch_conv_halo(const ConvHaloParams &p, int fp, unsigned grid, int lds, hipStream_t st)
+{
+    if constexpr (KA == OPK_U2 && !MULTI && !STAY) {     // 256 and 512 channels: granules of a tap known to the compiler
+        if (p.Cw == 8) return launch_conv_halo<KA, 2, 4, 2, MULTI, STAY>(p, fp, grid, lds, st);
+        if (p.Cw == 16) return launch_conv_halo<KA, 2, 4, 4, MULTI, STAY>(p, fp, grid, lds, st);
+    }
+    if (p.Cw % 4 == 0) return launch_conv_halo<KA, 2, 4, 0, MULTI, STAY>(p, fp, grid, lds, st);
+    if (p.Cw % 2 == 0) return launch_conv_halo<KA, 1, 2, 0, MULTI, STAY>(p, fp, grid, lds, st);
+    return launch_conv_halo<KA, 1, 1, 0, MULTI, STAY>(p, fp, grid, lds, st);
+}
+
+template <int KA, bool MULTI> bool launch_conv_halo(const ConvHaloParams &p, bool stay, int fp, unsigned grid, int lds, hipStream_t st)
+{
+    return stay ? launch_conv_halo<KA, MULTI, true>(p, fp, grid, lds, st) : launch_conv_halo<KA, MULTI, false>(p, fp, grid, lds, st);
+}
+
+bool launch_conv_halo_u1(const ConvHaloParams &p, bool stay, int fp, unsigned grid, int lds, hipStream_t st);
+bool launch_conv_halo_u2(const ConvHaloParams &p, bool stay, int fp, unsigned grid, int lds, hipStream_t st);
+bool launch_conv_halo_pm1(const ConvHaloParams &p, bool stay, int fp, unsigned grid, int lds, hipStream_t st);
+
+}  // namespace apnn

@@ -14,9 +14,9 @@ namespace apnn {
 // Kernel-choice overrides (tests, experiments).  Each is read from the process
 // environment once, the first time any of them is asked for, and can afterwards be
 // set or cleared through apnn_debug_force; the dispatch itself only loads an int.
-enum Override { OV_MFMA, OV_TILE, OV_MFMA_TILE, OV_MFMA_SHORTK, OV_MFMA_SMALL, OV_MFMA_NSPLIT, OV_MFMA_FN, OV_INT8, OV_COUNT };
+enum Override { OV_MFMA, OV_TILE, OV_MFMA_TILE, OV_MFMA_SHORTK, OV_MFMA_SMALL, OV_MFMA_NSPLIT, OV_MFMA_FN, OV_INT8, OV_MFMA_HALO, OV_COUNT };
 static const char *const kOverrideNames[OV_COUNT] = {"MFMA", "TILE", "MFMA_TILE", "MFMA_SHORTK", "MFMA_SMALL",
-                                                     "MFMA_NSPLIT", "MFMA_FN", "INT8"};
+                                                     "MFMA_NSPLIT", "MFMA_FN", "INT8", "MFMA_HALO"};
 static std::atomic<int> g_override[OV_COUNT];
 
 static void overrides_from_env()
@@ -203,6 +203,14 @@ static bool try_mfma(const Problem &pr, MfmaParams &mp, void *stream, int &rc, S
     if (pr.conv && kA == OPK_PM1) kA = OPK_PM1Z;         // -1/+1 features: taps outside the frame must contribute 0
     mp.PA = pr.PA; mp.PB = pr.PB;
     mp.out_scale = (kA == OPK_U2 ? 2.0f : 1.0f) * (kB == OPK_U2 ? 2.0f : 1.0f);
+    // (another form asked for by an override stays what it is)
+    const bool other = ov(OV_MFMA_TILE) >= 0 || ov(OV_MFMA_SMALL) >= 0 || ov(OV_MFMA_NSPLIT) >= 0 || ov(OV_MFMA_FN) >= 0;
+    const int halo = ov(OV_MFMA_HALO);
+    if (pr.conv && !plan && halo != 0 && (halo > 0 || !other) && launch_conv_halo &&
+        launch_conv_halo(mp, pr.images, kA, kB, halo, as_stream(stream))) {
+        rc = check_launch(pr.who);
+        return true;
+    }
     // 0 pad bits of two -1/+1 operands multiply to +1 at every padded K position
     int t = odd_words ? 32 : pick_mfma_tile(pr.M, pr.N, pr.conv);
     if (kA == OPK_PM1Z && t == 128) t = 64;              // instantiated for the 64-tile and the small-layer kernel
