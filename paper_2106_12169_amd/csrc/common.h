@@ -32,6 +32,9 @@ template <class F> void in_slices(int64_t items, F &&launch)
 }
 constexpr int64_t kMaxBlocks = (int64_t(1) << 24) - 1;      // of 256 threads
 
+// Override INPUT_TILE (layer.hip): -1 when it is not set.
+int input_tile_override();
+
 inline hipStream_t as_stream(void *s) { return reinterpret_cast<hipStream_t>(s); }
 
 // bits in 1..8; +-1 only with one bit (Sec. 3.2 defines it for 1-bit operands).

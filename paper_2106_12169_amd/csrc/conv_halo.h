@@ -8,13 +8,8 @@
 // the block's four waves; features of two planes are stored as interleaved pairs of bits, which leaves five vector
 // instructions per 32 codes in the main loop.
 //
-// The matrix instruction gets the weights as its row operand: accumulator register r of lane (half lh, lr) is channel
-// row 8 (r / 4) + 4 lh + r % 4 of a 32-channel tile and pixel lr.  A lane then holds sixteen channels of one pixel, and the
-// planes of their codes are made without a lane exchange per value: t / 4 clamped to [0, 1] by the multiply-add's own clamp,
-// truncated to FP4 codes 0, 0.5, 1, 1.5 (2 for t >= 4) two at a time by the converter's stochastic rounding with seed 0, whose two
-// low bits are the planes.  The weight rows are dealt to the matrix rows so that nibble j of dword q in half lh is channel
-// 4 j + 2 lh + q: both halves' nibbles interleave into the plane word with one lane swap.  2.5 vector instructions per value
-// against about 14 with a compare and lane writes per value (finish_rows8).
+// The matrix instruction gets the weights as its row operand, so that a lane holds sixteen channels of one pixel, and the
+// planes of their codes are made in the lane (plane_codes.h).
 //
 // Bound by the vector instructions its waves issue (stage 1 of the ResNet-18 shape at batch 128: 510 a wave tile of 64 x 64
 // outputs, 2040 of the 2100 cycles a SIMD spends on one, 1152 of them under matrix instructions; prologue 2.5 us).  Measured
@@ -22,14 +17,9 @@
 // 256 channels 29, 15; 512 channels 31, 16.
 #pragma once
 #include "mfma_kernel.h"
+#include "plane_codes.h"
 
 namespace apnn {
-
-// n / d = (n m) >> s for 0 <= n < 2^31 (round-up reciprocal)
-struct Divisor {
-    uint32_t m;
-    int s, d;
-};
 
 struct ConvHaloParams {
     const uint32_t *A, *B;   // features [pixel][PA][Cw], weights [Cout][PB][taps][Cw]
@@ -63,75 +53,6 @@ struct ConvHaloParams {
 
 // Most weight steps that stay in LDS for all tiles of a block, and of a chunk of longer ones (2 KiB of codes a step)
 constexpr int kHaloStay = 26, kHaloChunk = 8;
-
-__device__ __forceinline__ int divide(int n, const Divisor &d)
-{
-    return static_cast<int>((static_cast<uint64_t>(static_cast<uint32_t>(n)) * d.m) >> d.s);
-}
-
-// acc, scale, bias -> clamp(acc scale + bias, 0, 1); NaN gives 0 (the clamp bit of the instruction)
-__device__ __forceinline__ float fma_clamp(float a, float b, float c)
-{
-    float t;
-    asm("v_fma_f32 %0, %1, %2, %3 clamp" : "=v"(t) : "v"(a), "v"(b), "v"(c));
-    return t;
-}
-
-typedef float v2f_t __attribute__((ext_vector_type(2)));
-typedef float v4f_t __attribute__((ext_vector_type(4)));
-typedef int v4i_t __attribute__((ext_vector_type(4)));
-
-// Byte B of d: two FP4 codes of 2 t, truncated (stochastic rounding, seed 0).  Written out because the compiler's builtin
-// does not keep the other bytes of its destination.
-template <int B> __device__ __forceinline__ void two_codes(uint32_t &d, v2f_t t)
-{
-    if constexpr (B == 0) asm("v_cvt_scalef32_sr_pk_fp4_f32 %0, %1, 0, 0.5" : "+v"(d) : "v"(t));
-    else if constexpr (B == 1) asm("v_cvt_scalef32_sr_pk_fp4_f32 %0, %1, 0, 0.5 op_sel:[0,0,1,0]" : "+v"(d) : "v"(t));
-    else if constexpr (B == 2) asm("v_cvt_scalef32_sr_pk_fp4_f32 %0, %1, 0, 0.5 op_sel:[0,0,0,1]" : "+v"(d) : "v"(t));
-    else asm("v_cvt_scalef32_sr_pk_fp4_f32 %0, %1, 0, 0.5 op_sel:[0,0,1,1]" : "+v"(d) : "v"(t));
-}
-
-// (mask & a) | (~mask & b)
-__device__ __forceinline__ uint32_t bit_select(uint32_t mask, uint32_t a, uint32_t b) { return (mask & a) | (~mask & b); }
-
-// Eight values of a lane (results / 4 of the channels 4 j + 2 lh + q of a tile) -> eight nibbles: code k < 4 is k, everything
-// above it 4.  sc, bi: the channels' constants, bi a quarter of the bias; res: the residual's codes, a nibble each.
-__device__ __forceinline__ uint32_t nibbles(const ConvHaloParams &p, const float (&v)[8], const v4f_t (&sc)[2], const v4f_t (&bi)[2],
-                                            uint32_t res)
-{
-    uint32_t d = 0u;
-    if (p.res) {
-        static_for<4>([&](auto bc) {
-            constexpr int b = decltype(bc)::value;
-            const v2f_t c = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(res, 0.5f, b);        // code / 4
-            v2f_t t;
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-                t[i] = fma_clamp(p.res_scale, c[i], __fmaf_rn(sc[b / 2][2 * (b & 1) + i], v[2 * b + i], bi[b / 2][2 * (b & 1) + i]));
-            two_codes<b>(d, t);
-        });
-    } else {
-        static_for<4>([&](auto bc) {
-            constexpr int b = decltype(bc)::value;
-            v2f_t t;
-#pragma unroll
-            for (int i = 0; i < 2; ++i) t[i] = fma_clamp(sc[b / 2][2 * (b & 1) + i], v[2 * b + i], bi[b / 2][2 * (b & 1) + i]);
-            two_codes<b>(d, t);
-        });
-    }
-    return d;
-}
-
-// Nibbles of q = 0 and 1 -> plane words of the tile's 32 channels: lanes of half b return the word of plane b.
-__device__ __forceinline__ uint32_t plane_words(uint32_t x, uint32_t y, int q_out)
-{
-    // plane 0 = bit 0 | bit 2, plane 1 = bit 1 | bit 2; bits 0 (x) and 1 (y) of each nibble are kept
-    uint32_t p0 = bit_select(0x11111111u, x | (x >> 2), (y << 1) | (y >> 1));
-    const uint32_t p1 = bit_select(0x11111111u, (x >> 1) | (x >> 2), y | (y >> 1));
-    if (q_out == 1) p0 |= p1;                           // clamp at 1
-    const auto both = __builtin_amdgcn_permlane32_swap(p0, p1, false, false);    // half b: plane b of either half's channels
-    return bit_select(0x33333333u, both[0], both[1] << 2);
-}
 
 // HW: channel words (steps) read together from a record; SW: channel words of a plane staged together (HW = 2: 4; HW = 1: 2, or
 // 1 for an odd number of channel words); FC: 32-channel tiles; FP: 32-pixel tiles of a wave.  POOL (FP = 4): tile f of a wave
@@ -169,11 +90,11 @@ __global__ __launch_bounds__(256, FP == 4 ? 2 : FP == 2 ? 3 : 4) void conv_halo_
     const __amdgpu_buffer_rsrc_t bufB = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(p.B), 0, p.bytesB, 0x00020000);
     constexpr uint32_t NOWHERE = 0x80000000u;                    // beyond every buffer: reads as zero
 
-    // ---- weights.  Packed output: matrix row -> channel as the header says; int32 output: in order, four to a store.
+    // ---- weights.  Packed output: matrix row -> channel as plane_codes.h says; int32 output: in order, four to a store.
     // Rows beyond the last channel read that channel's (their results are not stored); steps beyond the last, and the step a
     // lane half lacks when the number of channel words is odd, read the first words (the features are zero there).
     const int wrow = lane & 31, wtile = lane >> 5;
-    const int wch = p.Y ? wrow : 16 * ((wrow >> 3) & 1) + 4 * (wrow & 3) + 2 * ((wrow >> 2) & 1) + (wrow >> 4);
+    const int wch = p.Y ? wrow : code_channel_of_row(wrow);
     const int Kw = p.R * p.S * p.Cw;
     const uint32_t wlane = 4u * static_cast<uint32_t>(min(n0 + 32 * wtile + wch, p.N - 1) * (p.PB * Kw));
     uint32_t wv[NI][2][HW];
@@ -302,10 +223,9 @@ __global__ __launch_bounds__(256, FP == 4 ? 2 : FP == 2 ? 3 : 4) void conv_halo_
     fetch_weights(0, 0, STAY ? p.steps : min(p.chunk, p.steps));
     fetch_pixels(now, tid);
     if (!p.Y && tid < 64 * FC) {                                 // scale (first half of the threads) and bias of a channel
-        const int k = tid % (32 * FC), r = k & 15, h = (k >> 4) & 1;
-        const int ch = n0 + (k & ~31) + 16 * ((r >> 2) & 1) + 4 * (r & 3) + 2 * h + (r >> 3);
+        const int k = tid % (32 * FC), ch = n0 + (k & ~31) + code_channel(k & 15, (k >> 4) & 1);
         float v = 0.0f;
-        if (ch < p.N) v = tid < 32 * FC ? p.scale[ch] : 0.25f * p.bias[ch];
+        if (ch < p.N) v = tid < 32 * FC ? p.scale[ch] : quarter(p.bias[ch]);
         sP[tid] = v;
     }
     write_weights(sB, STAY ? p.steps : p.chunk);
@@ -584,7 +504,7 @@ __global__ __launch_bounds__(256, FP == 4 ? 2 : FP == 2 ? 3 : 4) void conv_halo_
                     // the residual's plane words -> nibbles of this q
                     const uint32_t z0 = res[f][c][0] >> (2 * lh), z1 = res[f][c][1] >> (2 * lh);
                     const uint32_t e = q == 0 ? (z0 & 0x11111111u) | ((z1 << 1) & 0x22222222u) : ((z0 >> 1) & 0x11111111u) | (z1 & 0x22222222u);
-                    d[f][q] = nibbles(p, v, sc, bi, e);
+                    d[f][q] = nibbles(v, sc, bi, p.res != nullptr, p.res_scale, e);
                 });
             });
 #pragma unroll

@@ -6,16 +6,6 @@
 
 namespace apnn {
 
-static Divisor divisor(int64_t d)
-{
-    Divisor r{0, 0, static_cast<int>(d)};
-    int bits = 0;
-    while ((int64_t(1) << bits) < d) ++bits;
-    r.s = 31 + bits;                                     // n < 2^31: the error n (m d - 2^s) / 2^s stays below 1
-    r.m = static_cast<uint32_t>((uint64_t(1) << r.s) / static_cast<uint64_t>(d) + 1);
-    return r;
-}
-
 bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB, int force, hipStream_t st)
 {
     // int32 results alone, or planes of one or two bits alone (the epilogue keeps no other output)

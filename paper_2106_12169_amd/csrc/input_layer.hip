@@ -18,13 +18,13 @@
 // the per-channel constant 128 * sum_k w[k], made by the weight packer, is added
 // back in the epilogue; positions outside the frame are x = 0, i.e. -128, and are
 // covered by the same constant (zero-contribution padding, Sec. 4.2 (b)).
+#include <atomic>
+
 #include "common.h"
+#include "input_tile.h"
 #include "mfma_kernel.h"
 
 namespace apnn {
-
-typedef int v4i_t __attribute__((ext_vector_type(4)));
-typedef int v16i_t __attribute__((ext_vector_type(16)));
 
 struct InputParams {
     const uint8_t *img;     // N x C x H x W bytes
@@ -280,6 +280,66 @@ __global__ __launch_bounds__(256) void input_cterm_kernel(const int8_t *__restri
 
 static int64_t input_row_bytes(int64_t Cin, int R, int S) { return round_up(Cin * R * (S > 8 ? 2 : 1) * 8, 32); }
 
+template <int NT, int SEG, int COPIES> static bool launch_input_tile(const InputTileParams &p, unsigned grid, int lds, hipStream_t st)
+{
+    const auto kernel = input_tile_kernel<NT, SEG, COPIES>;
+    static std::atomic<int> granted{0};                  // most dynamic LDS asked for so far (per instance)
+    if (lds > granted.load(std::memory_order_relaxed)) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
+            return false;
+        granted.store(lds, std::memory_order_relaxed);
+    }
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(512), lds, st, p);
+    return true;
+}
+
+// input_tile_kernel for layers with one or two planes out, up to 64 channels and nothing else asked for, whose rows fit LDS.
+static bool try_input_tile(const MfmaParams &p, const InputParams &q, int64_t images, int64_t K_S, hipStream_t st)
+{
+    const int force = input_tile_override();
+    if (force == 0 || !p.out || p.q_out > 2 || p.Y || p.T || p.res || p.N > 64) return false;
+    const int seg = K_S > 8 ? 2 : 1, nt = p.N > 32 ? 2 : 1, copies = p.stride % 4 == 0 ? 1 : p.stride % 2 == 0 ? 2 : 4;
+    const int64_t Hq = p.H + 2 * static_cast<int64_t>(p.pad);
+    if ((images + 1) * Hq >= int64_t(1) << 31) return false;
+    InputTileParams t{};
+    t.img = q.img; t.w = q.w; t.cterm = q.cterm;
+    t.M = p.M; t.N = p.N; t.C = q.C; t.images = static_cast<int>(images); t.H = p.H; t.W = p.W; t.Hq = static_cast<int>(Hq);
+    t.per_image = divisor(static_cast<int64_t>(p.Ho) * p.Wo); t.per_row = divisor(p.Wo);
+    t.stride = p.stride; t.pad = p.pad; t.R = p.R; t.Kp = q.Kp; t.KS = q.KS; t.segments = q.nseg;
+    t.frame_lines = divisor(Hq); t.kernel_rows = divisor(p.R);
+    t.xmask = q.xmask; t.scale = p.scale; t.bias = p.bias; t.out = p.out; t.q_out = p.q_out; t.NW = p.NW;
+    // lines of the padded frames that 512 pixels touch: row steps and image steps between the first and the last
+    const int64_t new_rows = (511 + p.Wo - 1) / p.Wo, per_image = static_cast<int64_t>(p.Ho) * p.Wo;
+    const int64_t new_images = (511 + per_image - 1) / per_image, between = Hq - static_cast<int64_t>(p.Ho) * p.stride;
+    int64_t lines = new_rows * p.stride + new_images * (between > 0 ? between : 0) + p.R;
+    if (lines > images * Hq) lines = images * Hq;
+    const int64_t pitch = round_up(static_cast<int64_t>(p.Wo - 1) * p.stride + 8 * seg, 8);
+    t.row_groups = divisor(pitch / 8);
+    // (copies begin on different banks)
+    const int64_t plane = round_up(lines * pitch, 128) + 128 / copies;
+    const int64_t lds = 4 * (64 + 32) * nt + 16 * q.KS + 1024 * static_cast<int64_t>(q.KS) * nt + q.C * copies * plane;
+    if (lds > 160 * 1024 || 32 * nt + 4 * q.KS > 512 || lines * (pitch / 8) >= int64_t(1) << 30) return false;
+    t.pitch = static_cast<int>(pitch); t.plane = static_cast<int>(plane);
+    const int64_t blocks = ceil_div(p.M, 512);
+    if (blocks > kMaxBlocks / 2) return false;           // (512 threads each)
+    const unsigned g = static_cast<unsigned>(blocks);
+    const int b = static_cast<int>(lds);
+    switch ((nt == 2 ? 6 : 0) + (seg == 2 ? 3 : 0) + (copies == 4 ? 2 : copies == 2 ? 1 : 0)) {
+        case 0: return launch_input_tile<1, 1, 1>(t, g, b, st);
+        case 1: return launch_input_tile<1, 1, 2>(t, g, b, st);
+        case 2: return launch_input_tile<1, 1, 4>(t, g, b, st);
+        case 3: return launch_input_tile<1, 2, 1>(t, g, b, st);
+        case 4: return launch_input_tile<1, 2, 2>(t, g, b, st);
+        case 5: return launch_input_tile<1, 2, 4>(t, g, b, st);
+        case 6: return launch_input_tile<2, 1, 1>(t, g, b, st);
+        case 7: return launch_input_tile<2, 1, 2>(t, g, b, st);
+        case 8: return launch_input_tile<2, 1, 4>(t, g, b, st);
+        case 9: return launch_input_tile<2, 2, 1>(t, g, b, st);
+        case 10: return launch_input_tile<2, 2, 2>(t, g, b, st);
+        default: return launch_input_tile<2, 2, 4>(t, g, b, st);
+    }
+}
+
 }  // namespace apnn
 
 using namespace apnn;
@@ -387,6 +447,7 @@ extern "C" int apnn_input_layer(const apnn_layer_desc *desc, const void *W_dev, 
     q.xmask = 0x01010101u * ((1u << d.q) - 1u);
     q.w = static_cast<const int8_t *>(W_dev);
     q.cterm = reinterpret_cast<const int32_t *>(q.w + round_up(N * q.Kp, 16));
+    if (try_input_tile(p, q, d.N, d.S, as_stream(stream))) return check_launch(who);
     const unsigned grid = static_cast<unsigned>(ceil_div(M, 128));
     const int nt = static_cast<int>(ceil_div(N, 32));
     const bool two = d.S > 8;                           // two 8-byte segments per kernel row

@@ -14,9 +14,9 @@ namespace apnn {
 // Kernel-choice overrides (tests, experiments).  Each is read from the process
 // environment once, the first time any of them is asked for, and can afterwards be
 // set or cleared through apnn_debug_force; the dispatch itself only loads an int.
-enum Override { OV_MFMA, OV_TILE, OV_MFMA_TILE, OV_MFMA_SHORTK, OV_MFMA_SMALL, OV_MFMA_NSPLIT, OV_MFMA_FN, OV_INT8, OV_MFMA_HALO, OV_COUNT };
+enum Override { OV_MFMA, OV_TILE, OV_MFMA_TILE, OV_MFMA_SHORTK, OV_MFMA_SMALL, OV_MFMA_NSPLIT, OV_MFMA_FN, OV_INT8, OV_MFMA_HALO, OV_INPUT_TILE, OV_COUNT };
 static const char *const kOverrideNames[OV_COUNT] = {"MFMA", "TILE", "MFMA_TILE", "MFMA_SHORTK", "MFMA_SMALL",
-                                                     "MFMA_NSPLIT", "MFMA_FN", "INT8", "MFMA_HALO"};
+                                                     "MFMA_NSPLIT", "MFMA_FN", "INT8", "MFMA_HALO", "INPUT_TILE"};
 static std::atomic<int> g_override[OV_COUNT];
 
 static void overrides_from_env()
@@ -36,6 +36,8 @@ static int ov(Override which)
     (void)once;
     return g_override[which].load(std::memory_order_relaxed);
 }
+
+int input_tile_override() { return ov(OV_INPUT_TILE); }
 
 // Tile choice, the two-step heuristic of Sec. 4.3.  Candidates are ranked by thread-level parallelism (Eq. 3; here
 // the number of blocks: plane pairs are batched in time, not space, so p q does not multiply it).  If even the most
