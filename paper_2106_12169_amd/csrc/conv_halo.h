@@ -55,23 +55,22 @@ struct ConvHaloParams {
 constexpr int kHaloStay = 26, kHaloChunk = 8;
 
 // HW: channel words (steps) read together from a record; SW: channel words of a plane staged together (HW = 2: 4; HW = 1: 2, or
-// 1 for an odd number of channel words); FC: 32-channel tiles; FP: 32-pixel tiles of a wave.  POOL (FP = 4): tile f of a wave
-// holds member f of its 32 pooling grids, so that pooling is three instructions per output.  MULTI: features of more than
-// one digit.
-//
+// 1 for an odd number of channel words); FP, FW: 32-pixel and 32-channel tiles of a wave (FW = 1: two waves share the pixels).
+// MULTI: features of more than one digit.
+// POOL (FP = 4): tile f of a wave holds member f of its 32 pooling grids, so that pooling is three instructions per output.
 // STAY: the weights stay in LDS while the block walks over its tiles of pixels (grid-stride), and the next tile's pixels are in
 // flight during the main loop.  Otherwise a block has one tile, and the weights pass through two buffers, a chunk each, with
 // one barrier per chunk.
 // PT: granules of a tap, 0 if known at run time only.  A lone wave of a SIMD issues an instruction every four or five cycles, and
 // long sums on few pixels leave it alone: with PT the offsets inside a tap are part of the loads (s4 of the ResNet-18 shape
 // at batch 128, 23 instructions a step instead of 33).
-template <int KA, int HW, int SW, int FC, int FP, int PT, bool POOL, bool MULTI, bool STAY>
-__global__ __launch_bounds__(256, FP == 4 ? 2 : FP == 2 ? 3 : 4) void conv_halo_kernel(const ConvHaloParams p)
+template <int KA, int HW, int SW, int FP, int FW, int PT, bool POOL, bool MULTI, bool STAY>
+__global__ __launch_bounds__(256, FP == 1 ? 4 : FP * FW == 8 ? 2 : 3) void conv_halo_kernel(const ConvHaloParams p)
 {
     static_assert(!POOL || FP == 4, "a wave's four pixel tiles are the members of its pooling grids");
     constexpr int PL = KA == OPK_U1 ? 1 : 2, GW = PL * HW;       // words of a granule: HW steps of a digit
-    constexpr int BP = 128 * FP;                                 // pixels of a tile
-    static_assert(FC == 2, "the halves of a wave fetch the weights of one channel tile each");
+    constexpr int FC = 2;                                        // channel tiles of a block
+    constexpr int BP = 64 * FW * FP;                             // pixels of a tile
     constexpr int FETCH = STAY ? kHaloStay : kHaloChunk;         // weight steps in flight
     constexpr int NI = (FETCH * FC + 4 * HW - 1) / (4 * HW);      // granules of them a thread has in flight
     constexpr int U = SW == 1 ? 4 : 2;                           // staged pieces of pixels a thread has in flight
@@ -82,6 +81,7 @@ __global__ __launch_bounds__(256, FP == 4 ? 2 : FP == 2 ? 3 : 4) void conv_halo_
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lr = lane & 31, lh = lane >> 5;
+    const int wc = FW == 1 ? wave & 1 : 0, wp = FW == 1 ? wave >> 1 : wave;    // first channel tile, pixels of this wave
     // block -> channel tile, first tile of pixels
     const int tile0 = divide(static_cast<int>(blockIdx.x), p.per_column);
     const int n0 = (static_cast<int>(blockIdx.x) - tile0 * p.per_column.d) * 32 * FC;
@@ -270,20 +270,20 @@ __global__ __launch_bounds__(256, FP == 4 ? 2 : FP == 2 ? 3 : 4) void conv_halo_
         uint32_t base[FP];                                       // bytes: record of the first tap, this lane half's words
 #pragma unroll
         for (int f = 0; f < FP; ++f) {
-            gm[f] = POOL ? m0 + 4 * (32 * wave + lr) + f : m0 + (wave * FP + f) * 32 + lr;
+            gm[f] = POOL ? m0 + 4 * (32 * wp + lr) + f : m0 + (wp * FP + f) * 32 + lr;
             base[f] = 4u * static_cast<uint32_t>((position(min(gm[f], last)) - now.lo) * p.rec + lh * per_tap * GW);
         }
         // residual words and the next tile's first pixels: their latency hides behind the main loop
         constexpr int FO = POOL ? 1 : FP;                        // output tiles per channel tile
-        uint32_t res[FO][FC][2];
+        uint32_t res[FO][FW][2];
 #pragma unroll
         for (int f = 0; f < FO; ++f)
 #pragma unroll
-            for (int c = 0; c < FC; ++c) {
+            for (int c = 0; c < FW; ++c) {
                 res[f][c][0] = res[f][c][1] = 0u;
-                const int px = POOL ? gm[0] >> 2 : gm[f];
-                if (p.res && gm[f] < p.M && n0 + 32 * c < p.N) {
-                    const uint32_t *rp = p.res + static_cast<int64_t>(px) * (p.q_res * p.NW) + ((n0 >> 5) + c);
+                const int px = POOL ? gm[0] >> 2 : gm[f], ch = n0 + 32 * (wc + c);
+                if (p.res && gm[f] < p.M && ch < p.N) {
+                    const uint32_t *rp = p.res + static_cast<int64_t>(px) * (p.q_res * p.NW) + (ch >> 5);
                     res[f][c][0] = rp[0];
                     if (p.q_res == 2) res[f][c][1] = rp[p.NW];
                 }
@@ -296,16 +296,16 @@ __global__ __launch_bounds__(256, FP == 4 ? 2 : FP == 2 ? 3 : 4) void conv_halo_
             fetch_pixels(next_range, tid);
         }
 
-        v16f_t acc[FC][FP];
+        v16f_t acc[FW][FP];
         // The operands of a granule are read one granule ahead of its matrix instructions, into two sets of registers in turn;
         // the empty statements keep the compiler from moving the reads back to their use (128 -> 128 channels, 128 x 28 x 28:
         // 16.4 us where it puts them, 13.8 here; it makes no difference where PT is known).
         struct Operands {
             words_t w[FP];
-            v4i_t a[HW][FC];
+            v4i_t a[HW][FW];
             int scale;
         } even, odd;
-        const uint32_t *codes = sB + lane * 4;
+        const uint32_t *codes = sB + wc * 256 + lane * 4;
         int scaleB = static_cast<int>(reg_const(static_cast<uint32_t>(p.scaleB)));
         uint32_t off = 0;
         int g = 0, sc = 0, d = 0;
@@ -315,7 +315,7 @@ __global__ __launch_bounds__(256, FP == 4 ? 2 : FP == 2 ? 3 : 4) void conv_halo_
 #pragma unroll
             for (int i = 0; i < HW; ++i)
 #pragma unroll
-                for (int c = 0; c < FC; ++c) o.a[i][c] = *reinterpret_cast<const v4i_t *>(codes + (i * FC + c) * 256);
+                for (int c = 0; c < FW; ++c) o.a[i][c] = *reinterpret_cast<const v4i_t *>(codes + (i * FC + c) * 256);
             o.scale = MULTI ? scaleA + 0x02020202 * d : scaleA;
             asm volatile("" ::: "memory");
         };
@@ -337,7 +337,7 @@ __global__ __launch_bounds__(256, FP == 4 ? 2 : FP == 2 ? 3 : 4) void conv_halo_
                     v8i_t b;
                     expand(o.w[f], i, b);
 #pragma unroll
-                    for (int c = 0; c < FC; ++c)
+                    for (int c = 0; c < FW; ++c)
                         acc[c][f] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
                             v8i_t{o.a[i][c][0], o.a[i][c][1], o.a[i][c][2], o.a[i][c][3], 0, 0, 0, 0}, b,
                             decltype(first)::value && i == 0 ? v16f_t{} : acc[c][f], 4, 4, 0, scaleB, 0, o.scale);
@@ -376,7 +376,7 @@ __global__ __launch_bounds__(256, FP == 4 ? 2 : FP == 2 ? 3 : 4) void conv_halo_
 #pragma unroll
                 for (int i = 0; i < HW; ++i)
 #pragma unroll
-                    for (int c = 0; c < FC; ++c) o.a[i][c] = *reinterpret_cast<const v4i_t *>(codes + ((g * HW + i) * FC + c) * 256);
+                    for (int c = 0; c < FW; ++c) o.a[i][c] = *reinterpret_cast<const v4i_t *>(codes + ((g * HW + i) * FC + c) * 256);
                 o.scale = scaleA;
             };
             const uint8_t *src[FP];
@@ -427,7 +427,7 @@ __global__ __launch_bounds__(256, FP == 4 ? 2 : FP == 2 ? 3 : 4) void conv_halo_
                 half_buffer ^= 1;
                 uint32_t *const to = sB + half_buffer * (p.chunk * FC * 256);
                 write_weights(to, p.chunk);                      // read last before the barrier two chunks ago
-                codes = to + lane * 4;
+                codes = to + wc * 256 + lane * 4;
                 __syncthreads();
                 left = divide(min(p.chunk, p.steps - s0), p.halves);
                 point();
@@ -457,7 +457,7 @@ __global__ __launch_bounds__(256, FP == 4 ? 2 : FP == 2 ? 3 : 4) void conv_halo_
                 half_buffer ^= 1;
                 uint32_t *const to = sB + half_buffer * (p.chunk * FC * 256);
                 write_weights(to, p.chunk);                      // read last before the barrier two chunks ago
-                codes = to + lane * 4;
+                codes = to + wc * 256 + lane * 4;
                 __syncthreads();
                 left = min(p.chunk, p.steps - s0) / HW * (MULTI ? p.DA : 1);
                 load(odd);
@@ -474,9 +474,9 @@ __global__ __launch_bounds__(256, FP == 4 ? 2 : FP == 2 ? 3 : 4) void conv_halo_
         }
 
         // ---- outputs
-        static_for<FC>([&](auto cc) {
+        static_for<FW>([&](auto cc) {
             constexpr int c = decltype(cc)::value;
-            const int ch0 = n0 + 32 * c;
+            const int ch0 = n0 + 32 * (wc + c);
             if (ch0 >= p.N) return;
             if (p.Y) {
                 static_for<FP * 4>([&](auto fk) {
@@ -491,7 +491,7 @@ __global__ __launch_bounds__(256, FP == 4 ? 2 : FP == 2 ? 3 : 4) void conv_halo_
             uint32_t d[FO][2];
             static_for<2>([&](auto qc) {
                 constexpr int q = decltype(qc)::value;
-                const v4f_t *const at = reinterpret_cast<const v4f_t *>(sP + 32 * c + 16 * lh + 8 * q);
+                const v4f_t *const at = reinterpret_cast<const v4f_t *>(sP + 32 * (wc + c) + 16 * lh + 8 * q);
                 const v4f_t sc[2] = {at[0], at[1]}, bi[2] = {at[8 * FC], at[8 * FC + 1]};
                 static_for<FO>([&](auto fc) {
                     constexpr int f = decltype(fc)::value;

@@ -6,17 +6,37 @@
 
 namespace apnn {
 
+// Few or short sums on few pixels are better off with the kernels that split K over more waves and start sooner.  The two
+// sides' times as fitted to measured layers (us; tiles of 32 x 32 outputs, entries = steps times feature digits a weight digit):
+//   those kernels, up to 4096 tiles: 3.5 + tiles (1.5 + 0.1 entries) / 1000, 1.4 times the second term with several digits
+//   this one, while a compute unit has a tile or two: 4.3 + entries (0.07 with weights that stay, else 0.09; 0.15 with several
+//   feature digits; 0.1 more with an odd number of channel words)
+// e.g. 9 steps on 8 x 56 x 56, 64 channels 6.9 and 5.1; 18 on 8 x 28 x 28, 128 channels 5.7 and 5.4; 36 on 8 x 14 x 14, 256
+// channels 6.2 and 7.7; 50 entries on 3420 pixels, 64 -> 224 channels 10.8 and 11.9; 3 on 6885, 160 -> 96 4.9 and 5.7.
+// And the chip wants most of its compute units busy: not below 96 tiles of 64 x 128 outputs (128 where the stride spreads the
+// pixels: 9 steps with stride 2 on 98 tiles 4.9 and 5.4).
+static bool worth_staging(const MfmaParams &mp, int tilesN)
+{
+    const int64_t blocks = ceil_div(mp.M, mp.pool ? 256 : 128) * tilesN;
+    if (blocks < (mp.stride > 1 ? 128 : 96)) return false;
+    const int64_t tiles = ceil_div(mp.M, 32) * ceil_div(mp.N, 32);
+    const int64_t steps = static_cast<int64_t>(mp.R) * mp.S * ((mp.Cw + 1) / 2);
+    if (mp.Y && steps <= 2) return false;                // int32 results: their store is all there is (192 channels, 10.3 and 10.6)
+    if (tiles > 4096) return true;
+    const double entries = static_cast<double>(steps * mp.DA * mp.DB);
+    const double other = 3.5 + 1e-3 * tiles * (1.5 + 0.1 * entries) * (mp.DA * mp.DB > 1 ? 1.4 : 1.0);
+    const double per_entry = (mp.DA > 1 ? 0.15 : mp.DB == 1 && steps <= kHaloStay ? 0.07 : 0.09) + (mp.Cw % 2 != 0 ? 0.1 : 0.0);
+    return 4.3 + per_entry * entries <= other;
+}
+
 bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB, int force, hipStream_t st)
 {
     // int32 results alone, or planes of one or two bits alone (the epilogue keeps no other output)
     const bool ints = mp.Y && !mp.scale && !mp.T && !mp.pool && mp.N % 4 == 0;
     const bool planes = mp.out && !mp.Y && !mp.T && mp.q_out <= 2 && (!mp.res || mp.q_res <= 2);
     if (!ints && !planes) return false;
-    // Few tiles leave the chip to the layers that split K over more waves (tiles of 64 x 128 outputs, us, the other kernels
-    // first): 9 steps on 196 tiles 6.9, 5.1; 18 on 98 5.7, 5.4; 36 on 100 8.8, 7.9; 36 on 52 6.1, 7.7; stride 2: 9 on 98 4.9,
-    // 5.5, 36 on 104 8.9, 8.5; pooled, 72 on 104 28.3, 20.1, 36 on 28 8.4, 12.6.
     const int tilesN = static_cast<int>(ceil_div(mp.N, 64));
-    if (force < 0 && ceil_div(mp.M, mp.pool ? 512 : 128) * tilesN < (mp.stride > 1 ? 128 : 96)) return false;
+    if (force < 0 && !worth_staging(mp, tilesN)) return false;
     const int64_t Hq = mp.H + 2 * static_cast<int64_t>(mp.pad), Wq = mp.W + 2 * static_cast<int64_t>(mp.pad);
     const int64_t Kw = static_cast<int64_t>(mp.R) * mp.S * mp.Cw, lim = int64_t(1) << 31;
     if ((images + 1) * Hq * Wq >= lim || 4 * images * mp.H * mp.W * mp.PA * mp.Cw >= lim || 4 * mp.N * mp.PB * Kw >= lim) return false;
@@ -61,9 +81,9 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
     const int64_t codes = (stay ? 1 : 2) * p.chunk * 512;
 
     struct Tiling { int64_t tilesM, records, lds, blocks, buffers; };     // blocks: that a compute unit holds
-    auto tiling = [&](int fp) {
+    auto tiling = [&](int fp) {                            // fp: pixel tiles of a wave; pooled 4 with both channel tiles, 3 with one
         Tiling t{};
-        const int64_t pixels = 128 * fp;
+        const int64_t pixels = fp == 3 ? 256 : 128 * fp;
         t.tilesM = ceil_div(mp.M, pixels);
         // the longest range of padded positions a tile touches: row steps and image steps between its first and last pixel
         const int64_t px = mp.pool ? pixels / 4 : pixels, step = mp.pool ? 2 * mp.stride : mp.stride;
@@ -72,12 +92,18 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
         const int64_t reach = new_rows * step * Wq + (cols - 1) * step + new_images * (between > 0 ? between : 0) * Wq +
                               (mp.pool ? mp.stride * (Wq + 1) : 0) + (mp.R - 1) * Wq + mp.S;
         t.records = (reach < images * Hq * Wq ? reach : images * Hq * Wq) * p.rec;
-        const int64_t most = fp == 4 ? 2 : fp == 2 ? 3 : 4;                // by registers: waves a SIMD holds
-        for (t.buffers = stay ? 2 : 1; t.buffers > 0; --t.buffers) {
-            t.lds = 4 * (128 + codes + t.buffers * t.records);
+        const int64_t most = fp == 4 ? 2 : fp == 1 ? 4 : 3;    // by registers: waves a SIMD holds
+        auto fit = [&](int64_t buffers) {
+            t.buffers = buffers;
+            t.lds = 4 * (128 + codes + buffers * t.records);
             t.blocks = 160 * 1024 / t.lds < most ? 160 * 1024 / t.lds : most;
-            // a second buffer of records is for blocks that have a second tile
-            if (t.buffers == 1 || (t.blocks > 0 && t.tilesM * tilesN > 256 * t.blocks / tilesN * tilesN && 256 * t.blocks >= tilesN)) break;
+        };
+        fit(1);
+        // a second buffer of records is for blocks that have a second tile, and two of those to a compute unit
+        if (stay && t.tilesM * tilesN > 256 * t.blocks / tilesN * tilesN) {
+            const int64_t single = t.blocks;
+            fit(2);
+            if (t.blocks < (single < 2 ? single : 2) || 256 * t.blocks < tilesN) fit(1);
         }
         return t;
     };
@@ -85,10 +111,13 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
     //   weights that stay: 9 steps on 1568 tiles of 256 17.9, 15.3; 18 steps 23.6, 29.2; 9 steps with stride 2 on 784 13.5, 17.9
     //   chunks: what a compute unit holds of pixels decides; 36 steps on 392 tiles 17.2, 14.7 (512 pixels against 384); 72 steps
     //   on 784 tiles 47, 59 (256 either way)
-    // Pooled layers have one form, 64 channels x 128 pooled pixels.
-    int fp = 4;
-    Tiling t = tiling(mp.pool ? 4 : 1);
-    if (!mp.pool) {
+    // Pooled: 64 x 128 pooled outputs a block (a wave has both channel tiles), or 64 x 64 (one; fewer and smaller blocks fill the
+    // chip): 36 steps on 196 of the larger tiles 12.4, 18.0; 72 on 104 20.1, 16.0; 36 on 98 12, 9.9; 9 on 784 21.5, 20.9.
+    int fp = mp.pool ? 4 : 1;
+    Tiling t = tiling(fp);
+    if (mp.pool) {
+        if (force == 1 || (force < 0 && t.tilesM * tilesN < 150) || t.blocks < 1) t = tiling(fp = 3);
+    } else {
         const Tiling two = tiling(2);
         fp = force == 1 || force == 2 ? force
              : stay ? (p.steps <= 12 && mp.stride == 1 && two.blocks > 0 && two.tilesM * tilesN >= 256 ? 2 : 1)

@@ -6,10 +6,10 @@
 
 namespace apnn {
 
-template <int KA, int HW, int SW, int FP, int PT, bool POOL, bool MULTI, bool STAY>
+template <int KA, int HW, int SW, int FP, int FW, int PT, bool POOL, bool MULTI, bool STAY>
 bool launch_conv_halo(const ConvHaloParams &p, unsigned grid, int lds, hipStream_t st)
 {
-    const auto kernel = conv_halo_kernel<KA, HW, SW, 2, FP, PT, POOL, MULTI, STAY>;
+    const auto kernel = conv_halo_kernel<KA, HW, SW, FP, FW, PT, POOL, MULTI, STAY>;
     static std::atomic<int> granted{0};                  // most dynamic LDS asked for so far (per instance)
     if (lds > granted.load(std::memory_order_relaxed)) {
         if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
@@ -23,9 +23,10 @@ bool launch_conv_halo(const ConvHaloParams &p, unsigned grid, int lds, hipStream
 template <int KA, int HW, int SW, int PT, bool MULTI, bool STAY>
 bool launch_conv_halo(const ConvHaloParams &p, int fp, unsigned grid, int lds, hipStream_t st)
 {
-    if (p.pool) return launch_conv_halo<KA, HW, SW, 4, PT, true, MULTI, STAY>(p, grid, lds, st);
-    return fp == 2 ? launch_conv_halo<KA, HW, SW, 2, PT, false, MULTI, STAY>(p, grid, lds, st)
-                   : launch_conv_halo<KA, HW, SW, 1, PT, false, MULTI, STAY>(p, grid, lds, st);
+    if (p.pool) return fp == 4 ? launch_conv_halo<KA, HW, SW, 4, 2, PT, true, MULTI, STAY>(p, grid, lds, st)
+                               : launch_conv_halo<KA, HW, SW, 4, 1, PT, true, MULTI, STAY>(p, grid, lds, st);
+    return fp == 2 ? launch_conv_halo<KA, HW, SW, 2, 2, PT, false, MULTI, STAY>(p, grid, lds, st)
+                   : launch_conv_halo<KA, HW, SW, 1, 2, PT, false, MULTI, STAY>(p, grid, lds, st);
 }
 
 template <int KA, bool MULTI, bool STAY> bool launch_conv_halo(const ConvHaloParams &p, int fp, unsigned grid, int lds, hipStream_t st)
