@@ -200,8 +200,8 @@ __global__ __launch_bounds__(256, FP == 1 ? 4 : FP * FW == 8 ? 2 : 3) void conv_
                 if (KA == OPK_U1) {
                     w[i] = a0[u][i];
                 } else if (KA == OPK_U2) {                       // pairs of bits: even positions, odd positions
-                    w[PL * i] = bit_select(0x55555555u, a0[u][i], a1[u][i] << 1);
-                    w[PL * i + 1] = bit_select(0x55555555u, a0[u][i] >> 1, a1[u][i]);
+                    w[PL * i] = mask_select(0x55555555u, a0[u][i], a1[u][i] << 1);
+                    w[PL * i + 1] = mask_select(0x55555555u, a0[u][i] >> 1, a1[u][i]);
                 } else {                                         // signs, and the code's 1.0 inside the frame
                     w[PL * i] = in[u] ? ~a0[u][i] : 0u;
                     w[PL * i + 1] = in[u] ? 0x22222222u : 0u;

@@ -112,10 +112,10 @@ static int pick_mfma_tile(int64_t M, int64_t N, bool conv)
 // One pass over K whatever p and q are (the FP4 form needs ceil(p/2) ceil(q/2)), exact for every K the int32
 // result allows.  Its cost is the transposition of plane words into bytes, which grows with the plane counts, so it
 // is taken where it measured faster on 2048^3 ... 4096^3 products: five or more FP4 passes; four with both operands
-// above two bits (w3a5 24 against 37 us, w4a4 21 against 27 at 2048^3); four with a narrow operand (w2a8, w1a7) only up
-// to one 128 x 128 tile per compute unit (2048^3: 24.7 against 27.0 us; 3072^3: 89 against 81, 4096^3: 144 against
-// 117, where the FP4 form runs its 256 x 256 tiles) -- given enough tiles to occupy the chip, and whenever the FP4
-// form could not be exact (w8a8, K = 2048: 40 us against 1040 us of the AND+popcount kernel).  Override INT8: 0 never, 1 whenever it applies, 2 and 3
+// above two bits (w3a5 22 against 37 us, w4a4 20 against 26 at 2048^3); four with a narrow operand (w2a8, w1a7) only up
+// to one 128 x 128 tile per compute unit (2048^3: 23.0 against 27.1 us; 3072^3: 71 against 73 and w1a8 68 against 64,
+// 4096^3: 129 against 105, where the FP4 form runs its 256 x 256 tiles) -- given enough tiles to occupy the chip, and
+// whenever the FP4 form could not be exact (w8a8, K = 2048: 28 us against 1040 us of the AND+popcount kernel).  Override INT8: 0 never, 1 whenever it applies, 2 and 3
 // the same with the kernel that shares out the outputs / K among the waves.
 struct I8Operand { int cls; int alpha, off, flipped, pad; uint32_t flip; };
 
@@ -140,15 +140,18 @@ static bool try_int8(const Problem &pr, MfmaParams &mp, bool fp4_exact, void *st
     const int64_t tiles = ceil_div(pr.M, 128) * ceil_div(pr.N, 128);
     if (force < 1) {
         const int passes = ((pr.PA + 1) / 2) * ((pr.PB + 1) / 2);
-        const bool faster = passes >= 5 || (passes == 4 && ((pr.PA > 2 && pr.PB > 2) || tiles <= 256));
-        if (fp4_exact && (!faster || tiles < 64)) return false;
+        // outputs from which the tiles occupy the chip: 768 x 768 w3a5, K = 1024 10.7 against 13.4 us (512 x 512 8.2, 7.3), with a narrow
+        // operand 64 tiles (1024^3 w2a8 12.1 against 13.4, 768 x 768 11.7, 10.6)
+        const bool narrow = passes == 4 && !(pr.PA > 2 && pr.PB > 2);
+        const bool faster = narrow ? tiles >= 64 && tiles <= 256 : passes >= 4 && pr.M * pr.N >= (int64_t(1) << 19);
+        if (fp4_exact && !faster) return false;
     }
     const int64_t lim = int64_t(1) << 31;       // operands and output are addressed with 31-bit byte offsets
     if (4 * pr.M * pr.PA * mp.ldwA >= lim || 4 * pr.N * pr.PB * mp.ldwB >= lim || 4 * (pr.M + 128) * pr.N >= lim) return false;
     if (tiles > 0x7FFFFFFF) return false;
     const I8Operand a = i8_operand(pr.PA, pr.encA), b = i8_operand(pr.PB, pr.encB);
     mp.PA = pr.PA; mp.PB = pr.PB;
-    mp.nk = static_cast<int>(round_up(ceil_div(mp.Kw, 4), 4));       // chunks of 4 words; the kernel takes four per loop pass
+    mp.nk = static_cast<int>(round_up(ceil_div(mp.Kw, 4), 4));       // chunks of 4 words; the kernels take four per loop pass
     const int64_t K = pr.Ktotal, npad = static_cast<int64_t>(mp.nk) * 128 - K;
     mp.flipA = a.flip; mp.flipB = b.flip;
     mp.accmul = a.alpha * b.alpha;
@@ -161,11 +164,13 @@ static bool try_int8(const Problem &pr, MfmaParams &mp, bool fp4_exact, void *st
                                                    + K * a.off * b.off));
     mp.out_scale = 1.0f;
     mp.xcd_regions = (ceil_div(pr.M, 128) % 2 == 0 && ceil_div(pr.N, 128) % 4 == 0) ? 1 : 0;
-    // K shared out among the waves of a block (half the transposition work per matrix instruction, but one wave per
-    // SIMD and four partial results to add): measured faster from K of about 3000 up (2048 x 2048 outputs, w4a4:
-    // K = 2048 22.1 against 20.8 us, 4096 30.8 against 32.1, 8192 49.4 against 56.5; w3a5 4096^3 128 against 136).
+    // K shared out among the waves of a block (a fragment feeds four matrix instructions, but one wave per SIMD, loads that stay
+    // ahead of them by a whole group, and four partial results to add): level at K = 4096 with one tile per compute unit, ahead
+    // from there (2048 x 2048 outputs, us, mfma_i8_kernel first: w4a4 K = 2048 19.8, 21.8, K = 8192 51.2, 45.6; w3a5 22.0, 25.8
+    // and 59.1, 56.6); with more tiles behind for longer (4096^3 w3a5 118, 128).
     // Override INT8 = 2: never, 3: whenever the planes fit its LDS.
-    const bool wide = force != 2 && pr.PA + pr.PB <= 10 && !(a.cls == 2 && b.cls == 2) && (force == 3 || K >= 3072);
+    const bool wide = force != 2 && pr.PA + pr.PB <= 10 && !(a.cls == 2 && b.cls == 2) &&
+                      (force == 3 || K >= 8192 || (K >= 4096 && tiles <= 256));
     if (!(wide && launch_mfma_i8_wide(mp, a.cls, b.cls, static_cast<unsigned>(tiles), as_stream(stream))) &&
         !launch_mfma_i8(mp, a.cls, b.cls, static_cast<unsigned>(tiles), as_stream(stream)))
         return false;

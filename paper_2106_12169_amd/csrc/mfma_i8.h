@@ -27,19 +27,21 @@
 // being the decoded row sums sum_s 2^s popc(plane s), which the lanes accumulate
 // from the plane words they hold anyway (popcount, as in the AND+popcount kernel).
 //
-// Schedule.  Block tile (2 FM 32) x (2 FN 32), 2 x 2 waves, each FM x FN
-// instruction tiles, one wave per SIMD.  K advances in chunks of 4 words (128
-// positions = 4 instruction steps) and is fetched in groups of two or four chunks
-// (32 or 64 bytes of every plane row): global memory -> LDS directly, 16 bytes per
-// lane, adjacent lanes taking adjacent pieces of one plane row, two group buffers,
-// one barrier per group, the 16-byte pieces XOR-swizzled by row; lane half h of row r reads words 2h,
-// 2h + 1 of every plane of its fragment rows (8-byte LDS reads) one chunk ahead, and
-// each word, transposed, gives the bytes of two instruction steps.  The kernel is
-// bound by the vector instructions of the transposition (about 20 per matrix
-// instruction), so the matrix instructions of one word are issued between the pieces
-// of the next word's transposition and run underneath them.  The K order inside a
-// step is free as long as both operands agree: dword j, byte g of a transposed word
-// is the element at bit 8 g + j.
+// Schedule.  A block of eight waves owns 128 x 128 outputs and makes the bytes of its 128 + 128 operand rows once - a thread
+// per row and word - in LDS, where the waves read them as fragments: about 60 vector instructions a thread per chunk of four
+// words (128 positions) and eight matrix instructions at 3 x 5 bits.  (With every wave transposing the words of its own
+// fragments, a row's bytes are made by two waves and feed two matrix instructions each, 14 to 23 vector instructions per
+// matrix instruction.)  Waves 0 - 3 and 4 - 7 own the same four 64 x 64 tiles and take alternate pairs of steps of a chunk;
+// the results are added through LDS at the end.  One half of the waves multiplies a chunk before it makes the next one's
+// bytes, the other half after, so that the two waves of a SIMD use the matrix unit and the vector unit in turn.  LDS: [word]
+// [lane half][row] pieces of 16 bytes, 129 apart: reads of 32 rows and writes of 2 rows x 4 words both hit all banks.
+// The K order inside a step is free as long as both operands agree: dword j, byte g of a transposed word is the element
+// at bit 8 g + j.
+//
+// Measured (us; a form in which every wave transposed for itself, and this one): 2048^3 w3a5 24.9, 22.0; w4a4 20.4, 19.8; w5a5
+// 34.5, 23.5; w8a8 40.4, 28.0; 1024^3 w3a5 13.1, 11.0; 4096^3 w3a5 132, 118, w8a8 256, 168.  What is left at 2048^3 w3a5: per
+// chunk, without loads, 780 cycles of reads and matrix instructions (512 of them the matrix unit's) and 740 of
+// transposition, which overlap to 1340 only.
 #pragma once
 #include "mfma_big.h"
 
@@ -132,387 +134,210 @@ __device__ __forceinline__ void planes_to_bytes(const uint32_t (&w)[I8Slots<C>::
     }
 }
 
-// Bytes of LDS the kernel needs for PA + PB planes: two group buffers; with K split over wave pairs, room for the
-// exchange of half of every wave's accumulators (35 registers of 64 lanes for each of 8 waves).
-constexpr int mfma_i8_lds_bytes(int PA, int PB, int G, int NKS)
-{
-    const int tiles = 2 * (PA + PB) * 128 * G * 16, exchange = NKS == 2 ? 8 * 35 * 256 : 0;
-    return tiles > exchange ? tiles : exchange;
-}
+constexpr int kI8Pieces = 8 * 129;                 // 16-byte pieces of a chunk of one operand: (word, half) x rows, padded
+constexpr int kI8LdsBytes = 2 * 2 * kI8Pieces * 16 + 2 * 128 * 4;     // two buffers of both operands, row sums
 
-// NKS = 2: eight waves, two per SIMD; the two waves of a pair own the same 64 x 64 outputs and take alternate
-// chunks of K, and add their halves through LDS at the end.  A lone wave issues a vector instruction only every
-// six cycles or so (measured; two waves together reach one per four), and this kernel is bound by them.
-template <int CA, int CB, int FM, int FN, int G, int NKS>
-__global__ __launch_bounds__(256 * NKS, 1) void mfma_i8_kernel(const MfmaParams p)
+template <int CA, int CB> __global__ __launch_bounds__(512, 2) void mfma_i8_kernel(const MfmaParams p)
 {
-    static_assert(G == 2 || G == 4, "a group is two or four chunks");
-    static_assert(NKS == 1 || NKS == 2, "K is split over at most two waves");
-    static_assert(FM == 2 && FN == 2, "128 x 128 block tile");
-    constexpr int SA = I8Slots<CA>::value, SB = I8Slots<CB>::value;     // most planes of the class: width of the transposition
-    constexpr int BM = 2 * FM * 32, BN = 2 * FN * 32;
-    constexpr int NW = 4 * NKS;                         // waves
-    constexpr int RB = 64 / G;                          // rows one load instruction covers (G pieces each)
-    constexpr int NBR = BM / RB;                        // row blocks (load instructions) per plane
-    constexpr int CPW = G / NKS;                        // chunks of a group that one wave multiplies
-    // A group buffer holds, for G chunks: A planes [PA][BM rows][G pieces of 16 bytes], then B planes [PB][BN][G].
+    constexpr int SA = I8Slots<CA>::value, SB = I8Slots<CB>::value;
     extern __shared__ __attribute__((aligned(1024))) uint32_t smem[];
-    typedef __attribute__((address_space(3))) uint32_t *lds_ptr_t;
-    const uint32_t smem_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_ptr_t)smem));
-    const int a_bytes = p.PA * BM * G * 16, buf_bytes = a_bytes + p.PB * BN * G * 16;
-    // Plane counts for the "does this plane exist" tests around loads and reads.  Kept opaque (see fresh_counts) so
-    // that every test is a scalar compare where it stands; hoisted out of the loop, the two dozen tests lived as lane
-    // masks in scalar register pairs, which spilled.
-    int n_pa = p.PA, n_pb = p.PB;
-    auto fresh_counts = [&]() __attribute__((always_inline)) { asm volatile("" : "+s"(n_pa), "+s"(n_pb)); };
+    uint32_t *const sums = smem + 4 * kI8Pieces * 4;               // row sums of A, of B
 
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int pair = wave & 3, ks = wave >> 2;          // position in the 2 x 2 arrangement of wave tiles, K share
-    const int wm = pair >> 1, wn = pair & 1;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ks = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
     const int lr = lane & 31, lh = lane >> 5;
-
-    const int tilesN = (p.N + BN - 1) / BN;
+    const int tilesN = (p.N + 127) / 128;
     int tile = blockIdx.x;
-    if (p.xcd_regions) {                                // one rectangular region of tiles per XCD (see mfma_big_kernel)
-        const int tilesM = (p.M + BM - 1) / BM;
+    if (p.xcd_regions) {                                 // one rectangular region of tiles per XCD (see mfma_big_kernel)
+        const int tilesM = (p.M + 127) / 128;
         const int rw = tilesN >> 2, rh = tilesM >> 1, xcd = tile & 7, idx = tile >> 3;
         tile = ((xcd >> 2) * rh + idx / rw) * tilesN + (xcd & 3) * rw + idx % rw;
     }
-    const int m0 = (tile / tilesN) * BM, n0 = (tile % tilesN) * BN;
+    const int m0 = (tile / tilesN) * 128, n0 = (tile % tilesN) * 128;
 
     I8Masks km;
     km.m0f = reg_const(0x0F0F0F0Fu); km.m33 = reg_const(0x33333333u);
     km.m55 = reg_const(0x55555555u); km.m03 = reg_const(0x03030303u);
 
-    // ---- loader.  One load instruction moves the G pieces of RB consecutive rows of one plane: lanes G r' .. G r' +
-    // G - 1 fetch consecutive 16-byte pieces of one plane row, i.e. of one cache line (a first version had every lane
-    // in a line of its own and was bound by the tag look-ups of the first-level cache).  Piece j of row r' lands in
-    // slot j ^ swz(r') of the row, so that the reads of 8 consecutive rows spread over all banks.  The per-lane part
-    // of the byte offset is the same for every instruction; the rest (plane, row block, group) is wave-uniform and
-    // added on, and the whole sum is what the hardware checks against the operand's size: rows beyond M read zeros.
-    // The (plane, row block) pairs of an operand are dealt to the waves in turn.
-    auto swz = [](int r) { return G == 4 ? ((r >> 1) & 3) : ((r >> 2) & 1); };
-    const uint32_t bytesA = 4u * static_cast<uint32_t>(p.M) * p.PA * p.ldwA, bytesB = 4u * static_cast<uint32_t>(p.N) * p.PB * p.ldwB;
-    const v4u_t descA = make_raw_desc(p.A, bytesA), descB = make_raw_desc(p.B, bytesB);
-    constexpr uint32_t OUT_OF_RANGE = 0x80000000u;      // operands are smaller than 2 GiB (host check)
-    const int ld_row = lane / G, ld_piece = (lane % G) ^ swz(ld_row);
-    const uint32_t lane_offA = 4u * static_cast<uint32_t>(m0 + ld_row) * p.PA * p.ldwA + 16u * ld_piece;
-    const uint32_t lane_offB = 4u * static_cast<uint32_t>(n0 + ld_row) * p.PB * p.ldwB + 16u * ld_piece;
-    // state of the group being requested: per-lane offsets (out of range where its piece lies beyond K), buffer
-    uint32_t gl_offA = 0, gl_offB = 0;
-    uint32_t gl_lds = 0;
-    int gl_k = 0;
-    auto begin_group = [&](int group, uint32_t lds_bytes_base) __attribute__((always_inline)) {
-        const uint32_t dead = 4 * (group * G + ld_piece) < p.Kw ? 0u : OUT_OF_RANGE;
-        gl_offA = lane_offA | dead;
-        gl_offB = lane_offB | dead;
-        gl_lds = lds_bytes_base;
-        gl_k = __builtin_amdgcn_readfirstlane(group * G * 16);
+    // ---- a thread's row, and its words: 16 bytes of every plane row feed four chunks (word 4 w + c of sixteen goes to chunk c
+    // as its word w: the order of K is free), so that their loads are in flight for three or four chunks
+    const int row = tid >> 2, word = tid & 3;
+    constexpr uint32_t OUT_OF_RANGE = 0x80000000u;       // operands are smaller than 2 GiB (host check)
+    const uint32_t bytesA = 4u * p.M * p.PA * p.ldwA, bytesB = 4u * p.N * p.PB * p.ldwB;
+    const uint32_t atA = m0 + row < p.M ? 4u * (static_cast<uint32_t>(m0 + row) * p.PA * p.ldwA + 4 * word) : OUT_OF_RANGE;
+    const uint32_t atB = n0 + row < p.N ? 4u * (static_cast<uint32_t>(n0 + row) * p.PB * p.ldwB + 4 * word) : OUT_OF_RANGE;
+    struct Words { v4i_t a[SA], b[SB]; };
+    const __amdgpu_buffer_rsrc_t bufA = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(p.A), 0, bytesA, 0x00020000);
+    const __amdgpu_buffer_rsrc_t bufB = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(p.B), 0, bytesB, 0x00020000);
+    // Rows and words beyond the operand read zeros; planes that do not exist are never written and stay zero.  Everything but
+    // the two lane offsets is scalar, and only planes that the class may lack are tested (with a test, an address and zeroed
+    // registers per plane the loads took a quarter of the kernel: 70 us at K = 8192 with every one a hit of the first-level
+    // cache, 53 without them).
+    constexpr int FEWEST_A = SA == 8 ? 5 : SA == 4 ? 3 : 1, FEWEST_B = SB == 8 ? 5 : SB == 4 ? 3 : 1;
+    auto fetch = [&](int four, Words &w) __attribute__((always_inline)) {
+        const uint32_t dead = 16 * four + 4 * word < p.Kw ? 0u : OUT_OF_RANGE, la = atA | dead, lb = atB | dead;
+#pragma unroll
+        for (int s = 0; s < SA; ++s)
+            if (s < FEWEST_A || s < p.PA)
+                w.a[s] = __builtin_bit_cast(v4i_t, __builtin_amdgcn_raw_buffer_load_b128(bufA, la, 4u * (s * p.ldwA + 16 * four), 0));
+#pragma unroll
+        for (int s = 0; s < SB; ++s)
+            if (s < FEWEST_B || s < p.PB)
+                w.b[s] = __builtin_bit_cast(v4i_t, __builtin_amdgcn_raw_buffer_load_b128(bufB, lb, 4u * (s * p.ldwB + 16 * four), 0));
     };
-    // load instruction d of this wave for the group: (plane, row block) number wave + NW d of A, then of B;
-    // skipped for planes that do not exist
-    constexpr int NDA = (SA * NBR + NW - 1) / NW, NDB = (SB * NBR + NW - 1) / NW, NLOAD = NDA + NDB;
-    auto uniform_desc = [](v4u_t d) __attribute__((always_inline)) {     // (wave-uniform by construction; saying so at the point of use
-        v4u_t r;                                        // keeps the four words in scalar registers for the instruction)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) r[i] = __builtin_amdgcn_readfirstlane(d[i]);
-        return r;
-    };
-    auto load_one = [&](auto dc) __attribute__((always_inline)) {
-        constexpr int d = decltype(dc)::value;
-        if constexpr (d < NDA) {
-            const int n = wave + NW * d, s = n / NBR, b = n % NBR;
-            if (s < n_pa) {
-                const uint32_t uni = 4u * static_cast<uint32_t>(b * RB * p.PA + s) * p.ldwA + gl_k;
-                load_to_lds_16(uniform_desc(descA), __builtin_amdgcn_readfirstlane(gl_lds + n * 1024), gl_offA + uni, 0);
-            }
-        } else {
-            const int n = wave + NW * (d - NDA), s = n / NBR, b = n % NBR;
-            if (s < n_pb) {
-                const uint32_t uni = 4u * static_cast<uint32_t>(b * RB * p.PB + s) * p.ldwB + gl_k;
-                load_to_lds_16(uniform_desc(descB), __builtin_amdgcn_readfirstlane(gl_lds + a_bytes + n * 1024), gl_offB + uni, 0);
-            }
-        }
-    };
-    constexpr int WAIT_LOADS = 0x0F70;                  // s_waitcnt vmcnt(0) (expcnt, lgkmcnt untouched)
-
-    // ---- reader.  Lane (half h, row r) reads words 2h, 2h + 1 of chunk j of plane s of fragment row f at byte
-    //   buffer + ((s BM + tile row) G + (j ^ swz(r))) 16 + 8 h;
-    // the per-lane part (one register for each of this wave's chunks of a group, rebuilt when the buffer changes)
-    // plus a constant that fits the instruction's offset field.  This wave's chunks of a group: ks, ks + NKS, ...
-    uint32_t rd0A[CPW], rd0B[CPW], rdA[CPW], rdB[CPW];
-#pragma unroll
-    for (int t = 0; t < CPW; ++t) {
-        const int j = t * NKS + ks;
-        rd0A[t] = ((wm * FM * 32 + lr) * G + (j ^ swz(lr & (RB - 1)))) * 16 + 8 * lh;
-        rd0B[t] = a_bytes + ((wn * FN * 32 + lr) * G + (j ^ swz(lr & (RB - 1)))) * 16 + 8 * lh;
-    }
-    auto set_read_buffer = [&](uint32_t byte_base) __attribute__((always_inline)) {
-#pragma unroll
-        for (int t = 0; t < CPW; ++t) { rdA[t] = rd0A[t] + byte_base; rdB[t] = rd0B[t] + byte_base; }
-    };
-    struct Words { uint2 a[FM][SA], b[FN][SB]; };       // this lane's two words of every plane of its fragment rows
-    constexpr int NREAD = FM * SA + FN * SB;
-    // read r of this wave's chunk t of the group: (fragment, plane) of A, then of B; words of planes that do not
-    // exist stay zero
-    auto read_one = [&](auto tc, auto rc, Words &w) __attribute__((always_inline)) {
-        constexpr int t = decltype(tc)::value, r = decltype(rc)::value;
-        const char *lds = reinterpret_cast<const char *>(smem);
-        if constexpr (r < FM * SA) {
-            constexpr int f = r / SA, s = r % SA;
-            if (s < n_pa) w.a[f][s] = *reinterpret_cast<const uint2 *>(lds + rdA[t] + (s * BM + 32 * f) * G * 16);
-        } else {
-            constexpr int f = (r - FM * SA) / SB, s = (r - FM * SA) % SB;
-            if (s < n_pb) w.b[f][s] = *reinterpret_cast<const uint2 *>(lds + rdB[t] + (s * BN + 32 * f) * G * 16);
-        }
-    };
-
-    v16i_t acc[FM][FN];
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
-    uint32_t ra[FM], rb[FN];                            // decoded row sums of this lane's words (Sec. 3.2 Case III: J X)
-#pragma unroll
-    for (int i = 0; i < FM; ++i) ra[i] = 0;
-#pragma unroll
-    for (int j = 0; j < FN; ++j) rb[j] = 0;
     const bool need_ra = p.mulA != 0, need_rb = p.mulB != 0;
-    auto row_sums = [&](const Words &w) __attribute__((always_inline)) {      // (before the top plane of an 8-bit operand is inverted)
+    uint32_t ra = 0, rb = 0;                             // row sums of this thread's words
+    uint32_t *const mine = smem + ((2 * word) * 129 + row) * 4;
+    auto stage = [&](int buffer, const Words &w, auto cc) __attribute__((always_inline)) {       // bytes of word c of every piece
+        constexpr int c = decltype(cc)::value;
+        uint32_t wa[SA], wb[SB];
+#pragma unroll
+        for (int s = 0; s < SA; ++s) wa[s] = static_cast<uint32_t>(w.a[s][c]);
+#pragma unroll
+        for (int s = 0; s < SB; ++s) wb[s] = static_cast<uint32_t>(w.b[s][c]);
         if (need_ra) {
 #pragma unroll
-            for (int f = 0; f < FM; ++f)
-#pragma unroll
-                for (int s = 0; s < SA; ++s) ra[f] += static_cast<uint32_t>(__popc(w.a[f][s].x) + __popc(w.a[f][s].y)) << s;
+            for (int s = 0; s < SA; ++s) ra += static_cast<uint32_t>(__popc(wa[s])) << s;
         }
         if (need_rb) {
 #pragma unroll
-            for (int f = 0; f < FN; ++f)
+            for (int s = 0; s < SB; ++s) rb += static_cast<uint32_t>(__popc(wb[s])) << s;
+        }
+        if (CA == I8_C8) wa[SA - 1] ^= p.flipA;          // an 8-bit operand enters as value - 128
+        if (CB == I8_C8) wb[SB - 1] ^= p.flipB;
+        uint32_t x[8], d[8];
+        uint32_t *to = mine + buffer * (2 * kI8Pieces * 4);
+        planes_to_bytes<CA, 0>(wa, km, x, d);
+        planes_to_bytes<CA, 1>(wa, km, x, d);
+        *reinterpret_cast<uint4 *>(to) = make_uint4(d[0], d[1], d[2], d[3]);
+        *reinterpret_cast<uint4 *>(to + 129 * 4) = make_uint4(d[4], d[5], d[6], d[7]);
+        to += kI8Pieces * 4;
+        planes_to_bytes<CB, 0>(wb, km, x, d);
+        planes_to_bytes<CB, 1>(wb, km, x, d);
+        *reinterpret_cast<uint4 *>(to) = make_uint4(d[0], d[1], d[2], d[3]);
+        *reinterpret_cast<uint4 *>(to + 129 * 4) = make_uint4(d[4], d[5], d[6], d[7]);
+    };
+
+    v16i_t acc[2][2];
 #pragma unroll
-                for (int s = 0; s < SB; ++s) rb[f] += static_cast<uint32_t>(__popc(w.b[f][s].x) + __popc(w.b[f][s].y)) << s;
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = v16i_t{};
+    auto multiply = [&](int buffer) __attribute__((always_inline)) {
+        const uint32_t *from = smem + buffer * (2 * kI8Pieces * 4);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const uint32_t *at = from + (2 * (2 * ks + t) + lh) * (129 * 4) + lr * 4;
+            v4i_t a[2], b[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                a[i] = *reinterpret_cast<const v4i_t *>(at + (64 * wm + 32 * i) * 4);
+                b[i] = *reinterpret_cast<const v4i_t *>(at + kI8Pieces * 4 + (64 * wn + 32 * i) * 4);
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[i], b[j], acc[i][j], 0, 0, 0);
         }
     };
-    struct Bytes { uint32_t a[FM][8], b[FN][8]; };      // the bytes of two instruction steps (dwords 0-3, 4-7) per fragment
 
-    // One phase: the 2 FM FN matrix instructions of one word (bytes `cur`), each followed by its share of the
-    // transposition of word E of `wsrc` into `nxt` (cut into 2 (FM + FN) pieces) and by whatever memory
-    // instructions `hook` deals to that slot.  A wave issues in order: loads and LDS reads issued in a burst
-    // held up the vector instructions behind them, spread out like this they run underneath.
-    constexpr int NMI = 2 * FM * FN, NPART = 2 * (FM + FN);
-    auto phase = [&](const Bytes &cur, const Words &wsrc, auto enc, Bytes &nxt, auto &&hook) __attribute__((always_inline)) {
-        constexpr int E = decltype(enc)::value;
-        uint32_t x[8];
-        auto part = [&](auto pc) __attribute__((always_inline)) {
-            constexpr int pi = decltype(pc)::value, f = pi / 2, half = pi % 2;
-            if constexpr (f < FM) {
-                uint32_t w[SA];
-#pragma unroll
-                for (int s = 0; s < SA; ++s) w[s] = E ? wsrc.a[f][s].y : wsrc.a[f][s].x;
-                if (CA == I8_C8 && half == 0) w[SA - 1] ^= p.flipA;       // an 8-bit operand enters as value - 128
-                planes_to_bytes<CA, half>(w, km, x, nxt.a[f]);
-            } else {
-                constexpr int g = f - FM;
-                uint32_t w[SB];
-#pragma unroll
-                for (int s = 0; s < SB; ++s) w[s] = E ? wsrc.b[g][s].y : wsrc.b[g][s].x;
-                if (CB == I8_C8 && half == 0) w[SB - 1] ^= p.flipB;
-                planes_to_bytes<CB, half>(w, km, x, nxt.b[g]);
-            }
-        };
-        static_for<NMI>([&](auto qc) {
-            constexpr int q = decltype(qc)::value, h = q / (FM * FN), i = q / FN % FM, j = q % FN;
-            const v4i_t a = {static_cast<int>(cur.a[i][4 * h]), static_cast<int>(cur.a[i][4 * h + 1]),
-                             static_cast<int>(cur.a[i][4 * h + 2]), static_cast<int>(cur.a[i][4 * h + 3])};
-            const v4i_t b = {static_cast<int>(cur.b[j][4 * h]), static_cast<int>(cur.b[j][4 * h + 1]),
-                             static_cast<int>(cur.b[j][4 * h + 2]), static_cast<int>(cur.b[j][4 * h + 3])};
-            acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, acc[i][j], 0, 0, 0);
-            static_for<NPART *(q + 1) / NMI - NPART * q / NMI>([&](auto tc) {
-                part(std::integral_constant<int, NPART * q / NMI + decltype(tc)::value>{});
-            });
-            hook(qc);
-            __builtin_amdgcn_sched_barrier(0);
-        });
-    };
-    using E0 = std::integral_constant<int, 0>;
-    using E1 = std::integral_constant<int, 1>;
-
-    // Group g (chunks G g .. G g + G - 1) lives in buffer g mod 2.  A wave's half-iteration multiplies one of its
-    // chunks while it reads the words of its next chunk and transposes the second word of the one and the first of
-    // the other.  In its last half-iteration of group g: group g + 1 has landed (wait, barrier -- the only ones of the
-    // group), the reads move over to its buffer, and group g + 2 is requested into the buffer of group g, whose words
-    // every wave has in registers by then; it is needed a whole group later.  Chunks beyond the last are zeros.
-    Words w0, w1;
-    Bytes by0, by1;
-#pragma unroll
-    for (int f = 0; f < FM; ++f)
-#pragma unroll
-        for (int s = 0; s < SA; ++s) w0.a[f][s] = w1.a[f][s] = make_uint2(0u, 0u);
-#pragma unroll
-    for (int f = 0; f < FN; ++f)
-#pragma unroll
-        for (int s = 0; s < SB; ++s) w0.b[f][s] = w1.b[f][s] = make_uint2(0u, 0u);
-    begin_group(0, smem_base);
-    static_for<NLOAD>([&](auto dc) { load_one(dc); });
-    begin_group(1, smem_base + buf_bytes);
-    static_for<NLOAD>([&](auto dc) { load_one(dc); });
-    __builtin_amdgcn_s_waitcnt(WAIT_LOADS);
-    __syncthreads();
-    uint32_t cur_base = 0;                              // byte offset of the buffer the reads come from
-    set_read_buffer(cur_base);
-    static_for<NREAD>([&](auto rc) { read_one(E0{}, rc, w0); });
-    auto no_hook = [](auto) {};
-    {
-        Bytes dummy;                                    // (the matrix instructions of this warm-up phase multiply zeros into zero accumulators)
-#pragma unroll
-        for (int f = 0; f < FM; ++f)
-#pragma unroll
-            for (int d = 0; d < 8; ++d) dummy.a[f][d] = 0;
-#pragma unroll
-        for (int f = 0; f < FN; ++f)
-#pragma unroll
-            for (int d = 0; d < 8; ++d) dummy.b[f][d] = 0;
-        row_sums(w0);
-        phase(dummy, w0, E0{}, by0, no_hook);
-    }
-    int group = 0;                                      // group of the chunk being multiplied
-    auto half_iteration = [&](auto tc, Words &wc, Words &wn_) __attribute__((always_inline)) {
-        constexpr int t = decltype(tc)::value, tn = (t + 1) % CPW;     // this wave's chunk of the group being multiplied / read
-        constexpr bool LAST = t == CPW - 1;
-        fresh_counts();
-        if constexpr (LAST) {
-            __builtin_amdgcn_s_waitcnt(WAIT_LOADS);     // this wave's share of group + 1 is in LDS
+    auto four_chunks = [&](const Words &now, const Words &next) __attribute__((always_inline)) {
+        static_for<4>([&](auto cc) {
+            constexpr int c = decltype(cc)::value;
+            // buffer c + 1 was read last before the barrier that ended chunk c - 1
+            if (ks == 0) multiply(c & 1);
+            if constexpr (c < 3) stage((c + 1) & 1, now, std::integral_constant<int, c + 1>{});
+            else stage(0, next, std::integral_constant<int, 0>{});
+            if (ks) multiply(c & 1);
             __syncthreads();
-            begin_group(group + 2, smem_base + cur_base);
-            cur_base = cur_base ? 0u : static_cast<uint32_t>(buf_bytes);
-            set_read_buffer(cur_base);
-            ++group;
-        }
-        // first phase: the reads of the next chunk, and this wave's loads of the group (as early as the buffer is free)
-        phase(by0, wc, E1{}, by1, [&](auto qc) {
-            constexpr int q = decltype(qc)::value;
-            static_for<NREAD *(q + 1) / NMI - NREAD * q / NMI>([&](auto ic) {
-                read_one(std::integral_constant<int, tn>{}, std::integral_constant<int, NREAD * q / NMI + decltype(ic)::value>{}, wn_);
-            });
-            if constexpr (LAST)
-                static_for<NLOAD *(q + 1) / NMI - NLOAD * q / NMI>([&](auto ic) {
-                    load_one(std::integral_constant<int, NLOAD * q / NMI + decltype(ic)::value>{});
-                });
-        });
-        row_sums(wn_);
-        phase(by1, wn_, E0{}, by0, no_hook);
-    };
-    // (the host makes nk a multiple of 4: whole groups, and an even number of chunks for every wave)
-    constexpr int UNROLL = CPW % 2 == 0 ? CPW : 2 * CPW;
-    for (int u = 0; u < p.nk / NKS; u += UNROLL) {
-        static_for<UNROLL / 2>([&](auto vc) {
-            constexpr int v = decltype(vc)::value;
-            half_iteration(std::integral_constant<int, (2 * v) % CPW>{}, w0, w1);
-            half_iteration(std::integral_constant<int, (2 * v + 1) % CPW>{}, w1, w0);
-        });
-    }
-    __builtin_amdgcn_s_waitcnt(WAIT_LOADS);             // the loads requested for groups beyond the last one have landed
-
-    // The two lane halves hold the row sums of different words of the same row.
-#pragma unroll
-    for (int i = 0; i < FM; ++i) ra[i] += static_cast<uint32_t>(__shfl_xor(static_cast<int>(ra[i]), 32));
-#pragma unroll
-    for (int j = 0; j < FN; ++j) rb[j] += static_cast<uint32_t>(__shfl_xor(static_cast<int>(rb[j]), 32));
-
-    // ---- one row of wave tiles (32 rows x FN tiles): encoding recovery (Sec. 3.2) and the outputs.
-    //   Y = accmul acc + mulA RA[row] + mulB RB[column] + c0, in wrapping 32-bit arithmetic (the result fits int32,
-    // the host checks K (2^p - 1)(2^q - 1) < 2^31).
-    auto finish_tile_row = [&](int irow, v16i_t (&t)[FN], uint32_t ra_row) __attribute__((always_inline)) {
-        const uint32_t ra_m = ra_row * static_cast<uint32_t>(p.mulA);
-        uint32_t col[FN];
-#pragma unroll
-        for (int j = 0; j < FN; ++j) col[j] = rb[j] * static_cast<uint32_t>(p.mulB) + static_cast<uint32_t>(p.c0);
-        // accumulator register r of lane (lh, lr) is row 8 (r / 4) + 4 lh + r % 4, column lr
-        static_for<16>([&](auto rc) {
-            constexpr int r = decltype(rc)::value;
-            const int row = 8 * (r >> 2) + 4 * lh + (r & 3);
-            const uint32_t rowterm = need_ra ? static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(4 * row, static_cast<int>(ra_m))) : 0u;
-#pragma unroll
-            for (int j = 0; j < FN; ++j)
-                t[j][r] = static_cast<int>(static_cast<uint32_t>(t[j][r]) * static_cast<uint32_t>(p.accmul) + rowterm + col[j]);
-        });
-        const int mrow0 = m0 + wm * FM * 32 + irow * 32;            // first row of this row of wave tiles
-        if (p.Y) {
-            // int32 output straight from the accumulators: one store instruction writes two 128-byte row segments.
-            // The whole byte offset travels in the per-lane offset, which the hardware checks against M x N.
-            const __amdgpu_buffer_rsrc_t rsrcY =
-                __builtin_amdgcn_make_buffer_rsrc(p.Y, 0, 4u * static_cast<uint32_t>(p.M) * p.N, 0x00020000);
-            const int gn0 = n0 + wn * FN * 32 + lr;
-            const uint32_t vbase = 4u * (static_cast<uint32_t>(mrow0 + 4 * lh) * p.N + gn0);
-            static_for<FN * 16>([&](auto c) {
-                constexpr int j = decltype(c)::value / 16, r = decltype(c)::value % 16;
-                constexpr int row = 8 * (r >> 2) + (r & 3);
-                const uint32_t voff = (vbase + 128u * j) | (gn0 + 32 * j < p.N ? 0u : OUT_OF_RANGE);
-                __builtin_amdgcn_raw_buffer_store_b32(t[j][r], rsrcY, voff + 4u * row * static_cast<uint32_t>(p.N), 0, 0);
-            });
-        }
-        if (!p.scale) return;
-        MfmaParams pe = p;                              // the shared epilogue sees finished integers
-        pe.out_scale = 1.0f; pe.c0 = 0; pe.Y = nullptr;
-        static_for<FN>([&](auto jc) {
-            constexpr int j = decltype(jc)::value;
-            const int gn = n0 + wn * FN * 32 + j * 32 + lr;
-            float sc = 0.0f, bi = 0.0f;
-            if (gn < p.N) { sc = p.scale[gn]; bi = p.bias[gn]; }
-            static_for<4>([&](auto kc) {
-                constexpr int k = decltype(kc)::value;
-                const int row0 = mrow0 + 8 * k;
-                const float v4[4] = {static_cast<float>(t[j][4 * k]), static_cast<float>(t[j][4 * k + 1]),
-                                     static_cast<float>(t[j][4 * k + 2]), static_cast<float>(t[j][4 * k + 3])};
-                finish_rows8(pe, v4, row0, gn, sc, bi, load_res_rows8(pe, row0, gn >> 5, lane), lane, lr, lh);
-            });
         });
     };
-
-    if constexpr (NKS == 1) {
-        static_for<FM>([&](auto ic) { finish_tile_row(decltype(ic)::value, acc[decltype(ic)::value], ra[decltype(ic)::value]); });
-    } else {
-        // The waves of a pair add their halves: wave ks keeps tile row ks, hands the other one (and its row sums) to
-        // its partner through LDS, and finishes its own.  Per wave: FN 16 accumulator registers, one row-sum register
-        // of A, FN of B, of 64 lanes each.
-        constexpr int XREGS = FN * 16 + 1 + FN;
-        __syncthreads();                                // every wave is done with the operand tiles
-        uint32_t *xch = smem + (wave * XREGS) * 64 + lane, *from = smem + ((wave ^ 4) * XREGS) * 64 + lane;
-        v16i_t mine[FN];
-        uint32_t ra_mine;
-        if (ks == 0) {
-#pragma unroll
-            for (int j = 0; j < FN; ++j) {
-                mine[j] = acc[0][j];
-#pragma unroll
-                for (int r = 0; r < 16; ++r) xch[(j * 16 + r) * 64] = static_cast<uint32_t>(acc[1][j][r]);
-            }
-            ra_mine = ra[0];
-            xch[FN * 16 * 64] = ra[1];
-        } else {
-#pragma unroll
-            for (int j = 0; j < FN; ++j) {
-                mine[j] = acc[1][j];
-#pragma unroll
-                for (int r = 0; r < 16; ++r) xch[(j * 16 + r) * 64] = static_cast<uint32_t>(acc[0][j][r]);
-            }
-            ra_mine = ra[1];
-            xch[FN * 16 * 64] = ra[0];
-        }
-#pragma unroll
-        for (int j = 0; j < FN; ++j) xch[(FN * 16 + 1 + j) * 64] = rb[j];
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < FN; ++j) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) mine[j][r] += static_cast<int>(from[(j * 16 + r) * 64]);
-            rb[j] += from[(FN * 16 + 1 + j) * 64];
-        }
-        ra_mine += from[FN * 16 * 64];
-        finish_tile_row(ks, mine, ra_mine);
+    Words even{}, odd{};
+    fetch(0, even);
+    stage(0, even, std::integral_constant<int, 0>{});
+    __syncthreads();
+    for (int four = 0; four < p.nk / 4; four += 2) {     // (beyond the last words: zeros)
+        fetch(four + 1, odd);
+        four_chunks(even, odd);
+        if (four + 1 == p.nk / 4) break;
+        fetch(four + 2, even);
+        four_chunks(odd, even);
     }
+
+    // ---- row sums of the four words of a row; the wave halves' results: each keeps one row of tiles
+    ra += static_cast<uint32_t>(__shfl_xor(static_cast<int>(ra), 1));
+    ra += static_cast<uint32_t>(__shfl_xor(static_cast<int>(ra), 2));
+    rb += static_cast<uint32_t>(__shfl_xor(static_cast<int>(rb), 1));
+    rb += static_cast<uint32_t>(__shfl_xor(static_cast<int>(rb), 2));
+    if (word == 0) {
+        sums[row] = ra;
+        sums[128 + row] = rb;
+    }
+    v4i_t *const give = reinterpret_cast<v4i_t *>(smem) + wave * 512 + lane;     // (32 registers a wave: 64 KiB, the bytes are dead)
+    const v4i_t *const take = reinterpret_cast<const v4i_t *>(smem) + (wave ^ 4) * 512 + lane;
+    v16i_t out[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            v4i_t t;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                t[r] = ks ? acc[0][j][4 * q + r] : acc[1][j][4 * q + r];
+                out[j][4 * q + r] = ks ? acc[1][j][4 * q + r] : acc[0][j][4 * q + r];
+            }
+            give[(4 * j + q) * 64] = t;
+        }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const v4i_t t = take[(4 * j + q) * 64];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) out[j][4 * q + r] += t[r];
+        }
+
+    // ---- encoding recovery (Sec. 3.2), in wrapping 32-bit arithmetic: Y = accmul acc + mulA RA[row] + mulB RB[column] + c0
+    const int mrow0 = m0 + 64 * wm + 32 * ks;
+    uint32_t col[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+        col[j] = (need_rb ? sums[128 + 64 * wn + 32 * j + lr] * static_cast<uint32_t>(p.mulB) : 0u) + static_cast<uint32_t>(p.c0);
+    // accumulator register r of lane (lh, lr) is row 8 (r / 4) + 4 lh + r % 4, column lr
+    static_for<16>([&](auto rc) {
+        constexpr int r = decltype(rc)::value;
+        const uint32_t rowterm = need_ra ? sums[64 * wm + 32 * ks + 8 * (r >> 2) + 4 * lh + (r & 3)] * static_cast<uint32_t>(p.mulA) : 0u;
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+            out[j][r] = static_cast<int>(static_cast<uint32_t>(out[j][r]) * static_cast<uint32_t>(p.accmul) + rowterm + col[j]);
+    });
+    if (p.Y) {                                           // straight from the accumulators: two 128-byte row segments a store, rows beyond M out of range
+        const __amdgpu_buffer_rsrc_t bufY = __builtin_amdgcn_make_buffer_rsrc(p.Y, 0, 4u * static_cast<uint32_t>(p.M) * p.N, 0x00020000);
+        const int gn0 = n0 + 64 * wn + lr;
+        const uint32_t vbase = 4u * (static_cast<uint32_t>(mrow0 + 4 * lh) * p.N + gn0);
+        static_for<32>([&](auto c) {
+            constexpr int j = decltype(c)::value / 16, r = decltype(c)::value % 16, line = 8 * (r >> 2) + (r & 3);
+            const uint32_t at = (vbase + 128u * j) | (gn0 + 32 * j < p.N ? 0u : OUT_OF_RANGE);
+            __builtin_amdgcn_raw_buffer_store_b32(out[j][r], bufY, at + 4u * line * static_cast<uint32_t>(p.N), 0, 0);
+        });
+    }
+    if (!p.scale) return;
+    MfmaParams pe = p;                                   // the shared epilogue sees finished integers
+    pe.out_scale = 1.0f; pe.c0 = 0; pe.Y = nullptr;
+    static_for<2>([&](auto jc) {
+        constexpr int j = decltype(jc)::value;
+        const int gn = n0 + 64 * wn + 32 * j + lr;
+        float sc = 0.0f, bi = 0.0f;
+        if (gn < p.N) { sc = p.scale[gn]; bi = p.bias[gn]; }
+        static_for<4>([&](auto kc) {
+            constexpr int k = decltype(kc)::value;
+            const int row0 = mrow0 + 8 * k;
+            const float v4[4] = {static_cast<float>(out[j][4 * k]), static_cast<float>(out[j][4 * k + 1]),
+                                 static_cast<float>(out[j][4 * k + 2]), static_cast<float>(out[j][4 * k + 3])};
+            finish_rows8(pe, v4, row0, gn, sc, bi, load_res_rows8(pe, row0, gn >> 5, lane), lane, lr, lh);
+        });
+    });
 }
 
 }  // namespace apnn

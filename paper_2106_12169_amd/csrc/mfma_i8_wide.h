@@ -1,19 +1,16 @@
 // The 8-bit integer matrix form (mfma_i8.h) with the K steps, not the outputs, shared out among the waves.
 //
-// mfma_i8_kernel is bound by the vector instructions that transpose plane words into bytes, and with 64 x 64 wave
-// tiles one transposed fragment feeds only two matrix instructions.  Here a block still owns 128 x 128 outputs (so a
-// 2048^2 product still has a block for every compute unit), but each of its four waves computes ALL of them -- 4 x 4
-// instruction tiles, 256 accumulator registers, one wave per SIMD -- over its own quarter of K: wave w takes chunk w
-// of every group of four chunks.  One transposed fragment now feeds four matrix instructions, half the vector
-// instructions per matrix instruction (7 instead of 14.5 at 3 x 5 bits), and the four partial results are added
-// through LDS once, at the end.
+// A block owns 128 x 128 outputs, and each of its four waves computes ALL of them -- 4 x 4 instruction tiles, 256 accumulator
+// registers, one wave per SIMD -- over its own quarter of K: wave w takes chunk w of every group of four chunks of four words.
+// One fragment transposed in registers feeds four matrix instructions (7 vector instructions per matrix instruction at 3 x 5
+// bits), and the four partial results are added through LDS once, at the end.
 //
-// What it buys, measured: the K-dependent part is a quarter shorter (4.5 against 5.95 us per 1024 of K at 4 x 4 bits,
-// 2048^2 outputs), not half: a lone wave overlaps only about four vector instructions with a matrix instruction, the
-// rest add to it; and the K-independent part is 3.7 us longer (the exchange of 4 x 256 accumulator registers
-// through LDS).  So the dispatch takes this kernel for long K only.
+// Measured: 4.5 us per 1024 of K at 4 x 4 bits, 2048^2 outputs (mfma_i8_kernel 5.1), and 4 us more that do not depend on K (the
+// exchange of 4 x 256 accumulator registers through LDS): the dispatch takes this kernel for long K only.  A lone wave
+// overlaps only about four vector instructions with a matrix instruction, the rest add to it.
 //
-// Loader, LDS layout, transposition and encodings are those of mfma_i8_kernel.  Registers: the bytes of the word being
+// Planes go to LDS directly from global memory, 16 bytes per lane, adjacent lanes taking adjacent pieces of one plane row, two
+// group buffers, one barrier per group, the pieces XOR-swizzled by row.  Registers: the bytes of the word being
 // multiplied and of the next one (2 x 64), and the plane words of ONE fragment at a time, read from LDS two
 // matrix instructions before its transposition; the 32 matrix instructions of a word each carry one piece of work.
 #pragma once

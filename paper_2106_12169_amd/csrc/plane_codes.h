@@ -69,7 +69,7 @@ template <int B> __device__ __forceinline__ void two_codes(uint32_t &d, v2f_t t)
 }
 
 // (mask & a) | (~mask & b)
-__device__ __forceinline__ uint32_t bit_select(uint32_t mask, uint32_t a, uint32_t b) { return (mask & a) | (~mask & b); }
+__device__ __forceinline__ uint32_t mask_select(uint32_t mask, uint32_t a, uint32_t b) { return (mask & a) | (~mask & b); }
 
 // Eight values of a lane (results / 4 of the channels 4 j + 2 lh + q of a tile) -> eight nibbles: code k < 4 is k, everything
 // above it 4.  sc, bi: the channels' constants, bi a quarter of the bias; res: the residual's codes, a nibble each.
@@ -103,11 +103,11 @@ __device__ __forceinline__ uint32_t nibbles(const float (&v)[8], const v4f_t (&s
 __device__ __forceinline__ uint32_t plane_words(uint32_t x, uint32_t y, int q_out)
 {
     // plane 0 = bit 0 | bit 2, plane 1 = bit 1 | bit 2; bits 0 (x) and 1 (y) of each nibble are kept
-    uint32_t p0 = bit_select(0x11111111u, x | (x >> 2), (y << 1) | (y >> 1));
-    const uint32_t p1 = bit_select(0x11111111u, (x >> 1) | (x >> 2), y | (y >> 1));
+    uint32_t p0 = mask_select(0x11111111u, x | (x >> 2), (y << 1) | (y >> 1));
+    const uint32_t p1 = mask_select(0x11111111u, (x >> 1) | (x >> 2), y | (y >> 1));
     if (q_out == 1) p0 |= p1;                           // clamp at 1
     const auto both = __builtin_amdgcn_permlane32_swap(p0, p1, false, false);    // half b: plane b of either half's channels
-    return bit_select(0x33333333u, both[0], both[1] << 2);
+    return mask_select(0x33333333u, both[0], both[1] << 2);
 }
 
 }  // namespace apnn
