@@ -25,6 +25,9 @@
  *   MFMA_HALO     convolutions staged once per block: 0 never; 1 | 2: whenever it
  *                 applies, with 128 or 256 pixels a block (unset: not where
  *                 MFMA_TILE, _SMALL, _NSPLIT or _FN asks for another form)
+ *   MFMA_T16      products with 16 x 16 tiles: 0 never; 4 | 8: wherever it applies,
+ *                 with that many waves a block (unset: not where another of
+ *                 these asks for another form)
  *   INPUT_TILE    input layers with the image rows staged once per block: 0 never,
  *                 1 whenever it applies
  * A forced value the dispatch cannot honour for a call is ignored for that call.
