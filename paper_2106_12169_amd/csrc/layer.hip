@@ -230,20 +230,22 @@ static bool try_mfma(const Problem &pr, MfmaParams &mp, void *stream, int &rc, S
     if (short_k) t = 64;
     // Few outputs: 16 x 16 tiles bring four times the blocks, at twice the operand expansion per output.  They are
     // ahead up to two tiles per compute unit (128 x 1000, K = 4096, w1a2: 512 tiles, 4.7 against 5.3 us; 256 x 1000: 6.0
-    // against 5.5), up to four where K is short and the other form is the 64 x 64 tile (512 x 512, K = 128: 3.6 against 4.2;
+    // against 5.5; 3 x 3 convolution, 512 channels at 7 x 7: 4 images 5.9 against 6.3, 8 images 7.2 against 6.3), up to four where K is short and the other form is the 64 x 64 tile (512 x 512, K = 128: 3.6 against 4.2;
     // 1024 x 1024: 6.4 against 4.6), and at every count where a 32 x 32 tile would be half empty (1 x 32000, K = 4096: 7.9
     // against 9.6).  Override MFMA_T16: 0 never, 4 or 8 the form with that many waves wherever it applies.
     const int t16 = ov(OV_MFMA_T16);
     const int64_t tiles16 = ceil_div(pr.M, 16) * ceil_div(pr.N, 16);
     const bool few = (t == 32 || short_k) && (tiles16 <= (short_k ? 1024 : 512) || pr.M <= 16 || pr.N <= 16) && !other &&
                      ov(OV_MFMA_SHORTK) < 0;
-    if (!pr.conv && !plan && tiles16 <= kMaxBlocks / 2 && launch_mfma_tile16 && (t16 < 0 ? few : t16 > 0)) {
-        // eight waves from three groups of 512 K positions a wave (8 x 4096 outputs, w1a2: K = 9216 4.9 against 5.3 us
-        // with four, K = 4096 4.0 against 3.9), unless the blocks fill the chip (1 x 32000, K = 4096, w2a4: 18.0 against 14.4)
+    if (!plan && tiles16 <= kMaxBlocks / 2 && launch_mfma_tile16 && (t16 < 0 ? few : t16 > 0)) {
+        // eight waves from about three groups of 512 K positions a wave (8 x 4096 outputs, w1a2: K = 9216 4.9 against 5.3
+        // us with four, K = 4096 4.0 against 3.9; 98 x 512, K = 4608 5.0 against 5.2), later where the blocks fill the
+        // chip (196 x 512, K = 4608: 6.2 against 5.9) and never beyond (1 x 32000, K = 4096, w2a4: 18.0 against 14.4)
         const int64_t groups = ceil_div(mp.Kw, 16);
-        const int waves = t16 > 0 ? t16 : groups * mp.DA * mp.DB >= 12 && tiles16 <= 512 ? 8 : 4;
+        const int vw = !pr.conv ? 0 : mp.Cw % 4 == 0 ? 4 : odd_words ? 1 : 2;
+        const int waves = t16 > 0 ? t16 : groups * mp.DA * mp.DB >= (tiles16 <= 256 ? 9 : 12) && tiles16 <= 512 ? 8 : 4;
         mp.c0 = (kA == OPK_PM1 && kB == OPK_PM1) ? -static_cast<int>(groups * 512 - pr.Ktotal) : 0;
-        if (launch_mfma_tile16(mp, kA, kB, waves, static_cast<unsigned>(tiles16), as_stream(stream))) {
+        if (launch_mfma_tile16(mp, kA, kB, vw, waves, static_cast<unsigned>(tiles16), as_stream(stream))) {
             rc = check_launch(pr.who);
             return true;
         }

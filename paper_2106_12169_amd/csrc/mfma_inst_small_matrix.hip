@@ -1,8 +1,7 @@
-// Matrix-operand instances of the small-layer matrix-core kernels: lane-private operand loads, 32 x 32 tiles (one
-// tile per wave or K split over four waves) and 16 x 16 tiles (K split over four or eight waves).
+// Matrix-operand instances of the small-layer matrix-core kernel (lane-private
+// operand loads, 32 x 32 tiles): one tile per wave or K split over four waves.
 #include "mfma_launch.h"
 #include "mfma_small.h"
-#include "mfma_tile16.h"
 
 namespace apnn {
 
@@ -24,28 +23,6 @@ bool launch_mfma_small_matrix(const MfmaParams &p, int kindA, int kindB, int nsp
         case 6: go<2, 0>(p, nsplit, grid, st); return true;
         case 7: go<2, 1>(p, nsplit, grid, st); return true;
         case 8: go<2, 2>(p, nsplit, grid, st); return true;
-        default: return false;
-    }
-}
-
-template <int KA, int KB> static void go16(const MfmaParams &p, int waves, unsigned grid, hipStream_t st)
-{
-    if (waves == 4) hipLaunchKernelGGL((mfma_tile16_kernel<KA, KB, 4, 2>), dim3(grid), dim3(256), 0, st, p);
-    else hipLaunchKernelGGL((mfma_tile16_kernel<KA, KB, 8, 4>), dim3(grid), dim3(512), 0, st, p);
-}
-
-bool launch_mfma_tile16(const MfmaParams &p, int kindA, int kindB, int waves, unsigned grid, hipStream_t st)
-{
-    switch (kindA * 3 + kindB) {
-        case 0: go16<0, 0>(p, waves, grid, st); return true;
-        case 1: go16<0, 1>(p, waves, grid, st); return true;
-        case 2: go16<0, 2>(p, waves, grid, st); return true;
-        case 3: go16<1, 0>(p, waves, grid, st); return true;
-        case 4: go16<1, 1>(p, waves, grid, st); return true;
-        case 5: go16<1, 2>(p, waves, grid, st); return true;
-        case 6: go16<2, 0>(p, waves, grid, st); return true;
-        case 7: go16<2, 1>(p, waves, grid, st); return true;
-        case 8: go16<2, 2>(p, waves, grid, st); return true;
         default: return false;
     }
 }

@@ -364,6 +364,54 @@ __device__ __forceinline__ uint4 load_conv_b_words(const uint32_t *src, int left
     return v;
 }
 
+// Words kk .. kk + 3 of a pixel's receptive field for the lane-private kernels; VW = 4: they lie in one tap, 2: in two
+// taps of two words each, 1: load_conv_a_words.  `pix` is the first pixel of the row's image, `validity` asks for all
+// ones inside the frame.  The caller has checked kk < Kw.
+template <int VW>
+__device__ __forceinline__ uint4 load_conv_a(const MfmaParams &p, int64_t pix, int plane, int kk, int h0, int w0, bool validity)
+{
+    uint4 v = make_uint4(0, 0, 0, 0);
+    if constexpr (VW == 1) return load_conv_a_words(p, p.A + pix * p.PA * p.Cw, plane, kk, h0, w0, validity);
+#pragma unroll
+    for (int part = 0; part < 4 / VW; ++part) {
+        const int k = kk + part * VW;
+        if (k < p.Kw) {
+            const int tap = static_cast<int>((static_cast<float>(k) + 0.5f) * p.invCw);
+            const int cw = k - tap * p.Cw;
+            int r, sc;
+            tap_to_rs(p, tap, r, sc);
+            const int h = h0 + r, w = w0 + sc;
+            if (h >= 0 && h < p.H && w >= 0 && w < p.W) {
+                const uint32_t *src = p.A + ((pix + h * p.W + w) * p.PA + plane) * p.Cw + cw;
+                if (validity) {
+                    if (VW == 4) v = make_uint4(~0u, ~0u, ~0u, ~0u);
+                    else if (part == 0) { v.x = ~0u; v.y = ~0u; } else { v.z = ~0u; v.w = ~0u; }
+                } else if (VW == 4) {
+                    v = *reinterpret_cast<const uint4 *>(src);
+                } else {
+                    const uint2 t = *reinterpret_cast<const uint2 *>(src);
+                    if (part == 0) { v.x = t.x; v.y = t.y; } else { v.z = t.x; v.w = t.y; }
+                }
+            }
+        }
+    }
+    return v;
+}
+
+// Words 0 .. 3 of a convolution's weight row, `left` of them inside the row.
+template <int VW> __device__ __forceinline__ uint4 load_conv_b(const uint32_t *src, int left)
+{
+    if constexpr (VW == 1) return load_conv_b_words(src, left);
+    uint4 v = make_uint4(0, 0, 0, 0);           // rows are 8-byte aligned and an even number of words long
+    const uint2 lo = *reinterpret_cast<const uint2 *>(src);
+    v.x = lo.x; v.y = lo.y;
+    if (left >= 4) {
+        const uint2 hi = *reinterpret_cast<const uint2 *>(src + 2);
+        v.z = hi.x; v.w = hi.y;
+    }
+    return v;
+}
+
 // The four results of a pooling grid (exact integers in fp32): maximum or sum.
 __device__ __forceinline__ float pool4(int mode, float a, float b, float c, float d)
 {

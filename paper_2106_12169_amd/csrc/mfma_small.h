@@ -68,7 +68,6 @@ __device__ __forceinline__ void mfma_small_body(const MfmaParams &p, const int b
         a_pix = static_cast<int64_t>(n) * p.H * p.W;
     }
     const uint32_t *b_row = p.B + static_cast<int64_t>(gnB) * p.PB * p.ldwB;
-    const uint32_t *a_image = p.A + a_pix * p.PA * p.Cw;                          // convolution: this lane's image
     const uint32_t *a_row = p.A + static_cast<int64_t>(gmA) * p.PA * p.ldwA;      // matrix mode
 
     // Words kk .. kk+3 of plane `plane` of this lane's A row (zero beyond Kw / outside the frame).
@@ -77,33 +76,8 @@ __device__ __forceinline__ void mfma_small_body(const MfmaParams &p, const int b
         const bool validity = KA == OPK_PM1Z && plane == 1;     // all ones for taps inside the frame, made up here
         if (validity) plane = 0;
         if (!a_ok || kk >= p.Kw || plane >= p.PA) return v;
-        if constexpr (CONV && VW == 1) {        // up to four taps
-            v = load_conv_a_words(p, a_image, plane, kk, a_h0, a_w0, validity);
-        } else if (CONV) {
-            // VW = 4: the four words lie in one tap; VW = 2: two taps of two words each
-#pragma unroll
-            for (int part = 0; part < 4 / VW; ++part) {
-                const int k = kk + part * VW;
-                if (k < p.Kw) {
-                    const int tap = static_cast<int>((static_cast<float>(k) + 0.5f) * p.invCw);
-                    const int cw = k - tap * p.Cw;
-                    int r, sc;
-                    tap_to_rs(p, tap, r, sc);
-                    const int h = a_h0 + r, w = a_w0 + sc;
-                    if (h >= 0 && h < p.H && w >= 0 && w < p.W) {
-                        const uint32_t *src = p.A + ((a_pix + h * p.W + w) * p.PA + plane) * p.Cw + cw;
-                        if (validity) {
-                            if (VW == 4) v = make_uint4(~0u, ~0u, ~0u, ~0u);
-                            else if (part == 0) { v.x = ~0u; v.y = ~0u; } else { v.z = ~0u; v.w = ~0u; }
-                        } else if (VW == 4) {
-                            v = *reinterpret_cast<const uint4 *>(src);
-                        } else {
-                            const uint2 t = *reinterpret_cast<const uint2 *>(src);
-                            if (part == 0) { v.x = t.x; v.y = t.y; } else { v.z = t.x; v.w = t.y; }
-                        }
-                    }
-                }
-            }
+        if constexpr (CONV) {
+            v = load_conv_a<VW>(p, a_pix, plane, kk, a_h0, a_w0, validity);
         } else {
             v = *reinterpret_cast<const uint4 *>(a_row + static_cast<int64_t>(plane) * p.ldwA + kk);
         }
@@ -113,18 +87,8 @@ __device__ __forceinline__ void mfma_small_body(const MfmaParams &p, const int b
         uint4 v = make_uint4(0, 0, 0, 0);
         if (!b_ok || kk >= p.Kw || plane >= p.PB) return v;
         const uint32_t *src = b_row + static_cast<int64_t>(plane) * p.ldwB + kk;
-        if (!CONV) {
-            v = *reinterpret_cast<const uint4 *>(src);
-        } else if (VW == 1) {                   // conv weight rows of an odd number of words
-            v = load_conv_b_words(src, p.Kw - kk);
-        } else {                                // conv weight rows are 8-byte aligned and an even number of words long
-            const uint2 lo = *reinterpret_cast<const uint2 *>(src);
-            v.x = lo.x; v.y = lo.y;
-            if (kk + 4 <= p.Kw) {
-                const uint2 hi = *reinterpret_cast<const uint2 *>(src + 2);
-                v.z = hi.x; v.w = hi.y;
-            }
-        }
+        if constexpr (CONV) v = load_conv_b<VW>(src, p.Kw - kk);
+        else v = *reinterpret_cast<const uint4 *>(src);
         return v;
     };
 

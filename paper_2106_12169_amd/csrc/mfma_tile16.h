@@ -1,4 +1,4 @@
-// FP4 matrix-core kernel for products with few outputs: 16 x 16 tiles, the K range of a tile shared out among all
+// FP4 matrix-core kernel for products and convolutions with few outputs: 16 x 16 tiles, the K range of a tile shared out among all
 // waves of its block.
 //
 // Such a product lasts as long as one block does: a launch, one or two memory round trips, and about 35 vector
@@ -7,7 +7,8 @@
 // a quarter of the outputs (the same expansion work), so the same product is 256 blocks with half the steps, and eight
 // waves hide each other's latency where K is long.  Measured on w1a2 products in a replayed graph, 32 x 32 tiles before,
 // this after (us): 8 x 4096, K = 25088 16.9, 7.5; K = 9216 7.1, 4.9; K = 4096 5.0, 3.9; 64 x 1024, K = 1024 4.0, 3.3;
-// 128 x 128, K = 128 (64 x 64 tile before) 4.1, 3.2.
+// 128 x 128, K = 128 (64 x 64 tile before) 4.1, 3.2.  Convolutions: 7 x 7 of 512 channels to 8 x 1 x 1 x 4096 16.5, 8.8;
+// 3 x 3, 384 -> 256 channels at 13 x 13 5.9, 4.4.
 #pragma once
 #include "mfma_kernel.h"
 
@@ -18,8 +19,8 @@ typedef float v4f_t __attribute__((ext_vector_type(4)));
 // Block = one 16 x 16 tile of outputs.  A step is one 16 x 16 x 128 matrix instruction: lane group g = lane / 16
 // supplies 32 consecutive K positions (one plane word) of row / column lane % 16.  K is walked in groups of four
 // steps = 16 words, of which lane group g loads words 4 g .. 4 g + 3 (one 16-byte load per plane, 64 consecutive
-// bytes per row); wave w takes groups w, w + NSPLIT, ...  Words at and beyond Kw read as zero.
-template <int KA, int KB, int NSPLIT, int GMAX>
+// bytes per row of a matrix); wave w takes groups w, w + NSPLIT, ...  Words at and beyond Kw read as zero.
+template <int KA, int KB, int VW, bool CONV, int NSPLIT, int GMAX>
 __global__ __launch_bounds__(64 * NSPLIT) void mfma_tile16_kernel(const MfmaParams p)
 {
     constexpr int LA = DigitPlanes<KA>::value, LB = DigitPlanes<KB>::value;
@@ -32,8 +33,18 @@ __global__ __launch_bounds__(64 * NSPLIT) void mfma_tile16_kernel(const MfmaPara
     const int m0 = (blockIdx.x / tilesN) * 16, n0 = (blockIdx.x % tilesN) * 16;
     const int gmA = m0 + lr, gn = n0 + lr;
     const bool a_ok = gmA < p.M, b_ok = gn < p.N;
-    const uint32_t *a_row = p.A + static_cast<int64_t>(gmA) * p.PA * p.ldwA;
+    const uint32_t *a_row = p.A + static_cast<int64_t>(gmA) * p.PA * p.ldwA;      // matrix mode
     const uint32_t *b_row = p.B + static_cast<int64_t>(gn) * p.PB * p.ldwB;
+
+    int a_h0 = 0, a_w0 = 0;
+    int64_t a_pix = 0;
+    if constexpr (CONV) {
+        int wo, ho, n;
+        conv_row_to_pixel(p, gmA, n, ho, wo);
+        a_h0 = ho * p.stride - p.pad;
+        a_w0 = wo * p.stride - p.pad;
+        a_pix = static_cast<int64_t>(n) * p.H * p.W;
+    }
 
     Fp4Masks km;
     km.m1 = reg_const(0x11111111u); km.m2 = reg_const(0x22222222u);
@@ -42,15 +53,34 @@ __global__ __launch_bounds__(64 * NSPLIT) void mfma_tile16_kernel(const MfmaPara
     const int GT = (p.Kw + 15) / 16;
     const int G = wave < GT ? (GT - wave + NSPLIT - 1) / NSPLIT : 0;    // groups of this wave
 
-    auto load = [&](const uint32_t *row, bool ok, int plane, int planes, int ldw, int kk) -> uint4 {
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (ok && kk < p.Kw && plane < planes) v = *reinterpret_cast<const uint4 *>(row + static_cast<int64_t>(plane) * ldw + kk);
-        return v;
+    auto load_a = [&](int plane, int kk) -> uint4 {
+        const bool validity = KA == OPK_PM1Z && plane == 1;     // all ones for taps inside the frame, made up here
+        if (validity) plane = 0;
+        if (!a_ok || kk >= p.Kw || plane >= p.PA) return make_uint4(0, 0, 0, 0);
+        if constexpr (CONV) return load_conv_a<VW>(p, a_pix, plane, kk, a_h0, a_w0, validity);
+        else return *reinterpret_cast<const uint4 *>(a_row + static_cast<int64_t>(plane) * p.ldwA + kk);
+    };
+    auto load_b = [&](int plane, int kk) -> uint4 {
+        if (!b_ok || kk >= p.Kw || plane >= p.PB) return make_uint4(0, 0, 0, 0);
+        const uint32_t *src = b_row + static_cast<int64_t>(plane) * p.ldwB + kk;
+        if constexpr (CONV) return load_conv_b<VW>(src, p.Kw - kk);
+        else return *reinterpret_cast<const uint4 *>(src);
     };
 
     // the epilogue's per-channel parameters: their latency hides behind the main loop
     float sc = 0.0f, bi = 0.0f;
     if (p.scale && wave < 4 && b_ok) { sc = p.scale[gn]; bi = p.bias[gn]; }
+
+    uint32_t res01[2] = {0, 0};                         // ... and the residual's first two planes
+    const uint32_t *rp = p.res;
+    if (p.res && wave < 4 && b_ok) {
+        const int row = p.pool ? (m0 >> 2) + lg : m0 + 4 * lg + wave;
+        if (row < (p.pool ? p.M >> 2 : p.M)) {
+            rp += static_cast<int64_t>(row) * p.q_res * p.NW + (gn >> 5);
+            res01[0] = rp[0];
+            if (p.q_res > 1) res01[1] = rp[p.NW];
+        }
+    }
 
     // Digit pairs and the groups of each as one flat sequence, GMAX entries at a time with all their loads in
     // flight; the weight 4^(da + db) of a pair (Eq. 1) enters as the block scales of the matrix instruction.
@@ -66,9 +96,9 @@ __global__ __launch_bounds__(64 * NSPLIT) void mfma_tile16_kernel(const MfmaPara
             sa[g] = 0x7f7f7f7f + 0x02020202 * da;
             sb[g] = 0x7f7f7f7f + 0x02020202 * db;
 #pragma unroll
-            for (int pl = 0; pl < LB; ++pl) wb[g][pl] = load(b_row, b_ok, (LB == 2 ? 2 * db : db) + pl, p.PB, p.ldwB, kk);
+            for (int pl = 0; pl < LB; ++pl) wb[g][pl] = load_b((LB == 2 ? 2 * db : db) + pl, kk);
 #pragma unroll
-            for (int pl = 0; pl < LA; ++pl) wa[g][pl] = load(a_row, a_ok, (LA == 2 ? 2 * da : da) + pl, p.PA, p.ldwA, kk);
+            for (int pl = 0; pl < LA; ++pl) wa[g][pl] = load_a((LA == 2 ? 2 * da : da) + pl, kk);
             ++grp;                                      // next group, then next digit of B, then next digit of A
             const bool wg = grp == G;
             grp = wg ? 0 : grp;
@@ -98,22 +128,32 @@ __global__ __launch_bounds__(64 * NSPLIT) void mfma_tile16_kernel(const MfmaPara
 #pragma unroll
     for (int r = 0; r < 4; ++r) sRed[wave][r][lane] = acc[r];
     __syncthreads();
-    if (wave >= 4) return;
+    if (wave >= 4 || (p.pool && wave > 0)) return;
     float v = 0.0f;                                     // register `wave` of the tile: row 4 lg + wave, column lr
 #pragma unroll
     for (int k = 0; k < NSPLIT; ++k) v += sRed[k][wave][lane];
-    const int gm = m0 + 4 * lg + wave;
-    const bool ok = gm < p.M && b_ok;
-    const int y = static_cast<int>(v * p.out_scale) + p.c0;             // exact: v is a multiple of 1 / out_scale
+    int gm = m0 + 4 * lg + wave, M = p.M, c0 = p.c0;
+    if constexpr (CONV) {
+        if (p.pool) {                                   // the four registers of a lane are one pooling grid
+            float o[3] = {0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int k = 0; k < NSPLIT; ++k)
+#pragma unroll
+                for (int r = 0; r < 3; ++r) o[r] += sRed[k][r + 1][lane];
+            v = pool4(p.pool, v, o[0], o[1], o[2]);
+            gm >>= 2; M >>= 2;
+            c0 = p.pool == 2 ? 4 * c0 : c0;
+        }
+    }
+    const bool ok = gm < M && b_ok;
+    const int y = static_cast<int>(v * p.out_scale) + c0;             // exact: v is a multiple of 1 / out_scale
     if (p.Y && ok) p.Y[static_cast<int64_t>(gm) * p.N + gn] = y;
     if (!p.scale) return;
     float t = __fmaf_rn(sc, static_cast<float>(y), bi);
     if (p.res) {
-        uint32_t code = 0;
-        if (ok) {
-            const uint32_t *rp = p.res + static_cast<int64_t>(gm) * p.q_res * p.NW + (gn >> 5);
-            for (int b = 0; b < p.q_res; ++b) code |= ((rp[b * p.NW] >> (gn & 31)) & 1u) << b;
-        }
+        uint32_t code = ((res01[0] >> (gn & 31)) & 1u) | (((res01[1] >> (gn & 31)) & 1u) << 1);
+        if (ok)
+            for (int b = 2; b < p.q_res; ++b) code |= ((rp[b * p.NW] >> (gn & 31)) & 1u) << b;
         t = __fmaf_rn(p.res_scale, static_cast<float>(code), t);
     }
     if (p.T && ok) p.T[static_cast<int64_t>(gm) * p.N + gn] = t;

@@ -1,4 +1,4 @@
-"""mfma_tile16_kernel (products with few outputs) against the oracle: edges of its 16 x 16 tiles, lengths of K either side of
+"""mfma_tile16_kernel (products and convolutions with few outputs) against the oracle: edges of its 16 x 16 tiles, lengths of K either side of
 its groups of 512 positions and of the groups that its four or eight waves share, every kind of operand, the whole epilogue,
 and the sizes around the rule that takes it.  All results are whole numbers, or floats of one rounding: compared exactly."""
 import numpy as np
@@ -62,6 +62,47 @@ def test_layer(force, BS, Cout, K, p, encW, q, encX, q_out, with_res):
     assert np.array_equal(acc.cpu().numpy(), want) and np.array_equal(tf.cpu().numpy(), want_t)
     codes, pad_bits = hp.unpack_fmap(hp.words_u32(out), BS, 1, 1, Cout, q_out)
     assert np.array_equal(codes.reshape(BS, Cout), want_codes) and pad_bits == 0
+
+
+# BS, Cin, Cout, H, W, R, stride, pad, encW, p, encX, q, q_out, q_res, pool
+CONVS = [
+    (1, 256, 32, 6, 6, 6, 1, 0, P, 1, U, 2, 2, 0, 0),       # a fully connected layer: the kernel covers the frame
+    (3, 512, 96, 1, 1, 1, 1, 0, P, 1, U, 2, 2, 3, 0),       # 1 x 1 frame, residual of three planes
+    (2, 128, 64, 5, 7, 3, 1, 1, U, 2, U, 4, 3, 0, 0),       # 16-byte loads, two feature digits, three planes
+    (1, 64, 32, 9, 5, 3, 2, 1, P, 1, U, 2, 1, 1, 0),        # 8-byte loads: two taps in one
+    (2, 192, 32, 4, 4, 5, 1, 2, U, 3, U, 1, 2, 2, 0),
+    (1, 32, 64, 7, 3, 3, 1, 1, U, 1, U, 3, 2, 0, 0),        # word by word: four taps in one
+    (1, 96, 32, 6, 6, 5, 3, 2, P, 1, P, 1, 2, 0, 0),        # -1/+1 features, padding
+    (2, 128, 32, 5, 5, 3, 1, 1, U, 1, P, 1, 1, 1, 0),
+    (2, 64, 64, 7, 6, 3, 1, 1, P, 1, U, 2, 2, 0, 1),        # pooling, odd frame
+    (1, 256, 32, 6, 4, 3, 1, 1, U, 2, U, 2, 3, 2, 2),       # pooled sum with residual
+    (5, 32, 32, 4, 4, 3, 1, 1, U, 1, P, 1, 2, 3, 1),
+]
+
+
+@pytest.mark.parametrize("force", [-1, 4, 8])
+@pytest.mark.parametrize("BS,Cin,Cout,H,W,R,stride,pad,encW,p,encX,q,q_out,q_res,pool", CONVS)
+def test_conv(force, BS, Cin, Cout, H, W, R, stride, pad, encW, p, encX, q, q_out, q_res, pool):
+    Wv = wl.operand(102 + Cin, Cout, Cin * R * R, p, encW).reshape(Cout, Cin, R, R)
+    Xv = wl.operand(103 + H, BS * Cin, H * W, q, encX).reshape(BS, Cin, H, W)
+    d = B.Conv(BS, H, W, Cin, Cout, R, R, stride, pad, p, q, encW, encX)
+    want = oracle.conv2d(Wv, encW, p, Xv, encX, q, stride, pad)
+    if pool:
+        want = oracle.gridpool(want, 2, oracle.POOL_MAX if pool == B.POOL_MAX2 else oracle.POOL_SUM)
+    Hq, Wq = want.shape[2:]
+    scale = (wl.normals(104, (Cout,), 1.0, 0.3) * (1 << q_out) / 4 / (np.std(want) + 1.0)).astype(np.float32)
+    scale[::5] *= -1
+    bias = (0.5 * (1 << q_out) - scale * np.mean(want) + wl.normals(105, (Cout,), 0.0, 0.3)).astype(np.float32)
+    res = wl.uniform_codes(106, (BS, Cout, Hq, Wq), q_res) if q_res else None
+    acc = torch.empty((BS, Hq, Wq, Cout), dtype=torch.int32, device="cuda")
+    kw = dict(q_out=q_out, scale=dev(scale), bias=dev(bias), pool=pool, acc_out=acc)
+    if q_res:
+        kw.update(residual=B.apnn_pack_fmap(dev(res), B.LAYOUT_NCHW, q_res, U), q_res=q_res, res_scale=0.37)
+    Wp, Xp = B.apnn_pack_conv_weights(dev(Wv), p, encW), B.apnn_pack_fmap(dev(Xv), B.LAYOUT_NCHW, q, encX)
+    out = _run(force, lambda: B.apnn_layer(d, Wp, Xp, **kw))
+    codes, pad_bits = hp.unpack_fmap(hp.words_u32(out), BS, Hq, Wq, Cout, q_out)
+    assert np.array_equal(acc.cpu().numpy().transpose(0, 3, 1, 2), want)
+    assert pad_bits == 0 and np.array_equal(codes, oracle.epilogue(want, scale, bias, q_out, res=res, res_scale=0.37)[0])
 
 
 def test_thresholds():
