@@ -19,7 +19,8 @@
  *   TILE          8 | 4 | 2: per-thread register tile edge of the popcount kernel
  *   MFMA_TILE     256 | 128 | 64 | 32: block tile of the matrix-instruction kernels
  *   MFMA_SMALL    0: chunked K loop also for 32 x 32 tiles
- *   MFMA_NSPLIT   1 | 4: waves of a block that split K of a 32 x 32 tile
+ *   MFMA_NSPLIT   1 | 4 | 8: waves of a block that split K of a 32 x 32 tile
+ *                 (8: convolutions)
  *   MFMA_FN       1 | 2: 32 x 32 or 32 x 64 wave tiles of the small-layer kernel
  *   MFMA_SHORTK   0: no special case for K <= 256
  *   MFMA_HALO     convolutions staged once per block: 0 never; 1 | 2: whenever it

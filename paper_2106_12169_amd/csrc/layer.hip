@@ -259,7 +259,10 @@ static bool try_mfma(const Problem &pr, MfmaParams &mp, void *stream, int &rc, S
     bool ok;
     if (t == 32 && ov(OV_MFMA_SMALL) != 0) {                           // small layer: lane-private loads, no LDS staging (0: chunked kernel)
         int nsplit = tiles <= 4096 ? 4 : 1;                            // measured: the split wins up to a few thousand tiles
-        if (const int en = ov(OV_MFMA_NSPLIT); en == 1 || en == 4) nsplit = en;
+        // Eight waves a block where K is long enough to feed them (w1a2 3 x 3 convolutions, us, four waves first: 784 x 256,
+        // 72 words of K 5.6, 5.1; 784 x 512, 144 words 8.3, 7.8; 1568 x 512 12.6, 12.3; 800 x 512, 36 words 4.9, 5.2)
+        if (pr.conv && !plan && tiles <= 1024 && static_cast<int64_t>(mp.Kw) * mp.DA * mp.DB >= 72) nsplit = 8;
+        if (const int en = ov(OV_MFMA_NSPLIT); en == 1 || en == 4 || (en == 8 && pr.conv)) nsplit = en;
         const int64_t nse = round_up(ceil_div(mp.Kw, 2), 4);          // steps of the small-layer kernel (groups of four)
         mp.nk = 1;
         mp.c0 = (kA == OPK_PM1 && kB == OPK_PM1) ? -static_cast<int>(nse * 64 - pr.Ktotal) : 0;

@@ -9,6 +9,8 @@ namespace apnn {
 template <int KA, int KB, int VW> static void go_vw(const MfmaParams &p, int nsplit, int gmax, unsigned grid, hipStream_t st)
 {
     if (nsplit == 1) hipLaunchKernelGGL((mfma_small_kernel<KA, KB, VW, true, 1>), dim3(grid), dim3(256), 0, st, p);
+    else if (nsplit == 8 && gmax <= 2) hipLaunchKernelGGL((mfma_small_kernel<KA, KB, VW, true, 8, 2>), dim3(grid), dim3(512), 0, st, p);
+    else if (nsplit == 8) hipLaunchKernelGGL((mfma_small_kernel<KA, KB, VW, true, 8, 3>), dim3(grid), dim3(512), 0, st, p);
     else if (gmax == 1) hipLaunchKernelGGL((mfma_small_kernel<KA, KB, VW, true, 4, 1>), dim3(grid), dim3(256), 0, st, p);
     else if (gmax == 2) hipLaunchKernelGGL((mfma_small_kernel<KA, KB, VW, true, 4, 2>), dim3(grid), dim3(256), 0, st, p);
     else hipLaunchKernelGGL((mfma_small_kernel<KA, KB, VW, true, 4>), dim3(grid), dim3(256), 0, st, p);

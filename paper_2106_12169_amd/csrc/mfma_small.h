@@ -9,9 +9,9 @@
 // row that its matrix-instruction steps consume: piece (row lr, words 4i..4i+3)
 // is needed by exactly one lane of the block, nothing is loaded twice and there
 // is no barrier before the arithmetic.  All loads of up to GMAX groups of four
-// steps are issued before the first of them is used.  With NSPLIT = 4 the four
+// steps are issued before the first of them is used.  With NSPLIT = 4 or 8 the
 // waves of a block share one 32 x 32 tile and split its steps (layers with a long
-// K and few tiles); with NSPLIT = 1 every wave owns its own tile (layers with a
+// K and few tiles; the first four add up and finish it); with NSPLIT = 1 every wave owns its own tile (layers with a
 // short K and many tiles).  Arithmetic, operand encodings, digit passes and the
 // epilogue are those of mfma_fp4_kernel.
 //
@@ -32,7 +32,7 @@ __device__ __forceinline__ void mfma_small_body(const MfmaParams &p, const int b
     // with it the number of blocks a compute unit holds at once: 2 for layers with a short K and many blocks
     // (six waves per SIMD), 5 for a long K.
     constexpr int LA = DigitPlanes<KA>::value, LB = DigitPlanes<KB>::value;
-    constexpr int RPW = 16 / NSPLIT;                    // accumulator registers a wave finishes in the epilogue
+    constexpr int RPW = NSPLIT > 4 ? 4 : 16 / NSPLIT;   // accumulator registers a wave finishes in the epilogue (of eight waves: four finish)
 
     __shared__ float sRed[NSPLIT > 1 ? NSPLIT : 1][NSPLIT > 1 ? 16 : 1][64];
 
@@ -101,7 +101,7 @@ __device__ __forceinline__ void mfma_small_body(const MfmaParams &p, const int b
     uint32_t pre_res[NG];
 #pragma unroll
     for (int g = 0; g < NG; ++g)
-        pre_res[g] = (live && !p.pool) ? load_res_rows8(p, m0 + 8 * (NSPLIT > 1 ? ks : g), gn >> 5, lane) : 0u;
+        pre_res[g] = (live && !p.pool && (NSPLIT <= 4 || ks < 4)) ? load_res_rows8(p, m0 + 8 * (NSPLIT > 1 ? ks : g), gn >> 5, lane) : 0u;
 
     // Digit pairs (da, db) and the groups of four steps of each are walked as one
     // flat sequence, GMAX entries at a time with all their loads in flight together,
@@ -208,6 +208,7 @@ __device__ __forceinline__ void mfma_small_body(const MfmaParams &p, const int b
 #pragma unroll
         for (int r = 0; r < 16; ++r) sRed[ks][r][lane] = acc[r];
         __syncthreads();
+        if (NSPLIT > 4 && ks >= 4) return;
         if (p.pool) {                           // RPW = 4: this wave's share of the tile is one pooling grid per lane
             static_assert(NSPLIT == 1 || RPW == 4, "a K-split wave finishes whole pooling grids");
             float v4[4];
@@ -233,7 +234,7 @@ __device__ __forceinline__ void mfma_small_body(const MfmaParams &p, const int b
 }
 
 template <int KA, int KB, int VW, bool CONV, int NSPLIT, int GMAX = 5>
-__global__ __launch_bounds__(256) void mfma_small_kernel(const MfmaParams p)
+__global__ __launch_bounds__(NSPLIT == 8 ? 512 : 256) void mfma_small_kernel(const MfmaParams p)
 {
     mfma_small_body<KA, KB, VW, CONV, NSPLIT, GMAX>(p, blockIdx.x);
 }

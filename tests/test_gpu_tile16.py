@@ -1,6 +1,6 @@
 """mfma_tile16_kernel (products and convolutions with few outputs) against the oracle: edges of its 16 x 16 tiles, lengths of K either side of
 its groups of 512 positions and of the groups that its four or eight waves share, every kind of operand, the whole epilogue,
-and the sizes around the rule that takes it.  All results are whole numbers, or floats of one rounding: compared exactly."""
+and the sizes around the rule that takes it; for convolutions also the 32 x 32 tile whose K is split over eight waves.  All results are whole numbers, or floats of one rounding: compared exactly."""
 import numpy as np
 import pytest
 import torch
@@ -20,7 +20,10 @@ def dev(a):
 
 def _run(force, call):
     B.apnn_debug_reset()
-    B.apnn_debug_force("MFMA_T16", force)
+    if force == "32x8":                 # the 32 x 32 tile with K split over eight waves
+        B.apnn_debug_force("MFMA_NSPLIT", 8)
+    else:
+        B.apnn_debug_force("MFMA_T16", force)
     B.apnn_debug_force("INT8", 0)
     try:
         out = call()
@@ -80,7 +83,7 @@ CONVS = [
 ]
 
 
-@pytest.mark.parametrize("force", [-1, 4, 8])
+@pytest.mark.parametrize("force", [-1, 4, 8, "32x8"])
 @pytest.mark.parametrize("BS,Cin,Cout,H,W,R,stride,pad,encW,p,encX,q,q_out,q_res,pool", CONVS)
 def test_conv(force, BS, Cin, Cout, H, W, R, stride, pad, encW, p, encX, q, q_out, q_res, pool):
     Wv = wl.operand(102 + Cin, Cout, Cin * R * R, p, encW).reshape(Cout, Cin, R, R)
