@@ -10,11 +10,12 @@ template <int KA, int HW, int SW, int FP, int FW, int PT, bool POOL, bool MULTI,
 bool launch_conv_halo(const ConvHaloParams &p, unsigned grid, int lds, hipStream_t st)
 {
     const auto kernel = conv_halo_kernel<KA, HW, SW, FP, FW, PT, POOL, MULTI, STAY>;
-    static std::atomic<int> granted{0};                  // most dynamic LDS asked for so far (per instance)
-    if (lds > granted.load(std::memory_order_relaxed)) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
+    // all of a compute unit's LDS, once per instance: two threads that come here together ask for the same
+    static std::atomic<bool> granted{false};
+    if (!granted.load(std::memory_order_relaxed)) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
             return false;
-        granted.store(lds, std::memory_order_relaxed);
+        granted.store(true, std::memory_order_relaxed);
     }
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), lds, st, p);
     return true;

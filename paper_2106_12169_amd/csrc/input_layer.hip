@@ -283,11 +283,12 @@ static int64_t input_row_bytes(int64_t Cin, int R, int S) { return round_up(Cin 
 template <int NT, int SEG, int COPIES> static bool launch_input_tile(const InputTileParams &p, unsigned grid, int lds, hipStream_t st)
 {
     const auto kernel = input_tile_kernel<NT, SEG, COPIES>;
-    static std::atomic<int> granted{0};                  // most dynamic LDS asked for so far (per instance)
-    if (lds > granted.load(std::memory_order_relaxed)) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
+    // all of a compute unit's LDS, once per instance: two threads that come here together ask for the same
+    static std::atomic<bool> granted{false};
+    if (!granted.load(std::memory_order_relaxed)) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
             return false;
-        granted.store(lds, std::memory_order_relaxed);
+        granted.store(true, std::memory_order_relaxed);
     }
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(512), lds, st, p);
     return true;

@@ -228,11 +228,12 @@ static bool try_mfma(const Problem &pr, MfmaParams &mp, void *stream, int &rc, S
     // 8-word chunks: no step multiplies padding (override 0: no special case for short K)
     const bool short_k = !pr.conv && mp.Kw <= 8 && t <= 64 && ov(OV_MFMA_SHORTK) != 0;
     if (short_k) t = 64;
-    // Few outputs: 16 x 16 tiles bring four times the blocks, at twice the operand expansion per output.  They are
-    // ahead up to two tiles per compute unit (128 x 1000, K = 4096, w1a2: 512 tiles, 4.7 against 5.3 us; 256 x 1000: 6.0
-    // against 5.5; 3 x 3 convolution, 512 channels at 7 x 7: 4 images 5.9 against 6.3, 8 images 7.2 against 6.3), up to four where K is short and the other form is the 64 x 64 tile (512 x 512, K = 128: 3.6 against 4.2;
-    // 1024 x 1024: 6.4 against 4.6), and at every count where a 32 x 32 tile would be half empty (1 x 32000, K = 4096: 7.9
-    // against 9.6).  Override MFMA_T16: 0 never, 4 or 8 the form with that many waves wherever it applies.
+    // Few outputs: 16 x 16 tiles bring four times the blocks, at twice the operand expansion per output.  They are ahead up to
+    // two tiles per compute unit (128 x 1000, K = 4096, w1a2: 512 tiles, 4.7 against 5.3 us; 256 x 1000: 6.0 against 5.5; 3 x 3
+    // convolution, 512 channels at 7 x 7: 4 images 5.9 against 6.3, 8 images 7.2 against 6.3), up to four where K is short and
+    // the other form is the 64 x 64 tile (512 x 512, K = 128: 3.6 against 4.2; 1024 x 1024: 6.4 against 4.6), and at every
+    // count where a 32 x 32 tile would be half empty (1 x 32000, K = 4096: 7.9 against 9.6).  Override MFMA_T16: 0 never, 4 or
+    // 8 the form with that many waves wherever it applies.
     const int t16 = ov(OV_MFMA_T16);
     const int64_t tiles16 = ceil_div(pr.M, 16) * ceil_div(pr.N, 16);
     const bool few = (t == 32 || short_k) && (tiles16 <= (short_k ? 1024 : 512) || pr.M <= 16 || pr.N <= 16) && !other &&
