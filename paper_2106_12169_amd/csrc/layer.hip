@@ -244,9 +244,9 @@ static bool try_mfma(const Problem &pr, MfmaParams &mp, void *stream, int &rc, S
         // chip (196 x 512, K = 4608: 6.2 against 5.9) and never beyond (1 x 32000, K = 4096, w2a4: 18.0 against 14.4)
         const int64_t groups = ceil_div(mp.Kw, 16);
         const int vw = !pr.conv ? 0 : mp.Cw % 4 == 0 ? 4 : odd_words ? 1 : 2;
-        const int waves = t16 > 0 ? t16 : groups * mp.DA * mp.DB >= (tiles16 <= 256 ? 9 : 12) && tiles16 <= 512 ? 8 : 4;
+        mp.nk = t16 > 0 ? (t16 == 4 ? 4 : 8) : groups * mp.DA * mp.DB >= (tiles16 <= 256 ? 9 : 12) && tiles16 <= 512 ? 8 : 4;
         mp.c0 = (kA == OPK_PM1 && kB == OPK_PM1) ? -static_cast<int>(groups * 512 - pr.Ktotal) : 0;
-        if (launch_mfma_tile16(mp, kA, kB, vw, waves, static_cast<unsigned>(tiles16), as_stream(stream))) {
+        if (launch_mfma_tile16(mp, kA, kB, vw, static_cast<unsigned>(tiles16), as_stream(stream))) {
             rc = check_launch(pr.who);
             return true;
         }

@@ -67,7 +67,7 @@ struct MfmaParams {
     int DA, DB;              // base-4 digits (ceil(planes / 2); 1 for single-plane kinds)
     int ldwA, ldwB;          // words per plane row (A: matrix mode only)
     int Kw;                  // words per plane along K
-    int nk;                  // K chunks of KC words
+    int nk;                  // K chunks of KC words (mfma_tile16_kernel: waves of a block)
     int c0;                  // additive correction (pad positions of a -1/+1 x -1/+1 product)
     float out_scale;         // 2^(number of two-plane operands): those enter the matrix unit as value / 2
     // convolution geometry of the A operand (conv mode only)

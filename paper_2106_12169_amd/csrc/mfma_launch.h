@@ -26,8 +26,8 @@ bool launch_mfma_small_conv_pair(const MfmaParams &p0, unsigned grid0, const Mfm
                                  int kindB, int vw, int gmax, hipStream_t st);
 bool launch_mfma_small_matrix(const MfmaParams &p, int kindA, int kindB, int nsplit, unsigned grid, hipStream_t st);
 
-// 16 x 16 tiles, K split over the 4 or 8 waves of a block; grid = tiles; vw: 0 matrices, else as above.  (weak: as launch_conv_halo)
-__attribute__((weak)) bool launch_mfma_tile16(const MfmaParams &p, int kindA, int kindB, int vw, int waves, unsigned grid, hipStream_t st);
+// 16 x 16 tiles, K split over the p.nk = 4 or 8 waves of a block; grid = tiles; vw: 0 matrices, else as above.  (weak: as launch_conv_halo)
+__attribute__((weak)) bool launch_mfma_tile16(const MfmaParams &p, int kindA, int kindB, int vw, unsigned grid, hipStream_t st);
 
 // Convolutions with the input pixels staged once per block (conv_halo.h).  force: -1 the rule, else
 // wherever it applies.  Returns false if the layer is not one for it.

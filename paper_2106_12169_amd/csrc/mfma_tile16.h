@@ -9,6 +9,9 @@
 // this after (us): 8 x 4096, K = 25088 16.9, 7.5; K = 9216 7.1, 4.9; K = 4096 5.0, 3.9; 64 x 1024, K = 1024 4.0, 3.3;
 // 128 x 128, K = 128 (64 x 64 tile before) 4.1, 3.2.  Convolutions: 7 x 7 of 512 channels to 8 x 1 x 1 x 4096 16.5, 8.8;
 // 3 x 3, 384 -> 256 channels at 13 x 13 5.9, 4.4.
+// Four and eight waves are one kernel, two groups in flight: a network's first pass fetches every instance's code from memory, and
+// a second one for eight waves (four groups in flight) made that of the AlexNet shape at batch 1 5 to 10 us longer without
+// being faster after it (46.1 us either way).
 #pragma once
 #include "mfma_kernel.h"
 
@@ -19,13 +22,13 @@ typedef float v4f_t __attribute__((ext_vector_type(4)));
 // Block = one 16 x 16 tile of outputs.  A step is one 16 x 16 x 128 matrix instruction: lane group g = lane / 16
 // supplies 32 consecutive K positions (one plane word) of row / column lane % 16.  K is walked in groups of four
 // steps = 16 words, of which lane group g loads words 4 g .. 4 g + 3 (one 16-byte load per plane, 64 consecutive
-// bytes per row of a matrix); wave w takes groups w, w + NSPLIT, ...  Words at and beyond Kw read as zero.
-template <int KA, int KB, int VW, bool CONV, int NSPLIT, int GMAX>
-__global__ __launch_bounds__(64 * NSPLIT) void mfma_tile16_kernel(const MfmaParams p)
+// bytes per row of a matrix); wave w takes groups w, w + waves, ...
+// (p.nk: the waves of a block, four or eight)  Words at and beyond Kw read as zero.
+template <int KA, int KB, int VW, bool CONV, int GMAX>
+__global__ __launch_bounds__(512) void mfma_tile16_kernel(const MfmaParams p)
 {
     constexpr int LA = DigitPlanes<KA>::value, LB = DigitPlanes<KB>::value;
-    static_assert(NSPLIT >= 4, "wave w < 4 finishes accumulator register w");
-    __shared__ float sRed[NSPLIT][4][64];
+    __shared__ float sRed[8][4][64];                    // wave w < 4 finishes accumulator register w
 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lr = lane & 15, lg = lane >> 4;
@@ -51,7 +54,8 @@ __global__ __launch_bounds__(64 * NSPLIT) void mfma_tile16_kernel(const MfmaPara
     km.m4 = reg_const(0x44444444u); km.m8 = reg_const(0x88888888u);
 
     const int GT = (p.Kw + 15) / 16;
-    const int G = wave < GT ? (GT - wave + NSPLIT - 1) / NSPLIT : 0;    // groups of this wave
+    const int waves = p.nk, log_waves = waves == 8 ? 3 : 2;
+    const int G = wave < GT ? (GT - wave + waves - 1) >> log_waves : 0;    // groups of this wave
 
     auto load_a = [&](int plane, int kk) -> uint4 {
         const bool validity = KA == OPK_PM1Z && plane == 1;     // all ones for taps inside the frame, made up here
@@ -92,7 +96,7 @@ __global__ __launch_bounds__(64 * NSPLIT) void mfma_tile16_kernel(const MfmaPara
         int sa[GMAX], sb[GMAX];
 #pragma unroll
         for (int g = 0; g < GMAX; ++g) {
-            const int kk = e0 + g < total ? 16 * (wave + NSPLIT * grp) + 4 * lg : p.Kw;
+            const int kk = e0 + g < total ? 16 * (wave + (grp << log_waves)) + 4 * lg : p.Kw;
             sa[g] = 0x7f7f7f7f + 0x02020202 * da;
             sb[g] = 0x7f7f7f7f + 0x02020202 * db;
 #pragma unroll
@@ -131,13 +135,16 @@ __global__ __launch_bounds__(64 * NSPLIT) void mfma_tile16_kernel(const MfmaPara
     if (wave >= 4 || (p.pool && wave > 0)) return;
     float v = 0.0f;                                     // register `wave` of the tile: row 4 lg + wave, column lr
 #pragma unroll
-    for (int k = 0; k < NSPLIT; ++k) v += sRed[k][wave][lane];
+    for (int k = 0; k < 4; ++k) v += sRed[k][wave][lane];
+    if (waves == 8) {
+#pragma unroll
+        for (int k = 4; k < 8; ++k) v += sRed[k][wave][lane];
+    }
     int gm = m0 + 4 * lg + wave, M = p.M, c0 = p.c0;
     if constexpr (CONV) {
         if (p.pool) {                                   // the four registers of a lane are one pooling grid
             float o[3] = {0.0f, 0.0f, 0.0f};
-#pragma unroll
-            for (int k = 0; k < NSPLIT; ++k)
+            for (int k = 0; k < waves; ++k)
 #pragma unroll
                 for (int r = 0; r < 3; ++r) o[r] += sRed[k][r + 1][lane];
             v = pool4(p.pool, v, o[0], o[1], o[2]);
