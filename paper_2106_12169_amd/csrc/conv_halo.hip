@@ -39,13 +39,15 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
     if (force < 0 && !worth_staging(mp, tilesN)) return false;
     const int64_t Hq = mp.H + 2 * static_cast<int64_t>(mp.pad), Wq = mp.W + 2 * static_cast<int64_t>(mp.pad);
     const int64_t Kw = static_cast<int64_t>(mp.R) * mp.S * mp.Cw, lim = int64_t(1) << 31;
-    if ((images + 1) * Hq * Wq >= lim || 4 * images * mp.H * mp.W * mp.PA * mp.Cw >= lim || 4 * mp.N * mp.PB * Kw >= lim) return false;
+    // (in 64 bits from the first factor on: four times the channels alone can pass 2^31)
+    const int64_t bytesA = 4 * images * mp.H * mp.W * mp.PA * mp.Cw, bytesB = 4 * Kw * mp.PB * mp.N;
+    if ((images + 1) * Hq * Wq >= lim || bytesA >= lim || bytesB >= lim) return false;
     if (mp.M > lim - 1024) return false;
 
     ConvHaloParams p{};
     p.A = mp.A; p.B = mp.B;
-    p.bytesA = static_cast<uint32_t>(4 * images * mp.H * mp.W * mp.PA * mp.Cw);
-    p.bytesB = static_cast<uint32_t>(4 * mp.N * mp.PB * Kw);
+    p.bytesA = static_cast<uint32_t>(bytesA);
+    p.bytesB = static_cast<uint32_t>(bytesB);
     p.M = mp.M; p.N = mp.N;
     p.images = static_cast<int>(images); p.H = mp.H; p.W = mp.W;
     p.Hq = static_cast<int>(Hq); p.Wq = static_cast<int>(Wq);

@@ -1,0 +1,79 @@
+// launch_conv_halo (conv_halo.hip), the host side of the staged convolutions, under -fsanitize=address,undefined: which layers
+// it takes and the layout it asks for.  The launchers of the kernel's instances are the stand-ins below.
+#include <cstdint>
+#include <cstdio>
+
+#include "../../paper_2106_12169_amd/csrc/conv_halo_launch.h"
+
+namespace apnn {
+static ConvHaloParams g_p;
+static bool g_stay;
+static int g_fp, g_lds, g_kind;
+static unsigned g_grid;
+static bool took(int kind, const ConvHaloParams &p, bool stay, int fp, unsigned grid, int lds)
+{
+    g_kind = kind; g_p = p; g_stay = stay; g_fp = fp; g_grid = grid; g_lds = lds;
+    return true;
+}
+bool launch_conv_halo_u1(const ConvHaloParams &p, bool stay, int fp, unsigned grid, int lds, hipStream_t) { return took(OPK_U1, p, stay, fp, grid, lds); }
+bool launch_conv_halo_u2(const ConvHaloParams &p, bool stay, int fp, unsigned grid, int lds, hipStream_t) { return took(OPK_U2, p, stay, fp, grid, lds); }
+bool launch_conv_halo_pm1(const ConvHaloParams &p, bool stay, int fp, unsigned grid, int lds, hipStream_t) { return took(OPK_PM1Z, p, stay, fp, grid, lds); }
+bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB, int force, hipStream_t st);
+}  // namespace apnn
+
+using namespace apnn;
+
+static int failures = 0;
+#define EXPECT(cond) do { if (!(cond)) { std::printf("line %d: %s\n", __LINE__, #cond); ++failures; } } while (0)
+
+struct Layer {
+    int64_t images, H, W, Cin, Cout;
+    int R, S, stride, pad;
+    bool pm1_weights;
+    int p;
+    bool pm1_features;
+    int q;
+    int pool = 0;
+    bool ints = false;
+};
+
+// as apnn_layer's dispatch fills the parameters in
+static bool staged(const Layer &l, int force)
+{
+    MfmaParams mp{};
+    const int64_t Ho = (l.H + 2 * int64_t(l.pad) - l.R) / l.stride + 1, Wo = (l.W + 2 * int64_t(l.pad) - l.S) / l.stride + 1;
+    mp.H = static_cast<int>(l.H); mp.W = static_cast<int>(l.W); mp.Ho = static_cast<int>(Ho); mp.Wo = static_cast<int>(Wo);
+    mp.Hp = mp.Ho / 2; mp.Wp = mp.Wo / 2;
+    mp.M = static_cast<int>(l.pool ? l.images * mp.Hp * mp.Wp * 4 : l.images * Ho * Wo);
+    mp.N = static_cast<int>(l.Cout); mp.NW = mp.N / 32;
+    mp.R = l.R; mp.S = l.S; mp.stride = l.stride; mp.pad = l.pad; mp.pool = l.pool;
+    mp.Cw = static_cast<int>(l.Cin / 32); mp.Kw = mp.Cw * l.R * l.S;
+    mp.PA = l.q; mp.PB = l.p;
+    mp.DA = (l.q + 1) / 2; mp.DB = (l.p + 1) / 2;
+    alignas(16) static uint32_t there[4];                        // (addresses are passed on, never followed)
+    if (l.ints) {
+        mp.Y = reinterpret_cast<int32_t *>(there);
+    } else {
+        mp.out = there; mp.q_out = 2;
+        mp.scale = mp.bias = reinterpret_cast<const float *>(there);
+    }
+    g_kind = -1;
+    return launch_conv_halo(mp, l.images, l.pm1_features ? OPK_PM1Z : l.q == 1 ? OPK_U1 : OPK_U2,
+                            l.pm1_weights ? OPK_PM1 : l.p == 1 ? OPK_U1 : OPK_U2, force, nullptr);
+}
+
+int main()
+{
+    // weights of 2^31 bytes and more are not for 31-bit offsets, whatever their size is modulo 2^32
+    const int64_t most = (int64_t(1) << 31) / 8 - 64;            // channels of one 64-channel plane: 8 bytes each
+    EXPECT(staged({1, 8, 8, 64, most, 1, 1, 1, 0, true, 1, false, 2}, 1) && g_p.bytesB == 8u * static_cast<uint32_t>(most));
+    for (int64_t channels : {most + 64, int64_t(1) << 29, (int64_t(1) << 29) + 64, int64_t(1) << 30})
+        EXPECT(!staged({1, 8, 8, 64, channels, 1, 1, 1, 0, true, 1, false, 2}, 1));
+    EXPECT(!staged({1, 8, 8, 64, int64_t(1) << 26, 1, 1, 1, 0, false, 8, false, 2}, 1));      // 4 GiB: 0 in 32 bits
+    EXPECT(!staged({1, 8, 8, 64, int64_t(1) << 27, 1, 1, 1, 0, false, 4, false, 2}, 1));
+    EXPECT(!staged({1, 8, 8, 64, int64_t(1) << 28, 1, 1, 1, 0, false, 2, false, 2}, 1));
+    EXPECT(!staged({1, 8, 8, 32, 536870848, 1, 1, 1, 0, false, 3, false, 2}, 1));             // 6442450176: 2147482880
+
+    if (failures == 0) std::puts("staged convolution sanitizer run ok");
+    return failures != 0;
+}

@@ -28,14 +28,12 @@ def test_oracle_under_sanitizers(tmp_path):
     assert "oracle sanitizer run ok" in _run([exe])
 
 
-@pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
-def test_abi_host_side_under_sanitizers(tmp_path):
-    # the sanitizer flags go to the host pass only (each directly after -Xarch_host)
+def _host_program(tmp_path, name, units):
+    """The host side of `units` with sanitizers, linked to a program: the flags go to the host pass only (each directly
+    after -Xarch_host)."""
     host_san = [x for f in SAN for x in ("-Xarch_host", f)]
     common = ["hipcc", "--offload-arch=gfx950", "-O1", "-g", "-std=c++17", "-fno-omit-frame-pointer",
               "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-ffp-contract=off"]
-    units = [os.path.join(CSRC, n) for n in ("layer.hip", "pack.hip", "pool.hip", "input_layer.hip", "common.cpp")]
-    units.append(os.path.join(ROOT, "tests", "sanitize", "abi_host_driver.cpp"))
 
     def compile_one(src):
         obj = str(tmp_path / (os.path.splitext(os.path.basename(src))[0] + ".o"))
@@ -44,6 +42,19 @@ def test_abi_host_side_under_sanitizers(tmp_path):
 
     with ThreadPoolExecutor(max_workers=6) as ex:
         objs = list(ex.map(compile_one, units))
-    exe = str(tmp_path / "abi_san")
+    exe = str(tmp_path / name)
     _run(["hipcc", "--offload-arch=gfx950", *SAN, *objs, "-o", exe])
-    assert "abi host sanitizer run ok" in _run([exe])
+    return exe
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
+def test_abi_host_side_under_sanitizers(tmp_path):
+    units = [os.path.join(CSRC, n) for n in ("layer.hip", "pack.hip", "pool.hip", "input_layer.hip", "common.cpp")]
+    units.append(os.path.join(ROOT, "tests", "sanitize", "abi_host_driver.cpp"))
+    assert "abi host sanitizer run ok" in _run([_host_program(tmp_path, "abi_san", units)])
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
+def test_staged_convolution_layout_under_sanitizers(tmp_path):
+    units = [os.path.join(CSRC, "conv_halo.hip"), os.path.join(ROOT, "tests", "sanitize", "conv_halo_driver.cpp")]
+    assert "staged convolution sanitizer run ok" in _run([_host_program(tmp_path, "halo_san", units)])
