@@ -41,7 +41,7 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
     const int64_t Kw = static_cast<int64_t>(mp.R) * mp.S * mp.Cw, lim = int64_t(1) << 31;
     // (in 64 bits from the first factor on: four times the channels alone can pass 2^31)
     const int64_t bytesA = 4 * images * mp.H * mp.W * mp.PA * mp.Cw, bytesB = 4 * Kw * mp.PB * mp.N;
-    if ((images + 1) * Hq * Wq >= lim || bytesA >= lim || bytesB >= lim) return false;
+    if (Hq >= lim || Wq >= lim || Hq * Wq > (lim - 1) / (images + 1) || bytesA >= lim || bytesB >= lim) return false;
     if (mp.M > lim - 1024) return false;
 
     ConvHaloParams p{};
@@ -88,10 +88,11 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
         const int64_t pixels = fp == 3 ? 256 : 128 * fp;
         t.tilesM = ceil_div(mp.M, pixels);
         // the longest range of padded positions a tile touches: row steps and image steps between its first and last pixel
-        const int64_t px = mp.pool ? pixels / 4 : pixels, step = mp.pool ? 2 * mp.stride : mp.stride;
+        // (the stride of a single row is beyond its image: there the image step counts)
+        const int64_t px = mp.pool ? pixels / 4 : pixels, step = mp.pool ? 2 * mp.stride : mp.stride < Hq ? mp.stride : Hq;
         const int64_t new_rows = (px - 1 + cols - 1) / cols, new_images = (px - 1 + rows * cols - 1) / (rows * cols);
         const int64_t between = Hq - rows * step;          // lines an image has beyond its rows' steps
-        const int64_t reach = new_rows * step * Wq + (cols - 1) * step + new_images * (between > 0 ? between : 0) * Wq +
+        const int64_t reach = new_rows * step * Wq + (cols - 1) * (mp.pool ? 2 : 1) * mp.stride + new_images * (between > 0 ? between : 0) * Wq +
                               (mp.pool ? mp.stride * (Wq + 1) : 0) + (mp.R - 1) * Wq + mp.S;
         t.records = (reach < images * Hq * Wq ? reach : images * Hq * Wq) * p.rec;
         const int64_t most = fp == 4 ? 2 : fp == 1 ? 4 : 3;    // by registers: waves a SIMD holds

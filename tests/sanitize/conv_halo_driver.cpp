@@ -74,6 +74,13 @@ int main()
     EXPECT(!staged({1, 8, 8, 64, int64_t(1) << 28, 1, 1, 1, 0, false, 2, false, 2}, 1));
     EXPECT(!staged({1, 8, 8, 32, 536870848, 1, 1, 1, 0, false, 3, false, 2}, 1));             // 6442450176: 2147482880
 
+    // frames and strides near 2^30, of which few outputs are left: no size of them wraps
+    EXPECT(!staged({8, 8, 8, 64, 64, 3, 3, 1 << 29, 1 << 29, true, 1, false, 2}, 1));          // 9 * 2^60 positions
+    EXPECT(!staged({100, 1, 1, 64, 64, 1, 1, 1 << 29, 536870911, true, 1, false, 2}, 1));
+    EXPECT(!staged({1, 1, 1 << 28, 32, 64, 1, 1, 2147483647, 0, true, 1, false, 1}, 1));       // 127 strides of 2^28 positions
+    EXPECT(!staged({3, 1, 1 << 20, 32, 64, 1, 1, 2147483647, 0, true, 1, false, 1}, 1));
+    EXPECT(staged({300, 1, 1, 32, 64, 1, 1, 2147483647, 0, true, 1, false, 1}, 1) && g_p.words_records == 128 * g_p.rec);
+
     if (failures == 0) std::puts("staged convolution sanitizer run ok");
     return failures != 0;
 }
