@@ -64,8 +64,8 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
     p.scale = mp.scale; p.bias = mp.bias; p.res = mp.res; p.q_res = mp.q_res; p.res_scale = mp.res_scale;
     p.out = mp.out; p.q_out = mp.q_out; p.NW = mp.NW; p.Y = mp.Y;
     // a two-plane digit enters as half its value; planes are made of a quarter of the result
-    p.scaleA = 0x01010101 * (0x7f + (kindA == OPK_U2 ? 1 : 0) - (planes ? 2 : 0));
-    p.scaleB = 0x01010101 * (0x7f + (kindB == OPK_PM1 ? 0 : 1));
+    p.scaleA = static_cast<int>(0x01010101u * (0x7fu + (kindA == OPK_U2 ? 1u : 0u) - (planes ? 2u : 0u)));
+    p.scaleB = static_cast<int>(0x01010101u * (0x7fu + (kindB == OPK_PM1 ? 0u : 1u)));
 
     // steps read together, words staged together (as the launcher instantiates them)
     const int hw = p.Cw % 4 == 0 ? 2 : 1, sw = p.Cw % 4 == 0 ? 4 : p.Cw % 2 == 0 ? 2 : 1, granule = (kindA == OPK_U1 ? 1 : 2) * hw;

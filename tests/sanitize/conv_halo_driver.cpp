@@ -81,6 +81,12 @@ int main()
     EXPECT(!staged({3, 1, 1 << 20, 32, 64, 1, 1, 2147483647, 0, true, 1, false, 1}, 1));
     EXPECT(staged({300, 1, 1, 32, 64, 1, 1, 2147483647, 0, true, 1, false, 1}, 1) && g_p.words_records == 128 * g_p.rec);
 
+    // block scales: biased exponents in every byte, those of 0/1 weights and of int32 results from 2^7 up
+    EXPECT(staged({1, 8, 8, 64, 64, 3, 3, 1, 1, true, 1, false, 2}, 1) && g_p.scaleA == 0x7e7e7e7e && g_p.scaleB == 0x7f7f7f7f);
+    EXPECT(staged({4, 27, 31, 96, 160, 3, 3, 1, 1, false, 2, false, 4, 0, true}, 1));
+    EXPECT(static_cast<uint32_t>(g_p.scaleA) == 0x80808080u && static_cast<uint32_t>(g_p.scaleB) == 0x80808080u);
+    EXPECT(staged({1, 8, 8, 64, 64, 3, 3, 1, 1, false, 1, true, 1}, 1) && g_p.scaleA == 0x7d7d7d7d && static_cast<uint32_t>(g_p.scaleB) == 0x80808080u);
+
     if (failures == 0) std::puts("staged convolution sanitizer run ok");
     return failures != 0;
 }
