@@ -213,7 +213,7 @@ static bool try_mfma(const Problem &pr, MfmaParams &mp, void *stream, int &rc, S
     // (another form asked for by an override stays what it is)
     const bool other = ov(OV_MFMA_TILE) >= 0 || ov(OV_MFMA_SMALL) >= 0 || ov(OV_MFMA_NSPLIT) >= 0 || ov(OV_MFMA_FN) >= 0;
     const int halo = ov(OV_MFMA_HALO);
-    if (pr.conv && !plan && halo != 0 && (halo > 0 || !other) && launch_conv_halo &&
+    if (pr.conv && !plan && halo != 0 && (halo > 0 || !other) &&
         launch_conv_halo(mp, pr.images, kA, kB, halo, as_stream(stream))) {
         rc = check_launch(pr.who);
         return true;
@@ -238,7 +238,7 @@ static bool try_mfma(const Problem &pr, MfmaParams &mp, void *stream, int &rc, S
     const int64_t tiles16 = ceil_div(pr.M, 16) * ceil_div(pr.N, 16);
     const bool few = (t == 32 || short_k) && (tiles16 <= (short_k ? 1024 : 512) || pr.M <= 16 || pr.N <= 16) && !other &&
                      ov(OV_MFMA_SHORTK) < 0;
-    if (!plan && tiles16 <= kMaxBlocks / 2 && launch_mfma_tile16 && (t16 < 0 ? few : t16 > 0)) {
+    if (!plan && tiles16 <= kMaxBlocks / 2 && (t16 < 0 ? few : t16 > 0)) {
         // eight waves from about three groups of 512 K positions a wave (8 x 4096 outputs, w1a2: K = 9216 4.9 against 5.3
         // us with four, K = 4096 4.0 against 3.9; 98 x 512, K = 4608 5.0 against 5.2), later where the blocks fill the
         // chip (196 x 512, K = 4608: 6.2 against 5.9) and never beyond (1 x 32000, K = 4096, w2a4: 18.0 against 14.4)

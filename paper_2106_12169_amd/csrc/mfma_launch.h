@@ -26,19 +26,19 @@ bool launch_mfma_small_conv_pair(const MfmaParams &p0, unsigned grid0, const Mfm
                                  int kindB, int vw, int gmax, hipStream_t st);
 bool launch_mfma_small_matrix(const MfmaParams &p, int kindA, int kindB, int nsplit, unsigned grid, hipStream_t st);
 
-// 16 x 16 tiles, K split over the p.nk = 4 or 8 waves of a block; grid = tiles; vw: 0 matrices, else as above.  (weak: as launch_conv_halo)
-__attribute__((weak)) bool launch_mfma_tile16(const MfmaParams &p, int kindA, int kindB, int vw, unsigned grid, hipStream_t st);
+// 16 x 16 tiles, K split over the p.nk = 4 or 8 waves of a block; grid = tiles; vw: 0 matrices, else as above.
+bool launch_mfma_tile16(const MfmaParams &p, int kindA, int kindB, int vw, unsigned grid, hipStream_t st);
 
 // Convolutions with the input pixels staged once per block (conv_halo.h).  force: -1 the rule, else
 // wherever it applies.  Returns false if the layer is not one for it.
-// (weak: a program that links the dispatch without this kernel's units has none)
-__attribute__((weak)) bool launch_conv_halo(const MfmaParams &p, int64_t images, int kindA, int kindB, int force, hipStream_t st);
+bool launch_conv_halo(const MfmaParams &p, int64_t images, int kindA, int kindB, int force, hipStream_t st);
 
 // 8-bit integer matrix form (matrix operands, 128 x 128 block tile); class: 0, 1, 2 for up to 2, 4, 8 planes.
 bool launch_mfma_i8(const MfmaParams &p, int classA, int classB, unsigned grid, hipStream_t st);
 // The same with K, not the outputs, shared out among the four waves of a block (up to 10 planes in all, not both
 // operands above four); false if there is no such instance.
 bool launch_mfma_i8_wide(const MfmaParams &p, int classA, int classB, unsigned grid, hipStream_t st);
+
 // K words per chunk of each tile size (must match the instances).
 constexpr int mfma_chunk_words(int tile) { return tile == 256 ? 16 : tile == 128 ? 16 : 32; }
 

@@ -1,6 +1,6 @@
 // Host side of the C-ABI library under -fsanitize=address,undefined: size helpers, the batch-norm fold, the
 // override table, the tile choice, every argument check, and the dispatch itself.  The sources with the host logic
-// (layer.hip, pack.hip, pool.hip, input_layer.hip, common.cpp) are linked with the stand-ins below in place of the
+// (layer.hip, pack.hip, pool.hip, input_layer.hip, conv_halo.hip, common.cpp) are linked with the stand-ins below in place of the
 // kernel-instance launchers, which record what the dispatch asked for and launch nothing; so the whole decision path
 // of apnn_gemm / apnn_layer runs without a GPU and its constants can be checked.  Device pointers are fakes that host
 // code never dereferences.
@@ -12,6 +12,7 @@
 
 #include "../../include/apnn.h"
 #include "../../include/apnn_debug.h"
+#include "../../paper_2106_12169_amd/csrc/conv_halo_launch.h"
 #include "../../paper_2106_12169_amd/csrc/mfma_launch.h"
 #include "../../paper_2106_12169_amd/csrc/tile_launch.h"
 
@@ -21,6 +22,9 @@ static apnn::MfmaParams g_mp;
 static apnn::TileParams g_tp;
 static unsigned g_grid;
 static int g_pmz;
+static apnn::ConvHaloParams g_halo;
+static int g_fp;                      // its pixel tiles
+static bool g_stay;                   // ... and whether its weights stay in LDS
 
 namespace apnn {
 static bool took(const char *name, const MfmaParams &p, unsigned grid) { g_kernel = name; g_mp = p; g_grid = grid; return true; }
@@ -38,6 +42,15 @@ bool launch_mfma_small_conv_pair(const MfmaParams &p0, unsigned grid0, const Mfm
 bool launch_mfma_small_matrix(const MfmaParams &p, int, int, int, unsigned grid, hipStream_t) { return took("small_matrix", p, grid); }
 bool launch_mfma_i8(const MfmaParams &p, int, int, unsigned grid, hipStream_t) { return took("i8", p, grid); }
 bool launch_mfma_i8_wide(const MfmaParams &p, int, int, unsigned grid, hipStream_t) { return took("i8_wide", p, grid); }
+bool launch_mfma_tile16(const MfmaParams &p, int, int, int, unsigned grid, hipStream_t) { return took("tile16", p, grid); }
+static bool took_halo(const ConvHaloParams &p, bool stay, int fp, unsigned grid)
+{
+    g_kernel = "conv_halo"; g_halo = p; g_stay = stay; g_fp = fp; g_grid = grid;
+    return true;
+}
+bool launch_conv_halo_u1(const ConvHaloParams &p, bool stay, int fp, unsigned grid, int, hipStream_t) { return took_halo(p, stay, fp, grid); }
+bool launch_conv_halo_u2(const ConvHaloParams &p, bool stay, int fp, unsigned grid, int, hipStream_t) { return took_halo(p, stay, fp, grid); }
+bool launch_conv_halo_pm1(const ConvHaloParams &p, bool stay, int fp, unsigned grid, int, hipStream_t) { return took_halo(p, stay, fp, grid); }
 static bool took_tile(const char *name, const TileParams &p, bool pmz, unsigned grid) { g_kernel = name; g_tp = p; g_pmz = pmz; g_grid = grid; return true; }
 bool launch_tile8(const TileParams &p, bool conv, int vw, bool, bool pmz, unsigned grid, hipStream_t) { return conv && vw != 4 ? false : took_tile("tile8", p, pmz, grid); }
 bool launch_tile4(const TileParams &p, bool conv, int vw, bool, bool pmz, unsigned grid, hipStream_t) { return conv && vw == 1 ? false : took_tile("tile4", p, pmz, grid); }
@@ -124,7 +137,11 @@ int main()
     EXPECT(g_kernel == "i8" && g_mp.mulA == 128 && g_mp.mulB == 128 && g_mp.flipA == ~0u);
     EXPECT(g_mp.c0 == static_cast<int>(-(int64_t(g_mp.nk) * 128 - 4000) * 16384 - 16384 * int64_t(4000)));
     (void)apnn_gemm(fw, fw, fy, 64, 1024, 1024, 1, 2, APNN_ENC_PM1, APNN_ENC_UNSIGNED, nullptr);         // a paper-sized fully connected layer
-    EXPECT(g_kernel == "small_matrix");
+    EXPECT(g_kernel == "tile16" && g_grid == 4 * 64 && g_mp.nk == 4);
+    (void)apnn_gemm(fw, fw, fy, 8, 4096, 25088, 1, 2, APNN_ENC_PM1, APNN_ENC_UNSIGNED, nullptr);         // long K: eight waves
+    EXPECT(g_kernel == "tile16" && g_grid == 256 && g_mp.nk == 8);
+    (void)apnn_gemm(fw, fw, fy, 256, 1000, 4096, 1, 2, APNN_ENC_PM1, APNN_ENC_UNSIGNED, nullptr);        // more than two tiles a compute unit
+    EXPECT(g_kernel == "small_matrix" && g_grid == 8 * 32);
     (void)apnn_gemm(fw, fw, fy, 512, 512, 100, 1, 1, APNN_ENC_PM1, APNN_ENC_PM1, nullptr);               // Case II: pad positions multiply to +1
     EXPECT(g_mp.c0 < 0);
     EXPECT(apnn_debug_force("MFMA", 0) == APNN_OK);
@@ -148,9 +165,14 @@ int main()
     apnn_debug_reset();
     P.conv.Cin = 128;                                                                                       // matrix-core shape again
     (void)apnn_layer(&P, fw, fw, nullptr, nullptr);
+    EXPECT(g_kernel == "tile16" && g_mp.pool == 2 && g_grid == 8 * 4);
+    EXPECT(apnn_debug_force("MFMA_T16", 0) == APNN_OK);
+    (void)apnn_layer(&P, fw, fw, nullptr, nullptr);
     EXPECT(g_kernel == "small_conv" && g_mp.pool == 2);
+    apnn_debug_reset();
 
     // ---- 32-bit ranges of the large-layer kernel: operands below 2^31 bytes, one padded image below 2^27 words
+    EXPECT(apnn_debug_force("MFMA_HALO", 0) == APNN_OK && apnn_debug_force("MFMA_T16", 0) == APNN_OK);
     apnn_layer_desc V{};
     V.acc_out_dev = fy;
     auto chosen = [&](int64_t images, int64_t H, int64_t W, int64_t Cin, int64_t Cout, int R, int pad, int q, int stride = 1) {
@@ -173,9 +195,40 @@ int main()
     EXPECT(chosen(1, 32767, 32767, 32, 32, 1, 0, 2, 2) == "tile2");                                            // 32768^2 2 = 2^31
     EXPECT(chosen(1, 28, 28, 96, 64, 3, 1, 2) == "small_conv" && g_mp.Cw == 3);
     EXPECT(apnn_debug_force("MFMA_SMALL", 0) == APNN_OK && chosen(1, 28, 28, 96, 64, 3, 1, 2) == "tile2");
-    apnn_debug_reset();
+    EXPECT(apnn_debug_force("MFMA_SMALL", -1) == APNN_OK);
     EXPECT(chosen(64, 56, 56, 64, 64, 3, 1, 2) == "small_conv_wide" && chosen(64, 56, 56, 64, 96, 3, 1, 2) == "small_conv");
     EXPECT(chosen(1, 14, 14, 64, 64, 3, 1, 2) == "small_conv");                                             // few tiles: K split
+
+    // ---- the library's own choice: staged convolutions (int32 results here) in their limits
+    apnn_debug_reset();
+    EXPECT(chosen(64, 56, 56, 64, 64, 3, 1, 2) == "conv_halo" && g_stay && g_halo.bytesA == 64u * 56 * 56 * 16 && g_halo.bytesB == 64 * 9 * 8);
+    EXPECT(chosen(64, 56, 56, 64, 96, 3, 1, 2) == "conv_halo" && g_halo.per_column.d == 2);
+    EXPECT(chosen(1023, 128, 128, 512, 64, 3, 1, 2) == "conv_halo" && !g_stay);
+    EXPECT(chosen(1024, 128, 128, 512, 64, 3, 1, 2) == "small_conv");                                      // features of 2^31 bytes
+    EXPECT(chosen(1, 14, 14, 64, 64, 3, 1, 2) == "tile16");                                                 // few outputs
+    EXPECT(apnn_debug_force("MFMA_NSPLIT", 1) == APNN_OK && chosen(64, 56, 56, 64, 64, 3, 1, 2) == "small_conv_wide");   // another form asked for
+    EXPECT(apnn_debug_force("MFMA_HALO", 1) == APNN_OK && chosen(64, 56, 56, 64, 64, 3, 1, 2) == "conv_halo");
+    apnn_debug_reset();
+    // weights of 4 GiB: not for 31-bit offsets
+    V.conv = apnn_conv_desc{1, 8, 8, 64, int64_t(1) << 26, 1, 1, 1, 0, 8, 2, APNN_ENC_UNSIGNED, APNN_ENC_UNSIGNED};
+    g_kernel.clear();
+    (void)apnn_layer(&V, fw, fw, nullptr, nullptr);
+    EXPECT(g_kernel == "small_conv");
+    // planes of one or two bits without other outputs, else the kernels that write them
+    apnn_layer_desc Q{};
+    Q.scale_dev = Q.bias_dev = static_cast<const float *>(fake);
+    auto planes = [&](int64_t images, int64_t hw, int64_t Cin, int64_t Cout, int stride, int q_out, int pool) {
+        Q.conv = apnn_conv_desc{images, hw, hw, Cin, Cout, 3, 3, stride, 1, 1, 2, APNN_ENC_PM1, APNN_ENC_UNSIGNED};
+        Q.q_out = q_out; Q.pool = pool;
+        g_kernel.clear();
+        (void)apnn_layer(&Q, fw, fw, static_cast<uint32_t *>(fake), nullptr);
+        return g_kernel;
+    };
+    EXPECT(planes(128, 56, 64, 64, 1, 2, 0) == "conv_halo" && g_stay && g_fp == 2);
+    EXPECT(planes(128, 56, 64, 64, 1, 3, 0) == "small_conv_wide" && planes(128, 56, 64, 64, 1, 2, 1) == "conv_halo" && g_fp == 4);
+    Q.acc_out_dev = fy;
+    EXPECT(planes(128, 56, 64, 64, 1, 2, 0) == "small_conv_wide");
+    Q.acc_out_dev = nullptr;
 
     if (failures == 0) std::puts("abi host sanitizer run ok");
     return failures != 0;

@@ -49,7 +49,7 @@ def _host_program(tmp_path, name, units):
 
 @pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
 def test_abi_host_side_under_sanitizers(tmp_path):
-    units = [os.path.join(CSRC, n) for n in ("layer.hip", "pack.hip", "pool.hip", "input_layer.hip", "common.cpp")]
+    units = [os.path.join(CSRC, n) for n in ("layer.hip", "pack.hip", "pool.hip", "input_layer.hip", "conv_halo.hip", "common.cpp")]
     units.append(os.path.join(ROOT, "tests", "sanitize", "abi_host_driver.cpp"))
     assert "abi host sanitizer run ok" in _run([_host_program(tmp_path, "abi_san", units)])
 
@@ -58,3 +58,13 @@ def test_abi_host_side_under_sanitizers(tmp_path):
 def test_staged_convolution_layout_under_sanitizers(tmp_path):
     units = [os.path.join(CSRC, "conv_halo.hip"), os.path.join(ROOT, "tests", "sanitize", "conv_halo_driver.cpp")]
     assert "staged convolution sanitizer run ok" in _run([_host_program(tmp_path, "halo_san", units)])
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
+def test_no_launcher_may_be_missing(tmp_path):
+    """A library that lost a kernel's unit does not link: the dispatch has no weak reference to a launcher."""
+    obj = str(tmp_path / "layer.o")
+    _run(["hipcc", "--offload-arch=gfx950", "--cuda-host-only", "-O1", "-std=c++17", "-x", "hip", "-c", os.path.join(CSRC, "layer.hip"), "-o", obj])
+    names = [line.split() for line in _run(["nm", "-u", obj]).splitlines()]
+    launchers = [(kind, name) for kind, name in names if "launch_" in name]
+    assert len(launchers) > 10 and all(kind == "U" for kind, _ in launchers)
