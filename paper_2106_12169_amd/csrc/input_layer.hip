@@ -301,7 +301,7 @@ static bool try_input_tile(const MfmaParams &p, const InputParams &q, int64_t im
     if (force == 0 || !p.out || p.q_out > 2 || p.Y || p.T || p.res || p.N > 64) return false;
     const int seg = K_S > 8 ? 2 : 1, nt = p.N > 32 ? 2 : 1, copies = p.stride % 4 == 0 ? 1 : p.stride % 2 == 0 ? 2 : 4;
     const int64_t Hq = p.H + 2 * static_cast<int64_t>(p.pad);
-    if ((images + 1) * Hq >= int64_t(1) << 31) return false;
+    if ((images + 1) * Hq >= int64_t(1) << 31 || p.M > 0x7FFFFFFF - 512) return false;       // (a block's last pixel: below M + 512)
     InputTileParams t{};
     t.img = q.img; t.w = q.w; t.cterm = q.cterm;
     t.M = p.M; t.N = p.N; t.C = q.C; t.images = static_cast<int>(images); t.H = p.H; t.W = p.W; t.Hq = static_cast<int>(Hq);

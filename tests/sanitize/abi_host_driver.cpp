@@ -26,6 +26,15 @@ static apnn::ConvHaloParams g_halo;
 static int g_fp;                      // its pixel tiles
 static bool g_stay;                   // ... and whether its weights stay in LDS
 
+// the launches that the sources make themselves (nothing reaches the runtime)
+static unsigned g_block;
+extern "C" hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t, hipStream_t)
+{
+    g_grid = grid.x; g_block = block.x;
+    return hipErrorNoDevice;                                  // not launched
+}
+extern "C" hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int) { return hipSuccess; }
+
 namespace apnn {
 static bool took(const char *name, const MfmaParams &p, unsigned grid) { g_kernel = name; g_mp = p; g_grid = grid; return true; }
 bool launch_mfma256(const MfmaParams &p, int, int, bool, unsigned grid, hipStream_t) { return took("mfma256", p, grid); }
@@ -229,6 +238,21 @@ int main()
     Q.acc_out_dev = fy;
     EXPECT(planes(128, 56, 64, 64, 1, 2, 0) == "small_conv_wide");
     Q.acc_out_dev = nullptr;
+
+    // ---- input layers: 512 pixels a block with the rows staged, or 128
+    apnn_layer_desc I{};
+    I.scale_dev = I.bias_dev = static_cast<const float *>(fake);
+    I.q_out = 2;
+    auto input_pixels = [&](int64_t images, int64_t C, int64_t H, int64_t W, int R, int stride, int pad) {
+        I.conv = apnn_conv_desc{images, H, W, C, 64, R, R, stride, pad, 1, 8, APNN_ENC_PM1, APNN_ENC_UNSIGNED};
+        g_block = 0;
+        (void)apnn_input_layer(&I, fake, static_cast<const uint8_t *>(fake), static_cast<uint32_t *>(fake), nullptr);
+        return g_block == 512 ? 512 : g_block == 256 ? 128 : 0;
+    };
+    EXPECT(input_pixels(8, 3, 224, 224, 7, 2, 3) == 512 && g_grid == 8 * 112 * 112 / 512);
+    // the last block's pixel numbers stay below 2^31
+    EXPECT(input_pixels(1, 1, 268435391, 8, 1, 1, 0) == 512 && g_grid == (1u << 22) - 1);
+    EXPECT(input_pixels(1, 1, 268435392, 8, 1, 1, 0) == 128 && input_pixels(1, 1, 268435424, 8, 1, 1, 0) == 128);
 
     if (failures == 0) std::puts("abi host sanitizer run ok");
     return failures != 0;
