@@ -315,11 +315,12 @@ static bool try_input_tile(const MfmaParams &p, const InputParams &q, int64_t im
     int64_t lines = new_rows * p.stride + new_images * (between > 0 ? between : 0) + p.R;
     if (lines > images * Hq) lines = images * Hq;
     const int64_t pitch = round_up(static_cast<int64_t>(p.Wo - 1) * p.stride + 8 * seg, 8);
+    if (lines >= (int64_t(1) << 30) / (pitch / 8)) return false;         // (far beyond LDS; the products below stay small)
     t.row_groups = divisor(pitch / 8);
     // (copies begin on different banks)
     const int64_t plane = round_up(lines * pitch, 128) + 128 / copies;
     const int64_t lds = 4 * (64 + 32) * nt + 16 * q.KS + 1024 * static_cast<int64_t>(q.KS) * nt + q.C * copies * plane;
-    if (lds > 160 * 1024 || 32 * nt + 4 * q.KS > 512 || lines * (pitch / 8) >= int64_t(1) << 30) return false;
+    if (lds > 160 * 1024 || 32 * nt + 4 * q.KS > 512) return false;
     t.pitch = static_cast<int>(pitch); t.plane = static_cast<int>(plane);
     const int64_t blocks = ceil_div(p.M, 512);
     if (blocks > kMaxBlocks / 2) return false;           // (512 threads each)

@@ -253,6 +253,7 @@ int main()
     // the last block's pixel numbers stay below 2^31
     EXPECT(input_pixels(1, 1, 268435391, 8, 1, 1, 0) == 512 && g_grid == (1u << 22) - 1);
     EXPECT(input_pixels(1, 1, 268435392, 8, 1, 1, 0) == 128 && input_pixels(1, 1, 268435424, 8, 1, 1, 0) == 128);
+    EXPECT(input_pixels(1, 64, 8, 8, 1, (1 << 29) - 8, (1 << 29) - 8) == 128);                              // 2^59 bytes a channel
 
     if (failures == 0) std::puts("abi host sanitizer run ok");
     return failures != 0;
