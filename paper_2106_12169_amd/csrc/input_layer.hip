@@ -60,8 +60,8 @@ template <int NT, int SEG> __global__ __launch_bounds__(256, NT <= 2 ? 4 : 2) vo
     for (int g = 0; g < SEG; ++g) {
         const int xg = x0 + 8 * g, xs = min(max(xg, 0), p.W - 8), delta = xs - xg;
         col_ok[g] = a_ok && delta > -8 && delta < 8;
-        shl[g] = delta > 0 ? 8 * delta : 0;
-        shr[g] = delta < 0 ? -8 * delta : 0;
+        shl[g] = 8 * min(max(delta, 0), 7);              // (segments wholly outside the frame are zero as they are)
+        shr[g] = 8 * min(max(-delta, 0), 7);
         img_base[g] = n * q.C * p.H * p.W + xs;
     }
 

@@ -98,7 +98,7 @@ template <int NT, int SEG, int COPIES> __global__ __launch_bounds__(512, 2) void
                 xs[u][j] = min(max(x, 0), p.W - 8);
                 const int delta = xs[u][j] - x;
                 ok[u][j] = row_ok && delta > -8 && delta < 8;
-                shift[u][j] = 8 * delta;
+                shift[u][j] = 8 * min(max(delta, -7), 7);                // (groups wholly outside are zero as they are)
             }
         }
         for (int c0 = 0; c0 < p.C; c0 += 3) {                            // three channels in flight
