@@ -46,13 +46,9 @@ __device__ __forceinline__ int divide(int n, const Divisor &d)
     return static_cast<int>((static_cast<uint64_t>(static_cast<uint32_t>(n)) * d.m) >> d.s);
 }
 
-// acc, scale, bias -> clamp(acc scale + bias, 0, 1); NaN gives 0 (the clamp bit of the instruction)
-__device__ __forceinline__ float fma_clamp(float a, float b, float c)
-{
-    float t;
-    asm("v_fma_f32 %0, %1, %2, %3 clamp" : "=v"(t) : "v"(a), "v"(b), "v"(c));
-    return t;
-}
+// acc, scale, bias -> clamp(acc scale + bias, 0, 1); NaN gives 0.  The compiler makes the clamp bit of the multiply-add of it;
+// it has to see the instruction, because the first reader of an accumulator waits for the matrix instruction that writes it.
+__device__ __forceinline__ float fma_clamp(float a, float b, float c) { return __builtin_amdgcn_fmed3f(__fmaf_rn(a, b, c), 0.0f, 1.0f); }
 
 typedef float v2f_t __attribute__((ext_vector_type(2)));
 typedef float v4f_t __attribute__((ext_vector_type(4)));
