@@ -316,7 +316,7 @@ __global__ __launch_bounds__(256, FP == 1 ? 4 : FP * FW == 8 ? 2 : 3) void conv_
             for (int i = 0; i < HW; ++i)
 #pragma unroll
                 for (int c = 0; c < FW; ++c) o.a[i][c] = *reinterpret_cast<const v4i_t *>(codes + (i * FC + c) * 256);
-            o.scale = MULTI ? scaleA + 0x02020202 * d : scaleA;
+            o.scale = MULTI ? block_scale(scaleA, 2 * d) : scaleA;
             asm volatile("" ::: "memory");
         };
         auto advance = [&](bool more) __attribute__((always_inline)) {                          // more: of this chunk
@@ -420,7 +420,7 @@ __global__ __launch_bounds__(256, FP == 1 ? 4 : FP * FW == 8 ? 2 : 3) void conv_
                 if (!more) break;
                 if (nd != digit) {                               // the next weight digit starts at the first tap again
                     off = 0; sc = 0;
-                    scaleB += 0x02020202;
+                    scaleB = block_scale(scaleB, 2);
                 }
                 digit = nd;
                 s0 = ns;
@@ -450,7 +450,7 @@ __global__ __launch_bounds__(256, FP == 1 ? 4 : FP * FW == 8 ? 2 : 3) void conv_
                 if (!more) break;
                 if (nd != digit) {                               // the next weight digit starts at the first tap again
                     off = 0; g = 0; sc = 0; d = 0;
-                    scaleB += 0x02020202;
+                    scaleB = block_scale(scaleB, 2);
                 }
                 digit = nd;
                 s0 = ns;

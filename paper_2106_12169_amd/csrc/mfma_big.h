@@ -399,7 +399,7 @@ __global__ __launch_bounds__(64 * NWM * NWN, FM * FN >= 16 ? 1 : 2) void mfma_bi
 #endif
     for (int it = 0; it < total_it; ++it) {
         const int buf = it & 1;
-        int sa = 0x7f7f7f7f + 0x02020202 * cda + 0x01010101 * log2_out, sb = 0x7f7f7f7f + 0x02020202 * cdb;
+        int sa = block_scale(block_scale(0x7f7f7f7f, 2 * cda), log2_out), sb = block_scale(0x7f7f7f7f, 2 * cdb);
         asm volatile("" : "+v"(sa), "+v"(sb));          // in vector registers before the first portion
         __builtin_amdgcn_sched_barrier(0);
         //   multiply step | expand step (words, index) into | prepare pair (words, which) | memory

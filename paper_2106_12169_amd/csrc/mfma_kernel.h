@@ -108,6 +108,12 @@ __device__ __forceinline__ uint32_t reg_const(uint32_t k)
     return k;
 }
 
+// Block scale of a matrix operand (an exponent byte for each block of K) times 2^e; unsigned, since the bytes pass 2^7.
+__device__ __forceinline__ int block_scale(int scale, int e)
+{
+    return static_cast<int>(static_cast<uint32_t>(scale) + 0x01010101u * static_cast<uint32_t>(e));
+}
+
 struct Fp4Masks { uint32_t m1, m2, m4, m8; };
 
 // 32 K positions of one operand row -> 4 dwords of 8 FP4 codes; nibble i of

@@ -153,8 +153,8 @@ __device__ __forceinline__ void mfma_small_body(const MfmaParams &p, const int b
         for (int g = 0; g < GMAX; ++g) {
             const int planeA = LA == 2 ? 2 * da : da, planeB = LB == 2 ? 2 * db : db;
             const int kk = e0 + g < total ? kbase + 4 * NSPLIT * grp : p.Kw;    // beyond the end: reads as zero, not used
-            sa[g] = 0x7f7f7f7f + 0x02020202 * da;
-            sb[g] = 0x7f7f7f7f + 0x02020202 * db;
+            sa[g] = block_scale(0x7f7f7f7f, 2 * da);
+            sb[g] = block_scale(0x7f7f7f7f, 2 * db);
 #pragma unroll
             for (int pl = 0; pl < LA; ++pl) wa[g][pl] = load_a(planeA + pl, kk);
 #pragma unroll

@@ -240,8 +240,8 @@ __device__ __forceinline__ void mfma_small_wide_body(const MfmaParams &p, const 
             const int planeA = LA == 2 ? 2 * da : da, planeB = LB == 2 ? 2 * db : db;
             const int kk = kbase + 4 * grp;             // (beyond the end: read, not used; jumping over it measured slower)
             steps[g] = NS - 4 * grp;
-            sa[g] = 0x7f7f7f7f + 0x02020202 * da;
-            sb[g] = 0x7f7f7f7f + 0x02020202 * db;
+            sa[g] = block_scale(0x7f7f7f7f, 2 * da);
+            sb[g] = block_scale(0x7f7f7f7f, 2 * db);
             load_a(wa[g], planeA, t);
 #pragma unroll
             for (int j = 0; j < FN; ++j)

@@ -97,8 +97,8 @@ __global__ __launch_bounds__(512) void mfma_tile16_kernel(const MfmaParams p)
 #pragma unroll
         for (int g = 0; g < GMAX; ++g) {
             const int kk = e0 + g < total ? 16 * (wave + (grp << log_waves)) + 4 * lg : p.Kw;
-            sa[g] = 0x7f7f7f7f + 0x02020202 * da;
-            sb[g] = 0x7f7f7f7f + 0x02020202 * db;
+            sa[g] = block_scale(0x7f7f7f7f, 2 * da);
+            sb[g] = block_scale(0x7f7f7f7f, 2 * db);
 #pragma unroll
             for (int pl = 0; pl < LB; ++pl) wb[g][pl] = load_b((LB == 2 ? 2 * db : db) + pl, kk);
 #pragma unroll
