@@ -504,7 +504,7 @@ __global__ __launch_bounds__(256, FP == 1 ? 4 : FP * FW == 8 ? 2 : 3) void conv_
                     // the residual's plane words -> nibbles of this q
                     const uint32_t z0 = res[f][c][0] >> (2 * lh), z1 = res[f][c][1] >> (2 * lh);
                     const uint32_t e = q == 0 ? (z0 & 0x11111111u) | ((z1 << 1) & 0x22222222u) : ((z0 >> 1) & 0x11111111u) | (z1 & 0x22222222u);
-                    d[f][q] = nibbles(v, sc, bi, p.res != nullptr, p.res_scale, e);
+                    d[f][q] = nibbles<!POOL>(v, sc, bi, p.res != nullptr, p.res_scale, e);
                 });
             });
 #pragma unroll

@@ -196,7 +196,7 @@ template <int NT, int SEG, int COPIES> __global__ __launch_bounds__(512, 2) void
                 float v[8];
 #pragma unroll
                 for (int j = 0; j < 8; ++j) v[j] = static_cast<float>(acc[t][f][8 * q + j]);
-                d[f][q] = nibbles(v, sc, bi, false, 0.0f, 0u);
+                d[f][q] = nibbles<false>(v, sc, bi, false, 0.0f, 0u);
             });
         });
 #pragma unroll
