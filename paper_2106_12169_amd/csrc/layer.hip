@@ -263,7 +263,7 @@ static bool try_mfma(const Problem &pr, MfmaParams &mp, void *stream, int &rc, S
         // Eight waves a block where K is long enough to feed them (w1a2 3 x 3 convolutions, us, four waves first: 784 x 256,
         // 72 words of K 5.6, 5.1; 784 x 512, 144 words 8.3, 7.8; 1568 x 512 12.6, 12.3; 800 x 512, 36 words 4.9, 5.2)
         if (pr.conv && !plan && tiles <= 1024 && static_cast<int64_t>(mp.Kw) * mp.DA * mp.DB >= 72) nsplit = 8;
-        if (const int en = ov(OV_MFMA_NSPLIT); en == 1 || en == 4 || (en == 8 && pr.conv)) nsplit = en;
+        if (const int en = ov(OV_MFMA_NSPLIT); en == 1 || en == 4 || (en == 8 && pr.conv && tiles <= kMaxBlocks / 2)) nsplit = en;
         const int64_t nse = round_up(ceil_div(mp.Kw, 2), 4);          // steps of the small-layer kernel (groups of four)
         mp.nk = 1;
         mp.c0 = (kA == OPK_PM1 && kB == OPK_PM1) ? -static_cast<int>(nse * 64 - pr.Ktotal) : 0;

@@ -22,6 +22,7 @@ static apnn::MfmaParams g_mp;
 static apnn::TileParams g_tp;
 static unsigned g_grid;
 static int g_pmz;
+static int g_nsplit;                  // waves that split K of a tile of the small-layer kernel
 static apnn::ConvHaloParams g_halo;
 static int g_fp;                      // its pixel tiles
 static bool g_stay;                   // ... and whether its weights stay in LDS
@@ -42,7 +43,11 @@ bool launch_mfma128(const MfmaParams &p, int, int, bool, unsigned grid, hipStrea
 bool launch_mfma64(const MfmaParams &p, int, int, bool, unsigned grid, hipStream_t) { return took("mfma64", p, grid); }
 bool launch_mfma64_k8(const MfmaParams &p, int, int, unsigned grid, hipStream_t) { return took("mfma64_k8", p, grid); }
 bool launch_mfma32(const MfmaParams &p, int, int, bool, unsigned grid, hipStream_t) { return took("mfma32", p, grid); }
-bool launch_mfma_small_conv(const MfmaParams &p, int, int, int, int, int, unsigned grid, hipStream_t) { return took("small_conv", p, grid); }
+bool launch_mfma_small_conv(const MfmaParams &p, int, int, int, int nsplit, int, unsigned grid, hipStream_t)
+{
+    g_nsplit = nsplit;
+    return took("small_conv", p, grid);
+}
 bool launch_mfma_small_conv_wide(const MfmaParams &p, int, int, int, int, unsigned grid, hipStream_t) { return took("small_conv_wide", p, grid); }
 bool launch_mfma_small_conv_pair(const MfmaParams &p0, unsigned grid0, const MfmaParams &, unsigned grid1, int, int, int, int, hipStream_t)
 {
@@ -217,6 +222,10 @@ int main()
     EXPECT(chosen(1, 14, 14, 64, 64, 3, 1, 2) == "tile16");                                                 // few outputs
     EXPECT(apnn_debug_force("MFMA_NSPLIT", 1) == APNN_OK && chosen(64, 56, 56, 64, 64, 3, 1, 2) == "small_conv_wide");   // another form asked for
     EXPECT(apnn_debug_force("MFMA_HALO", 1) == APNN_OK && chosen(64, 56, 56, 64, 64, 3, 1, 2) == "conv_halo");
+    apnn_debug_reset();
+    // eight waves a tile: at most 2^23 - 1 blocks of 512 threads, else the value is ignored
+    EXPECT(apnn_debug_force("MFMA_NSPLIT", 8) == APNN_OK && chosen(255, 1024, 1024, 64, 32, 1, 0, 1) == "small_conv" && g_nsplit == 8);
+    EXPECT(chosen(256, 1024, 1024, 64, 32, 1, 0, 1) == "small_conv" && g_nsplit == 1 && g_grid == 256u << 13);
     apnn_debug_reset();
     // weights of 4 GiB: not for 31-bit offsets
     V.conv = apnn_conv_desc{1, 8, 8, 64, int64_t(1) << 26, 1, 1, 1, 0, 8, 2, APNN_ENC_UNSIGNED, APNN_ENC_UNSIGNED};
