@@ -3,6 +3,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstdarg>
 #include <cstdint>
 #include <cstdio>
@@ -31,6 +32,23 @@ template <class F> void in_slices(int64_t items, F &&launch)
         launch(first, static_cast<unsigned>(ceil_div(items - first < slice ? items - first : slice, 256)));
 }
 constexpr int64_t kMaxBlocks = (int64_t(1) << 24) - 1;      // of 256 threads
+
+// Lets a kernel take all of a compute unit's LDS on the calling thread's device, more than it may have unasked.  Asked for once
+// per kernel and device (`granted` has a bit for each): what was granted on one device does not hold on another.  Two
+// threads that come here together ask for the same.
+template <class Kernel> bool all_of_lds(Kernel kernel, std::atomic<uint64_t> &granted)
+{
+    int device = 0;
+    if (hipGetDevice(&device) != hipSuccess) return false;
+    const uint64_t bit = device < 64 ? uint64_t(1) << device : 0;       // (beyond 64 devices: asked for in every call)
+    if (granted.load(std::memory_order_relaxed) & bit) return true;
+    if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess) {
+        (void)hipGetLastError();                            // another kernel takes the call
+        return false;
+    }
+    granted.fetch_or(bit, std::memory_order_relaxed);
+    return true;
+}
 
 // Override INPUT_TILE (layer.hip): -1 when it is not set.
 int input_tile_override();

@@ -1,7 +1,6 @@
 // Launcher of conv_halo_kernel: one translation unit per kind of features, so they compile in parallel.
 #pragma once
-#include <atomic>
-
+#include "common.h"
 #include "conv_halo.h"
 
 namespace apnn {
@@ -10,13 +9,8 @@ template <int KA, int HW, int SW, int FP, int FW, int PT, bool POOL, bool MULTI,
 bool launch_conv_halo(const ConvHaloParams &p, unsigned grid, int lds, hipStream_t st)
 {
     const auto kernel = conv_halo_kernel<KA, HW, SW, FP, FW, PT, POOL, MULTI, STAY>;
-    // all of a compute unit's LDS, once per instance: two threads that come here together ask for the same
-    static std::atomic<bool> granted{false};
-    if (!granted.load(std::memory_order_relaxed)) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
-            return false;
-        granted.store(true, std::memory_order_relaxed);
-    }
+    static std::atomic<uint64_t> granted{0};
+    if (!all_of_lds(kernel, granted)) return false;
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), lds, st, p);
     return true;
 }

@@ -18,8 +18,6 @@
 // the per-channel constant 128 * sum_k w[k], made by the weight packer, is added
 // back in the epilogue; positions outside the frame are x = 0, i.e. -128, and are
 // covered by the same constant (zero-contribution padding, Sec. 4.2 (b)).
-#include <atomic>
-
 #include "common.h"
 #include "input_tile.h"
 #include "mfma_kernel.h"
@@ -283,13 +281,8 @@ static int64_t input_row_bytes(int64_t Cin, int R, int S) { return round_up(Cin 
 template <int NT, int SEG, int COPIES> static bool launch_input_tile(const InputTileParams &p, unsigned grid, int lds, hipStream_t st)
 {
     const auto kernel = input_tile_kernel<NT, SEG, COPIES>;
-    // all of a compute unit's LDS, once per instance: two threads that come here together ask for the same
-    static std::atomic<bool> granted{false};
-    if (!granted.load(std::memory_order_relaxed)) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
-            return false;
-        granted.store(true, std::memory_order_relaxed);
-    }
+    static std::atomic<uint64_t> granted{0};
+    if (!all_of_lds(kernel, granted)) return false;
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(512), lds, st, p);
     return true;
 }

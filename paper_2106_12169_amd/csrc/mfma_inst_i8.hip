@@ -1,20 +1,15 @@
 // Instances of mfma_i8_kernel: every pair of plane classes.
+#include "common.h"
 #include "mfma_i8.h"
 #include "mfma_launch.h"
-
-#include <atomic>
 
 namespace apnn {
 
 template <int CA, int CB> static bool go(const MfmaParams &p, unsigned grid, hipStream_t st)
 {
     const auto kernel = mfma_i8_kernel<CA, CB>;
-    static std::atomic<bool> granted{false};
-    if (!granted.load(std::memory_order_relaxed)) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kI8LdsBytes) != hipSuccess)
-            return false;
-        granted.store(true, std::memory_order_relaxed);
-    }
+    static std::atomic<uint64_t> granted{0};
+    if (!all_of_lds(kernel, granted)) return false;
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(512), kI8LdsBytes, st, p);
     return true;
 }

@@ -1,5 +1,6 @@
 // Instances of the 8-bit integer matrix kernel with K shared out among the waves (mfma_i8_wide.h) whose row operand
 // has plane class C4.
+#include "common.h"
 #include "mfma_i8_wide.h"
 #include "mfma_launch.h"
 
@@ -9,12 +10,8 @@ template <int CB> static bool go(const MfmaParams &p, unsigned grid, hipStream_t
 {
     auto kernel = mfma_i8_wide_kernel<I8_C4, CB>;
     const int lds = mfma_i8_wide_lds_bytes(p.PA, p.PB);
-    static int granted = 0;                              // most dynamic LDS asked for so far (per instance)
-    if (lds > granted) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
-            return false;
-        granted = lds;
-    }
+    static std::atomic<uint64_t> granted{0};
+    if (!all_of_lds(kernel, granted)) return false;
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), lds, st, p);
     return true;
 }

@@ -34,7 +34,10 @@ extern "C" hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t, 
     g_grid = grid.x; g_block = block.x;
     return hipErrorNoDevice;                                  // not launched
 }
-extern "C" hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int) { return hipSuccess; }
+static int g_device, g_asked;         // the current device, how often a kernel asked for LDS
+static hipError_t g_answer = hipSuccess;
+extern "C" hipError_t hipGetDevice(int *device) { *device = g_device; return hipSuccess; }
+extern "C" hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int) { ++g_asked; return g_answer; }
 
 namespace apnn {
 static bool took(const char *name, const MfmaParams &p, unsigned grid) { g_kernel = name; g_mp = p; g_grid = grid; return true; }
@@ -259,6 +262,18 @@ int main()
         return g_block == 512 ? 512 : g_block == 256 ? 128 : 0;
     };
     EXPECT(input_pixels(8, 3, 224, 224, 7, 2, 3) == 512 && g_grid == 8 * 112 * 112 / 512);
+    // LDS is asked for once on every device that the kernel runs on; where it is refused the other kernel takes the layer
+    auto asks = [&](int device) {
+        g_device = device; g_asked = 0;
+        EXPECT(input_pixels(8, 3, 224, 224, 7, 2, 3) == 512);
+        return g_asked;
+    };
+    EXPECT(asks(0) == 0 && asks(3) == 1 && asks(3) == 0 && asks(0) == 0 && asks(63) == 1 && asks(63) == 0 && asks(64) == 1 && asks(64) == 1);
+    g_device = 1; g_answer = hipErrorInvalidValue;
+    EXPECT(input_pixels(8, 3, 224, 224, 7, 2, 3) == 128);
+    g_answer = hipSuccess;
+    EXPECT(asks(1) == 1 && asks(1) == 0);
+    g_device = 0;
     // the last block's pixel numbers stay below 2^31
     EXPECT(input_pixels(1, 1, 268435391, 8, 1, 1, 0) == 512 && g_grid == (1u << 22) - 1);
     EXPECT(input_pixels(1, 1, 268435392, 8, 1, 1, 0) == 128 && input_pixels(1, 1, 268435424, 8, 1, 1, 0) == 128);
