@@ -87,6 +87,19 @@ int main()
     EXPECT(static_cast<uint32_t>(g_p.scaleA) == 0x80808080u && static_cast<uint32_t>(g_p.scaleB) == 0x80808080u);
     EXPECT(staged({1, 8, 8, 64, 64, 3, 3, 1, 1, false, 1, true, 1}, 1) && g_p.scaleA == 0x7d7d7d7d && static_cast<uint32_t>(g_p.scaleB) == 0x80808080u);
 
+    // blocks that walk over tiles, two buffers of pixels each: the layers of test_blocks_walk_over_tiles (tests/test_gpu_conv_halo.py)
+    // give every block a second tile and some a third, the last one ragged
+    struct { Layer l; int force, fp, pixels; } const walked[] = {
+        {{2, 112, 111, 32, 512, 3, 3, 1, 1, true, 1, false, 2}, 1, 1, 128},    {{2, 157, 158, 64, 480, 1, 1, 1, 0, true, 1, false, 2}, 2, 2, 256},
+        {{3, 105, 105, 32, 512, 1, 1, 1, 0, false, 1, false, 1}, 1, 1, 128},   {{3, 104, 105, 32, 512, 2, 1, 1, 1, true, 1, true, 1}, 1, 1, 128},
+        {{3, 105, 105, 64, 512, 1, 1, 1, 0, true, 1, false, 3}, 1, 1, 128},    {{1, 550, 551, 32, 64, 1, 1, 1, 0, true, 1, false, 2}, 1, 1, 128},
+        {{2, 158, 159, 32, 512, 1, 1, 1, 0, true, 1, false, 2, 1}, 1, 3, 256}, {{2, 183, 183, 32, 512, 1, 1, 1, 0, true, 1, false, 2, 2}, 2, 4, 512}};
+    for (const auto &w : walked) {
+        EXPECT(staged(w.l, w.force) && g_stay && g_fp == w.fp && g_p.tilesM > 2 * g_p.tile_step && g_p.M % w.pixels != 0);
+        EXPECT(g_grid == static_cast<unsigned>(g_p.tile_step * g_p.per_column.d) && g_grid % 256 == 0);
+        EXPECT(g_lds == 4 * (128 + g_p.words_codes + 2 * g_p.words_records));
+    }
+
     if (failures == 0) std::puts("staged convolution sanitizer run ok");
     return failures != 0;
 }

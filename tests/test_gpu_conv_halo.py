@@ -80,6 +80,27 @@ def test_layer(force, BS, Cin, Cout, H, W, R, S, stride, pad, encW, p, encX, q, 
     assert np.array_equal(codes, oracle.epilogue(want, scale, bias, q_out, res=res, res_scale=0.37)[0])
 
 
+# Layers whose blocks walk over three tiles and more, the last one ragged, with the next tile's pixels in flight: kernel form, layer.
+# (tests/sanitize/conv_halo_driver.cpp checks that the same layers get two buffers and as many tiles a block.)
+WALKED = [
+    (1, (2, 112, 111), (32, 512, 3, 3, 1, 1, P, 1, U, 2, 2, 2, 0)),     # eight channel tiles, ranges across images, residual
+    (2, (2, 157, 158), (64, 480, 1, 1, 1, 0, P, 1, U, 2, 2, 1, 0)),     # 256 pixels a tile, the last channel tile half empty
+    (1, (3, 105, 105), (32, 512, 1, 1, 1, 0, U, 1, U, 1, 1, 2, 0)),     # one feature plane
+    (1, (3, 104, 105), (32, 512, 2, 1, 1, 1, P, 1, P, 1, 2, 0, 0)),     # -1/+1 features, padding
+    (1, (3, 105, 105), (64, 512, 1, 1, 1, 0, P, 1, U, 3, 2, 2, 0)),     # two feature digits
+    (1, (1, 550, 551), (32, 64, 1, 1, 1, 0, P, 1, U, 2, 2, 2, 0)),      # one channel tile
+    (1, (2, 158, 159), (32, 512, 1, 1, 1, 0, P, 1, U, 2, 2, 2, 1)),     # pooled, 64 pooled pixels a tile
+    (2, (2, 183, 183), (32, 512, 1, 1, 1, 0, P, 1, U, 2, 2, 0, 2)),     # pooled sum, 128
+]
+
+
+@pytest.mark.parametrize("force,frames,layer", WALKED)
+def test_blocks_walk_over_tiles(force, frames, layer):
+    BS, H, W = frames
+    Cin, Cout, *rest = layer
+    test_layer(force, BS, Cin, Cout, H, W, *rest)
+
+
 @pytest.mark.parametrize("force", [1, 2])
 @pytest.mark.parametrize("BS,Cin,Cout,H,W,R,S,stride,pad,encW,p,encX,q", [
     (2, 96, 36, 9, 7, 3, 3, 1, 1, U, 2, U, 4), (1, 64, 4, 12, 12, 3, 3, 2, 1, P, 1, U, 2), (1, 512, 132, 5, 5, 3, 3, 1, 1, P, 1, P, 1),
@@ -117,8 +138,9 @@ def test_code_thresholds(with_res):
     assert np.array_equal(codes, want)
 
 
-def test_rule_takes_large_layers_only():
-    """Enough tiles: the same planes as the other kernels, from the library's own choice; a layer of the size either side."""
+def test_own_choice_has_the_same_planes():
+    """The library's own choice against the other kernels, for layers either side of its rule (which one it takes:
+    tests/sanitize/abi_host_driver.cpp)."""
     for BS in (8, 128):
         Wv, Xv, Wp, Xp = _operands(BS, 64, 64, 28, 28, 3, 3, P, 1, U, 2)
         d = B.Conv(BS, 28, 28, 64, 64, 3, 3, 1, 1, 1, 2, P, U)
