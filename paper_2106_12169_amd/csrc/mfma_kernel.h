@@ -378,8 +378,20 @@ __device__ __forceinline__ uint4 load_conv_a(const MfmaParams &p, int64_t pix, i
 {
     uint4 v = make_uint4(0, 0, 0, 0);
     if constexpr (VW == 1) return load_conv_a_words(p, p.A + pix * p.PA * p.Cw, plane, kk, h0, w0, validity);
+    if constexpr (VW == 4) {                    // (written out: as a round of the loop below it is five instructions more a piece)
+        const int tap = static_cast<int>((static_cast<float>(kk) + 0.5f) * p.invCw);
+        const int cw = kk - tap * p.Cw;
+        int r, sc;
+        tap_to_rs(p, tap, r, sc);
+        const int h = h0 + r, w = w0 + sc;
+        if (h >= 0 && h < p.H && w >= 0 && w < p.W) {
+            if (validity) v = make_uint4(~0u, ~0u, ~0u, ~0u);
+            else v = *reinterpret_cast<const uint4 *>(p.A + ((pix + h * p.W + w) * p.PA + plane) * p.Cw + cw);
+        }
+        return v;
+    }
 #pragma unroll
-    for (int part = 0; part < 4 / VW; ++part) {
+    for (int part = 0; part < 2; ++part) {
         const int k = kk + part * VW;
         if (k < p.Kw) {
             const int tap = static_cast<int>((static_cast<float>(k) + 0.5f) * p.invCw);
@@ -390,10 +402,7 @@ __device__ __forceinline__ uint4 load_conv_a(const MfmaParams &p, int64_t pix, i
             if (h >= 0 && h < p.H && w >= 0 && w < p.W) {
                 const uint32_t *src = p.A + ((pix + h * p.W + w) * p.PA + plane) * p.Cw + cw;
                 if (validity) {
-                    if (VW == 4) v = make_uint4(~0u, ~0u, ~0u, ~0u);
-                    else if (part == 0) { v.x = ~0u; v.y = ~0u; } else { v.z = ~0u; v.w = ~0u; }
-                } else if (VW == 4) {
-                    v = *reinterpret_cast<const uint4 *>(src);
+                    if (part == 0) { v.x = ~0u; v.y = ~0u; } else { v.z = ~0u; v.w = ~0u; }
                 } else {
                     const uint2 t = *reinterpret_cast<const uint2 *>(src);
                     if (part == 0) { v.x = t.x; v.y = t.y; } else { v.z = t.x; v.w = t.y; }
