@@ -261,8 +261,11 @@ static bool try_mfma(const Problem &pr, MfmaParams &mp, void *stream, int &rc, S
     if (t == 32 && ov(OV_MFMA_SMALL) != 0) {                           // small layer: lane-private loads, no LDS staging (0: chunked kernel)
         int nsplit = tiles <= 4096 ? 4 : 1;                            // measured: the split wins up to a few thousand tiles
         // Eight waves a block where K is long enough to feed them (w1a2 3 x 3 convolutions, us, four waves first: 784 x 256,
-        // 72 words of K 5.6, 5.1; 784 x 512, 144 words 8.3, 7.8; 1568 x 512 12.6, 12.3; 800 x 512, 36 words 4.9, 5.2)
-        if (pr.conv && !plan && tiles <= 1024 && static_cast<int64_t>(mp.Kw) * mp.DA * mp.DB >= 72) nsplit = 8;
+        // 72 words of K 5.6, 5.1; 784 x 512, 144 words 8.3, 7.8; 800 x 512, 36 words 4.9, 5.2).  More than 512 tiles are more
+        // blocks than the compute units hold at once: there from six groups a wave of four on (72 words, 784 tiles, 3 groups a
+        // wave 8.2, 8.6; w1a4, 2 groups of 2 pairs 7.0, 8.8; 144 words, 720 tiles, 5 groups 9.3, 10.0; 7 groups and more 1 to 12 % less).
+        const int64_t pairs = static_cast<int64_t>(mp.DA) * mp.DB, groups = ceil_div(ceil_div(mp.Kw, 2), 4);
+        if (pr.conv && !plan && (tiles <= 512 ? mp.Kw * pairs >= 72 : tiles <= 1024 && ceil_div(groups, 4) * pairs >= 6)) nsplit = 8;
         if (const int en = ov(OV_MFMA_NSPLIT); en == 1 || en == 4 || (en == 8 && pr.conv && tiles <= kMaxBlocks / 2)) nsplit = en;
         const int64_t nse = round_up(ceil_div(mp.Kw, 2), 4);          // steps of the small-layer kernel (groups of four)
         mp.nk = 1;

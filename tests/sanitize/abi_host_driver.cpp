@@ -216,6 +216,12 @@ int main()
     EXPECT(chosen(64, 56, 56, 64, 64, 3, 1, 2) == "small_conv_wide" && chosen(64, 56, 56, 64, 96, 3, 1, 2) == "small_conv");
     EXPECT(chosen(1, 14, 14, 64, 64, 3, 1, 2) == "small_conv");                                             // few tiles: K split
 
+    // eight waves a tile: from 72 words of K on up to 512 tiles, from six groups a wave of four on up to 1024
+    EXPECT(chosen(4, 14, 14, 256, 512, 3, 1, 2) == "small_conv" && g_nsplit == 8 && chosen(4, 14, 14, 128, 512, 3, 1, 2) == "small_conv" && g_nsplit == 4);
+    EXPECT(chosen(4, 28, 28, 256, 256, 3, 1, 2) == "small_conv" && g_nsplit == 4 && chosen(8, 28, 28, 128, 128, 3, 1, 4) == "small_conv" && g_nsplit == 4);
+    EXPECT(chosen(8, 14, 14, 512, 512, 3, 1, 2) == "small_conv" && g_nsplit == 4 && chosen(8, 14, 14, 512, 512, 3, 1, 4) == "small_conv" && g_nsplit == 8);
+    EXPECT(chosen(8, 28, 28, 512, 256, 3, 1, 4) == "small_conv" && g_nsplit == 4);
+
     // ---- the library's own choice: staged convolutions (int32 results here) in their limits
     apnn_debug_reset();
     EXPECT(chosen(64, 56, 56, 64, 64, 3, 1, 2) == "conv_halo" && g_stay && g_halo.bytesA == 64u * 56 * 56 * 16 && g_halo.bytesB == 64 * 9 * 8);
