@@ -228,7 +228,14 @@ int main()
     EXPECT(chosen(64, 56, 56, 64, 96, 3, 1, 2) == "conv_halo" && g_halo.per_column.d == 2);
     EXPECT(chosen(1023, 128, 128, 512, 64, 3, 1, 2) == "conv_halo" && !g_stay);
     EXPECT(chosen(1024, 128, 128, 512, 64, 3, 1, 2) == "small_conv");                                      // features of 2^31 bytes
-    EXPECT(chosen(1, 14, 14, 64, 64, 3, 1, 2) == "tile16");                                                 // few outputs
+    // few outputs, or rows of matrices or pixels that would be half of a 32 x 32 tile; not many pixels of few channels
+    EXPECT(chosen(1, 14, 14, 64, 64, 3, 1, 2) == "tile16" && chosen(1, 3, 3, 256, 16384, 3, 0, 2) == "tile16");
+    EXPECT(chosen(32, 56, 56, 64, 6, 3, 1, 2) == "small_conv" && chosen(32, 56, 56, 96, 10, 1, 0, 2) == "small_conv");
+    (void)apnn_gemm(fw, fw, fy, 25000, 10, 1024, 1, 2, APNN_ENC_PM1, APNN_ENC_UNSIGNED, nullptr);
+    EXPECT(g_kernel == "tile16");
+    // more than 256 of them with two groups of K for four waves: the 32 x 32 tiles
+    EXPECT(chosen(8, 13, 13, 64, 64, 3, 1, 2) == "small_conv" && chosen(8, 12, 12, 96, 64, 3, 1, 2) == "small_conv" && chosen(8, 13, 13, 128, 64, 3, 1, 2) == "tile16");
+    EXPECT(chosen(8, 13, 13, 128, 64, 1, 0, 2) == "tile16" && chosen(8, 13, 13, 96, 64, 1, 0, 2) == "small_conv" && chosen(8, 11, 11, 64, 64, 3, 1, 2) == "tile16");
     EXPECT(apnn_debug_force("MFMA_NSPLIT", 1) == APNN_OK && chosen(64, 56, 56, 64, 64, 3, 1, 2) == "small_conv_wide");   // another form asked for
     EXPECT(apnn_debug_force("MFMA_HALO", 1) == APNN_OK && chosen(64, 56, 56, 64, 64, 3, 1, 2) == "conv_halo");
     apnn_debug_reset();
@@ -253,6 +260,7 @@ int main()
     };
     EXPECT(planes(128, 56, 64, 64, 1, 2, 0) == "conv_halo" && g_stay && g_fp == 2);
     EXPECT(planes(128, 56, 64, 64, 1, 3, 0) == "small_conv_wide" && planes(128, 56, 64, 64, 1, 2, 1) == "conv_halo" && g_fp == 4);
+    EXPECT(planes(8, 13, 64, 64, 1, 2, 1) == "small_conv" && planes(8, 13, 128, 64, 1, 2, 1) == "tile16");
     Q.acc_out_dev = fy;
     EXPECT(planes(128, 56, 64, 64, 1, 2, 0) == "small_conv_wide");
     Q.acc_out_dev = nullptr;
