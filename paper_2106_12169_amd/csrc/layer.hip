@@ -234,13 +234,14 @@ static bool try_mfma(const Problem &pr, MfmaParams &mp, void *stream, int &rc, S
     // the other form is the 64 x 64 tile (512 x 512, K = 128: 3.6 against 4.2; 1024 x 1024: 6.4 against 4.6), and at every
     // count where a 32 x 32 tile would be half empty of a large operand's rows (1 x 32000, K = 4096: 7.9 against 9.6; 25000 x 16, K =
     // 1024 4.1, 5.2; convolutions with up to 16 pixels, 3 x 3, 256 -> 16384 4.6, 4.8, but not with up to 16 channels, whose many
-    // pixels are gathered: 32 x 56 x 56, 64 -> 6 12.5, 8.8).  Convolutions of more than a tile per compute unit whose K is up to
-    // 32 words, two groups for four waves, only with a single group, wide loads and without pooling (one wave pools a tile):
-    // 300 to 500 tiles, us, 32 x 32 tiles after: 18 words 4.1, 3.9; 27 words 4.4, 4.2; pooled, 18 words 4.4, 3.9, 4 words 4.0,
-    // 3.7; 4 words, not pooled 3.6, 3.7.  Override MFMA_T16: 0 never, 4 or 8 the form with that many waves wherever it applies.
+    // pixels are gathered: 32 x 56 x 56, 64 -> 6 12.5, 8.8).  More than a tile per compute unit whose K is 17 to 32 words is two groups
+    // for four waves: ahead for matrices of one or two pairs of digits only (300 to 500 tiles, us, 32 x 32 tiles after: w1a2 10 %
+    // ahead; w3a3 5.2, 4.7; w5a5 9.0, 6.8; convolutions, 18 words 4.1, 3.9; 27 words 4.4, 4.2), and convolutions of a single group need
+    // wide loads and no pooling (one wave pools a tile; pooled, 18 words 4.4, 3.9; 4 words 4.0, 3.7, not pooled 3.6, 3.7).  Override
+    // MFMA_T16: 0 never, 4 or 8 the form with that many waves wherever it applies.
     const int t16 = ov(OV_MFMA_T16);
     const int64_t tiles16 = ceil_div(pr.M, 16) * ceil_div(pr.N, 16);
-    const bool two_groups = pr.conv && tiles16 > 256 && mp.Kw <= 32 && (mp.Kw > 16 || odd_words || mp.pool);
+    const bool two_groups = tiles16 > 256 && mp.Kw <= 32 && (pr.conv ? mp.Kw > 16 || odd_words || mp.pool : mp.Kw > 16 && mp.DA * mp.DB > 2);
     const bool half_empty = pr.M <= 16 || (pr.N <= 16 && !pr.conv);
     const bool few = (t == 32 || short_k) && ((tiles16 <= (short_k ? 1024 : 512) && !two_groups) || half_empty) && !other &&
                      ov(OV_MFMA_SHORTK) < 0;

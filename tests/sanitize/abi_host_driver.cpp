@@ -234,6 +234,13 @@ int main()
     (void)apnn_gemm(fw, fw, fy, 25000, 10, 1024, 1, 2, APNN_ENC_PM1, APNN_ENC_UNSIGNED, nullptr);
     EXPECT(g_kernel == "tile16");
     // more than 256 of them with two groups of K for four waves: the 32 x 32 tiles
+    auto product = [&](int64_t M, int64_t N, int64_t K, int p, int q) {
+        g_kernel.clear();
+        (void)apnn_gemm(fw, fw, fy, M, N, K, p, q, APNN_ENC_UNSIGNED, APNN_ENC_UNSIGNED, nullptr);
+        return g_kernel;
+    };
+    EXPECT(product(380, 321, 580, 5, 5) == "small_matrix" && product(380, 321, 512, 5, 5) == "tile16" && product(380, 321, 1030, 5, 5) == "tile16");
+    EXPECT(product(256, 256, 580, 5, 5) == "tile16" && product(380, 321, 580, 2, 4) == "tile16" && product(380, 321, 580, 3, 3) == "small_matrix");
     EXPECT(chosen(8, 13, 13, 64, 64, 3, 1, 2) == "small_conv" && chosen(8, 12, 12, 96, 64, 3, 1, 2) == "small_conv" && chosen(8, 13, 13, 128, 64, 3, 1, 2) == "tile16");
     EXPECT(chosen(8, 13, 13, 128, 64, 1, 0, 2) == "tile16" && chosen(8, 13, 13, 96, 64, 1, 0, 2) == "small_conv" && chosen(8, 11, 11, 64, 64, 3, 1, 2) == "tile16");
     EXPECT(apnn_debug_force("MFMA_NSPLIT", 1) == APNN_OK && chosen(64, 56, 56, 64, 64, 3, 1, 2) == "small_conv_wide");   // another form asked for
