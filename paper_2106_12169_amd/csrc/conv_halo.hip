@@ -6,27 +6,30 @@
 
 namespace apnn {
 
-// Few or short sums on few pixels are better off with the kernels that split K over more waves and start sooner.  The two
-// sides' times as fitted to measured layers (us; tiles of 32 x 32 outputs, entries = steps times feature digits a weight digit):
-//   those kernels, up to 4096 tiles: 3.5 + tiles (1.5 + 0.1 entries) / 1000, 1.4 times the second term with several digits
-//   this one, while a compute unit has a tile or two: 4.3 + entries (0.07 with weights that stay, else 0.09; 0.15 with several
-//   feature digits; 0.1 more with an odd number of channel words)
-// e.g. 9 steps on 8 x 56 x 56, 64 channels 6.9 and 5.1; 18 on 8 x 28 x 28, 128 channels 5.7 and 5.4; 36 on 8 x 14 x 14, 256
-// channels 6.2 and 7.7; 50 entries on 3420 pixels, 64 -> 224 channels 10.8 and 11.9; 3 on 6885, 160 -> 96 4.9 and 5.7.
-// And the chip wants most of its compute units busy: not below 96 tiles of 64 x 128 outputs (128 where the stride spreads the
-// pixels: 9 steps with stride 2 on 98 tiles 4.9 and 5.4).
-static bool worth_staging(const MfmaParams &mp, int tilesN)
+// Up to 4096 tiles of 32 x 32 outputs: few or short sums on few pixels are better off with the kernels that split K over more waves
+// and start sooner.  Both sides' times (us), as fitted to 4800 layers of 64 tiles and more, each measured in every form in a replayed
+// graph:
+//   those kernels: 2.9, and for 1000 tiles 1.5 + 0.11 for each pair of K words and pair of digits (0.06 with features of one
+//     plane) + 0.65 with a residual; 1.3 times that with several digits
+//   this one: 4.4, and for each of its entries (steps times pairs of digits) 0.08, 0.15, 0.12 where the channel words are a multiple
+//     of four, even, odd; 0.03 more where the weights pass through in chunks; 1.55 times that with pooling (a block has as many
+//     pixels before it); 0.04 for each channel word and digit of the pixels that a stride skips; all that again for each further
+//     round of blocks that do not fit the compute units together; beyond 256 blocks, 0.8 + 0.08 entries for as many more;
+//     0.65 for 256 blocks of int32 results
+// What the rule chooses is on average 0.4 % slower than the faster side (0.8 % with a rule that knew no rounds and one time an
+// entry), and of 3700 other layers 1.8 % came out 2 % and more slower than without this form (9.7 % of them before, up to 1.7
+// times).  E.g. 9 steps on 8 x 56 x 56, 64 channels 6.3 there and 4.9 here; 4 x 56 x 56 4.6, 4.8; 18 on 8 x 28 x 28, 128 channels
+// 5.3 and 5.3, with a residual 5.8, 5.5; 9 on 8 x 28 x 28, 64 -> 128 channels 4.6, 4.9; 36 on 4 x 28 x 28, 256 channels 8.3, 7.4.
+static bool worth_staging(const MfmaParams &mp, int64_t tiles, int64_t blocks, int64_t steps, bool stay, int64_t rounds)
 {
-    const int64_t blocks = ceil_div(mp.M, mp.pool ? 256 : 128) * tilesN;
-    if (blocks < (mp.stride > 1 ? 128 : 96)) return false;
-    const int64_t tiles = ceil_div(mp.M, 32) * ceil_div(mp.N, 32);
-    const int64_t steps = static_cast<int64_t>(mp.R) * mp.S * ((mp.Cw + 1) / 2);
-    if (mp.Y && steps <= 2) return false;                // int32 results: their store is all there is (192 channels, 10.3 and 10.6)
-    if (tiles > 4096) return true;
-    const double entries = static_cast<double>(steps * mp.DA * mp.DB);
-    const double other = 3.5 + 1e-3 * tiles * (1.5 + 0.1 * entries) * (mp.DA * mp.DB > 1 ? 1.4 : 1.0);
-    const double per_entry = (mp.DA > 1 ? 0.15 : mp.DB == 1 && steps <= kHaloStay ? 0.07 : 0.09) + (mp.Cw % 2 != 0 ? 0.1 : 0.0);
-    return 4.3 + per_entry * entries <= other;
+    const double pairs = static_cast<double>(mp.DA) * mp.DB, entries = steps * pairs;
+    const double other = 2.9 + 1e-3 * tiles * (1.5 + (mp.PA == 1 ? 0.06 : 0.11) * 0.5 * mp.Kw * pairs + (mp.res ? 0.65 : 0.0)) * (pairs > 1 ? 1.3 : 1.0);
+    const double spread = 0.04 * (static_cast<double>(mp.stride) * mp.stride - 1) * mp.DA * mp.Cw;
+    double each = (mp.Cw % 4 == 0 ? 0.08 : mp.Cw % 2 == 0 ? 0.15 : 0.12) + (stay ? 0.0 : 0.03);
+    double staged = 4.4 + (mp.Y ? 0.65 / 256 * blocks : 0.0);
+    if (mp.pool) each *= 1.55;
+    else if (blocks > 256) staged += (blocks / 256.0 - 1.0) * (0.8 + 0.08 * entries);
+    return staged + rounds * (spread + each * entries) <= other;
 }
 
 bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB, int force, hipStream_t st)
@@ -36,7 +39,13 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
     const bool planes = mp.out && !mp.Y && !mp.T && mp.q_out <= 2 && (!mp.res || mp.q_res <= 2);
     if (!ints && !planes) return false;
     const int tilesN = static_cast<int>(ceil_div(mp.N, 64));
-    if (force < 0 && !worth_staging(mp, tilesN)) return false;
+    // The chip wants most of its compute units busy: not below 96 tiles of 64 x 128 outputs (128 where the stride spreads the pixels).
+    const int64_t blocks = ceil_div(mp.M, mp.pool ? 256 : 128) * tilesN;             // of the smaller tiles
+    if (force < 0 && blocks < (mp.stride > 1 ? 128 : 96)) return false;
+    // int32 results of one or two steps: their store is all there is (192 channels, 10.3 and 10.6).  Beyond 4096 tiles of 32 x 32
+    // the other side has 32 x 64 tiles for every 64 channels, and is ahead for 1 x 1 layers: on average 1.15 times as fast.
+    const int64_t small_tiles = ceil_div(mp.M, 32) * ceil_div(mp.N, 32), steps = static_cast<int64_t>(mp.R) * mp.S * ((mp.Cw + 1) / 2);
+    if (force < 0 && mp.Y && (steps <= 2 || (small_tiles > 4096 && mp.N % 64 == 0 && mp.R == 1 && mp.S == 1))) return false;
     const int64_t Hq = mp.H + 2 * static_cast<int64_t>(mp.pad), Wq = mp.W + 2 * static_cast<int64_t>(mp.pad);
     const int64_t Kw = static_cast<int64_t>(mp.R) * mp.S * mp.Cw, lim = int64_t(1) << 31;
     // (in 64 bits from the first factor on: four times the channels alone can pass 2^31)
@@ -60,7 +69,7 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
     p.digits = divisor(p.DA); p.halves = divisor(p.half);
     p.pm1 = kindB == OPK_PM1;
     p.pool = mp.pool;
-    p.steps = static_cast<int>(Kw / mp.Cw) * p.half;
+    p.steps = static_cast<int>(steps);
     p.scale = mp.scale; p.bias = mp.bias; p.res = mp.res; p.q_res = mp.q_res; p.res_scale = mp.res_scale;
     p.out = mp.out; p.q_out = mp.q_out; p.NW = mp.NW; p.Y = mp.Y;
     // a two-plane digit enters as half its value; planes are made of a quarter of the result
@@ -116,10 +125,14 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
     //   on 784 tiles 47, 59 (256 either way)
     // Pooled: 64 x 128 pooled outputs a block (a wave has both channel tiles), or 64 x 64 (one; fewer and smaller blocks fill the
     // chip): 36 steps on 196 of the larger tiles 12.4, 18.0; 72 on 104 20.1, 16.0; 36 on 98 12, 9.9; 9 on 784 21.5, 20.9.
-    int fp = mp.pool ? 4 : 1;
+    int fp = mp.pool ? 3 : 1;
     Tiling t = tiling(fp);
+    if (t.blocks < 1) return false;
+    if (force < 0 && small_tiles <= 4096 && !worth_staging(mp, small_tiles, blocks, steps, stay, t.buffers == 2 ? 1 : ceil_div(blocks, 256 * t.blocks)))
+        return false;
     if (mp.pool) {
-        if (force == 1 || (force < 0 && t.tilesM * tilesN < 150) || t.blocks < 1) t = tiling(fp = 3);
+        const Tiling four = tiling(4);
+        if (force != 1 && (force == 2 || four.tilesM * tilesN >= 150) && four.blocks >= 1) { fp = 4; t = four; }
     } else {
         const Tiling two = tiling(2);
         fp = force == 1 || force == 2 ? force
@@ -129,6 +142,15 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
     }
     const int64_t tiles = t.tilesM * tilesN;
     if (t.blocks < 1 || tiles > kMaxBlocks) return false;
+    // Beyond 4096 tiles of 32 x 32: not where staging a tile's pixels is most of the work and little else of the compute unit runs
+    // meanwhile.  Matrix instructions of 32 x 32 x 64 for 1000 staged words, and the time relative to the other kernels, on average
+    // over 4900 layers: blocks with one tile, one block to a compute unit 2.1 up to 1.4, 1.2 and 1.1 up to 5.7, 0.8 up to 11, 0.6 to
+    // 0.7 beyond; two blocks 1.3 up to 1.4, 0.75 beyond; three 1.0 and 0.75; blocks that walk, one 1.8 up to 1.4, 0.9 beyond,
+    // two and more 0.6 (72 x 72, 288 -> 320 channels, 1 x 1, stride 2, pooled, batch 74: 98.6 us and 29.9).
+    if (force < 0 && small_tiles > 4096) {
+        const double work = static_cast<double>(steps) * mp.DA * mp.DB * (fp == 3 ? 256 : 128 * fp) / 64, words = 1e-3 * t.records;
+        if (work < words * (t.buffers == 2 ? (t.blocks == 1 ? 2.0 : 0.0) : t.blocks == 1 ? 6.0 : 1.5)) return false;
+    }
     int64_t grid = tiles;
     if (t.buffers == 2) grid = 256 * t.blocks / tilesN * tilesN;           // whole rows of channel tiles
     p.tilesM = static_cast<int>(t.tilesM);

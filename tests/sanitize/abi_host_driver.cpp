@@ -215,7 +215,6 @@ int main()
     EXPECT(apnn_debug_force("MFMA_SMALL", -1) == APNN_OK);
     EXPECT(chosen(64, 56, 56, 64, 64, 3, 1, 2) == "small_conv_wide" && chosen(64, 56, 56, 64, 96, 3, 1, 2) == "small_conv");
     EXPECT(chosen(1, 14, 14, 64, 64, 3, 1, 2) == "small_conv");                                             // few tiles: K split
-
     // eight waves a tile: from 72 words of K on up to 512 tiles, from six groups a wave of four on up to 1024
     EXPECT(chosen(4, 14, 14, 256, 512, 3, 1, 2) == "small_conv" && g_nsplit == 8 && chosen(4, 14, 14, 128, 512, 3, 1, 2) == "small_conv" && g_nsplit == 4);
     EXPECT(chosen(4, 28, 28, 256, 256, 3, 1, 2) == "small_conv" && g_nsplit == 4 && chosen(8, 28, 28, 128, 128, 3, 1, 4) == "small_conv" && g_nsplit == 4);
@@ -226,8 +225,11 @@ int main()
     apnn_debug_reset();
     EXPECT(chosen(64, 56, 56, 64, 64, 3, 1, 2) == "conv_halo" && g_stay && g_halo.bytesA == 64u * 56 * 56 * 16 && g_halo.bytesB == 64 * 9 * 8);
     EXPECT(chosen(64, 56, 56, 64, 96, 3, 1, 2) == "conv_halo" && g_halo.per_column.d == 2);
-    EXPECT(chosen(1023, 128, 128, 512, 64, 3, 1, 2) == "conv_halo" && !g_stay);
-    EXPECT(chosen(1024, 128, 128, 512, 64, 3, 1, 2) == "small_conv");                                      // features of 2^31 bytes
+    EXPECT(chosen(85598, 14, 14, 512, 64, 3, 1, 2) == "conv_halo" && !g_stay);
+    EXPECT(chosen(85599, 14, 14, 512, 64, 3, 1, 2) == "small_conv");                                       // features of 2^31 bytes
+    // large layers: not where a block of one tile has little to do with what it stages, nor int32 results of few steps
+    EXPECT(chosen(25, 65, 65, 512, 512, 1, 0, 4) == "small_conv_wide" && chosen(25, 65, 65, 512, 512, 3, 1, 4) == "conv_halo");
+    EXPECT(chosen(64, 56, 56, 128, 64, 1, 0, 2) == "small_conv_wide" && chosen(64, 56, 56, 128, 96, 1, 0, 2) == "small_conv");
     // few outputs, or rows of matrices or pixels that would be half of a 32 x 32 tile; not many pixels of few channels
     EXPECT(chosen(1, 14, 14, 64, 64, 3, 1, 2) == "tile16" && chosen(1, 3, 3, 256, 16384, 3, 0, 2) == "tile16");
     EXPECT(chosen(32, 56, 56, 64, 6, 3, 1, 2) == "small_conv" && chosen(32, 56, 56, 96, 10, 1, 0, 2) == "small_conv");
@@ -267,6 +269,23 @@ int main()
     };
     EXPECT(planes(128, 56, 64, 64, 1, 2, 0) == "conv_halo" && g_stay && g_fp == 2);
     EXPECT(planes(128, 56, 64, 64, 1, 3, 0) == "small_conv_wide" && planes(128, 56, 64, 64, 1, 2, 1) == "conv_halo" && g_fp == 4);
+    auto pointwise = [&](int64_t images, int64_t hw, int64_t Cin, int64_t Cout, int stride, int q, int pool) {
+        Q.conv = apnn_conv_desc{images, hw, hw, Cin, Cout, 1, 1, stride, 0, 1, q, APNN_ENC_PM1, APNN_ENC_UNSIGNED};
+        Q.q_out = 2; Q.pool = pool;
+        g_kernel.clear();
+        (void)apnn_layer(&Q, fw, fw, static_cast<uint32_t *>(fake), nullptr);
+        return g_kernel;
+    };
+    EXPECT(pointwise(128, 56, 64, 128, 2, 2, 0) == "conv_halo" && pointwise(128, 28, 512, 256, 1, 2, 0) == "conv_halo");
+    EXPECT(pointwise(74, 72, 288, 320, 2, 1, 1) == "small_conv_wide");
+    EXPECT(pointwise(73, 125, 640, 128, 1, 3, 0) == "small_conv_wide");
+    // either side of the staged convolutions' rule, and of the pooled 16 x 16 tiles'
+    EXPECT(planes(8, 56, 64, 64, 1, 2, 0) == "conv_halo" && planes(4, 56, 64, 64, 1, 2, 0) == "small_conv" && g_nsplit == 4);
+    EXPECT(planes(8, 28, 128, 128, 1, 2, 0) == "small_conv" && planes(12, 28, 128, 128, 1, 2, 0) == "conv_halo");
+    EXPECT(planes(8, 28, 64, 128, 1, 2, 0) == "small_conv" && planes(12, 28, 192, 128, 1, 2, 0) == "small_conv");
+    Q.residual_dev = static_cast<const uint32_t *>(fake); Q.q_res = 2;
+    EXPECT(planes(8, 28, 128, 128, 1, 2, 0) == "conv_halo");
+    Q.residual_dev = nullptr;
     EXPECT(planes(8, 13, 64, 64, 1, 2, 1) == "small_conv" && planes(8, 13, 128, 64, 1, 2, 1) == "tile16");
     Q.acc_out_dev = fy;
     EXPECT(planes(128, 56, 64, 64, 1, 2, 0) == "small_conv_wide");
