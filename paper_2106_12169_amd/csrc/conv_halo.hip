@@ -145,11 +145,12 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
     // Beyond 4096 tiles of 32 x 32: not where staging a tile's pixels is most of the work and little else of the compute unit runs
     // meanwhile.  Matrix instructions of 32 x 32 x 64 for 1000 staged words, and the time relative to the other kernels, on average
     // over 4900 layers: blocks with one tile, one block to a compute unit 2.1 up to 1.4, 1.2 and 1.1 up to 5.7, 0.8 up to 11, 0.6 to
-    // 0.7 beyond; two blocks 1.3 up to 1.4, 0.75 beyond; three 1.0 and 0.75; blocks that walk, one 1.8 up to 1.4, 0.9 beyond,
-    // two and more 0.6 (72 x 72, 288 -> 320 channels, 1 x 1, stride 2, pooled, batch 74: 98.6 us and 29.9).
+    // 0.7 beyond; two blocks 1.3 up to 1.4, 0.75 beyond; three 1.0 up to 1.4, four 0.8; blocks that walk, one 1.8 up to 1.4, 0.9
+    // beyond, two and more 0.6 (72 x 72, 288 -> 320 channels, 1 x 1, stride 2, pooled, batch 74: 98.6 us and 29.9).
     if (force < 0 && small_tiles > 4096) {
         const double work = static_cast<double>(steps) * mp.DA * mp.DB * (fp == 3 ? 256 : 128 * fp) / 64, words = 1e-3 * t.records;
-        if (work < words * (t.buffers == 2 ? (t.blocks == 1 ? 2.0 : 0.0) : t.blocks == 1 ? 6.0 : 1.5)) return false;
+        const double least = t.buffers == 2 ? (t.blocks == 1 ? 2.0 : 0.0) : t.blocks == 1 ? 6.0 : t.blocks == 2 ? 1.5 : 0.0;
+        if (work < least * words) return false;
     }
     int64_t grid = tiles;
     if (t.buffers == 2) grid = 256 * t.blocks / tilesN * tilesN;           // whole rows of channel tiles

@@ -303,7 +303,7 @@ int main()
     };
     EXPECT(input_pixels(8, 3, 224, 224, 7, 2, 3) == 512 && g_grid == 8 * 112 * 112 / 512);
     EXPECT(input_pixels(5, 4, 55, 55, 3, 3, 1) == 128);
-    EXPECT(input_pixels(1000, 4, 55, 55, 3, 3, 1) == 512);
+    EXPECT(input_pixels(64, 3, 56, 56, 3, 1, 1) == 512);
     EXPECT(input_pixels(1, 3, 224, 224, 11, 4, 2) == 512);
     // LDS is asked for once on every device that the kernel runs on; where it is refused the other kernel takes the layer
     auto asks = [&](int device) {
