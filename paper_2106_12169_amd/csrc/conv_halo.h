@@ -11,10 +11,11 @@
 // The matrix instruction gets the weights as its row operand, so that a lane holds sixteen channels of one pixel, and the
 // planes of their codes are made in the lane (plane_codes.h).
 //
-// Bound by the vector instructions its waves issue (stage 1 of the ResNet-18 shape at batch 128: 510 a wave tile of 64 x 64
-// outputs, 2040 of the 2100 cycles a SIMD spends on one, 1152 of them under matrix instructions; prologue 2.5 us).  Measured
-// there, with and without residual: 46 and 32 us with lane-private loads, 16 and 15 here; 128 channels 29 and 23, 15 and 14;
-// 256 channels 29, 15; 512 channels 31, 16.
+// Bound by the vector instructions its waves issue up to 64 channels (stage 1 of the ResNet-18 shape at batch 128, by counters: a
+// SIMD issues them in 59 % of its cycles, its matrix unit is busy in 23 %; 650 a wave tile of 64 x 64 outputs, prologue
+// included), with more channels by what the two to four waves of a SIMD wait for in between (128 channels 44 and 23 %, 256 32
+// and 23 %, 512 28 and 21 %).  Measured there, with and without residual: 46 and 32 us with lane-private loads, 16 and 15 here;
+// 128 channels 29 and 23, 15 and 14; 256 channels 29, 15; 512 channels 31, 16.
 #pragma once
 #include "mfma_kernel.h"
 #include "plane_codes.h"

@@ -26,7 +26,9 @@ bool launch_conv_halo(const ConvHaloParams &p, int fp, unsigned grid, int lds, h
 
 template <int KA, bool MULTI, bool STAY> bool launch_conv_halo(const ConvHaloParams &p, int fp, unsigned grid, int lds, hipStream_t st)
 {
-    if constexpr (KA == OPK_U2 && !MULTI && !STAY) {     // 256 and 512 channels: granules of a tap known to the compiler
+    // 256 and 512 channels: granules of a tap known to the compiler, 23 instructions a step and not 33.  Every count would need an
+    // instance of its own (each is code that a first call fetches), so the other multiples of 128 take the general one.
+    if constexpr (KA == OPK_U2 && !MULTI && !STAY) {
         if (p.Cw == 8) return launch_conv_halo<KA, 2, 4, 2, MULTI, STAY>(p, fp, grid, lds, st);
         if (p.Cw == 16) return launch_conv_halo<KA, 2, 4, 4, MULTI, STAY>(p, fp, grid, lds, st);
     }

@@ -12,7 +12,8 @@
 //
 // Measured (64 channels, 7 x 7, stride 2, 224 x 224, batch 128 and 8): 41.7 and 6.1 us, with input_conv_kernel 80.0 and 10.4;
 // 3 x 3, stride 1: 118 and 12.3, 259 and 20.9; 11 x 11, stride 4: 20.6 and 8.1, 54.4 and 9.8.  Bound by vector instructions
-// (7 x 7: 77 % of the issue slots; 636 a wave, half of them staging, 130 a channel tile for the planes).
+// (7 x 7, batch 128, by counters: issued in 77 % of a SIMD's cycles; 640 a wave, half of them staging, 130 a channel tile for
+// the planes).  Small frames and batches are left to input_conv_kernel (the rule is where it is launched).
 #pragma once
 #include "mfma_kernel.h"
 #include "plane_codes.h"

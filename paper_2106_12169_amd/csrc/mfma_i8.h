@@ -1,11 +1,10 @@
 // Single-pass form of the arbitrary-precision product for operands of more than
 // two bits, on the 8-bit integer matrix instruction (v_mfma_i32_32x32x32_i8).
 //
-// The bit planes of the ABI stay packed in HBM and in LDS.  Per lane and in
-// registers, the plane words of 32 K positions are transposed into 32 bytes, each
-// holding all the bits of one element (Eq. 2 read backwards: the decoded integer),
-// and one matrix instruction multiplies 32 x 32 x 32 of them with int32
-// accumulation.  Where the 1-bit emulation takes p q plane-pair passes and the
+// The bit planes of the ABI stay packed in HBM.  The plane words of 32 K positions
+// are transposed into 32 bytes, each holding all the bits of one element (Eq. 2
+// read backwards: the decoded integer), once per block on their way to LDS, and one
+// matrix instruction multiplies 32 x 32 x 32 of them with int32 accumulation.  Where the 1-bit emulation takes p q plane-pair passes and the
 // two-plane FP4 form ceil(p/2) ceil(q/2) digit passes, this takes one; the paper
 // observes the same about built-in 8-bit arithmetic once operands grow (Sec. 6.1.1).
 // Results are the same integers (no range condition: the accumulator is int32, as
@@ -39,9 +38,9 @@
 // at bit 8 g + j.
 //
 // Measured (us; a form in which every wave transposed for itself, and this one): 2048^3 w3a5 24.9, 22.0; w4a4 20.4, 19.8; w5a5
-// 34.5, 23.5; w8a8 40.4, 28.0; 1024^3 w3a5 13.1, 11.0; 4096^3 w3a5 132, 118, w8a8 256, 168.  What is left at 2048^3 w3a5: per
-// chunk, without loads, 780 cycles of reads and matrix instructions (512 of them the matrix unit's) and 740 of
-// transposition, which overlap to 1340 only.
+// 34.5, 23.5; w8a8 40.4, 28.0; 1024^3 w3a5 13.1, 11.0; 4096^3 w3a5 132, 118, w8a8 256, 168.  At 2048^3 w3a5, by counters, a
+// SIMD issues vector instructions in 33 % of its cycles and its matrix unit is busy in 20 %: the halves of a block take turns
+// and meet at a barrier every chunk, and neither unit is the bound.
 #pragma once
 #include "mfma_big.h"
 

@@ -8,7 +8,8 @@
 // waves hide each other's latency where K is long.  Measured on w1a2 products in a replayed graph, 32 x 32 tiles before,
 // this after (us): 8 x 4096, K = 25088 16.9, 7.5; K = 9216 7.1, 4.9; K = 4096 5.0, 3.9; 64 x 1024, K = 1024 4.0, 3.3;
 // 128 x 128, K = 128 (64 x 64 tile before) 4.1, 3.2.  Convolutions: 7 x 7 of 512 channels to 8 x 1 x 1 x 4096 16.5, 8.8;
-// 3 x 3, 384 -> 256 channels at 13 x 13 5.9, 4.4.
+// 3 x 3, 384 -> 256 channels at 13 x 13 5.9, 4.4.  (A call outside a graph costs the host 3.5 to 4 us: of the smallest of these it
+// shows nothing.)
 // Four and eight waves are one kernel, two groups in flight: a network's first pass fetches every instance's code from memory, and
 // a second one for eight waves (four groups in flight) made that of the AlexNet shape at batch 1 5 to 10 us longer without
 // being faster after it (46.1 us either way).
