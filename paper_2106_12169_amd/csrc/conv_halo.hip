@@ -144,12 +144,12 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
     if (t.blocks < 1 || tiles > kMaxBlocks) return false;
     // Beyond 4096 tiles of 32 x 32: not where staging a tile's pixels is most of the work and little else of the compute unit runs
     // meanwhile.  Matrix instructions of 32 x 32 x 64 for 1000 staged words, and the time relative to the other kernels, on average
-    // over 4900 layers: blocks with one tile, one block to a compute unit 2.1 up to 1.4, 1.2 and 1.1 up to 5.7, 0.8 up to 11, 0.6 to
-    // 0.7 beyond; two blocks 1.3 up to 1.4, 0.75 beyond; three 1.0 up to 1.4, four 0.8; blocks that walk, one 1.8 up to 1.4, 0.9
+    // over 4900 layers: blocks with one tile, one block to a compute unit 2.1 up to 1.4, 1.2 up to 2.8, 1.1 up to 5.7 (level from 4.5 on),
+    // 0.8 up to 11, 0.6 to 0.7 beyond; two blocks 1.3 up to 1.4, 0.75 beyond; three 1.0 up to 1.4, four 0.8; blocks that walk, one 1.8 up to 1.4, 0.9
     // beyond, two and more 0.6 (72 x 72, 288 -> 320 channels, 1 x 1, stride 2, pooled, batch 74: 98.6 us and 29.9).
     if (force < 0 && small_tiles > 4096) {
         const double work = static_cast<double>(steps) * mp.DA * mp.DB * (fp == 3 ? 256 : 128 * fp) / 64, words = 1e-3 * t.records;
-        const double least = t.buffers == 2 ? (t.blocks == 1 ? 2.0 : 0.0) : t.blocks == 1 ? 6.0 : t.blocks == 2 ? 1.5 : 0.0;
+        const double least = t.buffers == 2 ? (t.blocks == 1 ? 2.0 : 0.0) : t.blocks == 1 ? 4.5 : t.blocks == 2 ? 1.5 : 0.0;
         if (work < least * words) return false;
     }
     int64_t grid = tiles;
