@@ -315,16 +315,18 @@ static bool try_input_tile(const MfmaParams &p, const InputParams &q, int64_t im
     const int64_t lds = 4 * (64 + 32) * nt + 16 * q.KS + 1024 * static_cast<int64_t>(q.KS) * nt + q.C * copies * plane;
     if (lds > 160 * 1024 || 32 * nt + 4 * q.KS > 512) return false;
     // Few blocks wait for their image rows with nothing beside them: the rule compares, in us, the eight-byte loads of a thread that
-    // stages (in every copy and channel, in every round of blocks) with what the other kernel spends more on planes, on its K
-    // steps, and, by the share of the chip's compute units that have a block, on loading and shifting each segment for itself.
-    // Fitted to 10800 layers of 1 to 2000 blocks measured both ways: 1.2 % of them are 5 % and more slower than with the other
-    // kernel alone (25 % without a rule, up to twice as slow); e.g. 55 x 55, stride 3, 3 x 3, four channels, 5 images 7.2 staged, 4.0;
-    // 7 x 7, stride 2, 224 x 224, batch 8 6.1, 10.4.
+    // stages (in every copy and channel, in every round of blocks) with what the other kernel spends more on planes, on its
+    // batches of six K steps, a memory round trip each, and, by the share of the chip's compute units that have a block, on
+    // loading and shifting each segment for itself.  Fitted to 10800 layers of 1 to 2000 blocks measured both ways: what it chooses
+    // is on average 0.4 % slower than the faster side, 0.7 % of the layers are 5 % and more slower than with the other kernel alone
+    // (25 % without a rule, up to twice as slow); e.g. 55 x 55, stride 3, 3 x 3, four channels, 5 images 7.2 staged, 4.0; 9 x 9, stride 2,
+    // one image of 138 x 138, 32 channels 5.8, 7.1; 7 x 7, stride 2, 224 x 224, batch 8 6.1, 10.4.
     if (force < 0) {
         const double loads = static_cast<double>(ceil_div(lines * (pitch / 8), 512)) * q.C * copies, share = p.M / 131072.0, ks = q.KS;
         const double rounds = static_cast<double>(ceil_div(ceil_div(p.M, 512), 256 * (lds > 80 * 1024 ? 1 : 2)));
-        const double planes = nt * (p.q_out == 2 ? 1.0 : 0.0);
-        const double more = nt * (0.1 + 0.02 * ks) + 0.01 * ks + 0.5 * planes - 0.4 + share * (1.0 + 0.3 * nt + 0.3 * planes + ks * (0.25 + 0.05 * nt));
+        const double batches = static_cast<double>(ceil_div(q.KS, 6) - 1), two_planes = p.q_out == 2 ? 0.69 : 0.0;
+        const double more = nt * (0.27 + two_planes) - 0.38 + batches * (0.53 + 0.41 * nt) - ks * (0.079 + 0.027 * nt) +
+                            share * (0.9 + 0.3 * nt + ks * (0.22 + 0.08 * nt));
         if (loads * (0.085 * rounds + 0.02 * share) > more) return false;
     }
     t.pitch = static_cast<int>(pitch); t.plane = static_cast<int>(plane);
