@@ -141,9 +141,11 @@ static bool try_int8(const Problem &pr, MfmaParams &mp, bool fp4_exact, void *st
     if (force < 1) {
         const int passes = ((pr.PA + 1) / 2) * ((pr.PB + 1) / 2);
         // outputs from which the tiles occupy the chip: 768 x 768 w3a5, K = 1024 10.7 against 13.4 us (512 x 512 8.2, 7.3), with a narrow
-        // operand 64 tiles (1024^3 w2a8 12.1 against 13.4, 768 x 768 11.7, 10.6)
+        // operand 64 tiles (1024^3 w2a8 12.1 against 13.4, 768 x 768 11.7, 10.6); four passes over a short K on fewer tiles are over sooner
+        // (1205 x 522, K = 208, w3a3 7.2 against 6.3; 240 x 2335, K = 701 9.5, 7.8; from K = 1500 on level and less)
         const bool narrow = passes == 4 && !(pr.PA > 2 && pr.PB > 2);
-        const bool faster = narrow ? tiles >= 64 && tiles <= 256 : passes >= 4 && pr.M * pr.N >= (int64_t(1) << 19);
+        const bool faster = narrow ? tiles >= 64 && tiles <= 256
+                                   : passes >= 4 && pr.M * pr.N >= (int64_t(1) << 19) && (passes > 4 || tiles >= 64 || pr.Ktotal >= 1500);
         if (fp4_exact && !faster) return false;
     }
     const int64_t lim = int64_t(1) << 31;       // operands and output are addressed with 31-bit byte offsets

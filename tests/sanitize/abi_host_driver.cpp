@@ -241,6 +241,8 @@ int main()
         (void)apnn_gemm(fw, fw, fy, M, N, K, p, q, APNN_ENC_UNSIGNED, APNN_ENC_UNSIGNED, nullptr);
         return g_kernel;
     };
+    EXPECT(product(1205, 522, 208, 3, 3) != "i8" && product(1205, 522, 1500, 3, 3) == "i8" && product(1205, 522, 208, 3, 5) == "i8");
+    EXPECT(product(1024, 1024, 208, 3, 3) == "i8" && product(512, 1000, 2048, 3, 3) != "i8");
     EXPECT(product(380, 321, 580, 5, 5) == "small_matrix" && product(380, 321, 512, 5, 5) == "tile16" && product(380, 321, 1030, 5, 5) == "tile16");
     EXPECT(product(256, 256, 580, 5, 5) == "tile16" && product(380, 321, 580, 2, 4) == "tile16" && product(380, 321, 580, 3, 3) == "small_matrix");
     EXPECT(chosen(8, 13, 13, 64, 64, 3, 1, 2) == "small_conv" && chosen(8, 12, 12, 96, 64, 3, 1, 2) == "small_conv" && chosen(8, 13, 13, 128, 64, 3, 1, 2) == "tile16");
