@@ -7,28 +7,33 @@
 namespace apnn {
 
 // Up to 4096 tiles of 32 x 32 outputs: few or short sums on few pixels are better off with the kernels that split K over more waves
-// and start sooner.  Both sides' times (us), as fitted to 4800 layers of 64 tiles and more, each measured in every form in a replayed
-// graph:
-//   those kernels: 2.9, and for 1000 tiles 1.5 + 0.11 for each pair of K words and pair of digits (0.06 with features of one
-//     plane) + 0.65 with a residual; 1.3 times that with several digits
-//   this one: 4.4, and for each of its entries (steps times pairs of digits) 0.08, 0.15, 0.12 where the channel words are a multiple
-//     of four, even, odd; 0.03 more where the weights pass through in chunks; 1.55 times that with pooling (a block has as many
-//     pixels before it); 0.04 for each channel word and digit of the pixels that a stride skips; all that again for each further
-//     round of blocks that do not fit the compute units together; beyond 256 blocks, 0.8 + 0.08 entries for as many more;
-//     0.65 for 256 blocks of int32 results
-// What the rule chooses is on average 0.4 % slower than the faster side (0.8 % with a rule that knew no rounds and one time an
-// entry), and of 3700 other layers 1.8 % came out 2 % and more slower than without this form (9.7 % of them before, up to 1.7
-// times).  E.g. 9 steps on 8 x 56 x 56, 64 channels 6.3 there and 4.9 here; 4 x 56 x 56 4.6, 4.8; 18 on 8 x 28 x 28, 128 channels
-// 5.3 and 5.3, with a residual 5.8, 5.5; 9 on 8 x 28 x 28, 64 -> 128 channels 4.6, 4.9; 36 on 4 x 28 x 28, 256 channels 8.3, 7.4.
+// and start sooner.  Both sides' times (us), as fitted to 16000 layers of 64 tiles and more, each measured in every form in a
+// replayed graph:
+//   those kernels: 2.95, and for 1000 tiles 1.5, for each pair of K words and pair of digits 0.11, 0.095, 0.125 where the channel
+//     words are a multiple of four, even, odd (a little over half of it with features of one plane, a tenth more with weights of
+//     several where the words are not odd), 0.05 more for odd ones from the fortieth pair on, 0.75 with a residual; 1.3 times
+//     that with several digits
+//   this one: 4.4, and for each of its entries (steps times pairs of digits) 0.08 where the channel words are a multiple of four,
+//     else 0.125; 0.03 more where the weights pass through in chunks; 1.6 times that with pooling (a block has as many pixels
+//     before it); 0.065 for each channel word and digit of the pixels that a stride skips; all that again for each further round
+//     of blocks that do not fit the compute units together; beyond 256 blocks, 1 + 0.07 entries for as many more; 0.75 for 256
+//     blocks of int32 results
+// What the rule chooses is on average 0.6 % slower than the faster side (1.2 % with a rule that knew no rounds and one time an entry),
+// and 1 % of the layers are 5 % and more slower than without this form (4 % with that rule, up to 1.7 times).  E.g. 9 steps on 8 x
+// 56 x 56, 64 channels 6.3 there and 4.9 here; 4 x 56 x 56 4.6, 4.8; 18 on 8 x 28 x 28, 128 channels 5.3 and 5.3, with a residual
+// 5.8, 5.5; 9 on 8 x 28 x 28, 64 -> 128 channels 4.6, 4.9; 36 on 4 x 28 x 28, 256 channels 8.3, 7.4.
 static bool worth_staging(const MfmaParams &mp, int64_t tiles, int64_t blocks, int64_t steps, bool stay, int64_t rounds)
 {
-    const double pairs = static_cast<double>(mp.DA) * mp.DB, entries = steps * pairs;
-    const double other = 2.9 + 1e-3 * tiles * (1.5 + (mp.PA == 1 ? 0.06 : 0.11) * 0.5 * mp.Kw * pairs + (mp.res ? 0.65 : 0.0)) * (pairs > 1 ? 1.3 : 1.0);
-    const double spread = 0.04 * (static_cast<double>(mp.stride) * mp.stride - 1) * mp.DA * mp.Cw;
-    double each = (mp.Cw % 4 == 0 ? 0.08 : mp.Cw % 2 == 0 ? 0.15 : 0.12) + (stay ? 0.0 : 0.03);
-    double staged = 4.4 + (mp.Y ? 0.65 / 256 * blocks : 0.0);
-    if (mp.pool) each *= 1.55;
-    else if (blocks > 256) staged += (blocks / 256.0 - 1.0) * (0.8 + 0.08 * entries);
+    const bool fours = mp.Cw % 4 == 0, odd = mp.Cw % 2 != 0;
+    const double pairs = static_cast<double>(mp.DA) * mp.DB, entries = steps * pairs, words = 0.5 * mp.Kw * pairs;
+    const double word = (odd ? 0.125 : fours ? 0.11 : 0.095) * (mp.PA == 1 ? 0.56 : 1.0) * (mp.PB > 1 && !odd ? 1.1 : 1.0);
+    const double tile = 1.5 + word * words + (odd && words > 40 ? 0.05 * (words - 40) : 0.0) + (mp.res ? 0.75 : 0.0);
+    const double other = 2.95 + 1e-3 * tiles * tile * (pairs > 1 ? 1.3 : 1.0);
+    const double spread = 0.065 * (static_cast<double>(mp.stride) * mp.stride - 1) * mp.DA * mp.Cw;
+    double each = (fours ? 0.08 : 0.125) + (stay ? 0.0 : 0.03);
+    double staged = 4.4 + (mp.Y ? 0.75 / 256 * blocks : 0.0);
+    if (mp.pool) each *= 1.6;
+    else if (blocks > 256) staged += (blocks / 256.0 - 1.0) * (1.0 + 0.07 * entries);
     return staged + rounds * (spread + each * entries) <= other;
 }
 
