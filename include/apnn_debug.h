@@ -24,8 +24,10 @@
  *   MFMA_FN       1 | 2: 32 x 32 or 32 x 64 wave tiles of the small-layer kernel
  *   MFMA_SHORTK   0: no special case for K <= 256
  *   MFMA_HALO     convolutions staged once per block: 0 never; 1 | 2: whenever it
- *                 applies, with 128 or 256 pixels a block (unset: not where
- *                 MFMA_TILE, _SMALL, _NSPLIT or _FN asks for another form)
+ *                 applies, with 128 or 256 pixels a block; 3 | 4: the same with
+ *                 128 channels a block, 5 | 6: features staged as bits, 7 | 8: as
+ *                 codes (unset: not where MFMA_TILE, _SMALL, _NSPLIT or _FN asks
+ *                 for another form)
  *   MFMA_T16      products with 16 x 16 tiles: 0 never; 4 | 8: wherever it applies,
  *                 with that many waves a block (unset: not where another of
  *                 these asks for another form)

@@ -2,20 +2,23 @@
 // give every compute unit a block.
 //
 // A block owns 32 FC output channels x 128 FP output pixels.  In raster order over a frame padded by `pad` on every side, the
-// pixels its taps touch are one contiguous range: the block stages the packed planes of that range in LDS once (the lane-private
-// kernels load and check every pixel once per tap and channel tile), padding as zero records, so that a tap is one added offset
-// and needs no range check.  Weights are expanded to FP4 codes while they are staged, chunk by chunk along K, and shared by
-// the block's four waves; features of two planes are stored as interleaved pairs of bits, which leaves five vector
-// instructions per 32 codes in the main loop.
+// pixels its taps touch are one contiguous range: the block stages that range in LDS once (the lane-private
+// kernels load and check every pixel once per tap and channel tile), padding as zero codes, so that a tap is one added offset
+// and needs no range check.  Features and weights become FP4 codes while they are staged, so the main loop only reads operands
+// and multiplies: a wave that is alone on its SIMD hides about four other instructions behind a matrix instruction, and five to
+// expand each fragment of features at every tap were most of what it issued (64 x 64 outputs a wave, the operands expanded in the
+// loop: 82 cycles a matrix instruction, here 54; 38 in a loop of nothing else).  Where twice the LDS for features costs
+// resident blocks, they are staged as pairs of bits (PACKED) and expanded in the loop.  Weights pass through in chunks: four lanes
+// share a row, since a lane a row made every load touch 64 cache lines (1024 a chunk and compute unit).  With more than 64
+// channels eight waves share the pixels of two pairs of channel tiles.
 //
 // The matrix instruction gets the weights as its row operand, so that a lane holds sixteen channels of one pixel, and the
 // planes of their codes are made in the lane (plane_codes.h).
 //
-// Bound by the vector instructions its waves issue up to 64 channels (stage 1 of the ResNet-18 shape at batch 128, by counters: a
-// SIMD issues them in 59 % of its cycles, its matrix unit is busy in 23 %; 650 a wave tile of 64 x 64 outputs, prologue
-// included), with more channels by what the two to four waves of a SIMD wait for in between (128 channels 44 and 23 %, 256 32
-// and 23 %, 512 28 and 21 %).  Measured there, with and without residual: 46 and 32 us with lane-private loads, 16 and 15 here;
-// 128 channels 29 and 23, 15 and 14; 256 channels 29, 15; 512 channels 31, 16.
+// Measured (us; lane-private loads, staged with the expansion in the loop, here): ResNet-18 shape at batch 128, 64 channels 32, 15.1,
+// 14.6; 128 22, 14.2, 12.9; 256 24, 13.6, 11.4; 512 28, 15.4, 13.8; 128 -> 256 with stride 2 14.5, 12.4, 10.1.  8 x 112 x 112, 128 channels,
+// pooled 19.7, 15.7, 10.8.  What is left: the board's matrix instructions take 20 to 22 ns each with such operands, which is 4.6 us of
+// these layers, and 77 % of the SIMDs have work (1568 wave tiles for 1024); launch, first loads and epilogue are 5 us.
 #pragma once
 #include "mfma_kernel.h"
 #include "plane_codes.h"
@@ -34,11 +37,14 @@ struct ConvHaloParams {
     int PA, PB, DA, DB;      // planes and base-4 digits of features / weights
     Divisor digits;          // DA
     int pm1;                 // weights -1/+1, else 0/1 planes
-    int rec;                 // words of a pixel's LDS record
-    int pieces, share;       // pieces a record is staged in, log2 of the threads that share it
-    int words_codes, words_records;          // LDS words of the weight codes, of one buffer of records
-    int steps, chunk;        // matrix steps of a weight digit, of a weight chunk
-    Divisor halves;          // half
+    int rec, plane;          // LDS words of a staged position's codes, from a channel word's codes to the next one's
+    int pieces, share;       // pieces a position is staged in, log2 of the threads that share it
+    int words_table, words_codes, words_records;     // LDS words of the step offsets, of them and the weight codes, of a buffer of feature codes
+    int steps, padded;       // matrix steps of a weight digit, of it as it is walked
+    int pairs, buffers;      // pairs of channel tiles of a block, buffers of feature codes
+    int packed;              // features are staged as bits, not as codes
+    Divisor halves, columns;                 // half, S
+    uint32_t second;         // bytes from the first step's codes to the second's
     int pool;                // 0 none, 1 maximum, 2 sum
     int scaleA, scaleB;      // block scales (exponent bytes) of features and weights
     Divisor per_column;      // channel tiles
@@ -55,34 +61,39 @@ struct ConvHaloParams {
 // Most weight steps that stay in LDS for all tiles of a block, and of a chunk of longer ones (2 KiB of codes a step)
 constexpr int kHaloStay = 26, kHaloChunk = 8;
 
-// HW: channel words (steps) read together from a record; SW: channel words of a plane staged together (HW = 2: 4; HW = 1: 2, or
-// 1 for an odd number of channel words); FP, FW: 32-pixel and 32-channel tiles of a wave (FW = 1: two waves share the pixels).
-// MULTI: features of more than one digit.
+// Steps whose operands a wave reads together: one step's four and more matrix instructions cover the latency of the next
+// one's reads, two instructions do not.
+constexpr int halo_granule(int fp, int fw) { return fp * fw >= 4 ? 1 : 2; }
+
+// SW: channel words of a plane staged together (4, 2, or 1 for an odd number of channel words); FP, FW: 32-pixel and 32-channel
+// tiles of a wave (FW = 1: two waves share the pixels).  MULTI: operands of more than one digit.
 // POOL (FP = 4): tile f of a wave holds member f of its 32 pooling grids, so that pooling is three instructions per output.
 // STAY: the weights stay in LDS while the block walks over its tiles of pixels (grid-stride), and the next tile's pixels are in
 // flight during the main loop.  Otherwise a block has one tile, and the weights pass through two buffers, a chunk each, with
 // one barrier per chunk.
-// PT: granules of a tap, 0 if known at run time only.  A lone wave of a SIMD issues an instruction every four or five cycles, and
-// long sums on few pixels leave it alone: with PT the offsets inside a tap are part of the loads (s4 of the ResNet-18 shape
-// at batch 128, 23 instructions a step instead of 33).
-template <int KA, int HW, int SW, int FP, int FW, int PT, bool POOL, bool MULTI, bool STAY>
-__global__ __launch_bounds__(256, FP == 1 ? 4 : FP * FW == 8 ? 2 : 3) void conv_halo_kernel(const ConvHaloParams p)
+template <int KA, int SW, int FP, int FW, int FC, bool POOL, bool MULTI, bool PACKED, bool STAY>
+__global__ __launch_bounds__(128 * FC, FC == 4 ? 2 : FP * FW == 8 ? 2 : FP == 1 && !STAY && !MULTI ? 4 : 3) void conv_halo_kernel(const ConvHaloParams p)
 {
     static_assert(!POOL || FP == 4, "a wave's four pixel tiles are the members of its pooling grids");
-    constexpr int PL = KA == OPK_U1 ? 1 : 2, GW = PL * HW;       // words of a granule: HW steps of a digit
-    constexpr int FC = 2;                                        // channel tiles of a block
+    constexpr int HW = SW == 8 ? 4 : SW == 4 ? 2 : 1, PW = SW == 8 ? 4 : SW;     // channel words of a weight load, of a piece of a pixel
+    constexpr int G = halo_granule(FP, FW);                      // steps of a granule
+    constexpr int E = MULTI ? 2 : 1;                             // LDS words of a table entry
+    constexpr int CW = PACKED ? 2 : 4;                           // LDS words of a channel word of a position
+    constexpr int NT = 128 * FC;                                 // threads: four waves for every two channel tiles
     constexpr int BP = 64 * FW * FP;                             // pixels of a tile
     constexpr int FETCH = STAY ? kHaloStay : kHaloChunk;         // weight steps in flight
-    constexpr int NI = (FETCH * FC + 4 * HW - 1) / (4 * HW);      // granules of them a thread has in flight
-    constexpr int U = SW == 1 ? 4 : 2;                           // staged pieces of pixels a thread has in flight
+    constexpr int NI = (FETCH * 2 + 4 * HW - 1) / (4 * HW);      // granules of them a thread has in flight
+    constexpr int U = PW == 1 ? 4 : 2;                           // staged pieces of pixels a thread has in flight
     extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
     float *const sP = reinterpret_cast<float *>(lds);            // scales, then biases / 4: [tile][half][register]
     uint32_t *const sB = lds + 64 * FC;                          // weight codes: [buffer][step][tile][lane][4]
-    uint32_t *const sA = sB + p.words_codes;                     // feature records: [buffer][pixel]
+    uint32_t *const sT = sB + p.words_codes - p.words_table;     // offsets of the entries
+    uint32_t *const sA = sB + p.words_codes;                     // feature codes: [buffer][digit][channel word][position][4]
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lr = lane & 31, lh = lane >> 5;
-    const int wc = FW == 1 ? wave & 1 : 0, wp = FW == 1 ? wave >> 1 : wave;    // first channel tile, pixels of this wave
+    const int wg = FC == 4 ? wave >> 2 : 0, w4 = FC == 4 ? wave & 3 : wave;    // pair of channel tiles, wave of the four that share it
+    const int wc = 2 * wg + (FW == 1 ? w4 & 1 : 0), wp = FW == 1 ? w4 >> 1 : w4;    // first channel tile, pixels of this wave
     // block -> channel tile, first tile of pixels
     const int tile0 = divide(static_cast<int>(blockIdx.x), p.per_column);
     const int n0 = (static_cast<int>(blockIdx.x) - tile0 * p.per_column.d) * 32 * FC;
@@ -94,55 +105,62 @@ __global__ __launch_bounds__(256, FP == 1 ? 4 : FP * FW == 8 ? 2 : 3) void conv_
     // ---- weights.  Packed output: matrix row -> channel as plane_codes.h says; int32 output: in order, four to a store.
     // Rows beyond the last channel read that channel's (their results are not stored); steps beyond the last, and the step a
     // lane half lacks when the number of channel words is odd, read the first words (the features are zero there).
-    const int wrow = lane & 31, wtile = lane >> 5;
+    // Four lanes share a row: (pair of granules, half).
+    const int wrow = (16 * w4 + (lane >> 2)) & 31, wtile = 2 * wg + (w4 >> 1), wh = lane & 1, wk = (lane >> 1) & 1;
     const int wch = p.Y ? wrow : code_channel_of_row(wrow);
     const int Kw = p.R * p.S * p.Cw;
     const uint32_t wlane = 4u * static_cast<uint32_t>(min(n0 + 32 * wtile + wch, p.N - 1) * (p.PB * Kw));
     uint32_t wv[NI][2][HW];
-    auto fetch_weights = [&](int digit, int s0, int end) {
-#pragma unroll
-        for (int u = 0; u < NI; ++u) {
-            const int it = wave + 4 * u, s = s0 + (it >> 1) * HW;    // (granule, half)
-            if (s >= end) break;                                 // uniform
-            const int tap = divide(s, p.halves), cw = (it & 1) * p.half + s - tap * p.half;
-            const uint32_t at = 4u * static_cast<uint32_t>(2 * digit * Kw + (cw < p.Cw ? tap * p.Cw + cw : 0));
-            const uint32_t second = 2 * digit + 1 < p.PB ? 4u * static_cast<uint32_t>(Kw) : 0u;
-            if constexpr (HW == 2) {
-                const auto t = __builtin_amdgcn_raw_buffer_load_b64(bufB, wlane, at, 0);
-                wv[u][0][0] = t[0]; wv[u][0][1] = t[1];
+    // granule u of this thread, from step s on: the words that its steps' codes are made of
+    auto fetch_granule = [&](int u, int digit, int s, auto pm1) __attribute__((always_inline)) {
+        const int tap = divide(s, p.halves), cw = wh * p.half + s - tap * p.half;
+        const uint32_t at = wlane + 4u * static_cast<uint32_t>(cw < p.Cw ? tap * p.Cw + cw : 0);
+        auto load = [&](uint32_t (&w)[HW], uint32_t plane) __attribute__((always_inline)) {
+            if constexpr (HW == 4) {
+                const auto t = __builtin_amdgcn_raw_buffer_load_b128(bufB, at, plane, 0);
+                w[0] = t[0]; w[1] = t[1]; w[2] = t[2]; w[3] = t[3];
+            } else if constexpr (HW == 2) {
+                const auto t = __builtin_amdgcn_raw_buffer_load_b64(bufB, at, plane, 0);
+                w[0] = t[0]; w[1] = t[1];
             } else {
-                wv[u][0][0] = __builtin_amdgcn_raw_buffer_load_b32(bufB, wlane, at, 0);
+                w[0] = __builtin_amdgcn_raw_buffer_load_b32(bufB, at, plane, 0);
             }
-            if (!p.pm1) {
-                if constexpr (HW == 2) {
-                    const auto t = __builtin_amdgcn_raw_buffer_load_b64(bufB, wlane, at + second, 0);
-                    wv[u][1][0] = second ? t[0] : 0u; wv[u][1][1] = second ? t[1] : 0u;
-                } else {
-                    const uint32_t t = __builtin_amdgcn_raw_buffer_load_b32(bufB, wlane, at + second, 0);
-                    wv[u][1][0] = second ? t : 0u;
-                }
-            }
-        }
+        };
+        load(wv[u][0], 8u * static_cast<uint32_t>(digit * Kw));
+        if constexpr (!decltype(pm1)::value) load(wv[u][1], 2 * digit + 1 < p.PB ? 8u * static_cast<uint32_t>(digit * Kw) + 4u * static_cast<uint32_t>(Kw) : NOWHERE);
     };
     Fp4Masks km;
     km.m1 = reg_const(0x11111111u); km.m2 = reg_const(0x22222222u);
     km.m4 = reg_const(0x44444444u); km.m8 = reg_const(0x88888888u);
-    auto write_weights = [&](uint32_t *codes, int steps) {
-        auto all = [&](auto kind) {
+    // ... -> codes; steps from `valid` on fill up a granule: zero codes
+    auto write_granule = [&](int u, uint32_t *codes, int s, int valid, auto pm1) __attribute__((always_inline)) {
 #pragma unroll
-            for (int u = 0; u < NI; ++u) {
-                const int it = wave + 4 * u, s = (it >> 1) * HW, h = it & 1;
-                if (s >= steps) break;                           // uniform
+        for (int i = 0; i < HW; ++i) {
+            v8i_t f;
+            Fp4Masks m = km;
+            if ((MULTI || G == 2) && s + i >= valid) m.m1 = m.m2 = m.m8 = 0u;
+            expand_fp4<decltype(pm1)::value ? OPK_PM1 : OPK_U2>(wv[u][0][i], wv[u][1][i], m, f);
+            *reinterpret_cast<int4 *>(codes + (((s + i) * FC + wtile) * 64 + 32 * wh + (wrow ^ (2 * wh))) * 4) = make_int4(f[0], f[1], f[2], f[3]);
+        }
+    };
+    // the first `steps` of a digit: weights that stay, or their first chunk
+    auto fetch_weights = [&](int steps) {
+        auto all = [&](auto pm1) {
 #pragma unroll
-                for (int i = 0; i < HW; ++i) {
-                    v8i_t f;
-                    expand_fp4<decltype(kind)::value>(wv[u][0][i], wv[u][1][i], km, f);
-                    *reinterpret_cast<int4 *>(codes + (((s + i) * FC + wtile) * 64 + 32 * h + wrow) * 4) = make_int4(f[0], f[1], f[2], f[3]);
-                }
-            }
+            for (int u = 0; u < NI; ++u)
+                if (2 * u * HW < steps) fetch_granule(u, 0, min((2 * u + wk) * HW, p.steps - HW), pm1);
         };
-        if (p.pm1) all(std::integral_constant<int, OPK_PM1>{});
-        else all(std::integral_constant<int, OPK_U2>{});
+        if (p.pm1) all(std::true_type{});
+        else all(std::false_type{});
+    };
+    auto write_weights = [&](int steps) {
+        auto all = [&](auto pm1) {
+#pragma unroll
+            for (int u = 0; u < NI; ++u)
+                if (const int s = (2 * u + wk) * HW; s < steps) write_granule(u, sB, s, p.steps, pm1);
+        };
+        if (p.pm1) all(std::true_type{});
+        else all(std::false_type{});
     };
 
     // ---- the pixels a tile's taps touch: positions lo .. lo + range - 1 of the padded frames
@@ -162,13 +180,13 @@ __global__ __launch_bounds__(256, FP == 1 ? 4 : FP * FW == 8 ? 2 : 3) void conv_
         return r;
     };
     const int tmask = (1 << p.share) - 1;
-    uint32_t a0[U][SW], a1[U][SW];                               // a piece: SW words of each plane of a digit
+    uint32_t a0[U][PW], a1[U][PW];                               // a piece: PW words of each plane of a digit
     bool in[U];
-    auto load_piece = [&](uint32_t bytes, uint32_t (&w)[SW]) {
-        if constexpr (SW == 4) {
+    auto load_piece = [&](uint32_t bytes, uint32_t (&w)[PW]) {
+        if constexpr (PW == 4) {
             const auto t = __builtin_amdgcn_raw_buffer_load_b128(bufA, bytes, 0, 0);
             w[0] = t[0]; w[1] = t[1]; w[2] = t[2]; w[3] = t[3];
-        } else if constexpr (SW == 2) {
+        } else if constexpr (PW == 2) {
             const auto t = __builtin_amdgcn_raw_buffer_load_b64(bufA, bytes, 0, 0);
             w[0] = t[0]; w[1] = t[1];
         } else {
@@ -178,10 +196,10 @@ __global__ __launch_bounds__(256, FP == 1 ? 4 : FP * FW == 8 ? 2 : 3) void conv_
     auto fetch_pixels = [&](Range r, int q0) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int q = q0 + 256 * u, pos = r.lo + (q >> p.share), g = q & tmask;
+            const int q = q0 + NT * u, pos = r.lo + (q >> p.share), g = q & tmask;
             const int n = divide(pos, p.frame), rem = pos - n * p.frame.d;
             const int yq = divide(rem, p.line), y = yq - p.pad, x = rem - yq * p.Wq - p.pad;
-            const int cs = MULTI ? divide(g, p.digits) : g, d = MULTI ? g - cs * p.DA : 0, cw = cs * SW;
+            const int cs = MULTI ? divide(g, p.digits) : g, d = MULTI ? g - cs * p.DA : 0, cw = cs * PW;
             in[u] = q < r.total && n < p.images && static_cast<unsigned>(y) < static_cast<unsigned>(p.H) &&
                     static_cast<unsigned>(x) < static_cast<unsigned>(p.W) && cw < p.Cw;
             const int at = (((n * p.H + y) * p.W + x) * p.PA + 2 * d) * p.Cw + cw;
@@ -189,90 +207,99 @@ __global__ __launch_bounds__(256, FP == 1 ? 4 : FP * FW == 8 ? 2 : 3) void conv_
             if (KA == OPK_U2) load_piece(in[u] && 2 * d + 1 < p.PA ? 4u * static_cast<uint32_t>(at + p.Cw) : NOWHERE, a1[u]);
         }
     };
-    auto write_pixels = [&](uint32_t *records, Range r, int q0) {
+    auto write_pixels = [&](uint32_t *features, Range r, int q0) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int q = q0 + 256 * u, g = q & tmask;
+            const int q = q0 + NT * u, g = q & tmask;
             if (q >= r.total || g >= p.pieces) continue;
             const int cs = MULTI ? divide(g, p.digits) : g, d = MULTI ? g - cs * p.DA : 0;
-            uint32_t w[SW * PL];
+            uint32_t *const dst = features + (d * 2 * p.half + cs * PW) * p.plane + CW * (q >> p.share);
 #pragma unroll
-            for (int i = 0; i < SW; ++i) {
-                if (KA == OPK_U1) {
-                    w[i] = a0[u][i];
-                } else if (KA == OPK_U2) {                       // pairs of bits: even positions, odd positions
-                    w[PL * i] = mask_select(0x55555555u, a0[u][i], a1[u][i] << 1);
-                    w[PL * i + 1] = mask_select(0x55555555u, a0[u][i] >> 1, a1[u][i]);
-                } else {                                         // signs, and the code's 1.0 inside the frame
-                    w[PL * i] = in[u] ? ~a0[u][i] : 0u;
-                    w[PL * i + 1] = in[u] ? 0x22222222u : 0u;
+            for (int i = 0; i < PW; ++i) {
+                const uint32_t x0 = a0[u][i], x1 = KA == OPK_U2 ? a1[u][i] : in[u] ? ~0u : 0u;
+                if constexpr (PACKED) {                          // two planes as pairs of bits: even positions, odd positions
+                    const uint2 w = KA == OPK_U2 ? make_uint2(mask_select(0x55555555u, x0, x1 << 1), mask_select(0x55555555u, x0 >> 1, x1)) : make_uint2(x0, x1);
+                    *reinterpret_cast<uint2 *>(dst + i * p.plane) = w;
+                } else {
+                    v8i_t f;
+                    expand_fp4<KA>(x0, x1, km, f);
+                    *reinterpret_cast<int4 *>(dst + i * p.plane) = make_int4(f[0], f[1], f[2], f[3]);
                 }
-            }
-            // the piece's granules, DA granules apart
-            uint32_t *dst = records + (q >> p.share) * p.rec + (cs * (SW / HW) * p.DA + d) * GW;
-            const int apart = MULTI ? p.DA * GW : GW;
-#pragma unroll
-            for (int k = 0; k < SW / HW; ++k) {
-                if constexpr (GW == 4) *reinterpret_cast<uint4 *>(dst + k * apart) = make_uint4(w[4 * k], w[4 * k + 1], w[4 * k + 2], w[4 * k + 3]);
-                else if constexpr (GW == 2) *reinterpret_cast<uint2 *>(dst + k * apart) = make_uint2(w[2 * k], w[2 * k + 1]);
-                else dst[k * apart] = w[k];
             }
         }
     };
 
+    // Weights that pass through: the chunk after one, in the order of the sums (digit DB: none).  A chunk's codes are written
+    // while the one before it is multiplied, from words that were fetched a whole chunk earlier.
+    struct Chunk { int digit, s0; };
+    auto after = [&](Chunk c) {
+        const bool wrap = c.s0 + kHaloChunk >= p.steps;
+        return Chunk{c.digit + (wrap ? 1 : 0), wrap ? 0 : c.s0 + kHaloChunk};
+    };
+    // (a chunk's steps beyond the digit's last read step s0; their codes are zero, or not used)
+    auto fetch_chunk = [&](Chunk c, auto pm1) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < NI; ++u) {
+            const int s = c.s0 + (2 * u + wk) * HW;
+            fetch_granule(u, min(c.digit, p.DB - 1), s < p.steps ? s : c.s0, pm1);
+        }
+    };
+    // writes the chunk after `c` to the buffer that c is not in (read last before the barrier that began c)
+    auto stage_next = [&](Chunk c, int half_buffer) __attribute__((always_inline)) {
+        const Chunk next = after(c);
+        if (next.digit >= p.DB) return false;
+        uint32_t *const to = sB + (half_buffer ^ 1) * (kHaloChunk * FC * 256);
+        auto all = [&](auto pm1) __attribute__((always_inline)) {
+#pragma unroll
+            for (int u = 0; u < NI; ++u) write_granule(u, to, (2 * u + wk) * HW, p.steps - next.s0, pm1);
+            fetch_chunk(after(next), pm1);
+        };
+        if (p.pm1) all(std::true_type{});
+        else all(std::false_type{});
+        return true;
+    };
+
     Range now = range_of(tile0);
-    fetch_weights(0, 0, STAY ? p.steps : min(p.chunk, p.steps));
+    fetch_weights(STAY ? p.steps : min(kHaloChunk, p.steps));
     fetch_pixels(now, tid);
+    // Where an entry's operands are, from those of the first one; an entry is a step or, with several digits, a step and a digit of the
+    // features: then the codes of its weights (in the chunk) with the digit in the low bits stand beside it.  Entry e is at e + G.
+    for (int i = tid; i < p.words_table / E; i += NT) {
+        const int e = max(i - G, 0), st = MULTI ? divide(e, p.digits) : e, d = MULTI ? e - st * p.DA : 0;
+        const int tap = divide(st, p.halves), r = divide(tap, p.columns);
+        sT[E * i] = st < p.steps ? 4u * CW * static_cast<uint32_t>(r * p.Wq + tap - r * p.S) +
+                                       4u * static_cast<uint32_t>((st - tap * p.half + d * 2 * p.half) * p.plane) : 0u;
+        if (MULTI) sT[E * i + 1] = 1024u * FC * static_cast<uint32_t>(STAY ? min(st, p.padded - 1) : st % kHaloChunk) + d;
+    }
     if (!p.Y && tid < 64 * FC) {                                 // scale (first half of the threads) and bias of a channel
         const int k = tid % (32 * FC), ch = n0 + (k & ~31) + code_channel(k & 15, (k >> 4) & 1);
         float v = 0.0f;
         if (ch < p.N) v = tid < 32 * FC ? p.scale[ch] : quarter(p.bias[ch]);
         sP[tid] = v;
     }
-    write_weights(sB, STAY ? p.steps : p.chunk);
+    write_weights(STAY ? p.padded : kHaloChunk);
+    if constexpr (!STAY) {
+        if (p.pm1) fetch_chunk(after(Chunk{0, 0}), std::true_type{});
+        else fetch_chunk(after(Chunk{0, 0}), std::false_type{});
+    }
     write_pixels(sA, now, tid);
-    for (int q = tid + 256 * U; q < now.total; q += 256 * U) {
+    for (int q = tid + NT * U; q < now.total; q += NT * U) {
         fetch_pixels(now, q);
         write_pixels(sA, now, q);
     }
     __syncthreads();
 
+    const int scaleA = static_cast<int>(reg_const(static_cast<uint32_t>(p.scaleA))), scaleB0 = static_cast<int>(reg_const(static_cast<uint32_t>(p.scaleB)));
     const uint32_t m3 = reg_const(0x33333333u);
-    typedef uint32_t words_t __attribute__((ext_vector_type(GW)));
-    auto expand = [&](const words_t &w, int i, v8i_t &o) {
-        if constexpr (KA == OPK_U1) {
-            expand_fp4<OPK_U1>(w[i], 0u, km, o);
-        } else if constexpr (KA == OPK_U2) {                     // both words shifted at once: the bits that cross are masked
-            const uint64_t two = (static_cast<uint64_t>(w[2 * i + 1]) << 32 | w[2 * i]) >> 2;
-            o[0] = w[2 * i] & m3;
-            o[1] = w[2 * i + 1] & m3;
-            o[2] = static_cast<uint32_t>(two) & m3;
-            o[3] = static_cast<uint32_t>(two >> 32) & m3;
-            o[4] = o[5] = o[6] = o[7] = 0;
-        } else {
-            const uint32_t a = w[2 * i], one = w[2 * i + 1];
-            o[0] = ((a << 3) & km.m8) | one;
-            o[1] = ((a << 2) & km.m8) | one;
-            o[2] = ((a << 1) & km.m8) | one;
-            o[3] = (a & km.m8) | one;
-            o[4] = o[5] = o[6] = o[7] = 0;
-        }
-    };
-    // K is walked granule by granule: the granules of a tap, and the digits of a granule, follow each other in the record.
-    const int per_tap = (p.half / HW) * (MULTI ? p.DA : 1);
-    const uint32_t tap_step = 4u * static_cast<uint32_t>(p.rec) - 4u * GW * (per_tap - 1);
-    const uint32_t row_step = tap_step + 4u * static_cast<uint32_t>((p.Wq - p.S) * p.rec);
-    const int scaleA = static_cast<int>(reg_const(static_cast<uint32_t>(p.scaleA)));
 
-    for (int tile = tile0, buffer = 0;; buffer ^= 1) {
+    for (int tile = tile0, buffer = 0;; buffer ^= p.buffers - 1) {
         const int m0 = tile * BP, last = min(m0 + BP, p.M) - 1;
-        const uint8_t *const records = reinterpret_cast<const uint8_t *>(sA + buffer * p.words_records);
         int gm[FP];                                              // this lane's pixels
-        uint32_t base[FP];                                       // bytes: record of the first tap, this lane half's words
+        const uint8_t *base[FP];                                 // the first tap's position, this lane half's words
 #pragma unroll
         for (int f = 0; f < FP; ++f) {
             gm[f] = POOL ? m0 + 4 * (32 * wp + lr) + f : m0 + (wp * FP + f) * 32 + lr;
-            base[f] = 4u * static_cast<uint32_t>((position(min(gm[f], last)) - now.lo) * p.rec + lh * per_tap * GW);
+            base[f] = reinterpret_cast<const uint8_t *>(sA + buffer * p.words_records + CW * (position(min(gm[f], last)) - now.lo) + lh * p.half * p.plane);
         }
         // residual words and the next tile's first pixels: their latency hides behind the main loop
         constexpr int FO = POOL ? 1 : FP;                        // output tiles per channel tile
@@ -297,178 +324,145 @@ __global__ __launch_bounds__(256, FP == 1 ? 4 : FP * FW == 8 ? 2 : 3) void conv_
             fetch_pixels(next_range, tid);
         }
 
+        // The sums.  K is walked granule by granule; the operands of a granule are read between the matrix instructions of the
+        // one before it, into two sets of registers in turn.  Each instruction is fenced, since the compiler otherwise moves the
+        // reads to their uses, where a lone wave of a SIMD waits for each.
         v16f_t acc[FW][FP];
-        // The operands of a granule are read one granule ahead of its matrix instructions, into two sets of registers in turn;
-        // the empty statements keep the compiler from moving the reads back to their use (128 -> 128 channels, 128 x 28 x 28:
-        // 16.4 us where it puts them, 13.8 here; it makes no difference where PT is known).
+        typedef int features_t __attribute__((ext_vector_type(CW)));
         struct Operands {
-            words_t w[FP];
-            v4i_t a[HW][FW];
-            int scale;
+            v4i_t a[G][FW];
+            features_t b[G][FP];
+            int scaleA[G], scaleB;
         } even, odd;
-        const uint32_t *codes = sB + wc * 256 + lane * 4;
-        int scaleB = static_cast<int>(reg_const(static_cast<uint32_t>(p.scaleB)));
-        uint32_t off = 0;
-        int g = 0, sc = 0, d = 0;
-        auto load = [&](Operands &o) __attribute__((always_inline)) {
-#pragma unroll
-            for (int f = 0; f < FP; ++f) o.w[f] = *reinterpret_cast<const words_t *>(records + (base[f] + off));
-#pragma unroll
-            for (int i = 0; i < HW; ++i)
-#pragma unroll
-                for (int c = 0; c < FW; ++c) o.a[i][c] = *reinterpret_cast<const v4i_t *>(codes + (i * FC + c) * 256);
-            o.scale = MULTI ? block_scale(scaleA, 2 * d) : scaleA;
-            asm volatile("" ::: "memory");
+        const uint32_t lane_codes = wc * 256 + (lane ^ (2 * lh)) * 4;
+        const uint32_t *codes = sB + lane_codes;
+        const uint32_t *table = sT + 2 * G * E;                  // offsets of the second and third granule
+        int sB_now = scaleB0;
+        typedef uint32_t offsets_t __attribute__((ext_vector_type(G * E)));      // of a granule
+        constexpr int READS = G * (FW + FP), PRODUCTS = G * FW * FP;
+        // read k of a granule at `off`, its weights at `codes` (several digits: the chunk's)
+        auto read = [&](Operands &o, auto kc, const offsets_t &off, const uint32_t *codes) __attribute__((always_inline)) {
+            constexpr int k = decltype(kc)::value, g = k / (FW + FP), i = k % (FW + FP);
+            if constexpr (i < FP) o.b[g][i] = *reinterpret_cast<const features_t *>(base[i] + off[E * g]);
+            else if constexpr (MULTI) o.a[g][i - FP] = *reinterpret_cast<const v4i_t *>(codes + ((off[E * g + 1] & ~1023u) >> 2) + (i - FP) * 256);
+            else o.a[g][i - FP] = *reinterpret_cast<const v4i_t *>(codes + (g * FC + i - FP) * 256);
+            if constexpr (MULTI && i == 0) o.scaleA[g] = scaleA + 2 * static_cast<int>(off[E * g + 1] & 1023u);      // (its lowest byte is read)
         };
-        auto advance = [&](bool more) __attribute__((always_inline)) {                          // more: of this chunk
-            const bool tap = ++g == per_tap;
-            g = tap ? 0 : g;
-            sc += tap ? 1 : 0;
-            const bool row = sc == p.S;
-            sc = row ? 0 : sc;
-            off += row ? row_step : tap ? tap_step : 4u * GW;
-            if (MULTI) d = d + 1 == p.DA ? 0 : d + 1;
-            codes += more && (!MULTI || d == 0) ? HW * FC * 256 : 0;
-        };
-        auto multiply = [&](auto first, const Operands &o) __attribute__((always_inline)) {     // the first granule starts the sums
-#pragma unroll
-            for (int i = 0; i < HW; ++i)
-#pragma unroll
-                for (int f = 0; f < FP; ++f) {
-                    v8i_t b;
-                    expand(o.w[f], i, b);
-#pragma unroll
-                    for (int c = 0; c < FW; ++c)
-                        acc[c][f] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-                            v8i_t{o.a[i][c][0], o.a[i][c][1], o.a[i][c][2], o.a[i][c][3], 0, 0, 0, 0}, b,
-                            decltype(first)::value && i == 0 ? v16f_t{} : acc[c][f], 4, 4, 0, scaleB, 0, o.scale);
+        v4i_t b;                                                 // the codes of a pixel tile
+        auto product = [&](const Operands &o, auto kc, auto first) __attribute__((always_inline)) {         // the first granule starts the sums
+            constexpr int k = decltype(kc)::value, g = k / (FW * FP), f = k / FW % FP, c = k % FW;
+            const v4i_t a = o.a[g][c];
+            if constexpr (!PACKED) {
+                b = o.b[g][f];
+            } else if constexpr (c == 0) {
+                const uint32_t w0 = o.b[g][f][0], w1 = o.b[g][f][1];
+                if constexpr (KA == OPK_U2) {                    // both words shifted at once: the bits that cross are masked
+                    const uint64_t two = (static_cast<uint64_t>(w1) << 32 | w0) >> 2;
+                    b = v4i_t{static_cast<int>(w0 & m3), static_cast<int>(w1 & m3), static_cast<int>(static_cast<uint32_t>(two) & m3), static_cast<int>(static_cast<uint32_t>(two >> 32) & m3)};
+                } else {
+                    v8i_t e;
+                    expand_fp4<KA>(w0, w1, km, e);
+                    b = v4i_t{e[0], e[1], e[2], e[3]};
                 }
+            }
+            acc[c][f] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(v8i_t{a[0], a[1], a[2], a[3], 0, 0, 0, 0},
+                                                                        v8i_t{b[0], b[1], b[2], b[3], 0, 0, 0, 0}, decltype(first)::value && g == 0 ? v16f_t{} : acc[c][f], 4, 4, 0,
+                                                                        MULTI ? o.scaleB : scaleB0, 0, MULTI ? o.scaleA[g] : scaleA);
+            __builtin_amdgcn_sched_barrier(0);
         };
-        // `left` granules of a chunk, the first one in odd; more: granules of this weight digit after the chunk
-        auto rest_of_chunk = [&](int left, bool more) __attribute__((always_inline)) {
-            for (; left >= 2; left -= 2) {
-                advance(true);
-                load(even);
-                multiply(std::false_type{}, odd);
-                advance(left > 2);
-                off = left > 2 || more ? off : 0u;               // (read, not used)
-                load(odd);
-                multiply(std::false_type{}, even);
-            }
-            if (left) {
-                multiply(std::false_type{}, odd);
-                advance(false);
-            }
+        auto multiply_and_read = [&](const Operands &o, Operands &next, const offsets_t &off, const uint32_t *codes, auto first) __attribute__((always_inline)) {
+            if (MULTI) next.scaleB = sB_now;
+            static_for<PRODUCTS>([&](auto kc) __attribute__((always_inline)) {
+                constexpr int k = decltype(kc)::value, from = k * READS / PRODUCTS, to = (k + 1) * READS / PRODUCTS;
+                static_for<to - from>([&](auto jc) __attribute__((always_inline)) { read(next, std::integral_constant<int, from + decltype(jc)::value>{}, off, codes); });
+                __builtin_amdgcn_sched_barrier(0);
+                product(o, kc, first);
+            });
         };
-        const int all = p.steps / HW * (MULTI ? p.DA : 1);       // granules of a weight digit
-        if constexpr (STAY) {
-            load(even);
-            advance(all > 1);
-            off = all > 1 ? off : 0u;
-            load(odd);
-            multiply(std::true_type{}, even);
-            rest_of_chunk(all - 1, false);
-        } else if constexpr (PT > 0) {
-            static_assert(PT % 2 == 0 && !MULTI);
-            // granule g of the tap at `off`, whose codes begin at `codes`
-            auto load_at = [&](Operands &o, int g, const uint8_t *const (&src)[FP]) __attribute__((always_inline)) {
+        struct Pair { offsets_t one, two; } t;                   // of the two granules after the one that is in `even`
+        auto read_table = [&]() __attribute__((always_inline)) {
+            typedef uint32_t pair_t __attribute__((ext_vector_type(2 * G * E), aligned(8 * G)));
+            const pair_t v = *reinterpret_cast<const pair_t *>(table);
 #pragma unroll
-                for (int f = 0; f < FP; ++f) o.w[f] = *reinterpret_cast<const words_t *>(src[f] + 4 * GW * g);
+            for (int i = 0; i < G * E; ++i) { t.one[i] = v[i]; t.two[i] = v[G * E + i]; }
+        };
+        read_table();
+        {                                                        // the first granule
+            offsets_t off;
+            if constexpr (MULTI) {
+                off = *reinterpret_cast<const offsets_t *>(sT + G * E);
+                even.scaleB = sB_now;
+            } else {
 #pragma unroll
-                for (int i = 0; i < HW; ++i)
-#pragma unroll
-                    for (int c = 0; c < FW; ++c) o.a[i][c] = *reinterpret_cast<const v4i_t *>(codes + ((g * HW + i) * FC + c) * 256);
-                o.scale = scaleA;
-            };
-            const uint8_t *src[FP];
-            auto point = [&]() __attribute__((always_inline)) {
-#pragma unroll
-                for (int f = 0; f < FP; ++f) src[f] = records + (base[f] + off);
-            };
-            // a tap, its first granule in even; `next`: the tap after it is in this chunk
-            auto tap = [&](auto first, bool next, bool more) __attribute__((always_inline)) {
-                static_for<PT>([&](auto gc) {
-                    constexpr int g = decltype(gc)::value;
-                    constexpr bool starts = decltype(first)::value && g == 0;
-                    if constexpr (g + 1 < PT) {
-                        if constexpr (g % 2 == 0) load_at(odd, g + 1, src);
-                        else load_at(even, g + 1, src);
-                    } else {
-                        const bool row = ++sc == p.S;
-                        sc = row ? 0 : sc;
-                        off += row ? row_step + 4u * GW * (PT - 1) : tap_step + 4u * GW * (PT - 1);
-                        off = more ? off : 0u;                   // (read, not used)
-                        codes += next ? PT * HW * FC * 256 : 0;
-                        point();
-                        load_at(even, 0, src);
-                    }
-                    multiply(std::integral_constant<bool, starts>{}, g % 2 == 0 ? even : odd);
-                });
-            };
-            int digit = 0, s0 = 0, half_buffer = 0;              // weight digit, first step and buffer of the chunk
-            constexpr int tap_steps = PT * HW, chunk_taps = kHaloChunk / tap_steps;
-            int left = min(chunk_taps, p.R * p.S);               // taps of the chunk that are to do
-            point();
-            load_at(even, 0, src);
-            tap(std::true_type{}, left > 1, all > PT);
-            --left;
-            while (true) {
-                int nd = digit, ns = s0 + p.chunk;               // the chunk after this one
-                if (ns >= p.steps) { ns = 0; ++nd; }
-                const bool more = nd < p.DB;
-                if (more) fetch_weights(nd, ns, min(ns + p.chunk, p.steps));
-                for (; left > 0; --left) tap(std::false_type{}, left > 1, left > 1 || (more && nd == digit));
-                if (!more) break;
-                if (nd != digit) {                               // the next weight digit starts at the first tap again
-                    off = 0; sc = 0;
-                    scaleB = block_scale(scaleB, 2);
-                }
-                digit = nd;
-                s0 = ns;
-                half_buffer ^= 1;
-                uint32_t *const to = sB + half_buffer * (p.chunk * FC * 256);
-                write_weights(to, p.chunk);                      // read last before the barrier two chunks ago
-                codes = to + wc * 256 + lane * 4;
-                __syncthreads();
-                left = divide(min(p.chunk, p.steps - s0), p.halves);
-                point();
-                load_at(even, 0, src);
+                for (int g = 0; g < G; ++g) off[g] = g == 0 ? 0u : p.second;
             }
-        } else {
-            int digit = 0, s0 = 0, half_buffer = 0;              // weight digit, first step and buffer of the chunk
-            int left = min(p.chunk, p.steps) / HW * (MULTI ? p.DA : 1) - 1;
-            load(even);
-            advance(left > 0);
-            off = all > 1 ? off : 0u;
-            load(odd);
-            multiply(std::true_type{}, even);
-            while (true) {
-                int nd = digit, ns = s0 + p.chunk;               // the chunk after this one
-                if (ns >= p.steps) { ns = 0; ++nd; }
-                const bool more = nd < p.DB;
-                if (more) fetch_weights(nd, ns, min(ns + p.chunk, p.steps));
-                rest_of_chunk(left, more && nd == digit);
-                if (!more) break;
-                if (nd != digit) {                               // the next weight digit starts at the first tap again
-                    off = 0; g = 0; sc = 0; d = 0;
-                    scaleB = block_scale(scaleB, 2);
-                }
-                digit = nd;
-                s0 = ns;
-                half_buffer ^= 1;
-                uint32_t *const to = sB + half_buffer * (p.chunk * FC * 256);
-                write_weights(to, p.chunk);                      // read last before the barrier two chunks ago
-                codes = to + wc * 256 + lane * 4;
-                __syncthreads();
-                left = min(p.chunk, p.steps - s0) / HW * (MULTI ? p.DA : 1);
-                load(odd);
-            }
+            static_for<READS>([&](auto kc) __attribute__((always_inline)) { read(even, kc, off, codes); });
         }
-        // the next tile's records, read last before the barrier that began this tile
+        Chunk at{0, 0};
+        int half_buffer = 0;
+        bool staged = STAY ? false : stage_next(at, half_buffer);            // the chunk after this one is on its way
+        // A run: the granules of a chunk.  All but the last one of a weight digit have an even number.
+        auto granules = [&]() __attribute__((always_inline)) {
+            const int left = (MULTI ? p.steps : p.padded) - at.s0;
+            return ((STAY ? left : min(kHaloChunk, left)) * (MULTI ? p.DA : 1) + G - 1) / G;
+        };
+        offsets_t off;
+        auto first_of_pair = [&](auto first) __attribute__((always_inline)) {
+            multiply_and_read(even, odd, t.one, MULTI ? codes : codes + G * FC * 256, first);
+            off = t.two;
+            if (!MULTI) codes += 2 * G * FC * 256;
+            table += 2 * G * E;
+        };
+        auto second_of_pair = [&]() __attribute__((always_inline)) {
+            read_table();
+            multiply_and_read(odd, even, off, codes, std::false_type{});
+        };
+        int n = granules();
+        if (n > 2) {
+            first_of_pair(std::true_type{});
+            second_of_pair();
+            n -= 2;
+        } else {
+#pragma unroll
+            for (int c = 0; c < FW; ++c)
+#pragma unroll
+                for (int f = 0; f < FP; ++f) acc[c][f] = v16f_t{};
+        }
+        while (true) {
+            for (int left = (n - 1) >> 1; left > 0; --left) {
+                first_of_pair(std::false_type{});
+                second_of_pair();
+            }
+            const bool pair = n % 2 == 0;                        // an odd last granule ends a digit: nothing is read ahead of the next
+            if (!MULTI && !pair) break;
+            if (!MULTI || pair) first_of_pair(std::false_type{});
+            if (STAY || !staged) {                               // nothing to read
+                if (!MULTI || pair) even = odd;
+                break;
+            }
+            const Chunk next = after(at);                        // on to the next run
+            const bool digit = MULTI && next.digit != at.digit;
+            at = next;
+            half_buffer ^= 1;
+            __syncthreads();
+            codes = sB + half_buffer * (kHaloChunk * FC * 256) + lane_codes;
+            if (digit) {
+                sB_now = block_scale(sB_now, 2);
+                off = *reinterpret_cast<const offsets_t *>(sT + G * E);
+                table = sT + 2 * G * E;
+            }
+            if (MULTI && !pair) odd = even;
+            second_of_pair();
+            staged = stage_next(at, half_buffer);
+            n = granules();
+        }
+        static_for<PRODUCTS>([&](auto kc) __attribute__((always_inline)) { product(even, kc, std::false_type{}); });    // the last granule
+        // the next tile's codes, read last before the barrier that began this tile
         if (more_tiles) {
-            uint32_t *const to = sA + (buffer ^ 1) * p.words_records;
+            if (p.buffers == 1) __syncthreads();                 // (the only buffer: every wave is through with it)
+            uint32_t *const to = sA + (p.buffers == 1 ? 0 : buffer ^ 1) * p.words_records;
             write_pixels(to, next_range, tid);
-            for (int q = tid + 256 * U; q < next_range.total; q += 256 * U) {
+            for (int q = tid + NT * U; q < next_range.total; q += NT * U) {
                 fetch_pixels(next_range, q);
                 write_pixels(to, next_range, q);
             }

@@ -37,6 +37,24 @@ static bool worth_staging(const MfmaParams &mp, int64_t tiles, int64_t blocks, i
     return staged + rounds * (spread + each * entries) <= other;
 }
 
+// Time (us) of a layer in one of the forms of its blocks, as fitted to 500 layers each measured in all of them (the mean error is 12 %;
+// what it chooses is on average 1.4 % slower than the fastest form).  A compute unit works on `resident` blocks in a round, the last
+// round's fewer ones share it with nobody.  A round costs its blocks' first loads (less where a block walks: the next tile's pixels are
+// in flight), 0.43 for each pair of output tiles of a wave, 0.11 for a thousand words of pixels, and for each matrix instruction 0.022 on
+// a SIMD with several waves, 0.041 with a lone one that has four and more to a step, 0.061 with two; a little more where the pixels
+// are staged as bits.
+static double tiling_cost(int fp, int pairs, int64_t tiles, int64_t resident, bool walks, double words, int64_t entries, bool packed)
+{
+    const double products = fp == 4 ? 8.0 : fp == 1 ? 2.0 : 4.0, lone = (products >= 4 ? 0.041 : 0.061) + (packed ? 0.005 : 0.0), shared = packed ? 0.029 : 0.0224;
+    auto cost = [&](int64_t blocks) {
+        const double waves = static_cast<double>(blocks * pairs);
+        return (walks ? 1.2 : 3.6) + waves * 0.43 * (fp >= 3 ? products / 2 : products) + 0.11e-3 * blocks * words +
+               (waves > 1 ? shared * waves : lone) * products * entries;
+    };
+    const int64_t round = 256 * resident, rest = tiles % round;
+    return static_cast<double>(tiles / round) * cost(resident) + (rest ? cost(ceil_div(rest, 256)) : 0.0);
+}
+
 bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB, int force, hipStream_t st)
 {
     // int32 results alone, or planes of one or two bits alone (the epilogue keeps no other output)
@@ -71,7 +89,7 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
     p.stride = mp.stride; p.pad = mp.pad; p.R = mp.R; p.S = mp.S;
     p.Cw = mp.Cw; p.half = (mp.Cw + 1) / 2;
     p.PA = mp.PA; p.PB = mp.PB; p.DA = mp.DA; p.DB = mp.DB;
-    p.digits = divisor(p.DA); p.halves = divisor(p.half);
+    p.digits = divisor(p.DA); p.halves = divisor(p.half); p.columns = divisor(p.S);
     p.pm1 = kindB == OPK_PM1;
     p.pool = mp.pool;
     p.steps = static_cast<int>(steps);
@@ -81,23 +99,19 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
     p.scaleA = static_cast<int>(0x01010101u * (0x7fu + (kindA == OPK_U2 ? 1u : 0u) - (planes ? 2u : 0u)));
     p.scaleB = static_cast<int>(0x01010101u * (0x7fu + (kindB == OPK_PM1 ? 0u : 1u)));
 
-    // steps read together, words staged together (as the launcher instantiates them)
-    const int hw = p.Cw % 4 == 0 ? 2 : 1, sw = p.Cw % 4 == 0 ? 4 : p.Cw % 2 == 0 ? 2 : 1, granule = (kindA == OPK_U1 ? 1 : 2) * hw;
-    // records are an odd number of granules apart: a step's reads of consecutive pixels hit all banks
-    const int granules = p.DA * 2 * (p.half / hw);
-    p.rec = granule * (granules % 2 == 0 ? granules + 1 : granules);
-    p.pieces = p.DA * static_cast<int>(ceil_div(2 * p.half, sw));
-    while ((1 << p.share) < p.pieces) ++p.share;
+    // words of a pixel staged together (as the launcher instantiates them)
+    const int sw = p.Cw % 4 == 0 ? 4 : p.Cw % 2 == 0 ? 2 : 1;
 
-    // Weights of up to kHaloStay steps stay in LDS while a block walks over its tiles; longer ones pass through in chunks of
-    // whole taps.
-    const bool stay = p.DB == 1 && p.steps <= kHaloStay;
+    // Weights of up to kHaloStay steps stay in LDS while a block walks over its tiles; longer ones pass through in chunks.
+    const bool multi = p.DA > 1 || p.DB > 1;
+    auto padded = [&](int fp) { return round_up(steps, halo_granule(fp == 3 ? 4 : fp, fp == 3 ? 1 : 2)); };
+    const bool stay = p.DB == 1 && padded(1) <= kHaloStay;
     if (!stay && p.half > kHaloChunk) return false;
-    p.chunk = stay ? p.steps : kHaloChunk / p.half * p.half;
-    const int64_t codes = (stay ? 1 : 2) * p.chunk * 512;
 
-    struct Tiling { int64_t tilesM, records, lds, blocks, buffers; };     // blocks: that a compute unit holds
-    auto tiling = [&](int fp) {                            // fp: pixel tiles of a wave; pooled 4 with both channel tiles, 3 with one
+    struct Tiling { bool packed; int64_t tilesM, padded, plane, records, table, codes, lds, blocks, buffers; bool walks; };     // blocks: that a compute unit holds
+    // fp: pixel tiles of a wave; pooled 4 with both channel tiles, 3 with one; pairs: of channel tiles; packed: features are staged as
+    // bits, not as codes
+    auto tiling = [&](int fp, int pairs, bool packed) {
         Tiling t{};
         const int64_t pixels = fp == 3 ? 256 : 128 * fp;
         t.tilesM = ceil_div(mp.M, pixels);
@@ -108,61 +122,76 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
         const int64_t between = Hq - rows * step;          // lines an image has beyond its rows' steps
         const int64_t reach = new_rows * step * Wq + (cols - 1) * (mp.pool ? 2 : 1) * mp.stride + new_images * (between > 0 ? between : 0) * Wq +
                               (mp.pool ? mp.stride * (Wq + 1) : 0) + (mp.R - 1) * Wq + mp.S;
-        t.records = (reach < images * Hq * Wq ? reach : images * Hq * Wq) * p.rec;
-        const int64_t most = fp == 4 ? 2 : fp == 1 ? 4 : 3;    // by registers: waves a SIMD holds
+        // (with four words a lane an odd number of positions: those that neighbouring lanes write fall on different banks)
+        t.plane = (packed ? 2 : 4) * ((reach < images * Hq * Wq ? reach : images * Hq * Wq) | (sw == 4 ? 1 : 0));
+        t.packed = packed;
+        t.records = t.plane * 2 * p.half * p.DA;
+        t.padded = padded(fp);
+        t.table = round_up((t.padded * p.DA + 5 * halo_granule(fp == 3 ? 4 : fp, fp == 3 ? 1 : 2)) * (multi ? 2 : 1), 4);
+        t.codes = (stay ? t.padded : 2 * kHaloChunk) * 512 * pairs + t.table;
+        const int64_t most = pairs == 2 ? 1 : fp == 4 ? 2 : fp == 1 && !stay && !multi ? 4 : 3;    // by registers: waves a SIMD holds
         auto fit = [&](int64_t buffers) {
             t.buffers = buffers;
-            t.lds = 4 * (128 + codes + buffers * t.records);
+            t.lds = 4 * (128 * pairs + t.codes + buffers * t.records);
             t.blocks = 160 * 1024 / t.lds < most ? 160 * 1024 / t.lds : most;
         };
         fit(1);
-        // a second buffer of records is for blocks that have a second tile, and two of those to a compute unit
-        if (stay && t.tilesM * tilesN > 256 * t.blocks / tilesN * tilesN) {
-            const int64_t single = t.blocks;
+        // blocks that have a second tile walk, with a second buffer of records where as many of them fit
+        const int64_t columns = ceil_div(mp.N, 64 * pairs), single = t.blocks;
+        t.walks = stay && t.tilesM * columns > 256 * t.blocks / columns * columns && 256 * t.blocks >= columns;
+        if (t.walks) {
             fit(2);
-            if (t.blocks < (single < 2 ? single : 2) || 256 * t.blocks < tilesN) fit(1);
+            if (t.blocks < (force == 1 || force == 2 ? 1 : single) || 256 * t.blocks < columns) fit(1);
         }
         return t;
     };
-    // 64 x 256 outputs a block, or 64 x 128 (measured, us, 64 x 128 against 64 x 256):
-    //   weights that stay: 9 steps on 1568 tiles of 256 17.9, 15.3; 18 steps 23.6, 29.2; 9 steps with stride 2 on 784 13.5, 17.9
-    //   chunks: what a compute unit holds of pixels decides; 36 steps on 392 tiles 17.2, 14.7 (512 pixels against 384); 72 steps
-    //   on 784 tiles 47, 59 (256 either way)
-    // Pooled: 64 x 128 pooled outputs a block (a wave has both channel tiles), or 64 x 64 (one; fewer and smaller blocks fill the
-    // chip): 36 steps on 196 of the larger tiles 12.4, 18.0; 72 on 104 20.1, 16.0; 36 on 98 12, 9.9; 9 on 784 21.5, 20.9.
-    int fp = mp.pool ? 3 : 1;
-    Tiling t = tiling(fp);
-    if (t.blocks < 1) return false;
-    if (force < 0 && small_tiles <= 4096 && !worth_staging(mp, small_tiles, blocks, steps, stay, t.buffers == 2 ? 1 : ceil_div(blocks, 256 * t.blocks)))
-        return false;
-    if (mp.pool) {
-        const Tiling four = tiling(4);
-        if (force != 1 && (force == 2 || four.tilesM * tilesN >= 150) && four.blocks >= 1) { fp = 4; t = four; }
-    } else {
-        const Tiling two = tiling(2);
-        fp = force == 1 || force == 2 ? force
-             : stay ? (p.steps <= 12 && mp.stride == 1 && two.blocks > 0 && two.tilesM * tilesN >= 256 ? 2 : 1)
-                    : (2 * two.blocks > t.blocks && two.tilesM * tilesN >= 192 ? 2 : 1);
-        if (fp == 2) t = two;
+    int fp = mp.pool ? 3 : 1, pairs = 1;
+    Tiling t{};
+    double best = 0.0;
+    for (int i = 0; i < 4; ++i) {
+        const int f = (mp.pool ? 3 : 1) + (i & 1), n = 1 + (i >> 1);
+        if (force > 0 && force != i + 1 && !(n == 1 && (force == 5 + (i & 1) || force == 7 + (i & 1)))) continue;
+        if (n == 2 && (sw != 4 || multi || mp.N <= 64)) continue;
+        for (const bool packed : {false, true}) {
+            if (packed ? n == 2 || force > 6 : multi || force == 5 || force == 6) continue;
+            const Tiling c = tiling(f, n, packed);
+            if (c.blocks < 1) continue;
+            const double cost = tiling_cost(f, n, c.tilesM * ceil_div(mp.N, 64 * n), c.blocks, c.walks, packed ? 2.0 * c.records : c.records, steps * p.DA * p.DB, packed);
+            if (t.blocks > 0 && cost >= best) continue;
+            best = cost; t = c; fp = f; pairs = n;
+        }
     }
-    const int64_t tiles = t.tilesM * tilesN;
-    if (t.blocks < 1 || tiles > kMaxBlocks) return false;
+    if (t.blocks < 1) return false;
+    if (force < 0 && small_tiles <= 4096 && !worth_staging(mp, small_tiles, blocks, steps, stay, t.walks ? 1 : ceil_div(blocks, 256 * t.blocks)))
+        return false;
+    const int columns = static_cast<int>(ceil_div(mp.N, 64 * pairs));
+    const int64_t tiles = t.tilesM * columns;
+    if (tiles > kMaxBlocks) return false;
     // Beyond 4096 tiles of 32 x 32: not where staging a tile's pixels is most of the work and little else of the compute unit runs
     // meanwhile.  Matrix instructions of 32 x 32 x 64 for 1000 staged words, and the time relative to the other kernels, on average
     // over 4900 layers: blocks with one tile, one block to a compute unit 2.1 up to 1.4, 1.2 up to 2.8, 1.1 up to 5.7 (level from 4.5 on),
     // 0.8 up to 11, 0.6 to 0.7 beyond; two blocks 1.3 up to 1.4, 0.75 beyond; three 1.0 up to 1.4, four 0.8; blocks that walk, one 1.8 up to 1.4, 0.9
     // beyond, two and more 0.6 (72 x 72, 288 -> 320 channels, 1 x 1, stride 2, pooled, batch 74: 98.6 us and 29.9).
     if (force < 0 && small_tiles > 4096) {
-        const double work = static_cast<double>(steps) * mp.DA * mp.DB * (fp == 3 ? 256 : 128 * fp) / 64, words = 1e-3 * t.records;
-        const double least = t.buffers == 2 ? (t.blocks == 1 ? 2.0 : 0.0) : t.blocks == 1 ? 4.5 : t.blocks == 2 ? 1.5 : 0.0;
+        const double work = static_cast<double>(steps) * mp.DA * mp.DB * (fp == 3 ? 256 : 128 * fp) / 64, words = 1e-3 * t.records / (t.packed ? 1 : 2);
+        const double least = t.walks ? (t.blocks == 1 ? 2.0 : 0.0) : t.blocks == 1 ? 4.5 : t.blocks == 2 ? 1.5 : 0.0;
         if (work < least * words) return false;
     }
     int64_t grid = tiles;
-    if (t.buffers == 2) grid = 256 * t.blocks / tilesN * tilesN;           // whole rows of channel tiles
+    if (t.walks) grid = 256 * t.blocks / columns * columns;           // whole rows of channel tiles
     p.tilesM = static_cast<int>(t.tilesM);
-    p.per_column = divisor(tilesN);
-    p.words_codes = static_cast<int>(codes);
-    p.tile_step = static_cast<int>(grid / tilesN);
+    p.per_column = divisor(columns);
+    p.packed = t.packed;
+    p.rec = (t.packed ? 4 : 8) * p.half * p.DA;
+    p.pieces = p.DA * static_cast<int>(ceil_div(2 * p.half, sw));
+    while ((1 << p.share) < p.pieces) ++p.share;
+    p.pairs = pairs; p.buffers = static_cast<int>(t.buffers);
+    p.plane = static_cast<int>(t.plane);
+    p.padded = static_cast<int>(t.padded);
+    p.second = steps == 1 ? 0u : p.half > 1 ? 4u * static_cast<uint32_t>(t.plane) : (t.packed ? 8u : 16u) * static_cast<uint32_t>(p.S > 1 ? 1 : p.Wq);
+    p.words_table = static_cast<int>(t.table);
+    p.words_codes = static_cast<int>(t.codes);
+    p.tile_step = static_cast<int>(grid / columns);
     p.words_records = static_cast<int>(t.records);
     const unsigned g = static_cast<unsigned>(grid);
     const int bytes = static_cast<int>(t.lds);

@@ -5,7 +5,7 @@ namespace apnn {
 
 bool launch_conv_halo_pm1(const ConvHaloParams &p, bool stay, int fp, unsigned grid, int lds, hipStream_t st)
 {
-    return launch_conv_halo<OPK_PM1Z, false>(p, stay, fp, grid, lds, st);
+    return launch_conv_halo<OPK_PM1Z>(p, stay, fp, grid, lds, st);
 }
 
 }  // namespace apnn

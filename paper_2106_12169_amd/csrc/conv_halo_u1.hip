@@ -5,7 +5,7 @@ namespace apnn {
 
 bool launch_conv_halo_u1(const ConvHaloParams &p, bool stay, int fp, unsigned grid, int lds, hipStream_t st)
 {
-    return launch_conv_halo<OPK_U1, false>(p, stay, fp, grid, lds, st);
+    return launch_conv_halo<OPK_U1>(p, stay, fp, grid, lds, st);
 }
 
 }  // namespace apnn

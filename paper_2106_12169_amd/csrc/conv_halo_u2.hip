@@ -5,7 +5,7 @@ namespace apnn {
 
 bool launch_conv_halo_u2(const ConvHaloParams &p, bool stay, int fp, unsigned grid, int lds, hipStream_t st)
 {
-    return p.DA > 1 ? launch_conv_halo<OPK_U2, true>(p, stay, fp, grid, lds, st) : launch_conv_halo<OPK_U2, false>(p, stay, fp, grid, lds, st);
+    return launch_conv_halo<OPK_U2>(p, stay, fp, grid, lds, st);
 }
 
 }  // namespace apnn
