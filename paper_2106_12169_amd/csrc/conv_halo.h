@@ -44,7 +44,7 @@ struct ConvHaloParams {
     int pairs, buffers;      // pairs of channel tiles of a block, buffers of feature codes
     int packed;              // features are staged as bits, not as codes
     Divisor halves, columns;                 // half, S
-    uint32_t second;         // bytes from the first step's codes to the second's
+    uint32_t second;         // bytes from the first entry's codes to the second's
     int pool;                // 0 none, 1 maximum, 2 sum
     int scaleA, scaleB;      // block scales (exponent bytes) of features and weights
     Divisor per_column;      // channel tiles
@@ -389,12 +389,11 @@ __global__ __launch_bounds__(128 * FC, FC == 4 ? 2 : FP * FW == 8 ? 2 : FP == 1 
         read_table();
         {                                                        // the first granule
             offsets_t off;
-            if constexpr (MULTI) {
-                off = *reinterpret_cast<const offsets_t *>(sT + G * E);
-                even.scaleB = sB_now;
-            } else {
+            if (MULTI) even.scaleB = sB_now;
 #pragma unroll
-                for (int g = 0; g < G; ++g) off[g] = g == 0 ? 0u : p.second;
+            for (int g = 0; g < G; ++g) {
+                off[E * g] = g == 0 ? 0u : p.second;
+                if (MULTI) off[E * g + 1] = g == 0 ? 0u : p.DA > 1 ? 1u : 1024u * FC;  // (one step: the one that fills up)
             }
             static_for<READS>([&](auto kc) __attribute__((always_inline)) { read(even, kc, off, codes); });
         }

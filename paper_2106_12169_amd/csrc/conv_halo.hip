@@ -162,8 +162,22 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
         }
     }
     if (t.blocks < 1) return false;
-    if (force < 0 && small_tiles <= 4096 && !worth_staging(mp, small_tiles, blocks, steps, stay, t.walks ? 1 : ceil_div(blocks, 256 * t.blocks)))
-        return false;
+    if (force < 0 && small_tiles <= 4096) {
+        // rounds of the blocks that the model was fitted to: the smaller tiles, chunks of whole taps, features as bits in records of an
+        // odd number of granules
+        const Tiling small = tiling(mp.pool ? 3 : 1, 1, true);
+        const int64_t codes = (stay ? steps : 2 * (kHaloChunk / p.half * p.half)) * 512, most = mp.pool ? 3 : 4;
+        const int64_t hw = sw == 4 ? 2 : 1, granules = p.DA * 2 * (p.half / hw);
+        const int64_t records = small.plane / 2 * (kindA == OPK_U1 ? 1 : 2) * hw * (granules | 1);
+        auto resident = [&](int64_t buffers) {
+            const int64_t n = 160 * 1024 / (4 * (128 + codes + buffers * records));
+            return n < most ? n : most;
+        };
+        const int64_t one = resident(1), two = resident(2);
+        if (one < 1) return false;
+        const bool walks = stay && small.tilesM * tilesN > 256 * one / tilesN * tilesN && two >= (one < 2 ? one : 2) && 256 * two >= tilesN;
+        if (!worth_staging(mp, small_tiles, blocks, steps, stay, walks ? 1 : ceil_div(blocks, 256 * one))) return false;
+    }
     const int columns = static_cast<int>(ceil_div(mp.N, 64 * pairs));
     const int64_t tiles = t.tilesM * columns;
     if (tiles > kMaxBlocks) return false;
@@ -174,7 +188,8 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
     // beyond, two and more 0.6 (72 x 72, 288 -> 320 channels, 1 x 1, stride 2, pooled, batch 74: 98.6 us and 29.9).
     if (force < 0 && small_tiles > 4096) {
         const double work = static_cast<double>(steps) * mp.DA * mp.DB * (fp == 3 ? 256 : 128 * fp) / 64, words = 1e-3 * t.records / (t.packed ? 1 : 2);
-        const double least = t.walks ? (t.blocks == 1 ? 2.0 : 0.0) : t.blocks == 1 ? 4.5 : t.blocks == 2 ? 1.5 : 0.0;
+        const int64_t groups = t.blocks * pairs;                 // of four waves (128 x 28 x 28, 128 -> 256, 1 x 1, stride 2: 9.3 us, 6.7 in one of eight)
+        const double least = t.walks ? (groups == 1 ? 2.0 : 0.0) : groups == 1 ? 4.5 : groups == 2 ? 1.5 : 0.0;
         if (work < least * words) return false;
     }
     int64_t grid = tiles;
@@ -188,7 +203,7 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
     p.pairs = pairs; p.buffers = static_cast<int>(t.buffers);
     p.plane = static_cast<int>(t.plane);
     p.padded = static_cast<int>(t.padded);
-    p.second = steps == 1 ? 0u : p.half > 1 ? 4u * static_cast<uint32_t>(t.plane) : (t.packed ? 8u : 16u) * static_cast<uint32_t>(p.S > 1 ? 1 : p.Wq);
+    p.second = p.DA > 1 ? 8u * static_cast<uint32_t>(p.half) * static_cast<uint32_t>(t.plane) : steps == 1 ? 0u : p.half > 1 ? 4u * static_cast<uint32_t>(t.plane) : (t.packed ? 8u : 16u) * static_cast<uint32_t>(p.S > 1 ? 1 : p.Wq);
     p.words_table = static_cast<int>(t.table);
     p.words_codes = static_cast<int>(t.codes);
     p.tile_step = static_cast<int>(grid / columns);
