@@ -65,6 +65,19 @@ constexpr int kHaloStay = 26, kHaloChunk = 8;
 // one's reads, two instructions do not.
 constexpr int halo_granule(int fp, int fw) { return fp * fw >= 4 ? 1 : 2; }
 
+// Where a lane whose words of plane 0 are at byte `at` of the weights finds them in another plane: its own offset and the one that
+// all lanes share.  A plane that is not there (the second one of an odd last digit) reads as zero by the lane's own offset, which
+// the load checks against the buffer; the shared offset is no part of that check, so it stays inside the buffer.
+struct PlaneOffset {
+    uint32_t lane, shared;
+};
+constexpr uint32_t kNowhere = 0x80000000u;                       // beyond every buffer (2^31 bytes at most): reads as zero
+__host__ __device__ __forceinline__ PlaneOffset plane_offset(uint32_t at, int plane, int planes, int Kw)
+{
+    if (plane >= planes) return {kNowhere, 0u};
+    return {at, 4u * static_cast<uint32_t>(plane) * static_cast<uint32_t>(Kw)};
+}
+
 // SW: channel words of a plane staged together (4, 2, or 1 for an odd number of channel words); FP, FW: 32-pixel and 32-channel
 // tiles of a wave (FW = 1: two waves share the pixels).  MULTI: operands of more than one digit.
 // POOL (FP = 4): tile f of a wave holds member f of its 32 pooling grids, so that pooling is three instructions per output.
@@ -100,7 +113,6 @@ __global__ __launch_bounds__(128 * FC, FC == 4 ? 2 : FP * FW == 8 ? 2 : FP == 1 
 
     const __amdgpu_buffer_rsrc_t bufA = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(p.A), 0, p.bytesA, 0x00020000);
     const __amdgpu_buffer_rsrc_t bufB = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(p.B), 0, p.bytesB, 0x00020000);
-    constexpr uint32_t NOWHERE = 0x80000000u;                    // beyond every buffer: reads as zero
 
     // ---- weights.  Packed output: matrix row -> channel as plane_codes.h says; int32 output: in order, four to a store.
     // Rows beyond the last channel read that channel's (their results are not stored); steps beyond the last, and the step a
@@ -115,19 +127,19 @@ __global__ __launch_bounds__(128 * FC, FC == 4 ? 2 : FP * FW == 8 ? 2 : FP == 1 
     auto fetch_granule = [&](int u, int digit, int s, auto pm1) __attribute__((always_inline)) {
         const int tap = divide(s, p.halves), cw = wh * p.half + s - tap * p.half;
         const uint32_t at = wlane + 4u * static_cast<uint32_t>(cw < p.Cw ? tap * p.Cw + cw : 0);
-        auto load = [&](uint32_t (&w)[HW], uint32_t plane) __attribute__((always_inline)) {
+        auto load = [&](uint32_t (&w)[HW], PlaneOffset from) __attribute__((always_inline)) {
             if constexpr (HW == 4) {
-                const auto t = __builtin_amdgcn_raw_buffer_load_b128(bufB, at, plane, 0);
+                const auto t = __builtin_amdgcn_raw_buffer_load_b128(bufB, from.lane, from.shared, 0);
                 w[0] = t[0]; w[1] = t[1]; w[2] = t[2]; w[3] = t[3];
             } else if constexpr (HW == 2) {
-                const auto t = __builtin_amdgcn_raw_buffer_load_b64(bufB, at, plane, 0);
+                const auto t = __builtin_amdgcn_raw_buffer_load_b64(bufB, from.lane, from.shared, 0);
                 w[0] = t[0]; w[1] = t[1];
             } else {
-                w[0] = __builtin_amdgcn_raw_buffer_load_b32(bufB, at, plane, 0);
+                w[0] = __builtin_amdgcn_raw_buffer_load_b32(bufB, from.lane, from.shared, 0);
             }
         };
-        load(wv[u][0], 8u * static_cast<uint32_t>(digit * Kw));
-        if constexpr (!decltype(pm1)::value) load(wv[u][1], 2 * digit + 1 < p.PB ? 8u * static_cast<uint32_t>(digit * Kw) + 4u * static_cast<uint32_t>(Kw) : NOWHERE);
+        load(wv[u][0], plane_offset(at, 2 * digit, p.PB, Kw));
+        if constexpr (!decltype(pm1)::value) load(wv[u][1], plane_offset(at, 2 * digit + 1, p.PB, Kw));
     };
     Fp4Masks km;
     km.m1 = reg_const(0x11111111u); km.m2 = reg_const(0x22222222u);
@@ -203,8 +215,8 @@ __global__ __launch_bounds__(128 * FC, FC == 4 ? 2 : FP * FW == 8 ? 2 : FP == 1 
             in[u] = q < r.total && n < p.images && static_cast<unsigned>(y) < static_cast<unsigned>(p.H) &&
                     static_cast<unsigned>(x) < static_cast<unsigned>(p.W) && cw < p.Cw;
             const int at = (((n * p.H + y) * p.W + x) * p.PA + 2 * d) * p.Cw + cw;
-            load_piece(in[u] ? 4u * static_cast<uint32_t>(at) : NOWHERE, a0[u]);
-            if (KA == OPK_U2) load_piece(in[u] && 2 * d + 1 < p.PA ? 4u * static_cast<uint32_t>(at + p.Cw) : NOWHERE, a1[u]);
+            load_piece(in[u] ? 4u * static_cast<uint32_t>(at) : kNowhere, a0[u]);
+            if (KA == OPK_U2) load_piece(in[u] && 2 * d + 1 < p.PA ? 4u * static_cast<uint32_t>(at + p.Cw) : kNowhere, a1[u]);
         }
     };
     auto write_pixels = [&](uint32_t *features, Range r, int q0) {

@@ -100,6 +100,20 @@ int main()
         EXPECT(g_lds == 4 * (128 + g_p.words_codes + 2 * g_p.words_records));
     }
 
+    // weight planes: one that is there is inside the weights by both offsets, one that is not is beyond them by the lane's own (the load's
+    // range check leaves the shared one out)
+    for (int planes = 1; planes <= 8; ++planes)
+        for (int Kw : {1, 18, 4608}) {
+            const uint32_t row = 4u * static_cast<uint32_t>(planes * Kw), bytes = 640u * row;      // of a channel, of all
+            for (int plane = 0; plane < 2 * ((planes + 1) / 2); ++plane) {
+                const uint32_t at = 639u * row + 4u * static_cast<uint32_t>(Kw - 1);              // the last word of the last channel
+                const PlaneOffset o = plane_offset(at, plane, planes, Kw);
+                EXPECT(o.shared < bytes);
+                if (plane < planes) EXPECT(o.lane == at && o.shared == 4u * static_cast<uint32_t>(plane * Kw) && o.lane + o.shared < bytes);
+                else EXPECT(o.lane >= uint32_t(1) << 31);
+            }
+        }
+
     if (failures == 0) std::puts("staged convolution sanitizer run ok");
     return failures != 0;
 }
