@@ -37,7 +37,7 @@ struct ConvHaloParams {
     int PA, PB, DA, DB;      // planes and base-4 digits of features / weights
     Divisor digits;          // DA
     int pm1;                 // weights -1/+1, else 0/1 planes
-    int rec, plane;          // LDS words of a staged position's codes, from a channel word's codes to the next one's
+    int plane;               // LDS words from a channel word's codes of the staged positions to the next one's
     int pieces, share;       // pieces a position is staged in, log2 of the threads that share it
     int words_table, words_codes, words_records;     // LDS words of the step offsets, of them and the weight codes, of a buffer of feature codes
     int steps, padded;       // matrix steps of a weight digit, of it as it is walked

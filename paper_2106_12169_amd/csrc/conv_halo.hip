@@ -197,7 +197,6 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
     p.tilesM = static_cast<int>(t.tilesM);
     p.per_column = divisor(columns);
     p.packed = t.packed;
-    p.rec = (t.packed ? 4 : 8) * p.half * p.DA;
     p.pieces = p.DA * static_cast<int>(ceil_div(2 * p.half, sw));
     while ((1 << p.share) < p.pieces) ++p.share;
     p.pairs = pairs; p.buffers = static_cast<int>(t.buffers);

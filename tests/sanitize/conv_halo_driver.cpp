@@ -79,7 +79,8 @@ int main()
     EXPECT(!staged({100, 1, 1, 64, 64, 1, 1, 1 << 29, 536870911, true, 1, false, 2}, 1));
     EXPECT(!staged({1, 1, 1 << 28, 32, 64, 1, 1, 2147483647, 0, true, 1, false, 1}, 1));       // 127 strides of 2^28 positions
     EXPECT(!staged({3, 1, 1 << 20, 32, 64, 1, 1, 2147483647, 0, true, 1, false, 1}, 1));
-    EXPECT(staged({300, 1, 1, 32, 64, 1, 1, 2147483647, 0, true, 1, false, 1}, 1) && g_p.words_records == 128 * g_p.rec);
+    EXPECT(staged({300, 1, 1, 32, 64, 1, 1, 2147483647, 0, true, 1, false, 1}, 1) && g_p.words_records == 2 * g_p.plane);
+    EXPECT(g_p.plane == (g_p.packed ? 2 : 4) * 128);                                          // 128 positions of 300 frames
 
     // block scales: biased exponents in every byte, those of 0/1 weights and of int32 results from 2^7 up
     EXPECT(staged({1, 8, 8, 64, 64, 3, 3, 1, 1, true, 1, false, 2}, 1) && g_p.scaleA == 0x7e7e7e7e && g_p.scaleB == 0x7f7f7f7f);
