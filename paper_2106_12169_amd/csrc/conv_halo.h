@@ -44,7 +44,7 @@ struct ConvHaloParams {
     int pairs, buffers;      // pairs of channel tiles of a block, buffers of feature codes
     int packed;              // features are staged as bits, not as codes
     Divisor halves, columns;                 // half, S
-    uint32_t second;         // bytes from the first entry's codes to the second's
+    uint32_t first[4], first_codes[4];       // the first entries' words of the table of offsets
     int pool;                // 0 none, 1 maximum, 2 sum
     int scaleA, scaleB;      // block scales (exponent bytes) of features and weights
     Divisor per_column;      // channel tiles
@@ -62,8 +62,9 @@ struct ConvHaloParams {
 constexpr int kHaloStay = 26, kHaloChunk = 8;
 
 // Steps whose operands a wave reads together: one step's four and more matrix instructions cover the latency of the next
-// one's reads, two instructions do not.
-constexpr int halo_granule(int fp, int fw) { return fp * fw >= 4 ? 1 : 2; }
+// one's reads, two instructions do not -- unless four waves share a SIMD, as those of the smaller tile of bits do where weights stay
+// (1x1 sums of one to four steps of several digits, relative to two steps with three waves: 0.95).
+constexpr int halo_granule(int fp, int fw, bool shared) { return shared || fp * fw >= 4 ? 1 : 2; }
 
 // Where a lane whose words of plane 0 are at byte `at` of the weights finds them in another plane: its own offset and the one that
 // all lanes share.  A plane that is not there (the second one of an odd last digit) reads as zero by the lane's own offset, which
@@ -85,11 +86,11 @@ __host__ __device__ __forceinline__ PlaneOffset plane_offset(uint32_t at, int pl
 // flight during the main loop.  Otherwise a block has one tile, and the weights pass through two buffers, a chunk each, with
 // one barrier per chunk.
 template <int KA, int SW, int FP, int FW, int FC, bool POOL, bool MULTI, bool PACKED, bool STAY>
-__global__ __launch_bounds__(128 * FC, FC == 4 ? 2 : FP * FW == 8 ? 2 : FP == 1 && !STAY && !MULTI ? 4 : 3) void conv_halo_kernel(const ConvHaloParams p)
+__global__ __launch_bounds__(128 * FC, FC == 4 ? 2 : FP * FW == 8 ? 2 : FP == 1 && (STAY ? PACKED : !MULTI) ? 4 : 3) void conv_halo_kernel(const ConvHaloParams p)
 {
     static_assert(!POOL || FP == 4, "a wave's four pixel tiles are the members of its pooling grids");
     constexpr int HW = SW == 8 ? 4 : SW == 4 ? 2 : 1, PW = SW == 8 ? 4 : SW;     // channel words of a weight load, of a piece of a pixel
-    constexpr int G = halo_granule(FP, FW);                      // steps of a granule
+    constexpr int G = halo_granule(FP, FW, PACKED && STAY);      // steps of a granule
     constexpr int E = MULTI ? 2 : 1;                             // LDS words of a table entry
     constexpr int CW = PACKED ? 2 : 4;                           // LDS words of a channel word of a position
     constexpr int NT = 128 * FC;                                 // threads: four waves for every two channel tiles
@@ -168,8 +169,10 @@ __global__ __launch_bounds__(128 * FC, FC == 4 ? 2 : FP * FW == 8 ? 2 : FP == 1 
     auto write_weights = [&](int steps) {
         auto all = [&](auto pm1) {
 #pragma unroll
-            for (int u = 0; u < NI; ++u)
+            for (int u = 0; u < NI; ++u) {
+                if (2 * u * HW >= steps) break;                  // uniform
                 if (const int s = (2 * u + wk) * HW; s < steps) write_granule(u, sB, s, p.steps, pm1);
+            }
         };
         if (p.pm1) all(std::true_type{});
         else all(std::false_type{});
@@ -241,6 +244,15 @@ __global__ __launch_bounds__(128 * FC, FC == 4 ? 2 : FP * FW == 8 ? 2 : FP == 1 
         }
     };
 
+    // all of a tile's pieces, the first ones of which are fetched already
+    auto write_tile = [&](uint32_t *features, Range r) {
+        write_pixels(features, r, tid);
+        for (int q = tid + NT * U; q < r.total; q += NT * U) {
+            fetch_pixels(r, q);
+            write_pixels(features, r, q);
+        }
+    };
+
     // Weights that pass through: the chunk after one, in the order of the sums (digit DB: none).  A chunk's codes are written
     // while the one before it is multiplied, from words that were fetched a whole chunk earlier.
     struct Chunk { int digit, s0; };
@@ -272,47 +284,53 @@ __global__ __launch_bounds__(128 * FC, FC == 4 ? 2 : FP * FW == 8 ? 2 : FP == 1 
     };
 
     Range now = range_of(tile0);
+    float constant = 0.0f;                                       // scale (first half of the threads) or bias of a channel
+    if (!p.Y && tid < 64 * FC) {
+        const int k = tid % (32 * FC), ch = n0 + (k & ~31) + code_channel(k & 15, (k >> 4) & 1);
+        if (ch < p.N) constant = (tid < 32 * FC ? p.scale : p.bias)[ch];
+    }
     fetch_weights(STAY ? p.steps : min(kHaloChunk, p.steps));
     fetch_pixels(now, tid);
+    // what needs no load is made while these are in flight
+    int gm[FP];                                                  // this lane's pixels
+    const uint8_t *base[FP];                                     // the first tap's position, this lane half's words
+    auto point = [&](int tile, int buffer) {
+        const int m0 = tile * BP, last = min(m0 + BP, p.M) - 1;
+#pragma unroll
+        for (int f = 0; f < FP; ++f) {
+            gm[f] = POOL ? m0 + 4 * (32 * wp + lr) + f : m0 + (wp * FP + f) * 32 + lr;
+            base[f] = reinterpret_cast<const uint8_t *>(sA + buffer * p.words_records + CW * (position(min(gm[f], last)) - now.lo) + lh * p.half * p.plane);
+        }
+    };
+    point(tile0, 0);
+    // Weights that stay: granules of a tile's sums.  One or two of them come without the table, their offsets with the launch: in sums
+    // of up to four steps the table, the step that fills up and what stood between the loads and the barrier were up to a tenth of
+    // the layer (40 layers of one digit, 1.054 times what they had taken with operands expanded in the loop, now 1.00 to 1.03; 18 of
+    // several digits 1.033, now 1.02; 80 x 32 x 25, 32 -> 64 channels, four feature planes 6.13 us, now 5.98).
+    const int entries = (MULTI ? p.steps * p.DA : p.steps), stay_granules = (entries + G - 1) / G;
+    const bool few = STAY && stay_granules <= 2;
     // Where an entry's operands are, from those of the first one; an entry is a step or, with several digits, a step and a digit of the
     // features: then the codes of its weights (in the chunk) with the digit in the low bits stand beside it.  Entry e is at e + G.
-    for (int i = tid; i < p.words_table / E; i += NT) {
+    for (int i = few ? p.words_table : tid; i < p.words_table / E; i += NT) {
         const int e = max(i - G, 0), st = MULTI ? divide(e, p.digits) : e, d = MULTI ? e - st * p.DA : 0;
         const int tap = divide(st, p.halves), r = divide(tap, p.columns);
         sT[E * i] = st < p.steps ? 4u * CW * static_cast<uint32_t>(r * p.Wq + tap - r * p.S) +
                                        4u * static_cast<uint32_t>((st - tap * p.half + d * 2 * p.half) * p.plane) : 0u;
         if (MULTI) sT[E * i + 1] = 1024u * FC * static_cast<uint32_t>(STAY ? min(st, p.padded - 1) : st % kHaloChunk) + d;
     }
-    if (!p.Y && tid < 64 * FC) {                                 // scale (first half of the threads) and bias of a channel
-        const int k = tid % (32 * FC), ch = n0 + (k & ~31) + code_channel(k & 15, (k >> 4) & 1);
-        float v = 0.0f;
-        if (ch < p.N) v = tid < 32 * FC ? p.scale[ch] : quarter(p.bias[ch]);
-        sP[tid] = v;
-    }
     write_weights(STAY ? p.padded : kHaloChunk);
     if constexpr (!STAY) {
         if (p.pm1) fetch_chunk(after(Chunk{0, 0}), std::true_type{});
         else fetch_chunk(after(Chunk{0, 0}), std::false_type{});
     }
-    write_pixels(sA, now, tid);
-    for (int q = tid + NT * U; q < now.total; q += NT * U) {
-        fetch_pixels(now, q);
-        write_pixels(sA, now, q);
-    }
+    if (!p.Y && tid < 64 * FC) sP[tid] = tid < 32 * FC ? constant : quarter(constant);
+    write_tile(sA, now);
     __syncthreads();
 
     const int scaleA = static_cast<int>(reg_const(static_cast<uint32_t>(p.scaleA))), scaleB0 = static_cast<int>(reg_const(static_cast<uint32_t>(p.scaleB)));
     const uint32_t m3 = reg_const(0x33333333u);
 
     for (int tile = tile0, buffer = 0;; buffer ^= p.buffers - 1) {
-        const int m0 = tile * BP, last = min(m0 + BP, p.M) - 1;
-        int gm[FP];                                              // this lane's pixels
-        const uint8_t *base[FP];                                 // the first tap's position, this lane half's words
-#pragma unroll
-        for (int f = 0; f < FP; ++f) {
-            gm[f] = POOL ? m0 + 4 * (32 * wp + lr) + f : m0 + (wp * FP + f) * 32 + lr;
-            base[f] = reinterpret_cast<const uint8_t *>(sA + buffer * p.words_records + CW * (position(min(gm[f], last)) - now.lo) + lh * p.half * p.plane);
-        }
         // residual words and the next tile's first pixels: their latency hides behind the main loop
         constexpr int FO = POOL ? 1 : FP;                        // output tiles per channel tile
         uint32_t res[FO][FW][2];
@@ -398,85 +416,93 @@ __global__ __launch_bounds__(128 * FC, FC == 4 ? 2 : FP * FW == 8 ? 2 : FP == 1 
 #pragma unroll
             for (int i = 0; i < G * E; ++i) { t.one[i] = v[i]; t.two[i] = v[G * E + i]; }
         };
-        read_table();
-        {                                                        // the first granule
+        auto launched = [&](int k) __attribute__((always_inline)) {          // offsets of granule k < 2
             offsets_t off;
-            if (MULTI) even.scaleB = sB_now;
 #pragma unroll
             for (int g = 0; g < G; ++g) {
-                off[E * g] = g == 0 ? 0u : p.second;
-                if (MULTI) off[E * g + 1] = g == 0 ? 0u : p.DA > 1 ? 1u : 1024u * FC;  // (one step: the one that fills up)
+                off[E * g] = p.first[G * k + g];
+                if (MULTI) off[E * g + 1] = p.first_codes[G * k + g];
             }
-            static_for<READS>([&](auto kc) __attribute__((always_inline)) { read(even, kc, off, codes); });
-        }
-        Chunk at{0, 0};
-        int half_buffer = 0;
-        bool staged = STAY ? false : stage_next(at, half_buffer);            // the chunk after this one is on its way
-        // A run: the granules of a chunk.  All but the last one of a weight digit have an even number.
-        auto granules = [&]() __attribute__((always_inline)) {
-            const int left = (MULTI ? p.steps : p.padded) - at.s0;
-            return ((STAY ? left : min(kHaloChunk, left)) * (MULTI ? p.DA : 1) + G - 1) / G;
+            return off;
         };
-        offsets_t off;
-        auto first_of_pair = [&](auto first) __attribute__((always_inline)) {
-            multiply_and_read(even, odd, t.one, MULTI ? codes : codes + G * FC * 256, first);
-            off = t.two;
-            if (!MULTI) codes += 2 * G * FC * 256;
-            table += 2 * G * E;
+        // the sums' last granule: without the step that fills it up, where weights stay
+        auto multiply_last = [&](const Operands &o, auto first) __attribute__((always_inline)) {
+            static_for<FW * FP>([&](auto kc) __attribute__((always_inline)) { product(o, kc, first); });
+            if (G == 2 && (!STAY || entries % 2 == 0))
+                static_for<PRODUCTS - FW * FP>([&](auto kc) __attribute__((always_inline)) { product(o, std::integral_constant<int, FW * FP + decltype(kc)::value>{}, first); });
         };
-        auto second_of_pair = [&]() __attribute__((always_inline)) {
-            read_table();
-            multiply_and_read(odd, even, off, codes, std::false_type{});
-        };
-        int n = granules();
-        if (n > 2) {
-            first_of_pair(std::true_type{});
-            second_of_pair();
-            n -= 2;
+        if (MULTI) even.scaleB = sB_now;
+        const offsets_t off0 = launched(0);
+        t.one = launched(1);
+        if (!few) t.two = *reinterpret_cast<const offsets_t *>(table + G * E);
+        static_for<READS>([&](auto kc) __attribute__((always_inline)) { read(even, kc, off0, codes); });
+        if (STAY && FP * FW == 2 && !MULTI && stay_granules == 1) {              // (one granule starts and ends the sums; larger tiles would spill registers)
+            multiply_last(even, std::true_type{});
         } else {
-#pragma unroll
-            for (int c = 0; c < FW; ++c)
-#pragma unroll
-                for (int f = 0; f < FP; ++f) acc[c][f] = v16f_t{};
-        }
-        while (true) {
-            for (int left = (n - 1) >> 1; left > 0; --left) {
-                first_of_pair(std::false_type{});
+            Chunk at{0, 0};
+            int half_buffer = 0;
+            bool staged = STAY ? false : stage_next(at, half_buffer);            // the chunk after this one is on its way
+            // A run: the granules of a chunk.  All but the last one of a weight digit have an even number.
+            auto granules = [&]() __attribute__((always_inline)) {
+                const int left = (MULTI ? p.steps : p.padded) - at.s0;
+                return ((STAY ? left : min(kHaloChunk, left)) * (MULTI ? p.DA : 1) + G - 1) / G;
+            };
+            offsets_t off;
+            auto first_of_pair = [&](auto first) __attribute__((always_inline)) {
+                multiply_and_read(even, odd, t.one, MULTI ? codes : codes + G * FC * 256, first);
+                off = t.two;
+                if (!MULTI) codes += 2 * G * FC * 256;
+                table += 2 * G * E;
+            };
+            auto second_of_pair = [&]() __attribute__((always_inline)) {
+                read_table();
+                multiply_and_read(odd, even, off, codes, std::false_type{});
+            };
+            int n = granules();
+            if (n > 2) {
+                first_of_pair(std::true_type{});
                 second_of_pair();
+                n -= 2;
+            } else {
+#pragma unroll
+                for (int c = 0; c < FW; ++c)
+#pragma unroll
+                    for (int f = 0; f < FP; ++f) acc[c][f] = v16f_t{};
             }
-            const bool pair = n % 2 == 0;                        // an odd last granule ends a digit: nothing is read ahead of the next
-            if (!MULTI && !pair) break;
-            if (!MULTI || pair) first_of_pair(std::false_type{});
-            if (STAY || !staged) {                               // nothing to read
-                if (!MULTI || pair) even = odd;
-                break;
+            while (true) {
+                for (int left = (n - 1) >> 1; left > 0; --left) {
+                    first_of_pair(std::false_type{});
+                    second_of_pair();
+                }
+                const bool pair = n % 2 == 0;                        // an odd last granule ends a digit: nothing is read ahead of the next
+                if (!MULTI && !pair) break;
+                if (!MULTI || pair) first_of_pair(std::false_type{});
+                if (STAY || !staged) {                               // nothing to read
+                    if (!MULTI || pair) even = odd;
+                    break;
+                }
+                const Chunk next = after(at);                        // on to the next run
+                const bool digit = MULTI && next.digit != at.digit;
+                at = next;
+                half_buffer ^= 1;
+                __syncthreads();
+                codes = sB + half_buffer * (kHaloChunk * FC * 256) + lane_codes;
+                if (digit) {
+                    sB_now = block_scale(sB_now, 2);
+                    off = *reinterpret_cast<const offsets_t *>(sT + G * E);
+                    table = sT + 2 * G * E;
+                }
+                if (MULTI && !pair) odd = even;
+                second_of_pair();
+                staged = stage_next(at, half_buffer);
+                n = granules();
             }
-            const Chunk next = after(at);                        // on to the next run
-            const bool digit = MULTI && next.digit != at.digit;
-            at = next;
-            half_buffer ^= 1;
-            __syncthreads();
-            codes = sB + half_buffer * (kHaloChunk * FC * 256) + lane_codes;
-            if (digit) {
-                sB_now = block_scale(sB_now, 2);
-                off = *reinterpret_cast<const offsets_t *>(sT + G * E);
-                table = sT + 2 * G * E;
-            }
-            if (MULTI && !pair) odd = even;
-            second_of_pair();
-            staged = stage_next(at, half_buffer);
-            n = granules();
+            multiply_last(even, std::false_type{});
         }
-        static_for<PRODUCTS>([&](auto kc) __attribute__((always_inline)) { product(even, kc, std::false_type{}); });    // the last granule
         // the next tile's codes, read last before the barrier that began this tile
         if (more_tiles) {
             if (p.buffers == 1) __syncthreads();                 // (the only buffer: every wave is through with it)
-            uint32_t *const to = sA + (p.buffers == 1 ? 0 : buffer ^ 1) * p.words_records;
-            write_pixels(to, next_range, tid);
-            for (int q = tid + NT * U; q < next_range.total; q += NT * U) {
-                fetch_pixels(next_range, q);
-                write_pixels(to, next_range, q);
-            }
+            write_tile(sA + (p.buffers == 1 ? 0 : buffer ^ 1) * p.words_records, next_range);
         }
 
         // ---- outputs
@@ -524,6 +550,7 @@ __global__ __launch_bounds__(128 * FC, FC == 4 ? 2 : FP * FW == 8 ? 2 : FP == 1 
         if (!more_tiles) break;
         tile = next_tile;
         now = next_range;
+        point(tile, buffer ^ (p.buffers - 1));
         __syncthreads();
     }
 }

@@ -104,8 +104,8 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
 
     // Weights of up to kHaloStay steps stay in LDS while a block walks over its tiles; longer ones pass through in chunks.
     const bool multi = p.DA > 1 || p.DB > 1;
-    auto padded = [&](int fp) { return round_up(steps, halo_granule(fp == 3 ? 4 : fp, fp == 3 ? 1 : 2)); };
-    const bool stay = p.DB == 1 && padded(1) <= kHaloStay;
+    const bool stay = p.DB == 1 && round_up(steps, 2) <= kHaloStay;
+    auto padded = [&](int fp, bool packed) { return round_up(steps, halo_granule(fp == 3 ? 4 : fp, fp == 3 ? 1 : 2, stay && packed)); };
     if (!stay && p.half > kHaloChunk) return false;
 
     struct Tiling { bool packed; int64_t tilesM, padded, plane, records, table, codes, lds, blocks, buffers; bool walks; };     // blocks: that a compute unit holds
@@ -126,10 +126,10 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
         t.plane = (packed ? 2 : 4) * ((reach < images * Hq * Wq ? reach : images * Hq * Wq) | (sw == 4 ? 1 : 0));
         t.packed = packed;
         t.records = t.plane * 2 * p.half * p.DA;
-        t.padded = padded(fp);
-        t.table = round_up((t.padded * p.DA + 5 * halo_granule(fp == 3 ? 4 : fp, fp == 3 ? 1 : 2)) * (multi ? 2 : 1), 4);
+        t.padded = padded(fp, packed);
+        t.table = round_up((t.padded * p.DA + 5 * halo_granule(fp == 3 ? 4 : fp, fp == 3 ? 1 : 2, stay && packed)) * (multi ? 2 : 1), 4);
         t.codes = (stay ? t.padded : 2 * kHaloChunk) * 512 * pairs + t.table;
-        const int64_t most = pairs == 2 ? 1 : fp == 4 ? 2 : fp == 1 && !stay && !multi ? 4 : 3;    // by registers: waves a SIMD holds
+        const int64_t most = pairs == 2 ? 1 : fp == 4 ? 2 : fp == 1 && (stay ? packed : !multi) ? 4 : 3;    // by registers: waves a SIMD holds
         auto fit = [&](int64_t buffers) {
             t.buffers = buffers;
             t.lds = 4 * (128 * pairs + t.codes + buffers * t.records);
@@ -202,7 +202,12 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
     p.pairs = pairs; p.buffers = static_cast<int>(t.buffers);
     p.plane = static_cast<int>(t.plane);
     p.padded = static_cast<int>(t.padded);
-    p.second = p.DA > 1 ? 8u * static_cast<uint32_t>(p.half) * static_cast<uint32_t>(t.plane) : steps == 1 ? 0u : p.half > 1 ? 4u * static_cast<uint32_t>(t.plane) : (t.packed ? 8u : 16u) * static_cast<uint32_t>(p.S > 1 ? 1 : p.Wq);
+    for (int e = 0; e < 4; ++e) {
+        const int64_t st = e / p.DA, d = e % p.DA, tap = st / p.half, r = tap / p.S;
+        if (st >= steps) break;                            // (zero offsets; codes of a step that fills up a granule)
+        p.first[e] = static_cast<uint32_t>((t.packed ? 8 : 16) * (r * p.Wq + tap - r * p.S) + 4 * (st - tap * p.half + d * 2 * p.half) * t.plane);
+    }
+    for (int e = 0; multi && e < 4; ++e) p.first_codes[e] = static_cast<uint32_t>(1024 * 2 * (e / p.DA < t.padded ? e / p.DA : t.padded - 1) + e % p.DA);
     p.words_table = static_cast<int>(t.table);
     p.words_codes = static_cast<int>(t.codes);
     p.tile_step = static_cast<int>(grid / columns);

@@ -101,6 +101,25 @@ int main()
         EXPECT(g_lds == 4 * (128 + g_p.words_codes + 2 * g_p.words_records));
     }
 
+    // the offsets that come with the launch are the first ones of the table that the kernel makes: an entry is a step and a digit of the
+    // features, one beyond the last step starts over, on the codes of the step that fills a granule up (if there is one)
+    for (int Cin : {32, 64, 96, 160, 512})
+        for (int R = 1; R <= 3; R += 2)
+            for (int q = 1; q <= 5; ++q)
+                for (int weights = 1; weights <= 3; weights += 2)
+                    for (int force = 1; force <= 8; ++force) {
+                        if (!staged({2, 9, 11, Cin, 128, R, R, 1, R / 2, false, weights, false, q}, force)) continue;
+                        const bool multi = g_p.DA > 1 || g_p.DB > 1;
+                        for (int e = 0; e < 4; ++e) {
+                            const int st = e / g_p.DA, d = e % g_p.DA, tap = st / g_p.half, cw = st % g_p.half;
+                            const int at = (tap / R * g_p.Wq + tap % R) * (g_p.packed ? 2 : 4) + (cw + 2 * d * g_p.half) * g_p.plane;
+                            EXPECT(g_p.first[e] == (st < g_p.steps ? 4u * static_cast<uint32_t>(at) : 0u));
+                            if (!multi) EXPECT(g_p.first_codes[e] == 0);
+                            else if (st < g_p.padded) EXPECT(g_p.first_codes[e] == 2048u * static_cast<uint32_t>(st) + static_cast<uint32_t>(d));
+                        }
+                        EXPECT(g_p.padded >= g_p.steps && g_p.padded <= g_p.steps + 1);
+                    }
+
     // weight planes: one that is there is inside the weights by both offsets, one that is not is beyond them by the lane's own (the load's
     // range check leaves the shared one out)
     for (int planes = 1; planes <= 8; ++planes)

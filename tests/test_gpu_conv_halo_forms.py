@@ -39,6 +39,20 @@ def test_integer_results(force, BS, Cin, Cout, H, W, R, p, encW, q):
     assert np.array_equal(out.cpu().numpy().reshape(want.transpose(0, 2, 3, 1).shape), want.transpose(0, 2, 3, 1))
 
 
+# Cin, R, S, encW, p, q, pool: sums of one to three granules of one and of two steps
+SHORT = [
+    (32, 1, 1, P, 1, 1, 0), (32, 1, 1, P, 1, 2, 1), (64, 1, 1, U, 2, 2, 2), (32, 1, 2, P, 1, 2, 0), (128, 1, 1, U, 1, 2, 1), (96, 1, 1, P, 1, 2, 0),
+    (32, 3, 1, P, 1, 2, 0), (192, 1, 1, P, 1, 1, 1), (256, 1, 1, P, 1, 2, 0), (160, 1, 1, P, 1, 2, 0), (64, 5, 1, U, 1, 2, 1), (192, 1, 2, P, 1, 2, 0),
+    (32, 1, 1, P, 1, 3, 0), (32, 1, 1, U, 2, 6, 0), (64, 1, 1, U, 1, 4, 0), (128, 1, 1, P, 1, 4, 0), (96, 1, 1, U, 2, 5, 0), (32, 1, 3, P, 1, 4, 0),
+]
+
+
+@pytest.mark.parametrize("force", [1, 2, 5, 6, 7, 8])
+@pytest.mark.parametrize("Cin,R,S,encW,p,q,pool", SHORT)
+def test_short_sums(force, Cin, R, S, encW, p, q, pool):
+    _layer(force, 3, Cin, 96, 10, 13, R, S, 1, 0, encW, p, U, q, 2, 0 if pool else 2, pool)
+
+
 @pytest.mark.parametrize("force", [7, 8])
 def test_blocks_walk_with_one_buffer(force):
     """Frames whose rows fill more than half of what two buffers would leave: every block walks over its tiles in one."""
