@@ -66,6 +66,9 @@ constexpr int kHaloStay = 26, kHaloChunk = 8;
 // (1x1 sums of one to four steps of several digits, relative to two steps with three waves: 0.95).
 constexpr int halo_granule(int fp, int fw, bool shared) { return shared || fp * fw >= 4 ? 1 : 2; }
 
+// LDS words of a channel word of a position: codes; pairs of bits; the bits of one plane, or of -1/+1 features and which of them are there
+constexpr int halo_words(int kind, bool packed) { return !packed ? 4 : kind == OPK_U1 ? 1 : 2; }
+
 // Where a lane whose words of plane 0 are at byte `at` of the weights finds them in another plane: its own offset and the one that
 // all lanes share.  A plane that is not there (the second one of an odd last digit) reads as zero by the lane's own offset, which
 // the load checks against the buffer; the shared offset is no part of that check, so it stays inside the buffer.
@@ -92,7 +95,7 @@ __global__ __launch_bounds__(128 * FC, FC == 4 ? 2 : FP * FW == 8 ? 2 : FP == 1 
     constexpr int HW = SW == 8 ? 4 : SW == 4 ? 2 : 1, PW = SW == 8 ? 4 : SW;     // channel words of a weight load, of a piece of a pixel
     constexpr int G = halo_granule(FP, FW, PACKED && STAY);      // steps of a granule
     constexpr int E = MULTI ? 2 : 1;                             // LDS words of a table entry
-    constexpr int CW = PACKED ? 2 : 4;                           // LDS words of a channel word of a position
+    constexpr int CW = halo_words(KA, PACKED);                   // LDS words of a channel word of a position
     constexpr int NT = 128 * FC;                                 // threads: four waves for every two channel tiles
     constexpr int BP = 64 * FW * FP;                             // pixels of a tile
     constexpr int FETCH = STAY ? kHaloStay : kHaloChunk;         // weight steps in flight
@@ -232,7 +235,9 @@ __global__ __launch_bounds__(128 * FC, FC == 4 ? 2 : FP * FW == 8 ? 2 : FP == 1 
 #pragma unroll
             for (int i = 0; i < PW; ++i) {
                 const uint32_t x0 = a0[u][i], x1 = KA == OPK_U2 ? a1[u][i] : in[u] ? ~0u : 0u;
-                if constexpr (PACKED) {                          // two planes as pairs of bits: even positions, odd positions
+                if constexpr (PACKED && CW == 1) {
+                    dst[i * p.plane] = x0;
+                } else if constexpr (PACKED) {                   // two planes as pairs of bits: even positions, odd positions
                     const uint2 w = KA == OPK_U2 ? make_uint2(mask_select(0x55555555u, x0, x1 << 1), mask_select(0x55555555u, x0 >> 1, x1)) : make_uint2(x0, x1);
                     *reinterpret_cast<uint2 *>(dst + i * p.plane) = w;
                 } else {
@@ -385,7 +390,7 @@ __global__ __launch_bounds__(128 * FC, FC == 4 ? 2 : FP * FW == 8 ? 2 : FP == 1 
             if constexpr (!PACKED) {
                 b = o.b[g][f];
             } else if constexpr (c == 0) {
-                const uint32_t w0 = o.b[g][f][0], w1 = o.b[g][f][1];
+                const uint32_t w0 = o.b[g][f][0], w1 = o.b[g][f][CW - 1];    // (of one plane: not read)
                 if constexpr (KA == OPK_U2) {                    // both words shifted at once: the bits that cross are masked
                     const uint64_t two = (static_cast<uint64_t>(w1) << 32 | w0) >> 2;
                     b = v4i_t{static_cast<int>(w0 & m3), static_cast<int>(w1 & m3), static_cast<int>(static_cast<uint32_t>(two) & m3), static_cast<int>(static_cast<uint32_t>(two >> 32) & m3)};

@@ -123,7 +123,7 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
         const int64_t reach = new_rows * step * Wq + (cols - 1) * (mp.pool ? 2 : 1) * mp.stride + new_images * (between > 0 ? between : 0) * Wq +
                               (mp.pool ? mp.stride * (Wq + 1) : 0) + (mp.R - 1) * Wq + mp.S;
         // (with four words a lane an odd number of positions: those that neighbouring lanes write fall on different banks)
-        t.plane = (packed ? 2 : 4) * ((reach < images * Hq * Wq ? reach : images * Hq * Wq) | (sw == 4 ? 1 : 0));
+        t.plane = halo_words(kindA, packed) * ((reach < images * Hq * Wq ? reach : images * Hq * Wq) | (sw == 4 ? 1 : 0));
         t.packed = packed;
         t.records = t.plane * 2 * p.half * p.DA;
         t.padded = padded(fp, packed);
@@ -156,7 +156,7 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
             if (packed ? n == 2 || force > 6 : multi || force == 5 || force == 6) continue;
             const Tiling c = tiling(f, n, packed);
             if (c.blocks < 1) continue;
-            const double cost = tiling_cost(f, n, c.tilesM * ceil_div(mp.N, 64 * n), c.blocks, c.walks, packed ? 2.0 * c.records : c.records, steps * p.DA * p.DB, packed);
+            const double cost = tiling_cost(f, n, c.tilesM * ceil_div(mp.N, 64 * n), c.blocks, c.walks, 4.0 / halo_words(kindA, packed) * c.records, steps * p.DA * p.DB, packed);
             if (t.blocks > 0 && cost >= best) continue;
             best = cost; t = c; fp = f; pairs = n;
         }
@@ -168,7 +168,7 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
         const Tiling small = tiling(mp.pool ? 3 : 1, 1, true);
         const int64_t codes = (stay ? steps : 2 * (kHaloChunk / p.half * p.half)) * 512, most = mp.pool ? 3 : 4;
         const int64_t hw = sw == 4 ? 2 : 1, granules = p.DA * 2 * (p.half / hw);
-        const int64_t records = small.plane / 2 * (kindA == OPK_U1 ? 1 : 2) * hw * (granules | 1);
+        const int64_t records = small.plane / halo_words(kindA, true) * (kindA == OPK_U1 ? 1 : 2) * hw * (granules | 1);
         auto resident = [&](int64_t buffers) {
             const int64_t n = 160 * 1024 / (4 * (128 + codes + buffers * records));
             return n < most ? n : most;
@@ -187,7 +187,7 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
     // 0.8 up to 11, 0.6 to 0.7 beyond; two blocks 1.3 up to 1.4, 0.75 beyond; three 1.0 up to 1.4, four 0.8; blocks that walk, one 1.8 up to 1.4, 0.9
     // beyond, two and more 0.6 (72 x 72, 288 -> 320 channels, 1 x 1, stride 2, pooled, batch 74: 98.6 us and 29.9).
     if (force < 0 && small_tiles > 4096) {
-        const double work = static_cast<double>(steps) * mp.DA * mp.DB * (fp == 3 ? 256 : 128 * fp) / 64, words = 1e-3 * t.records / (t.packed ? 1 : 2);
+        const double work = static_cast<double>(steps) * mp.DA * mp.DB * (fp == 3 ? 256 : 128 * fp) / 64, words = 2e-3 * t.records / halo_words(kindA, t.packed);
         const int64_t groups = t.blocks * pairs;                 // of four waves (128 x 28 x 28, 128 -> 256, 1 x 1, stride 2: 9.3 us, 6.7 in one of eight)
         const double least = t.walks ? (groups == 1 ? 2.0 : 0.0) : groups == 1 ? 4.5 : groups == 2 ? 1.5 : 0.0;
         if (work < least * words) return false;
@@ -205,7 +205,7 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
     for (int e = 0; e < 4; ++e) {
         const int64_t st = e / p.DA, d = e % p.DA, tap = st / p.half, r = tap / p.S;
         if (st >= steps) break;                            // (zero offsets; codes of a step that fills up a granule)
-        p.first[e] = static_cast<uint32_t>((t.packed ? 8 : 16) * (r * p.Wq + tap - r * p.S) + 4 * (st - tap * p.half + d * 2 * p.half) * t.plane);
+        p.first[e] = static_cast<uint32_t>(4 * halo_words(kindA, t.packed) * (r * p.Wq + tap - r * p.S) + 4 * (st - tap * p.half + d * 2 * p.half) * t.plane);
     }
     for (int e = 0; multi && e < 4; ++e) p.first_codes[e] = static_cast<uint32_t>(1024 * 2 * (e / p.DA < t.padded ? e / p.DA : t.padded - 1) + e % p.DA);
     p.words_table = static_cast<int>(t.table);

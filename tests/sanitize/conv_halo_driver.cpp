@@ -80,7 +80,7 @@ int main()
     EXPECT(!staged({1, 1, 1 << 28, 32, 64, 1, 1, 2147483647, 0, true, 1, false, 1}, 1));       // 127 strides of 2^28 positions
     EXPECT(!staged({3, 1, 1 << 20, 32, 64, 1, 1, 2147483647, 0, true, 1, false, 1}, 1));
     EXPECT(staged({300, 1, 1, 32, 64, 1, 1, 2147483647, 0, true, 1, false, 1}, 1) && g_p.words_records == 2 * g_p.plane);
-    EXPECT(g_p.plane == (g_p.packed ? 2 : 4) * 128);                                          // 128 positions of 300 frames
+    EXPECT(g_p.plane == halo_words(OPK_U1, g_p.packed) * 128);                                // 128 positions of 300 frames
 
     // block scales: biased exponents in every byte, those of 0/1 weights and of int32 results from 2^7 up
     EXPECT(staged({1, 8, 8, 64, 64, 3, 3, 1, 1, true, 1, false, 2}, 1) && g_p.scaleA == 0x7e7e7e7e && g_p.scaleB == 0x7f7f7f7f);
@@ -112,13 +112,19 @@ int main()
                         const bool multi = g_p.DA > 1 || g_p.DB > 1;
                         for (int e = 0; e < 4; ++e) {
                             const int st = e / g_p.DA, d = e % g_p.DA, tap = st / g_p.half, cw = st % g_p.half;
-                            const int at = (tap / R * g_p.Wq + tap % R) * (g_p.packed ? 2 : 4) + (cw + 2 * d * g_p.half) * g_p.plane;
+                            const int at = (tap / R * g_p.Wq + tap % R) * halo_words(g_kind, g_p.packed) + (cw + 2 * d * g_p.half) * g_p.plane;
                             EXPECT(g_p.first[e] == (st < g_p.steps ? 4u * static_cast<uint32_t>(at) : 0u));
                             if (!multi) EXPECT(g_p.first_codes[e] == 0);
                             else if (st < g_p.padded) EXPECT(g_p.first_codes[e] == 2048u * static_cast<uint32_t>(st) + static_cast<uint32_t>(d));
                         }
                         EXPECT(g_p.padded >= g_p.steps && g_p.padded <= g_p.steps + 1);
                     }
+
+    // a position of one plane takes half the LDS of one of two: wide frames of many channels fit with the one alone
+    for (const Layer &l : {Layer{8, 96, 96, 512, 128, 5, 5, 1, 2, true, 1, false, 1}, Layer{8, 192, 192, 512, 128, 3, 3, 1, 1, true, 1, false, 1},
+                           Layer{8, 320, 320, 256, 128, 5, 5, 1, 2, true, 1, false, 1}}) {
+        EXPECT(staged(l, -1) && g_kind == OPK_U1 && g_p.packed && g_lds <= 160 * 1024);
+    }
 
     // weight planes: one that is there is inside the weights by both offsets, one that is not is beyond them by the lane's own (the load's
     // range check leaves the shared one out)

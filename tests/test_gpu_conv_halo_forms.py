@@ -13,8 +13,15 @@ from tests.test_gpu_conv_halo import LAYERS, P, U, _operands, _run, dev, test_la
 pytestmark = pytest.mark.gpu
 
 
+# one-plane features, staged as one word of bits: weights that stay and that pass through, an odd number of channel words, pooling
+ONE_PLANE = [
+    (2, 128, 96, 9, 11, 3, 3, 1, 1, P, 1, U, 1, 2, 2, 0), (2, 96, 64, 7, 12, 3, 3, 1, 1, U, 1, U, 1, 2, 0, 0), (3, 256, 64, 9, 6, 3, 3, 1, 1, P, 1, U, 1, 1, 0, 0),
+    (2, 256, 128, 8, 10, 3, 3, 1, 1, P, 1, U, 1, 2, 0, 1), (3, 64, 64, 12, 9, 3, 3, 2, 1, P, 1, U, 1, 2, 1, 2), (2, 64, 64, 9, 8, 3, 3, 1, 1, U, 3, U, 1, 2, 0, 0),
+]
+
+
 @pytest.mark.parametrize("force", [3, 4, 5, 6, 7, 8])
-@pytest.mark.parametrize("layer", LAYERS)
+@pytest.mark.parametrize("layer", LAYERS + ONE_PLANE)
 def test_forms(force, layer):
     _layer(force, *layer)
 
