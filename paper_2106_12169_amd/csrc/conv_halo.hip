@@ -130,10 +130,14 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
         t.table = round_up((t.padded * p.DA + 5 * halo_granule(fp == 3 ? 4 : fp, fp == 3 ? 1 : 2, stay && packed)) * (multi ? 2 : 1), 4);
         t.codes = (stay ? t.padded : 2 * kHaloChunk) * 512 * pairs + t.table;
         const int64_t most = pairs == 2 ? 1 : fp == 4 ? 2 : fp == 1 && (stay ? packed : !multi) ? 4 : 3;    // by registers: waves a SIMD holds
+        // LDS is given out in granules of 1280 bytes, 128 to a compute unit: three blocks of 42 are resident together, of 43 (53.8 to 54.6 KB,
+        // three times that is below 160 KB) two, and a grid of walking blocks for three then takes a second turn (168 x 11 x 74,
+        // 128 -> 192 channels, 3 x 3, one buffer of bits: 30.5 us, 23.6 with two).
         auto fit = [&](int64_t buffers) {
             t.buffers = buffers;
             t.lds = 4 * (128 * pairs + t.codes + buffers * t.records);
-            t.blocks = 160 * 1024 / t.lds < most ? 160 * 1024 / t.lds : most;
+            const int64_t held = 128 / ceil_div(t.lds, 1280);
+            t.blocks = held < most ? held : most;
         };
         fit(1);
         // blocks that have a second tile walk, with a second buffer of records where as many of them fit

@@ -101,6 +101,14 @@ int main()
         EXPECT(g_lds == 4 * (128 + g_p.words_codes + 2 * g_p.words_records));
     }
 
+    // blocks that walk are as many as are resident: a compute unit has 128 granules of 1280 bytes of LDS
+    EXPECT(staged({168, 11, 74, 128, 192, 3, 3, 1, 1, true, 1, false, 2}, 5) && g_p.packed && g_grid == 510);
+    for (int frame = 8; frame <= 200; ++frame)
+        for (int Cin : {32, 96, 128, 192})
+            for (int force = 1; force <= 8; ++force)
+                if (staged({24, frame, frame + 3, Cin, 192, 3, 3, 1, 1, true, 1, false, 2}, force) && g_stay && g_p.tile_step < g_p.tilesM)
+                    EXPECT(static_cast<int>(g_grid + 255) / 256 * ((g_lds + 1279) / 1280) <= 128);
+
     // the offsets that come with the launch are the first ones of the table that the kernel makes: an entry is a step and a digit of the
     // features, one beyond the last step starts over, on the codes of the step that fills a granule up (if there is one)
     for (int Cin : {32, 64, 96, 160, 512})
