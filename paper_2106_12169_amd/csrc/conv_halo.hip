@@ -6,53 +6,88 @@
 
 namespace apnn {
 
-// Up to 4096 tiles of 32 x 32 outputs: few or short sums on few pixels are better off with the kernels that split K over more waves
-// and start sooner.  Both sides' times (us), as fitted to 16000 layers of 64 tiles and more, each measured in every form in a
-// replayed graph:
-//   those kernels: 2.95, and for 1000 tiles 1.5, for each pair of K words and pair of digits 0.11, 0.095, 0.125 where the channel
-//     words are a multiple of four, even, odd (a little over half of it with features of one plane, a tenth more with weights of
-//     several where the words are not odd), 0.05 more for odd ones from the fortieth pair on, 0.75 with a residual; 1.3 times
-//     that with several digits
-//   this one: 4.4, and for each of its entries (steps times pairs of digits) 0.08 where the channel words are a multiple of four,
-//     else 0.125; 0.03 more where the weights pass through in chunks; 1.6 times that with pooling (a block has as many pixels
-//     before it); 0.065 for each channel word and digit of the pixels that a stride skips; all that again for each further round
-//     of blocks that do not fit the compute units together; beyond 256 blocks, 1 + 0.07 entries for as many more; 0.75 for 256
-//     blocks of int32 results
-// What the rule chooses is on average 0.6 % slower than the faster side (1.2 % with a rule that knew no rounds and one time an entry),
-// and 1 % of the layers are 5 % and more slower than without this form (4 % with that rule, up to 1.7 times).  E.g. 9 steps on 8 x
-// 56 x 56, 64 channels 6.3 there and 4.9 here; 4 x 56 x 56 4.6, 4.8; 18 on 8 x 28 x 28, 128 channels 5.3 and 5.3, with a residual
-// 5.8, 5.5; 9 on 8 x 28 x 28, 64 -> 128 channels 4.6, 4.9; 36 on 4 x 28 x 28, 256 channels 8.3, 7.4.
-static bool worth_staging(const MfmaParams &mp, int64_t tiles, int64_t blocks, int64_t steps, bool stay, int64_t rounds)
+// Which layers are staged, and in which form: the least of the times (us) that the forms below and the kernels with lane-private
+// loads are expected to take.  Both were fitted to 24 500 layers (8 to 20 000 blocks of 64 x 128 outputs, 1 x 1 to 7 x 7, strides 1 and
+// 2, up to three planes of weights and four of features, planes and int32 results, each measured in every form in a replayed graph);
+// the mean error near the line is 6 and 7 %.  On 5052 other layers what is chosen takes 1.2 % more than the fastest of them all, 1.6 %
+// beyond 4096 tiles of 32 x 32 (with the rules before: 3.7 and 5.4 %).  By classes: profiles/staged_convolutions_choice.txt.
+
+// The form of a layer's blocks.  fp: pixel tiles of a wave (pooled 4 with both channel tiles of a pair, 3 with one); pairs: of channel
+// tiles; packed: features are staged as bits, not as codes; blocks: that a compute unit holds
+struct Tiling {
+    int fp, pairs;
+    bool packed, walks;
+    int64_t tilesM, columns, padded, plane, records, table, codes, lds, blocks, buffers, grid;
+};
+
+// A compute unit works on its resident blocks in rounds.  In one of them
+//   the sums read 1.5 operands from LDS for each matrix instruction with one pixel tile a wave, 1 with two, 1.25 and 0.75 pooled, and
+//   these reads are most of what an instruction takes: 0.017 each and 0.004 on top, nearly twice that on a SIMD with a lone wave;
+//   staging passes over the pixels: every thread fetches two pieces (four of one word) and waits, 0.36 a pass, and more for each wave
+//   that expands and writes them;
+//   the epilogue takes 0.2 for a 32 x 32 tile of planes, and 0.03 for each other block that writes into the same lines.
+// Where blocks walk, a third of the shorter of the sums and the rest is hidden, by the other waves or by the next tile's pixels being in
+// flight; with one buffer and a lone wave nothing is.
+static double staged_cost(const MfmaParams &mp, const Tiling &t, int kindA, int64_t steps, bool stay, int sw)
 {
-    const bool fours = mp.Cw % 4 == 0, odd = mp.Cw % 2 != 0;
-    const double pairs = static_cast<double>(mp.DA) * mp.DB, entries = steps * pairs, words = 0.5 * mp.Kw * pairs;
-    const double word = (odd ? 0.125 : fours ? 0.11 : 0.095) * (mp.PA == 1 ? 0.56 : 1.0) * (mp.PB > 1 && !odd ? 1.1 : 1.0);
-    const double tile = 1.5 + word * words + (odd && words > 40 ? 0.05 * (words - 40) : 0.0) + (mp.res ? 0.75 : 0.0);
-    const double other = 2.95 + 1e-3 * tiles * tile * (pairs > 1 ? 1.3 : 1.0);
-    const double spread = 0.065 * (static_cast<double>(mp.stride) * mp.stride - 1) * mp.DA * mp.Cw;
-    double each = (fours ? 0.08 : 0.125) + (stay ? 0.0 : 0.03);
-    double staged = 4.4 + (mp.Y ? 0.75 / 256 * blocks : 0.0);
-    if (mp.pool) each *= 1.6;
-    else if (blocks > 256) staged += (blocks / 256.0 - 1.0) * (1.0 + 0.07 * entries);
-    return staged + rounds * (spread + each * entries) <= other;
+    const bool pooled = t.fp >= 3, one_plane = mp.PA == 1;
+    const double products = t.fp == 4 ? 8.0 : t.fp == 1 ? 2.0 : 4.0, reads = t.fp == 1 ? 1.5 : t.fp == 2 ? 1.0 : t.fp == 3 ? 1.25 : 0.75;
+    const double entries = static_cast<double>(steps) * mp.DA * mp.DB, filled = mp.N / (64.0 * t.pairs * t.columns);
+    double outputs = pooled ? 0.11 + 0.147 * products : (mp.Y ? 0.618 : 0.2) * products;
+    if (mp.res) outputs += 0.1 * (pooled ? products / 4 : products);
+    outputs *= filled;
+    if (!pooled && !mp.Y) outputs += 0.0321 * products * static_cast<double>(t.columns < 8 ? t.columns - 1 : 7);
+    int share = 1;                                               // threads that share a position
+    while (share < mp.DA * ceil_div(2 * ((mp.Cw + 1) / 2), sw)) share *= 2;
+    const double passes = static_cast<double>(ceil_div(t.plane / halo_words(kindA, t.packed) * share, 256 * t.pairs * (sw == 1 ? 4 : 2)));
+    const double pass = (sw == 1 ? 0.172 : sw == 2 ? 0.0348 : 0.0107) + (t.packed ? 0.0 : sw == 4 ? 0.0438 : 0.0219) - (one_plane ? 0.0685 : 0.0);
+    const double shared = 0.00422 + 0.0167 * reads + (t.packed ? 0.00324 : 0.0), lone = 0.0288 * reads + (t.packed ? 0.0042 : 0.0);
+    const bool two = t.buffers == 2;
+    const double resident = static_cast<double>(t.blocks * t.pairs), first = 1.27;                   // the first loads of a round
+    const double fixed = !t.walks ? first + (stay ? 0.0 : 0.0141 * steps * mp.DB) : two ? 1.03 / resident - 0.202 : 1.27 / resident - 0.597;
+    const double weights = stay ? (sw == 1 ? 0.014 : 0.00264) * steps * mp.DB * t.pairs : 0.0;
+    auto round = [&](int64_t blocks) {
+        const double n = static_cast<double>(blocks), waves = n * t.pairs;
+        const double rest = waves * outputs + passes * (0.358 + waves * pass), sums = products * entries * (lone > shared * waves ? lone : shared * waves);
+        const double hidden = t.walks && (two || waves > 1) ? 0.647 : 1.0;
+        return fixed + (rest > sums ? rest + hidden * sums : sums + hidden * rest) + (t.walks ? 0.0 : n * weights);
+    };
+    const int64_t tiles = t.tilesM * t.columns;
+    double cost = 2.42;                                          // the launch
+    if (t.walks) {
+        const int64_t step = t.grid / t.columns, full = ceil_div(t.tilesM, step) - 1, rest = ceil_div((t.tilesM - full * step) * t.columns, 256);
+        cost += full * round(t.blocks) + round(rest < t.blocks ? rest : t.blocks) + (first > fixed ? first - fixed : 0.0) + t.blocks * weights;
+    } else {
+        const int64_t full = tiles / (256 * t.blocks), rest = tiles % (256 * t.blocks);
+        cost += full * round(t.blocks) + (rest ? round(ceil_div(rest, 256)) : 0.0);
+    }
+    // int32 results: 1 x 1 layers are 1.12 times as long as that where the other side has tiles of 32 x 64 (605 of them), and beyond the
+    // 256 MB that the last cache holds both sides' stores slow down, these more (1 x 1, from 5.0 to 3.9 TB/s, the others from 4.5 to 3.8)
+    if (mp.Y && mp.R * mp.S == 1 && mp.N % 64 == 0 && ceil_div(mp.M, 32) * ceil_div(mp.N, 32) > 4096) cost *= 1.12;
+    if (mp.Y && static_cast<double>(mp.M) * mp.N > 67108864.0) cost *= 1.14;
+    return cost;
 }
 
-// Time (us) of a layer in one of the forms of its blocks, as fitted to 500 layers each measured in all of them (the mean error is 12 %;
-// what it chooses is on average 1.4 % slower than the fastest form).  A compute unit works on `resident` blocks in a round, the last
-// round's fewer ones share it with nobody.  A round costs its blocks' first loads (less where a block walks: the next tile's pixels are
-// in flight), 0.43 for each pair of output tiles of a wave, 0.11 for a thousand words of pixels, and for each matrix instruction 0.022 on
-// a SIMD with several waves, 0.041 with a lone one that has four and more to a step, 0.061 with two; a little more where the pixels
-// are staged as bits.
-static double tiling_cost(int fp, int pairs, int64_t tiles, int64_t resident, bool walks, double words, int64_t entries, bool packed)
+// The kernels with lane-private loads: so much for a tile of 32 x 32 and for each pair of K words and pair of digits of it, more for
+// those from the tenth and the fiftieth on.  Up to 4096 tiles four waves share one; beyond, a wave has one, or two of 32 x 32 where the
+// channels are a multiple of 64.
+static double private_cost(const MfmaParams &mp, int64_t tiles)
 {
-    const double products = fp == 4 ? 8.0 : fp == 1 ? 2.0 : 4.0, lone = (products >= 4 ? 0.041 : 0.061) + (packed ? 0.005 : 0.0), shared = packed ? 0.029 : 0.0224;
-    auto cost = [&](int64_t blocks) {
-        const double waves = static_cast<double>(blocks * pairs);
-        return (walks ? 1.2 : 3.6) + waves * 0.43 * (fp >= 3 ? products / 2 : products) + 0.11e-3 * blocks * words +
-               (waves > 1 ? shared * waves : lone) * products * entries;
-    };
-    const int64_t round = 256 * resident, rest = tiles % round;
-    return static_cast<double>(tiles / round) * cost(resident) + (rest ? cost(ceil_div(rest, 256)) : 0.0);
+    struct Size { double launch, chain, residual, pooled, one_plane, weight_planes, from10, from50, tile[3], pair[3]; };   // channel words a multiple of four, even, odd
+    static constexpr Size sizes[3] = {{3.69, 0.0192, 0.366, -0.209, 0.594, 1.49, 0.0609, 0, {1.29, 1.48, 1.64}, {0.0424, 0.0503, 0.0941}},
+                                      {5.19, 0.0815, 0.508, -0.155, 0.785, 1.85, 0.0215, 0.0338, {0.513, 0.555, 0.644}, {0.0326, 0.0357, 0.0762}},
+                                      {5.22, 0.0221, 0.606, -0.167, 0.521, 1.44, 0.0454, 0.0388, {0.942, 1.16, 1.28}, {0.0535, 0.0734, 0.113}}};
+    const Size &z = sizes[tiles <= 4096 ? 0 : mp.N % 64 == 0 ? 1 : 2];
+    const int words = mp.Cw % 4 == 0 ? 0 : mp.Cw % 2 == 0 ? 1 : 2;
+    const int digits = mp.DA * mp.DB;
+    const double pairs = 0.5 * mp.Kw * digits;
+    double sums = z.pair[words] * pairs + (pairs > 10.0 ? z.from10 * (pairs - 10.0) : 0.0) + (pairs > 50.0 ? z.from50 * (pairs - 50.0) : 0.0);
+    if (mp.PA == 1) sums *= z.one_plane;
+    if (mp.PB > 1) sums *= z.weight_planes;
+    if (digits > 1) sums *= digits > 2 ? 0.781 : 0.905;
+    if (mp.stride > 1) sums *= 1.13;
+    const double tile = z.tile[words] * (digits > 1 ? 1.41 : 1.0) + (mp.res ? z.residual : 0.0) + (mp.pool ? z.pooled : 0.0) + sums;
+    return z.launch + z.chain * pairs + 1e-3 * tiles * tile;
 }
 
 bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB, int force, hipStream_t st)
@@ -61,14 +96,9 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
     const bool ints = mp.Y && !mp.scale && !mp.T && !mp.pool && mp.N % 4 == 0;
     const bool planes = mp.out && !mp.Y && !mp.T && mp.q_out <= 2 && (!mp.res || mp.q_res <= 2);
     if (!ints && !planes) return false;
-    const int tilesN = static_cast<int>(ceil_div(mp.N, 64));
-    // The chip wants most of its compute units busy: not below 96 tiles of 64 x 128 outputs (128 where the stride spreads the pixels).
-    const int64_t blocks = ceil_div(mp.M, mp.pool ? 256 : 128) * tilesN;             // of the smaller tiles
-    if (force < 0 && blocks < (mp.stride > 1 ? 128 : 96)) return false;
-    // int32 results of one or two steps: their store is all there is (192 channels, 10.3 and 10.6).  Beyond 4096 tiles of 32 x 32
-    // the other side has 32 x 64 tiles for every 64 channels, and is ahead for 1 x 1 layers: on average 1.15 times as fast.
-    const int64_t small_tiles = ceil_div(mp.M, 32) * ceil_div(mp.N, 32), steps = static_cast<int64_t>(mp.R) * mp.S * ((mp.Cw + 1) / 2);
-    if (force < 0 && mp.Y && (steps <= 2 || (small_tiles > 4096 && mp.N % 64 == 0 && mp.R == 1 && mp.S == 1))) return false;
+    // (the times below hold from 64 tiles of 64 x 128 outputs on)
+    if (force < 0 && ceil_div(mp.M, mp.pool ? 256 : 128) * ceil_div(mp.N, 64) < 64) return false;
+    const int64_t steps = static_cast<int64_t>(mp.R) * mp.S * ((mp.Cw + 1) / 2);
     const int64_t Hq = mp.H + 2 * static_cast<int64_t>(mp.pad), Wq = mp.W + 2 * static_cast<int64_t>(mp.pad);
     const int64_t Kw = static_cast<int64_t>(mp.R) * mp.S * mp.Cw, lim = int64_t(1) << 31;
     // (in 64 bits from the first factor on: four times the channels alone can pass 2^31)
@@ -108,12 +138,11 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
     auto padded = [&](int fp, bool packed) { return round_up(steps, halo_granule(fp == 3 ? 4 : fp, fp == 3 ? 1 : 2, stay && packed)); };
     if (!stay && p.half > kHaloChunk) return false;
 
-    struct Tiling { bool packed; int64_t tilesM, padded, plane, records, table, codes, lds, blocks, buffers; bool walks; };     // blocks: that a compute unit holds
-    // fp: pixel tiles of a wave; pooled 4 with both channel tiles, 3 with one; pairs: of channel tiles; packed: features are staged as
-    // bits, not as codes
     auto tiling = [&](int fp, int pairs, bool packed) {
         Tiling t{};
         const int64_t pixels = fp == 3 ? 256 : 128 * fp;
+        t.fp = fp; t.pairs = pairs; t.packed = packed;
+        t.columns = ceil_div(mp.N, 64 * pairs);
         t.tilesM = ceil_div(mp.M, pixels);
         // the longest range of padded positions a tile touches: row steps and image steps between its first and last pixel
         // (the stride of a single row is beyond its image: there the image step counts)
@@ -124,7 +153,6 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
                               (mp.pool ? mp.stride * (Wq + 1) : 0) + (mp.R - 1) * Wq + mp.S;
         // (with four words a lane an odd number of positions: those that neighbouring lanes write fall on different banks)
         t.plane = halo_words(kindA, packed) * ((reach < images * Hq * Wq ? reach : images * Hq * Wq) | (sw == 4 ? 1 : 0));
-        t.packed = packed;
         t.records = t.plane * 2 * p.half * p.DA;
         t.padded = padded(fp, packed);
         t.table = round_up((t.padded * p.DA + 5 * halo_granule(fp == 3 ? 4 : fp, fp == 3 ? 1 : 2, stay && packed)) * (multi ? 2 : 1), 4);
@@ -141,15 +169,15 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
         };
         fit(1);
         // blocks that have a second tile walk, with a second buffer of records where as many of them fit
-        const int64_t columns = ceil_div(mp.N, 64 * pairs), single = t.blocks;
-        t.walks = stay && t.tilesM * columns > 256 * t.blocks / columns * columns && 256 * t.blocks >= columns;
+        const int64_t single = t.blocks;
+        t.walks = stay && t.tilesM * t.columns > 256 * t.blocks / t.columns * t.columns && 256 * t.blocks >= t.columns;
         if (t.walks) {
             fit(2);
-            if (t.blocks < (force == 1 || force == 2 ? 1 : single) || 256 * t.blocks < columns) fit(1);
+            if (t.blocks < (force == 1 || force == 2 ? 1 : single) || 256 * t.blocks < t.columns) fit(1);
         }
+        t.grid = t.walks ? 256 * t.blocks / t.columns * t.columns : t.tilesM * t.columns;          // whole rows of channel tiles
         return t;
     };
-    int fp = mp.pool ? 3 : 1, pairs = 1;
     Tiling t{};
     double best = 0.0;
     for (int i = 0; i < 4; ++i) {
@@ -160,50 +188,19 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
             if (packed ? n == 2 || force > 6 : multi || force == 5 || force == 6) continue;
             const Tiling c = tiling(f, n, packed);
             if (c.blocks < 1) continue;
-            const double cost = tiling_cost(f, n, c.tilesM * ceil_div(mp.N, 64 * n), c.blocks, c.walks, 4.0 / halo_words(kindA, packed) * c.records, steps * p.DA * p.DB, packed);
+            const double cost = staged_cost(mp, c, kindA, steps, stay, sw);
             if (t.blocks > 0 && cost >= best) continue;
-            best = cost; t = c; fp = f; pairs = n;
+            best = cost; t = c;
         }
     }
-    if (t.blocks < 1) return false;
-    if (force < 0 && small_tiles <= 4096) {
-        // rounds of the blocks that the model was fitted to: the smaller tiles, chunks of whole taps, features as bits in records of an
-        // odd number of granules
-        const Tiling small = tiling(mp.pool ? 3 : 1, 1, true);
-        const int64_t codes = (stay ? steps : 2 * (kHaloChunk / p.half * p.half)) * 512, most = mp.pool ? 3 : 4;
-        const int64_t hw = sw == 4 ? 2 : 1, granules = p.DA * 2 * (p.half / hw);
-        const int64_t records = small.plane / halo_words(kindA, true) * (kindA == OPK_U1 ? 1 : 2) * hw * (granules | 1);
-        auto resident = [&](int64_t buffers) {
-            const int64_t n = 160 * 1024 / (4 * (128 + codes + buffers * records));
-            return n < most ? n : most;
-        };
-        const int64_t one = resident(1), two = resident(2);
-        if (one < 1) return false;
-        const bool walks = stay && small.tilesM * tilesN > 256 * one / tilesN * tilesN && two >= (one < 2 ? one : 2) && 256 * two >= tilesN;
-        if (!worth_staging(mp, small_tiles, blocks, steps, stay, walks ? 1 : ceil_div(blocks, 256 * one))) return false;
-    }
-    const int columns = static_cast<int>(ceil_div(mp.N, 64 * pairs));
-    const int64_t tiles = t.tilesM * columns;
-    if (tiles > kMaxBlocks) return false;
-    // Beyond 4096 tiles of 32 x 32: not where staging a tile's pixels is most of the work and little else of the compute unit runs
-    // meanwhile.  Matrix instructions of 32 x 32 x 64 for 1000 staged words, and the time relative to the other kernels, on average
-    // over 4900 layers: blocks with one tile, one block to a compute unit 2.1 up to 1.4, 1.2 up to 2.8, 1.1 up to 5.7 (level from 4.5 on),
-    // 0.8 up to 11, 0.6 to 0.7 beyond; two blocks 1.3 up to 1.4, 0.75 beyond; three 1.0 up to 1.4, four 0.8; blocks that walk, one 1.8 up to 1.4, 0.9
-    // beyond, two and more 0.6 (72 x 72, 288 -> 320 channels, 1 x 1, stride 2, pooled, batch 74: 98.6 us and 29.9).
-    if (force < 0 && small_tiles > 4096) {
-        const double work = static_cast<double>(steps) * mp.DA * mp.DB * (fp == 3 ? 256 : 128 * fp) / 64, words = 2e-3 * t.records / halo_words(kindA, t.packed);
-        const int64_t groups = t.blocks * pairs;                 // of four waves (128 x 28 x 28, 128 -> 256, 1 x 1, stride 2: 9.3 us, 6.7 in one of eight)
-        const double least = t.walks ? (groups == 1 ? 2.0 : 0.0) : groups == 1 ? 4.5 : groups == 2 ? 1.5 : 0.0;
-        if (work < least * words) return false;
-    }
-    int64_t grid = tiles;
-    if (t.walks) grid = 256 * t.blocks / columns * columns;           // whole rows of channel tiles
+    if (t.blocks < 1 || t.tilesM * t.columns > kMaxBlocks) return false;
+    if (force < 0 && best > private_cost(mp, ceil_div(mp.M, 32) * ceil_div(mp.N, 32))) return false;
     p.tilesM = static_cast<int>(t.tilesM);
-    p.per_column = divisor(columns);
+    p.per_column = divisor(t.columns);
     p.packed = t.packed;
     p.pieces = p.DA * static_cast<int>(ceil_div(2 * p.half, sw));
     while ((1 << p.share) < p.pieces) ++p.share;
-    p.pairs = pairs; p.buffers = static_cast<int>(t.buffers);
+    p.pairs = t.pairs; p.buffers = static_cast<int>(t.buffers);
     p.plane = static_cast<int>(t.plane);
     p.padded = static_cast<int>(t.padded);
     for (int e = 0; e < 4; ++e) {
@@ -214,14 +211,14 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
     for (int e = 0; multi && e < 4; ++e) p.first_codes[e] = static_cast<uint32_t>(1024 * 2 * (e / p.DA < t.padded ? e / p.DA : t.padded - 1) + e % p.DA);
     p.words_table = static_cast<int>(t.table);
     p.words_codes = static_cast<int>(t.codes);
-    p.tile_step = static_cast<int>(grid / columns);
+    p.tile_step = static_cast<int>(t.grid / t.columns);
     p.words_records = static_cast<int>(t.records);
-    const unsigned g = static_cast<unsigned>(grid);
+    const unsigned g = static_cast<unsigned>(t.grid);
     const int bytes = static_cast<int>(t.lds);
     switch (kindA) {
-        case OPK_U1: return launch_conv_halo_u1(p, stay, fp, g, bytes, st);
-        case OPK_U2: return launch_conv_halo_u2(p, stay, fp, g, bytes, st);
-        default: return launch_conv_halo_pm1(p, stay, fp, g, bytes, st);
+        case OPK_U1: return launch_conv_halo_u1(p, stay, t.fp, g, bytes, st);
+        case OPK_U2: return launch_conv_halo_u2(p, stay, t.fp, g, bytes, st);
+        default: return launch_conv_halo_pm1(p, stay, t.fp, g, bytes, st);
     }
 }
 

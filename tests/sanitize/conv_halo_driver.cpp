@@ -109,6 +109,12 @@ int main()
                 if (staged({24, frame, frame + 3, Cin, 192, 3, 3, 1, 1, true, 1, false, 2}, force) && g_stay && g_p.tile_step < g_p.tilesM)
                     EXPECT(static_cast<int>(g_grid + 255) / 256 * ((g_lds + 1279) / 1280) <= 128);
 
+    // blocks that walk with one buffer wait for each tile's pixels: not where these are most of the work (224 x 38 x 44, 192 -> 192 channels,
+    // 1 x 1, pooled 15.8 us there, 20.8 here), but as soon as there are sums to hide (3 x 3, 128 -> 192, int32 33 there, 24 here)
+    EXPECT(!staged({224, 38, 44, 192, 192, 1, 1, 2, 0, true, 1, true, 1, 1}, -1));
+    EXPECT(staged({224, 38, 44, 192, 192, 1, 1, 2, 0, true, 1, true, 1, 1}, 5) && g_p.buffers == 1 && g_p.tile_step < g_p.tilesM);
+    EXPECT(staged({168, 11, 74, 128, 192, 3, 3, 1, 1, true, 1, false, 2, 0, true}, -1));
+
     // the offsets that come with the launch are the first ones of the table that the kernel makes: an entry is a step and a digit of the
     // features, one beyond the last step starts over, on the codes of the step that fills a granule up (if there is one)
     for (int Cin : {32, 64, 96, 160, 512})
