@@ -284,7 +284,7 @@ int main()
     // either side of the staged convolutions' rule, and of the pooled 16 x 16 tiles'
     EXPECT(planes(8, 56, 64, 64, 1, 2, 0) == "conv_halo" && planes(3, 56, 64, 64, 1, 2, 0) == "small_conv" && g_nsplit == 4);
     EXPECT(planes(8, 28, 128, 128, 1, 2, 0) == "small_conv" && planes(12, 28, 128, 128, 1, 2, 0) == "conv_halo");
-    EXPECT(planes(8, 28, 64, 128, 1, 2, 0) == "small_conv" && planes(8, 28, 192, 128, 1, 2, 0) == "small_conv");
+    EXPECT(planes(7, 28, 64, 128, 1, 2, 0) == "small_conv" && planes(9, 28, 192, 128, 1, 2, 0) == "small_conv");
     Q.residual_dev = static_cast<const uint32_t *>(fake); Q.q_res = 2;
     EXPECT(planes(8, 28, 128, 128, 1, 2, 0) == "small_conv" && planes(9, 28, 128, 128, 1, 2, 0) == "conv_halo");
     Q.residual_dev = nullptr;
