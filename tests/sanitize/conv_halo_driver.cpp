@@ -35,6 +35,7 @@ struct Layer {
     int q;
     int pool = 0;
     bool ints = false;
+    int q_out = 2, q_res = 0;
 };
 
 // as apnn_layer's dispatch fills the parameters in
@@ -54,7 +55,8 @@ static bool staged(const Layer &l, int force)
     if (l.ints) {
         mp.Y = reinterpret_cast<int32_t *>(there);
     } else {
-        mp.out = there; mp.q_out = 2;
+        mp.out = there; mp.q_out = l.q_out;
+        if (l.q_res) { mp.res = there; mp.q_res = l.q_res; }
         mp.scale = mp.bias = reinterpret_cast<const float *>(there);
     }
     g_kind = -1;
@@ -62,8 +64,28 @@ static bool staged(const Layer &l, int force)
                             l.pm1_weights ? OPK_PM1 : l.p == 1 ? OPK_U1 : OPK_U2, force, nullptr);
 }
 
-int main()
+// Layers from a file, a line each: the fields of Layer, then the override.  Of each: whether it is staged, and how.
+static int layouts(const char *file)
 {
+    std::FILE *const f = std::fopen(file, "r");
+    if (!f) return 2;
+    Layer l{};
+    int pm1w, pm1f, ints, force;
+    while (std::fscanf(f, "%ld %ld %ld %ld %ld %d %d %d %d %d %d %d %d %d %d %d %d %d", &l.images, &l.H, &l.W, &l.Cin, &l.Cout, &l.R, &l.S, &l.stride, &l.pad,
+                       &pm1w, &l.p, &pm1f, &l.q, &l.pool, &ints, &l.q_out, &l.q_res, &force) == 18) {
+        l.pm1_weights = pm1w; l.pm1_features = pm1f; l.ints = ints;
+        if (!staged(l, force)) std::printf("0\n");
+        else std::printf("1 kind %d stay %d fp %d pairs %d packed %d buffers %d tilesM %d step %d grid %u lds %d records %d steps %d\n", g_kind, g_stay, g_fp, g_p.pairs,
+                         g_p.packed, g_p.buffers, g_p.tilesM, g_p.tile_step, g_grid, g_lds, g_p.words_records, g_p.steps);
+    }
+    std::fclose(f);
+    return 0;
+}
+
+int main(int argc, char **argv)
+{
+    if (argc > 1) return layouts(argv[1]);
+
     // weights of 2^31 bytes and more are not for 31-bit offsets, whatever their size is modulo 2^32
     const int64_t most = (int64_t(1) << 31) / 8 - 64;            // channels of one 64-channel plane: 8 bytes each
     EXPECT(staged({1, 8, 8, 64, most, 1, 1, 1, 0, true, 1, false, 2}, 1) && g_p.bytesB == 8u * static_cast<uint32_t>(most));
