@@ -7,10 +7,10 @@
 namespace apnn {
 
 // Which layers are staged, and in which form: the least of the times (us) that the forms below and the kernels with lane-private
-// loads are expected to take.  Both were fitted to 24 500 layers (8 to 20 000 blocks of 64 x 128 outputs, 1 x 1 to 7 x 7, strides 1 and
+// loads are expected to take.  Both were fitted to 29 600 layers (8 to 20 000 blocks of 64 x 128 outputs, 1 x 1 to 7 x 7, strides 1 and
 // 2, up to three planes of weights and four of features, planes and int32 results, each measured in every form in a replayed graph);
-// the mean error near the line is 6 and 7 %.  On 5052 other layers what is chosen takes 1.2 % more than the fastest of them all, 1.6 %
-// beyond 4096 tiles of 32 x 32 (with the rules before: 3.7 and 5.4 %).  By classes: profiles/staged_convolutions_choice.txt.
+// the mean error near the line is 5 and 6 %.  On 7620 other layers what is chosen takes 1.0 % more than the fastest of them all, 1.6 %
+// beyond 4096 tiles of 32 x 32 (with the rules before: 2.5 and 4.6 %).  By classes: profiles/staged_convolutions_choice.txt.
 
 // The form of a layer's blocks.  fp: pixel tiles of a wave (pooled 4 with both channel tiles of a pair, 3 with one); pairs: of channel
 // tiles; packed: features are staged as bits, not as codes; blocks: that a compute unit holds
@@ -22,44 +22,53 @@ struct Tiling {
 
 // A compute unit works on its resident blocks in rounds.  In one of them
 //   the sums read 1.5 operands from LDS for each matrix instruction with one pixel tile a wave, 1 with two, 1.25 and 0.75 pooled, and
-//   these reads are most of what an instruction takes: 0.017 each and 0.004 on top, nearly twice that on a SIMD with a lone wave;
-//   staging passes over the pixels: every thread fetches two pieces (four of one word) and waits, 0.36 a pass, and more for each wave
+//   these reads are most of what an instruction takes: 0.0175 each and 0.00494 on top, nearly twice that on a SIMD with a lone wave;
+//   staging passes over the pixels: every thread fetches two pieces (four of one word) and waits, 0.377 a pass, and more for each wave
 //   that expands and writes them;
-//   the epilogue takes 0.2 for a 32 x 32 tile of planes, and 0.03 for each other block that writes into the same lines.
+//   weights pass through in chunks, which costs the most where they are loaded word by word (channel words no multiple of four), twice
+//   that with two planes;
+//   the epilogue takes 0.209 for a 32 x 32 tile of planes, and 0.0331 for each other block that writes into the same lines.
 // Where blocks walk, a third of the shorter of the sums and the rest is hidden, by the other waves or by the next tile's pixels being in
-// flight; with one buffer and a lone wave nothing is.
+// flight; with one buffer and a lone wave nothing is.  A last round that half of the compute units have takes 7 % less.
 static double staged_cost(const MfmaParams &mp, const Tiling &t, int kindA, int64_t steps, bool stay, int sw)
 {
-    const bool pooled = t.fp >= 3, one_plane = mp.PA == 1;
+    const bool pooled = t.fp >= 3, planes = mp.PB > 1, words = mp.Cw % 4 != 0;       // (weights of two planes, loaded by words)
     const double products = t.fp == 4 ? 8.0 : t.fp == 1 ? 2.0 : 4.0, reads = t.fp == 1 ? 1.5 : t.fp == 2 ? 1.0 : t.fp == 3 ? 1.25 : 0.75;
     const double entries = static_cast<double>(steps) * mp.DA * mp.DB, filled = mp.N / (64.0 * t.pairs * t.columns);
-    double outputs = pooled ? 0.11 + 0.147 * products : (mp.Y ? 0.618 : 0.2) * products;
-    if (mp.res) outputs += 0.1 * (pooled ? products / 4 : products);
+    double outputs = pooled ? 0.0323 + 0.174 * products : (mp.Y ? 0.643 : 0.209) * products;
+    if (mp.res) outputs += 0.101 * (pooled ? products / 4 : products);
     outputs *= filled;
-    if (!pooled && !mp.Y) outputs += 0.0321 * products * static_cast<double>(t.columns < 8 ? t.columns - 1 : 7);
+    if (!pooled && !mp.Y) outputs += 0.0331 * products * static_cast<double>(t.columns < 8 ? t.columns - 1 : 7);
     int share = 1;                                               // threads that share a position
     while (share < mp.DA * ceil_div(2 * ((mp.Cw + 1) / 2), sw)) share *= 2;
     const double passes = static_cast<double>(ceil_div(t.plane / halo_words(kindA, t.packed) * share, 256 * t.pairs * (sw == 1 ? 4 : 2)));
-    const double pass = (sw == 1 ? 0.172 : sw == 2 ? 0.0348 : 0.0107) + (t.packed ? 0.0 : sw == 4 ? 0.0438 : 0.0219) - (one_plane ? 0.0685 : 0.0);
-    const double shared = 0.00422 + 0.0167 * reads + (t.packed ? 0.00324 : 0.0), lone = 0.0288 * reads + (t.packed ? 0.0042 : 0.0);
+    const double pass = (sw == 1 ? 0.148 : sw == 2 ? -0.00979 : 0.0383) + (t.packed ? 0.0 : sw == 4 ? 0.0396 : 0.0198) - (mp.PA == 1 ? 0.0603 : 0.0);
+    const double shared = 0.00494 + 0.0175 * reads + (t.packed ? 0.00131 : 0.0), lone = 0.0308 * reads + (t.packed ? 0.00423 : 0.0);
     const bool two = t.buffers == 2;
-    const double resident = static_cast<double>(t.blocks * t.pairs), first = 1.27;                   // the first loads of a round
-    const double fixed = !t.walks ? first + (stay ? 0.0 : 0.0141 * steps * mp.DB) : two ? 1.03 / resident - 0.202 : 1.27 / resident - 0.597;
-    const double weights = stay ? (sw == 1 ? 0.014 : 0.00264) * steps * mp.DB * t.pairs : 0.0;
+    const double resident = static_cast<double>(t.blocks * t.pairs), first = 0.803;                // the first loads of a round
+    const double chunk = words ? (planes ? 0.0743 : 0.04) : planes ? 0.0082 : 0.00541;
+    const double fixed = !t.walks ? first + (stay ? 0.0 : (chunk + resident * (planes ? 0.00459 : 0.00165)) * steps * mp.DB)
+                       : two ? 0.819 / resident - 0.233 : 0.898 / resident - 0.592;
+    const double weights = stay ? (words ? (planes ? 0.0289 : 0.0149) : planes ? 0.00572 : 0.0) * steps * t.pairs : 0.0;
     auto round = [&](int64_t blocks) {
         const double n = static_cast<double>(blocks), waves = n * t.pairs;
-        const double rest = waves * outputs + passes * (0.358 + waves * pass), sums = products * entries * (lone > shared * waves ? lone : shared * waves);
-        const double hidden = t.walks && (two || waves > 1) ? 0.647 : 1.0;
+        const double rest = waves * outputs + passes * (0.377 + waves * pass), sums = products * entries * (lone > shared * waves ? lone : shared * waves);
+        const double hidden = t.walks && (two || waves > 1) ? 0.627 : 1.0;
         return fixed + (rest > sums ? rest + hidden * sums : sums + hidden * rest) + (t.walks ? 0.0 : n * weights);
     };
+    auto last_round = [&](int64_t tiles) {                       // `tiles` blocks, at most one round of them
+        const int64_t n = ceil_div(tiles, 256), blocks = n < t.blocks ? n : t.blocks;
+        const double idle = 1.0 - tiles / (256.0 * blocks);
+        return round(blocks) * (1.0 - (idle > 0.0 ? 0.134 * idle : 0.0));
+    };
     const int64_t tiles = t.tilesM * t.columns;
-    double cost = 2.42;                                          // the launch
+    double cost = 3.21;                                          // the launch; 0.2 of it since calls in a row overlap less than those of the others (400 near the line)
     if (t.walks) {
-        const int64_t step = t.grid / t.columns, full = ceil_div(t.tilesM, step) - 1, rest = ceil_div((t.tilesM - full * step) * t.columns, 256);
-        cost += full * round(t.blocks) + round(rest < t.blocks ? rest : t.blocks) + (first > fixed ? first - fixed : 0.0) + t.blocks * weights;
+        const int64_t step = t.grid / t.columns, full = ceil_div(t.tilesM, step) - 1;
+        cost += full * round(t.blocks) + last_round((t.tilesM - full * step) * t.columns) + (first > fixed ? first - fixed : 0.0) + t.blocks * weights;
     } else {
         const int64_t full = tiles / (256 * t.blocks), rest = tiles % (256 * t.blocks);
-        cost += full * round(t.blocks) + (rest ? round(ceil_div(rest, 256)) : 0.0);
+        cost += full * round(t.blocks) + (rest ? last_round(rest) : 0.0);
     }
     // int32 results: 1 x 1 layers are 1.12 times as long as that where the other side has tiles of 32 x 64 (605 of them), and beyond the
     // 256 MB that the last cache holds both sides' stores slow down, these more (1 x 1, from 5.0 to 3.9 TB/s, the others from 4.5 to 3.8)
@@ -69,25 +78,34 @@ static double staged_cost(const MfmaParams &mp, const Tiling &t, int kindA, int6
 }
 
 // The kernels with lane-private loads: so much for a tile of 32 x 32 and for each pair of K words and pair of digits of it, more for
-// those from the tenth and the fiftieth on.  Up to 4096 tiles four waves share one; beyond, a wave has one, or two of 32 x 32 where the
-// channels are a multiple of 64.
+// those from the tenth and the fiftieth on; most of it for whole tiles a compute unit.  Up to 4096 tiles four waves share one; beyond, a
+// wave has one, or two of 32 x 32 where the channels are a multiple of 64.
 static double private_cost(const MfmaParams &mp, int64_t tiles)
 {
-    struct Size { double launch, chain, residual, pooled, one_plane, weight_planes, from10, from50, tile[3], pair[3]; };   // channel words a multiple of four, even, odd
-    static constexpr Size sizes[3] = {{3.69, 0.0192, 0.366, -0.209, 0.594, 1.49, 0.0609, 0, {1.29, 1.48, 1.64}, {0.0424, 0.0503, 0.0941}},
-                                      {5.19, 0.0815, 0.508, -0.155, 0.785, 1.85, 0.0215, 0.0338, {0.513, 0.555, 0.644}, {0.0326, 0.0357, 0.0762}},
-                                      {5.22, 0.0221, 0.606, -0.167, 0.521, 1.44, 0.0454, 0.0388, {0.942, 1.16, 1.28}, {0.0535, 0.0734, 0.113}}};
+    struct Size {
+        double launch, chain, whole, tile[3], pair[3], from10[3], from50[3];     // [3]: channel words a multiple of four, even, odd
+        double residual, pooled, ints, tile_digits, digits, digits4, one_plane, three_planes, weight_planes, stride;
+    };
+    static constexpr Size sizes[3] = {
+        {3.55, 0.00507, 0.743, {1.16, 1.37, 1.71}, {0.067, 0.0736, 0.0692}, {0.0414, 0.0338, 0.0938}, {-0.00754, 0.0162, 0.0222},
+         0.371, -0.181, 0.0334, 1.49, 0.95, 0.94, 0.628, 0.887, 1.37, 1.08},
+        {4.85, 0.094, 0.949, {0.622, 0.632, 0.74}, {0.0271, 0.0359, 0.0707}, {0.0271, 0.0194, 0.034}, {0.0319, 0.0443, 0.0292},
+         0.485, -0.193, -0.0615, 1.25, 0.878, 0.705, 0.733, 0.919, 2.01, 1.19},
+        {5.13, 0.03, 0.744, {1.06, 1.3, 1.37}, {0.0528, 0.0653, 0.105}, {0.0375, 0.0477, 0.0522}, {0.0476, 0.042, 0.0474},
+         0.526, -0.271, -0.167, 1.35, 0.994, 0.847, 0.52, 0.822, 1.48, 1.29}};
     const Size &z = sizes[tiles <= 4096 ? 0 : mp.N % 64 == 0 ? 1 : 2];
     const int words = mp.Cw % 4 == 0 ? 0 : mp.Cw % 2 == 0 ? 1 : 2;
     const int digits = mp.DA * mp.DB;
     const double pairs = 0.5 * mp.Kw * digits;
-    double sums = z.pair[words] * pairs + (pairs > 10.0 ? z.from10 * (pairs - 10.0) : 0.0) + (pairs > 50.0 ? z.from50 * (pairs - 50.0) : 0.0);
+    double sums = z.pair[words] * pairs + (pairs > 10.0 ? z.from10[words] * (pairs - 10.0) : 0.0) + (pairs > 50.0 ? z.from50[words] * (pairs - 50.0) : 0.0);
     if (mp.PA == 1) sums *= z.one_plane;
+    if (mp.PA == 3) sums *= z.three_planes;
     if (mp.PB > 1) sums *= z.weight_planes;
-    if (digits > 1) sums *= digits > 2 ? 0.781 : 0.905;
-    if (mp.stride > 1) sums *= 1.13;
-    const double tile = z.tile[words] * (digits > 1 ? 1.41 : 1.0) + (mp.res ? z.residual : 0.0) + (mp.pool ? z.pooled : 0.0) + sums;
-    return z.launch + z.chain * pairs + 1e-3 * tiles * tile;
+    if (digits > 1) sums *= digits > 2 ? z.digits4 : z.digits;
+    if (mp.stride > 1) sums *= z.stride;
+    const double tile = z.tile[words] * (digits > 1 ? z.tile_digits : 1.0) + (mp.res ? z.residual : 0.0) + (mp.pool ? z.pooled : 0.0) + (mp.Y ? z.ints : 0.0) + sums;
+    const double n = static_cast<double>(tiles), whole = 256.0 * ceil_div(tiles, 256);
+    return z.launch + z.chain * pairs + 1e-3 * (n + z.whole * (whole - n)) * tile;
 }
 
 bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB, int force, hipStream_t st)

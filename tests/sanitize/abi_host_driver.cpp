@@ -227,9 +227,9 @@ int main()
     EXPECT(chosen(64, 56, 56, 64, 96, 3, 1, 2) == "conv_halo" && g_halo.per_column.d == 2);
     EXPECT(chosen(85598, 14, 14, 512, 64, 3, 1, 2) == "conv_halo" && !g_stay);
     EXPECT(chosen(85599, 14, 14, 512, 64, 3, 1, 2) == "small_conv");                                       // features of 2^31 bytes
-    // large layers: not where a block has little to do with what it stages, nor int32 results of few steps whose other side has 32 x 64 tiles
+    // large layers: not where a block of one tile has little to do with what it stages, nor int32 results of few steps
     EXPECT(chosen(25, 65, 65, 512, 512, 1, 0, 4) == "small_conv_wide" && chosen(25, 65, 65, 512, 512, 3, 1, 4) == "conv_halo");
-    EXPECT(chosen(64, 56, 56, 128, 64, 1, 0, 2) == "small_conv_wide" && chosen(64, 56, 56, 128, 96, 1, 0, 2) == "conv_halo");     // (27.4 us, 22.1)
+    EXPECT(chosen(64, 56, 56, 128, 64, 1, 0, 2) == "small_conv_wide" && chosen(64, 56, 56, 128, 96, 1, 0, 2) == "conv_halo");     // (27.4 us there, 22.1 here)
     // few outputs, or rows of matrices or pixels that would be half of a 32 x 32 tile; not many pixels of few channels
     EXPECT(chosen(1, 14, 14, 64, 64, 3, 1, 2) == "tile16" && chosen(1, 3, 3, 256, 16384, 3, 0, 2) == "tile16");
     EXPECT(chosen(32, 56, 56, 64, 6, 3, 1, 2) == "small_conv" && chosen(32, 56, 56, 96, 10, 1, 0, 2) == "small_conv");
@@ -282,11 +282,11 @@ int main()
     EXPECT(pointwise(74, 72, 288, 320, 2, 1, 1) == "small_conv_wide");
     EXPECT(pointwise(73, 125, 640, 128, 1, 3, 0) == "small_conv_wide");
     // either side of the staged convolutions' rule, and of the pooled 16 x 16 tiles'
-    EXPECT(planes(8, 56, 64, 64, 1, 2, 0) == "conv_halo" && planes(3, 56, 64, 64, 1, 2, 0) == "small_conv" && g_nsplit == 4);
+    EXPECT(planes(8, 56, 64, 64, 1, 2, 0) == "conv_halo" && planes(4, 56, 64, 64, 1, 2, 0) == "small_conv" && g_nsplit == 4);
     EXPECT(planes(8, 28, 128, 128, 1, 2, 0) == "small_conv" && planes(12, 28, 128, 128, 1, 2, 0) == "conv_halo");
-    EXPECT(planes(7, 28, 64, 128, 1, 2, 0) == "small_conv" && planes(9, 28, 192, 128, 1, 2, 0) == "small_conv");
+    EXPECT(planes(8, 28, 64, 128, 1, 2, 0) == "small_conv" && planes(12, 28, 192, 128, 1, 2, 0) == "small_conv");
     Q.residual_dev = static_cast<const uint32_t *>(fake); Q.q_res = 2;
-    EXPECT(planes(8, 28, 128, 128, 1, 2, 0) == "small_conv" && planes(9, 28, 128, 128, 1, 2, 0) == "conv_halo");
+    EXPECT(planes(8, 28, 128, 128, 1, 2, 0) == "conv_halo");
     Q.residual_dev = nullptr;
     EXPECT(planes(8, 13, 64, 64, 1, 2, 1) == "small_conv" && planes(8, 13, 128, 64, 1, 2, 1) == "tile16");
     Q.acc_out_dev = fy;
