@@ -1,7 +1,7 @@
 // Convolution layers whose input pixels are staged once per block: the form for layers with enough output pixels to
 // give every compute unit a block.
 //
-// A block owns 32 FC output channels x 128 FP output pixels.  In raster order over a frame padded by `pad` on every side, the
+// A block owns 32 FC output channels x 64 FW FP output pixels.  In raster order over a frame padded by `pad` on every side, the
 // pixels its taps touch are one contiguous range: the block stages that range in LDS once (the lane-private
 // kernels load and check every pixel once per tap and channel tile), padding as zero codes, so that a tap is one added offset
 // and needs no range check.  Features and weights become FP4 codes while they are staged, so the main loop only reads operands

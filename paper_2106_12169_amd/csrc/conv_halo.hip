@@ -9,8 +9,8 @@ namespace apnn {
 // Which layers are staged, and in which form: the least of the times (us) that the forms below and the kernels with lane-private
 // loads are expected to take.  Both were fitted to 29 600 layers (8 to 20 000 blocks of 64 x 128 outputs, 1 x 1 to 7 x 7, strides 1 and
 // 2, up to three planes of weights and four of features, planes and int32 results, each measured in every form in a replayed graph);
-// the mean error near the line is 5 and 6 %.  On 7620 other layers what is chosen takes 1.0 % more than the fastest of them all, 1.6 %
-// beyond 4096 tiles of 32 x 32 (with the rules before: 2.5 and 4.6 %).  By classes: profiles/staged_convolutions_choice.txt.
+// the mean error near the line is 5 and 6 %.  On 7620 other layers what is chosen takes about 1 % more than the fastest of them all (with
+// the rules before 3 %, beyond 4096 tiles of 32 x 32 5 %).  By classes: profiles/staged_convolutions_choice.txt.
 
 // The form of a layer's blocks.  fp: pixel tiles of a wave (pooled 4 with both channel tiles of a pair, 3 with one); pairs: of channel
 // tiles; packed: features are staged as bits, not as codes; blocks: that a compute unit holds
@@ -22,44 +22,45 @@ struct Tiling {
 
 // A compute unit works on its resident blocks in rounds.  In one of them
 //   the sums read 1.5 operands from LDS for each matrix instruction with one pixel tile a wave, 1 with two, 1.25 and 0.75 pooled, and
-//   these reads are most of what an instruction takes: 0.0175 each and 0.00494 on top, nearly twice that on a SIMD with a lone wave;
-//   staging passes over the pixels: every thread fetches two pieces (four of one word) and waits, 0.377 a pass, and more for each wave
+//   these reads are most of what an instruction takes: 0.0172 each and 0.00511 on top, nearly twice that on a SIMD with a lone wave;
+//   staging passes over the pixels: every thread fetches two pieces (four of one word) and waits, 0.389 a pass, and more for each wave
 //   that expands and writes them;
 //   weights pass through in chunks, which costs the most where they are loaded word by word (channel words no multiple of four), twice
 //   that with two planes;
-//   the epilogue takes 0.209 for a 32 x 32 tile of planes, and 0.0331 for each other block that writes into the same lines.
+//   the epilogue takes 0.206 for a 32 x 32 tile of planes, and 0.0335 for each other block that writes into the same lines.
 // Where blocks walk, a third of the shorter of the sums and the rest is hidden, by the other waves or by the next tile's pixels being in
-// flight; with one buffer and a lone wave nothing is.  A last round that half of the compute units have takes 7 % less.
+// flight; with one buffer and a lone wave nothing is.  A last round that half of the compute units have takes 7 % less, and a lone last
+// tile of several blocks that walk 23 %.
 static double staged_cost(const MfmaParams &mp, const Tiling &t, int kindA, int64_t steps, bool stay, int sw)
 {
     const bool pooled = t.fp >= 3, planes = mp.PB > 1, words = mp.Cw % 4 != 0;       // (weights of two planes, loaded by words)
     const double products = t.fp == 4 ? 8.0 : t.fp == 1 ? 2.0 : 4.0, reads = t.fp == 1 ? 1.5 : t.fp == 2 ? 1.0 : t.fp == 3 ? 1.25 : 0.75;
     const double entries = static_cast<double>(steps) * mp.DA * mp.DB, filled = mp.N / (64.0 * t.pairs * t.columns);
-    double outputs = pooled ? 0.0323 + 0.174 * products : (mp.Y ? 0.643 : 0.209) * products;
+    double outputs = pooled ? 0.0161 + 0.178 * products : (mp.Y ? 0.642 : 0.206) * products;
     if (mp.res) outputs += 0.101 * (pooled ? products / 4 : products);
     outputs *= filled;
-    if (!pooled && !mp.Y) outputs += 0.0331 * products * static_cast<double>(t.columns < 8 ? t.columns - 1 : 7);
+    if (!pooled && !mp.Y) outputs += 0.0335 * products * static_cast<double>(t.columns < 8 ? t.columns - 1 : 7);
     int share = 1;                                               // threads that share a position
     while (share < mp.DA * ceil_div(2 * ((mp.Cw + 1) / 2), sw)) share *= 2;
     const double passes = static_cast<double>(ceil_div(t.plane / halo_words(kindA, t.packed) * share, 256 * t.pairs * (sw == 1 ? 4 : 2)));
-    const double pass = (sw == 1 ? 0.148 : sw == 2 ? -0.00979 : 0.0383) + (t.packed ? 0.0 : sw == 4 ? 0.0396 : 0.0198) - (mp.PA == 1 ? 0.0603 : 0.0);
-    const double shared = 0.00494 + 0.0175 * reads + (t.packed ? 0.00131 : 0.0), lone = 0.0308 * reads + (t.packed ? 0.00423 : 0.0);
+    const double pass = (sw == 1 ? 0.139 : sw == 2 ? -0.0177 : 0.0272) + (t.packed ? 0.0 : sw == 4 ? 0.0353 : 0.0177) - (mp.PA == 1 ? 0.0597 : 0.0);
+    const double shared = 0.00511 + 0.0172 * reads + (t.packed ? 0.0015 : 0.0), lone = 0.0307 * reads + (t.packed ? 0.00421 : 0.0);
     const bool two = t.buffers == 2;
-    const double resident = static_cast<double>(t.blocks * t.pairs), first = 0.803;                // the first loads of a round
-    const double chunk = words ? (planes ? 0.0743 : 0.04) : planes ? 0.0082 : 0.00541;
-    const double fixed = !t.walks ? first + (stay ? 0.0 : (chunk + resident * (planes ? 0.00459 : 0.00165)) * steps * mp.DB)
-                       : two ? 0.819 / resident - 0.233 : 0.898 / resident - 0.592;
-    const double weights = stay ? (words ? (planes ? 0.0289 : 0.0149) : planes ? 0.00572 : 0.0) * steps * t.pairs : 0.0;
+    const double resident = static_cast<double>(t.blocks * t.pairs), first = 0.806;                // the first loads of a round
+    const double chunk = words ? (planes ? 0.075 : 0.0406) : planes ? 0.00908 : 0.00623;
+    const double fixed = !t.walks ? first + (stay ? 0.0 : (chunk + resident * (planes ? 0.00463 : 0.00167)) * steps * mp.DB)
+                       : two ? 0.466 / resident - 0.0524 : 0.455 / resident - 0.286;
+    const double weights = stay ? (words ? (planes ? 0.0302 : 0.0162) : planes ? 0.00681 : 0.0) * steps * t.pairs : 0.0;
     auto round = [&](int64_t blocks) {
         const double n = static_cast<double>(blocks), waves = n * t.pairs;
-        const double rest = waves * outputs + passes * (0.377 + waves * pass), sums = products * entries * (lone > shared * waves ? lone : shared * waves);
-        const double hidden = t.walks && (two || waves > 1) ? 0.627 : 1.0;
+        const double rest = waves * outputs + passes * (0.389 + waves * pass), sums = products * entries * (lone > shared * waves ? lone : shared * waves);
+        const double hidden = t.walks && (two || waves > 1) ? 0.619 : 1.0;
         return fixed + (rest > sums ? rest + hidden * sums : sums + hidden * rest) + (t.walks ? 0.0 : n * weights);
     };
     auto last_round = [&](int64_t tiles) {                       // `tiles` blocks, at most one round of them
         const int64_t n = ceil_div(tiles, 256), blocks = n < t.blocks ? n : t.blocks;
-        const double idle = 1.0 - tiles / (256.0 * blocks);
-        return round(blocks) * (1.0 - (idle > 0.0 ? 0.134 * idle : 0.0));
+        if (t.walks) return round(blocks) * (blocks == 1 && t.blocks > 1 ? 0.766 : 1.0);
+        return round(blocks) * (1.0 - 0.137 * (1.0 - tiles / (256.0 * blocks)));
     };
     const int64_t tiles = t.tilesM * t.columns;
     double cost = 3.21;                                          // the launch; 0.2 of it since calls in a row overlap less than those of the others (400 near the line)
@@ -175,7 +176,8 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
         t.padded = padded(fp, packed);
         t.table = round_up((t.padded * p.DA + 5 * halo_granule(fp == 3 ? 4 : fp, fp == 3 ? 1 : 2, stay && packed)) * (multi ? 2 : 1), 4);
         t.codes = (stay ? t.padded : 2 * kHaloChunk) * 512 * pairs + t.table;
-        const int64_t most = pairs == 2 ? 1 : fp == 4 ? 2 : fp == 1 && (stay ? packed : !multi) ? 4 : 3;    // by registers: waves a SIMD holds
+        const int64_t most = pairs == 2 ? 1 : fp == 4 ? 2 : fp == 1 && (stay ? packed : !multi) ? 4 : 3;    // by registers: waves a SIMD holds (eight waves
+        // in chunks of 128 pixels take 127: two such blocks can be resident; the times were fitted with one)
         // LDS is given out in granules of 1280 bytes, 128 to a compute unit: three blocks of 42 are resident together, of 43 (53.8 to 54.6 KB,
         // three times that is below 160 KB) two, and a grid of walking blocks for three then takes a second turn (168 x 11 x 74,
         // 128 -> 192 channels, 3 x 3, one buffer of bits: 30.5 us, 23.6 with two).
@@ -186,7 +188,7 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
             t.blocks = held < most ? held : most;
         };
         fit(1);
-        // blocks that have a second tile walk, with a second buffer of records where as many of them fit
+        // blocks that have a second tile walk, with a second buffer of records where as many of them fit (overrides 1 and 2: where any fits)
         const int64_t single = t.blocks;
         t.walks = stay && t.tilesM * t.columns > 256 * t.blocks / t.columns * t.columns && 256 * t.blocks >= t.columns;
         if (t.walks) {
