@@ -43,6 +43,7 @@ struct ConvHaloParams {
     int steps, padded;       // matrix steps of a weight digit, of it as it is walked
     int pairs, buffers;      // pairs of channel tiles of a block, buffers of feature codes
     int packed;              // features are staged as bits, not as codes
+    int three;               // (host) three blocks a compute unit at most, steps are read in pairs
     Divisor halves, columns;                 // half, S
     uint32_t first[4], first_codes[4];       // the first entries' words of the table of offsets
     int pool;                // 0 none, 1 maximum, 2 sum
@@ -62,8 +63,10 @@ struct ConvHaloParams {
 constexpr int kHaloStay = 26, kHaloChunk = 8;
 
 // Steps whose operands a wave reads together: one step's four and more matrix instructions cover the latency of the next
-// one's reads, two instructions do not -- unless four waves share a SIMD, as those of the smaller tile of bits do where weights stay
-// (1x1 sums of one to four steps of several digits, relative to two steps with three waves: 0.95).
+// one's reads, two instructions do not -- unless four waves share a SIMD, as those of the smaller tile of bits do where weights stay.
+// THREE: several digits on 768 tiles at most, or in so much LDS that a compute unit holds three blocks at most, in pairs of steps (time
+// relative to one step with room for four waves: from 19 entries on 0.93 on 256 tiles at most, 0.97 on 768, with one or two blocks a unit 0.96;
+// with four 1.03 at up to 8 entries).
 constexpr int halo_granule(int fp, int fw, bool shared) { return shared || fp * fw >= 4 ? 1 : 2; }
 
 // LDS words of a channel word of a position: codes; pairs of bits; the bits of one plane, or of -1/+1 features and which of them are there
@@ -88,12 +91,12 @@ __host__ __device__ __forceinline__ PlaneOffset plane_offset(uint32_t at, int pl
 // STAY: the weights stay in LDS while the block walks over its tiles of pixels (grid-stride), and the next tile's pixels are in
 // flight during the main loop.  Otherwise a block has one tile, and the weights pass through two buffers, a chunk each, with
 // one barrier per chunk.
-template <int KA, int SW, int FP, int FW, int FC, bool POOL, bool MULTI, bool PACKED, bool STAY>
-__global__ __launch_bounds__(128 * FC, FC == 4 ? 2 : FP * FW == 8 ? 2 : FP == 1 && (STAY ? PACKED : !MULTI) ? 4 : 3) void conv_halo_kernel(const ConvHaloParams p)
+template <int KA, int SW, int FP, int FW, int FC, bool POOL, bool MULTI, bool PACKED, bool STAY, bool THREE>
+__global__ __launch_bounds__(128 * FC, FC == 4 ? 2 : FP * FW == 8 ? 2 : FP == 1 && !THREE && (STAY ? PACKED : !MULTI) ? 4 : 3) void conv_halo_kernel(const ConvHaloParams p)
 {
     static_assert(!POOL || FP == 4, "a wave's four pixel tiles are the members of its pooling grids");
     constexpr int HW = SW == 8 ? 4 : SW == 4 ? 2 : 1, PW = SW == 8 ? 4 : SW;     // channel words of a weight load, of a piece of a pixel
-    constexpr int G = halo_granule(FP, FW, PACKED && STAY);      // steps of a granule
+    constexpr int G = halo_granule(FP, FW, PACKED && STAY && !THREE);      // steps of a granule
     constexpr int E = MULTI ? 2 : 1;                             // LDS words of a table entry
     constexpr int CW = halo_words(KA, PACKED);                   // LDS words of a channel word of a position
     constexpr int NT = 128 * FC;                                 // threads: four waves for every two channel tiles

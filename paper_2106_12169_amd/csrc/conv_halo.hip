@@ -16,7 +16,7 @@ namespace apnn {
 // tiles; packed: features are staged as bits, not as codes; blocks: that a compute unit holds
 struct Tiling {
     int fp, pairs;
-    bool packed, walks;
+    bool packed, walks, three;
     int64_t tilesM, columns, padded, plane, records, table, codes, lds, blocks, buffers, grid;
 };
 
@@ -154,10 +154,9 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
     // Weights of up to kHaloStay steps stay in LDS while a block walks over its tiles; longer ones pass through in chunks.
     const bool multi = p.DA > 1 || p.DB > 1;
     const bool stay = p.DB == 1 && round_up(steps, 2) <= kHaloStay;
-    auto padded = [&](int fp, bool packed) { return round_up(steps, halo_granule(fp == 3 ? 4 : fp, fp == 3 ? 1 : 2, stay && packed)); };
     if (!stay && p.half > kHaloChunk) return false;
 
-    auto tiling = [&](int fp, int pairs, bool packed) {
+    auto tiling = [&](int fp, int pairs, bool packed, bool three) {
         Tiling t{};
         const int64_t pixels = fp == 3 ? 256 : 128 * fp;
         t.fp = fp; t.pairs = pairs; t.packed = packed;
@@ -173,10 +172,12 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
         // (with four words a lane an odd number of positions: those that neighbouring lanes write fall on different banks)
         t.plane = halo_words(kindA, packed) * ((reach < images * Hq * Wq ? reach : images * Hq * Wq) | (sw == 4 ? 1 : 0));
         t.records = t.plane * 2 * p.half * p.DA;
-        t.padded = padded(fp, packed);
-        t.table = round_up((t.padded * p.DA + 5 * halo_granule(fp == 3 ? 4 : fp, fp == 3 ? 1 : 2, stay && packed)) * (multi ? 2 : 1), 4);
+        t.three = three;
+        const int granule = halo_granule(fp == 3 ? 4 : fp, fp == 3 ? 1 : 2, stay && packed && !three);
+        t.padded = round_up(steps, granule);
+        t.table = round_up((t.padded * p.DA + 5 * granule) * (multi ? 2 : 1), 4);
         t.codes = (stay ? t.padded : 2 * kHaloChunk) * 512 * pairs + t.table;
-        const int64_t most = pairs == 2 ? 1 : fp == 4 ? 2 : fp == 1 && (stay ? packed : !multi) ? 4 : 3;    // by registers: waves a SIMD holds (eight waves
+        const int64_t most = pairs == 2 ? 1 : fp == 4 ? 2 : fp == 1 && !three && (stay ? packed : !multi) ? 4 : 3;    // by registers: waves a SIMD holds (eight waves
         // in chunks of 128 pixels take 127: two such blocks can be resident; the times were fitted with one)
         // LDS is given out in granules of 1280 bytes, 128 to a compute unit: three blocks of 42 are resident together, of 43 (53.8 to 54.6 KB,
         // three times that is below 160 KB) two, and a grid of walking blocks for three then takes a second turn (168 x 11 x 74,
@@ -206,7 +207,8 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
         if (n == 2 && (sw != 4 || multi || mp.N <= 64)) continue;
         for (const bool packed : {false, true}) {
             if (packed ? n == 2 || force > 6 : multi || force == 5 || force == 6) continue;
-            const Tiling c = tiling(f, n, packed);
+            Tiling c = tiling(f, n, packed, false);
+            if (multi && stay && f == 1 && (c.tilesM * c.columns <= 768 || c.blocks < 4)) c = tiling(f, n, packed, true);
             if (c.blocks < 1) continue;
             const double cost = staged_cost(mp, c, kindA, steps, stay, sw);
             if (t.blocks > 0 && cost >= best) continue;
@@ -217,7 +219,7 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
     if (force < 0 && best > private_cost(mp, ceil_div(mp.M, 32) * ceil_div(mp.N, 32))) return false;
     p.tilesM = static_cast<int>(t.tilesM);
     p.per_column = divisor(t.columns);
-    p.packed = t.packed;
+    p.packed = t.packed; p.three = t.three;
     p.pieces = p.DA * static_cast<int>(ceil_div(2 * p.half, sw));
     while ((1 << p.share) < p.pieces) ++p.share;
     p.pairs = t.pairs; p.buffers = static_cast<int>(t.buffers);

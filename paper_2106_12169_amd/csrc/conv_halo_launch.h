@@ -5,10 +5,10 @@
 
 namespace apnn {
 
-template <int KA, int SW, int FP, int FW, int FC, bool POOL, bool MULTI, bool PACKED, bool STAY>
+template <int KA, int SW, int FP, int FW, int FC, bool POOL, bool MULTI, bool PACKED, bool STAY, bool THREE = false>
 bool launch_conv_halo(const ConvHaloParams &p, unsigned grid, int lds, hipStream_t st)
 {
-    const auto kernel = conv_halo_kernel<KA, SW, FP, FW, FC, POOL, MULTI, PACKED, STAY>;
+    const auto kernel = conv_halo_kernel<KA, SW, FP, FW, FC, POOL, MULTI, PACKED, STAY, THREE>;
     static std::atomic<uint64_t> granted{0};
     if (!all_of_lds(kernel, granted)) return false;
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(128 * FC), lds, st, p);
@@ -19,6 +19,9 @@ template <int KA, int SW, int FC, bool MULTI, bool PACKED, bool STAY> bool launc
 {
     if (p.pool) return fp == 4 ? launch_conv_halo<KA, SW, 4, 2, FC, true, MULTI, PACKED, STAY>(p, grid, lds, st)
                                : launch_conv_halo<KA, SW, 4, 1, FC, true, MULTI, PACKED, STAY>(p, grid, lds, st);
+    if constexpr (MULTI && STAY) {
+        if (p.three) return launch_conv_halo<KA, SW, 1, 2, FC, false, MULTI, PACKED, STAY, true>(p, grid, lds, st);
+    }
     return fp == 2 ? launch_conv_halo<KA, SW, 2, 2, FC, false, MULTI, PACKED, STAY>(p, grid, lds, st)
                    : launch_conv_halo<KA, SW, 1, 2, FC, false, MULTI, PACKED, STAY>(p, grid, lds, st);
 }

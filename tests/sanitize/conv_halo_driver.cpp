@@ -75,8 +75,8 @@ static int layouts(const char *file)
                        &pm1w, &l.p, &pm1f, &l.q, &l.pool, &ints, &l.q_out, &l.q_res, &force) == 18) {
         l.pm1_weights = pm1w; l.pm1_features = pm1f; l.ints = ints;
         if (!staged(l, force)) std::printf("0\n");
-        else std::printf("1 kind %d stay %d fp %d pairs %d packed %d buffers %d tilesM %d step %d grid %u lds %d records %d steps %d\n", g_kind, g_stay, g_fp, g_p.pairs,
-                         g_p.packed, g_p.buffers, g_p.tilesM, g_p.tile_step, g_grid, g_lds, g_p.words_records, g_p.steps);
+        else std::printf("1 kind %d stay %d fp %d pairs %d packed %d three %d buffers %d tilesM %d step %d grid %u lds %d records %d steps %d\n", g_kind, g_stay, g_fp, g_p.pairs,
+                         g_p.packed, g_p.three, g_p.buffers, g_p.tilesM, g_p.tile_step, g_grid, g_lds, g_p.words_records, g_p.steps);
     }
     std::fclose(f);
     return 0;

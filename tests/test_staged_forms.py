@@ -76,12 +76,22 @@ def test_walked_layers_walk(layouts):
     assert {(f in (3, 4), buffers, bool(layer[-1])) for f, buffers, layer in forms.WALKS} >= {(True, b, pool) for b in (1, 2) for pool in (False, True)}
 
 
+def test_several_digits_are_read_in_pairs_where_three_blocks_share_a_unit(layouts):
+    """Steps in pairs up to 768 tiles, or where LDS leaves room for three blocks a compute unit; else one by one with four."""
+    layer = (2, 32, 64, 1130, 60, 1, 1, 1, 0, base.P, 1, base.U, 5, 2, 0, 0)          # 1060 tiles
+    few = (1, *layer[1:])
+    large = (2, 96, 64, 1130, 60, 3, 3, 1, 1, base.P, 1, base.U, 5, 2, 0, 0)
+    got = layouts([(5, layer, False), (5, few, False), (5, large, False), (7, (2, 64, 64, 56, 56, 3, 3, 1, 1, base.P, 1, base.U, 2, 2, 0, 0), False)])
+    assert [g["three"] for g in got] == [0, 1, 1, 0]
+    assert got[2]["tilesM"] > 768 and 4 * -(-got[2]["lds"] // 1280) > 128
+
+
 def test_short_sums_come_without_the_table(layouts):
     """Granules (two steps; one where bits stay, in larger tiles and in pooled ones) of the sums: one, two and three of each."""
     cases = [(f, forms.short_layer(*s), False) for f, s in forms.SHORT_FORMS if f > 2]
     seen = set()
     for (force, layer, _), got in zip(cases, layouts(cases)):
-        one = got["packed"] or got["fp"] > 1
+        one = (got["packed"] and not got["three"]) or got["fp"] > 1
         entries = got["steps"] * ((layer[12] + 1) // 2)
         seen.add((bool(one), min(entries if one else (entries + 1) // 2, 3)))
     assert seen == {(one, n) for one in (False, True) for n in (1, 2, 3)}
