@@ -22,48 +22,48 @@ struct Tiling {
 
 // A compute unit works on its resident blocks in rounds.  In one of them
 //   the sums read 1.5 operands from LDS for each matrix instruction with one pixel tile a wave, 1 with two, 1.25 and 0.75 pooled, and
-//   these reads are most of what an instruction takes: 0.0172 each and 0.00511 on top, nearly twice that on a SIMD with a lone wave;
-//   staging passes over the pixels: every thread fetches two pieces (four of one word) and waits, 0.389 a pass, and more for each wave
+//   these reads are most of what an instruction takes: 0.0169 each and 0.00537 on top, nearly twice that on a SIMD with a lone wave;
+//   staging passes over the pixels: every thread fetches two pieces (four of one word) and waits, 0.393 a pass, and more for each wave
 //   that expands and writes them;
 //   weights pass through in chunks, which costs the most where they are loaded word by word (channel words no multiple of four), twice
 //   that with two planes;
-//   the epilogue takes 0.206 for a 32 x 32 tile of planes, and 0.0335 for each other block that writes into the same lines.
+//   the epilogue takes 0.21 for a 32 x 32 tile of planes, and 0.0334 for each other block that writes into the same lines.
 // Where blocks walk, a third of the shorter of the sums and the rest is hidden, by the other waves or by the next tile's pixels being in
 // flight; with one buffer and a lone wave nothing is.  A last round that half of the compute units have takes 7 % less, and a lone last
-// tile of several blocks that walk 23 %.
+// tile of several blocks that walk 24 %.
 static double staged_cost(const MfmaParams &mp, const Tiling &t, int kindA, int64_t steps, bool stay, int sw)
 {
     const bool pooled = t.fp >= 3, planes = mp.PB > 1, words = mp.Cw % 4 != 0;       // (weights of two planes, loaded by words)
     const double products = t.fp == 4 ? 8.0 : t.fp == 1 ? 2.0 : 4.0, reads = t.fp == 1 ? 1.5 : t.fp == 2 ? 1.0 : t.fp == 3 ? 1.25 : 0.75;
     const double entries = static_cast<double>(steps) * mp.DA * mp.DB, filled = mp.N / (64.0 * t.pairs * t.columns);
-    double outputs = pooled ? 0.0161 + 0.178 * products : (mp.Y ? 0.642 : 0.206) * products;
-    if (mp.res) outputs += 0.101 * (pooled ? products / 4 : products);
+    double outputs = pooled ? 0.0379 + 0.177 * products : (mp.Y ? 0.645 : 0.21) * products;
+    if (mp.res) outputs += 0.1 * (pooled ? products / 4 : products);
     outputs *= filled;
-    if (!pooled && !mp.Y) outputs += 0.0335 * products * static_cast<double>(t.columns < 8 ? t.columns - 1 : 7);
+    if (!pooled && !mp.Y) outputs += 0.0334 * products * static_cast<double>(t.columns < 8 ? t.columns - 1 : 7);
     int share = 1;                                               // threads that share a position
     while (share < mp.DA * ceil_div(2 * ((mp.Cw + 1) / 2), sw)) share *= 2;
     const double passes = static_cast<double>(ceil_div(t.plane / halo_words(kindA, t.packed) * share, 256 * t.pairs * (sw == 1 ? 4 : 2)));
-    const double pass = (sw == 1 ? 0.139 : sw == 2 ? -0.0177 : 0.0272) + (t.packed ? 0.0 : sw == 4 ? 0.0353 : 0.0177) - (mp.PA == 1 ? 0.0597 : 0.0);
-    const double shared = 0.00511 + 0.0172 * reads + (t.packed ? 0.0015 : 0.0), lone = 0.0307 * reads + (t.packed ? 0.00421 : 0.0);
+    const double pass = (sw == 1 ? 0.135 : sw == 2 ? -0.0215 : 0.0215) + (t.packed ? 0.0 : sw == 4 ? 0.0406 : 0.0203) - (mp.PA == 1 ? 0.059 : 0.0);
+    const double shared = 0.00537 + 0.0169 * reads + (t.packed ? 0.0016 : 0.0), lone = 0.0302 * reads + (t.packed ? 0.00438 : 0.0);
     const bool two = t.buffers == 2;
     const double resident = static_cast<double>(t.blocks * t.pairs), first = 0.806;                // the first loads of a round
-    const double chunk = words ? (planes ? 0.075 : 0.0406) : planes ? 0.00908 : 0.00623;
-    const double fixed = !t.walks ? first + (stay ? 0.0 : (chunk + resident * (planes ? 0.00463 : 0.00167)) * steps * mp.DB)
-                       : two ? 0.466 / resident - 0.0524 : 0.455 / resident - 0.286;
-    const double weights = stay ? (words ? (planes ? 0.0302 : 0.0162) : planes ? 0.00681 : 0.0) * steps * t.pairs : 0.0;
+    const double chunk = words ? (planes ? 0.0778 : 0.0428) : planes ? 0.0115 : 0.00859;
+    const double fixed = !t.walks ? first + (stay ? 0.0 : (chunk + resident * (planes ? 0.00441 : 0.00145)) * steps * mp.DB)
+                       : two ? 0.441 / resident - 0.0695 : 0.474 / resident - 0.304;
+    const double weights = stay ? (words ? (planes ? 0.0297 : 0.0163) : planes ? 0.00655 : 0.0) * steps * t.pairs : 0.0;
     auto round = [&](int64_t blocks) {
         const double n = static_cast<double>(blocks), waves = n * t.pairs;
-        const double rest = waves * outputs + passes * (0.389 + waves * pass), sums = products * entries * (lone > shared * waves ? lone : shared * waves);
-        const double hidden = t.walks && (two || waves > 1) ? 0.619 : 1.0;
+        const double rest = waves * outputs + passes * (0.393 + waves * pass), sums = products * entries * (lone > shared * waves ? lone : shared * waves);
+        const double hidden = t.walks && (two || waves > 1) ? 0.631 : 1.0;
         return fixed + (rest > sums ? rest + hidden * sums : sums + hidden * rest) + (t.walks ? 0.0 : n * weights);
     };
     auto last_round = [&](int64_t tiles) {                       // `tiles` blocks, at most one round of them
         const int64_t n = ceil_div(tiles, 256), blocks = n < t.blocks ? n : t.blocks;
-        if (t.walks) return round(blocks) * (blocks == 1 && t.blocks > 1 ? 0.766 : 1.0);
+        if (t.walks) return round(blocks) * (blocks == 1 && t.blocks > 1 ? 0.758 : 1.0);
         return round(blocks) * (1.0 - 0.137 * (1.0 - tiles / (256.0 * blocks)));
     };
     const int64_t tiles = t.tilesM * t.columns;
-    double cost = 3.21;                                          // the launch; 0.2 of it since calls in a row overlap less than those of the others (400 near the line)
+    double cost = 3.2;                                          // the launch; 0.2 of it since calls in a row overlap less than those of the others (400 near the line)
     if (t.walks) {
         const int64_t step = t.grid / t.columns, full = ceil_div(t.tilesM, step) - 1;
         cost += full * round(t.blocks) + last_round((t.tilesM - full * step) * t.columns) + (first > fixed ? first - fixed : 0.0) + t.blocks * weights;
@@ -88,12 +88,12 @@ static double private_cost(const MfmaParams &mp, int64_t tiles)
         double residual, pooled, ints, tile_digits, digits, digits4, one_plane, three_planes, weight_planes, stride;
     };
     static constexpr Size sizes[3] = {
-        {3.55, 0.00507, 0.743, {1.16, 1.37, 1.71}, {0.067, 0.0736, 0.0692}, {0.0414, 0.0338, 0.0938}, {-0.00754, 0.0162, 0.0222},
-         0.371, -0.181, 0.0334, 1.49, 0.95, 0.94, 0.628, 0.887, 1.37, 1.08},
-        {4.85, 0.094, 0.949, {0.622, 0.632, 0.74}, {0.0271, 0.0359, 0.0707}, {0.0271, 0.0194, 0.034}, {0.0319, 0.0443, 0.0292},
-         0.485, -0.193, -0.0615, 1.25, 0.878, 0.705, 0.733, 0.919, 2.01, 1.19},
-        {5.13, 0.03, 0.744, {1.06, 1.3, 1.37}, {0.0528, 0.0653, 0.105}, {0.0375, 0.0477, 0.0522}, {0.0476, 0.042, 0.0474},
-         0.526, -0.271, -0.167, 1.35, 0.994, 0.847, 0.52, 0.822, 1.48, 1.29}};
+        {3.55, 0.00498, 0.732, {1.17, 1.38, 1.71}, {0.0671, 0.0741, 0.0697}, {0.042, 0.0339, 0.0938}, {-0.00792, 0.0155, 0.022},
+         0.374, -0.182, 0.0282, 1.49, 0.952, 0.942, 0.628, 0.886, 1.37, 1.08},
+        {4.83, 0.0959, 0.839, {0.625, 0.629, 0.737}, {0.027, 0.0367, 0.0715}, {0.0271, 0.0186, 0.0337}, {0.0328, 0.0447, 0.0292},
+         0.493, -0.188, -0.0585, 1.25, 0.877, 0.707, 0.725, 0.916, 2, 1.19},
+        {5.14, 0.0291, 0.953, {1.06, 1.3, 1.37}, {0.0546, 0.0665, 0.108}, {0.0356, 0.0449, 0.0492}, {0.0489, 0.0432, 0.0488},
+         0.526, -0.278, -0.174, 1.34, 1, 0.876, 0.515, 0.809, 1.46, 1.28}};
     const Size &z = sizes[tiles <= 4096 ? 0 : mp.N % 64 == 0 ? 1 : 2];
     const int words = mp.Cw % 4 == 0 ? 0 : mp.Cw % 2 == 0 ? 1 : 2;
     const int digits = mp.DA * mp.DB;
@@ -208,7 +208,10 @@ bool launch_conv_halo(const MfmaParams &mp, int64_t images, int kindA, int kindB
         for (const bool packed : {false, true}) {
             if (packed ? n == 2 || force > 6 : multi || force == 5 || force == 6) continue;
             Tiling c = tiling(f, n, packed, false);
-            if (multi && stay && f == 1 && (c.tilesM * c.columns <= 768 || c.blocks < 4)) c = tiling(f, n, packed, true);
+            if (multi && stay && f == 1 && (c.tilesM * c.columns <= 768 || c.blocks < 4)) {
+                const Tiling three = tiling(f, n, packed, true);
+                if (three.blocks > 0) c = three;
+            }
             if (c.blocks < 1) continue;
             const double cost = staged_cost(mp, c, kindA, steps, stay, sw);
             if (t.blocks > 0 && cost >= best) continue;
