@@ -16,7 +16,7 @@
 // planes of their codes are made in the lane (plane_codes.h).
 //
 // Measured (us; lane-private loads, staged with the expansion in the loop, here): ResNet-18 shape at batch 128, 64 channels 32, 15.1,
-// 14.6; 128 22, 14.2, 12.9; 256 24, 13.6, 11.4; 512 28, 15.4, 13.8; 128 -> 256 with stride 2 14.5, 12.4, 10.1.  8 x 112 x 112, 128 channels,
+// 14.6; 128 22, 14.2, 12.9; 256 24, 13.6, 11.4; 512 28, 15.4, 13.8; 128 -> 256 with stride 2 14.5, 12.4, 9.7.  8 x 112 x 112, 128 channels,
 // pooled 19.7, 15.7, 10.8.  What is left: the board's matrix instructions take 20 to 22 ns each with such operands, which is 4.6 us of
 // these layers, and 77 % of the SIMDs have work (1568 wave tiles for 1024); launch, first loads and epilogue are 5 us.
 #pragma once
@@ -366,7 +366,7 @@ __global__ __launch_bounds__(128 * FC, FC == 4 ? 2 : FP * FW == 8 ? 2 : FP == 1 
         // one before it, into two sets of registers in turn.  Each instruction is fenced, since the compiler otherwise moves the
         // reads to their uses, where a lone wave of a SIMD waits for each.
         v16f_t acc[FW][FP];
-        typedef int features_t __attribute__((ext_vector_type(CW)));
+        typedef int features_t __attribute__((ext_vector_type(CW == 1 ? 2 : CW)));      // (a vector of one ends up in scratch)
         struct Operands {
             v4i_t a[G][FW];
             features_t b[G][FP];
@@ -381,7 +381,8 @@ __global__ __launch_bounds__(128 * FC, FC == 4 ? 2 : FP * FW == 8 ? 2 : FP == 1 
         // read k of a granule at `off`, its weights at `codes` (several digits: the chunk's)
         auto read = [&](Operands &o, auto kc, const offsets_t &off, const uint32_t *codes) __attribute__((always_inline)) {
             constexpr int k = decltype(kc)::value, g = k / (FW + FP), i = k % (FW + FP);
-            if constexpr (i < FP) o.b[g][i] = *reinterpret_cast<const features_t *>(base[i] + off[E * g]);
+            if constexpr (i < FP && CW == 1) o.b[g][i] = features_t{*reinterpret_cast<const int *>(base[i] + off[E * g]), 0};
+            else if constexpr (i < FP) o.b[g][i] = *reinterpret_cast<const features_t *>(base[i] + off[E * g]);
             else if constexpr (MULTI) o.a[g][i - FP] = *reinterpret_cast<const v4i_t *>(codes + ((off[E * g + 1] & ~1023u) >> 2) + (i - FP) * 256);
             else o.a[g][i - FP] = *reinterpret_cast<const v4i_t *>(codes + (g * FC + i - FP) * 256);
             if constexpr (MULTI && i == 0) o.scaleA[g] = scaleA + 2 * static_cast<int>(off[E * g + 1] & 1023u);      // (its lowest byte is read)
@@ -393,7 +394,7 @@ __global__ __launch_bounds__(128 * FC, FC == 4 ? 2 : FP * FW == 8 ? 2 : FP == 1 
             if constexpr (!PACKED) {
                 b = o.b[g][f];
             } else if constexpr (c == 0) {
-                const uint32_t w0 = o.b[g][f][0], w1 = o.b[g][f][CW - 1];    // (of one plane: not read)
+                const uint32_t w0 = o.b[g][f][0], w1 = o.b[g][f][1];    // (of one plane: not read)
                 if constexpr (KA == OPK_U2) {                    // both words shifted at once: the bits that cross are masked
                     const uint64_t two = (static_cast<uint64_t>(w1) << 32 | w0) >> 2;
                     b = v4i_t{static_cast<int>(w0 & m3), static_cast<int>(w1 & m3), static_cast<int>(static_cast<uint32_t>(two) & m3), static_cast<int>(static_cast<uint32_t>(two >> 32) & m3)};
